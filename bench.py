@@ -861,19 +861,22 @@ def main():
         step()
     torch.cuda.synchronize()
     progress(f"{args.steps} timed steps")
-    launches_per_step = sched["kmax"] * N * sched["lmax"]
-    # Every 7th Phi launch of the timed steps is bracketed by HIP events (7 is
-    # coprime to the 10 inner iterations and 3 modes, so every mode and inner
-    # position is sampled); an event pair holds the stream for about 5 us on
-    # either side of its kernel, so timing all launches would cost the job 3 %.
-    cpapr.cpapr_prof_enable_sampled(launches_per_step * args.steps // PROF_EVERY + 16, PROF_EVERY)
+    # MU: an event pair per inner loop (all its Phi passes); row solves: per launch
+    passes = sched["lmax"] if args.method == "mu" else 1
+    every = 2 if args.method == "mu" else PROF_EVERY
+    launches_per_step = sched["kmax"] * N * sched["lmax"] // passes
+    # Every 2nd inner loop (row solves: every 7th launch) of the timed steps is
+    # bracketed by HIP events (2 and 7 are coprime to the 3 modes, 7 to the 10
+    # inner iterations, so every mode and position is sampled); an event pair
+    # holds the stream for about 5 us on either side.
+    cpapr.cpapr_prof_enable_sampled(launches_per_step * args.steps // every + 16, every)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for _ in range(args.steps):
         st, segs = step()
     torch.cuda.synchronize()
     t1 = time.perf_counter()
-    recs = cpapr.cpapr_prof_read(launches_per_step * args.steps // PROF_EVERY + 16)
+    recs = cpapr.cpapr_prof_read(launches_per_step * args.steps // every + 16)
     cpapr.cpapr_prof_disable()
 
     ms_per_step = (t1 - t0) * 1000.0 / args.steps
@@ -883,7 +886,7 @@ def main():
     value = visits / (ms_per_step / 1000.0)
     # launches enqueued after an inner loop stopped exit at once; time only real ones
     med = sorted(ms for _, ms in recs)[len(recs) // 2] if recs else 0.0
-    recs = [(m, ms) for m, ms in recs if ms > 0.2 * med]
+    recs = [(m, ms / passes) for m, ms in recs if ms > 0.2 * med]  # per Phi pass
     word = 4 if prec == cpapr.CPAPR_MIXED else 8
     dims = list(X.dims)
     pdnr = method == cpapr.CPAPR_METHOD_PDNR
@@ -915,7 +918,8 @@ def main():
                    "tol": sched["tau"], "precision": args.precision},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic},
-        "phi_kernel": {"kernel": "pdnr_hess_kernel" if pdnr else "phi_seg_kernel",
+        "phi_kernel": {"kernel": "pdnr_hess_kernel" if pdnr else "phi_seg_kernel" if args.method != "mu" else
+                       "the inner loop's kernels (resident_kernel, hot_kernel, hot_step_kernel), per Phi pass",
                        "launches": len(recs), "avg_ms": avg_ms, "avg_ms_per_mode": per_mode_ms,
                        "nnz_per_s": X.nnz / (avg_ms / 1000.0),
                        "min_bytes_per_launch": tot_bytes / max(1, len(recs)),
@@ -924,9 +928,9 @@ def main():
                        "issued_bytes_per_launch": issued / max(1, len(recs)),
                        "issued_GBs": issued / (tot_ms / 1000.0) / 1e9,
                        "measured_bytes_per_launch": traffic_bytes,
-                       "segments": segs, "sampled_every": PROF_EVERY,
-                       # the sampled launches stand for PROF_EVERY launches each
-                       "share_of_step": PROF_EVERY * tot_ms / (ms_per_step * args.steps)},
+                       "segments": segs, "sampled_every": every,
+                       # the sampled launches stand for `every` launches each
+                       "share_of_step": every * passes * tot_ms / (ms_per_step * args.steps)},
         "solve": {"method": args.method, "outer": st["outer_iters"], "inner_updates": st["inner_iters"],
                   "phi_evals": st["phi_evals"], "trial_evals": st["trial_evals"], "row_steps": st["row_steps"],
                   "converged": bool(st["converged"]), "kkt": st["kkt_violation"], "loglik": st["loglik"]},

@@ -187,6 +187,14 @@ int cpapr_plan_set_shape(cpapr_plan* plan, int32_t group, int32_t chunk);
  * (4 up to R = 4, 8 up to R = 32, then 16 or 64). Host-only. */
 int cpapr_plan_shape(const cpapr_plan* plan, int32_t* group, int32_t* chunk);
 
+/* MU inner loops on a plan with the model's launch shape keep the nonzeros of a
+ * row in registers over all iterations; a row too long for one workgroup is
+ * shared by a team of workgroups that meet after every iteration. This sets how
+ * long (in 10 ns ticks, default 50 ms) a workgroup waits for its team to have
+ * been started (other kernels may occupy the device) before the row is left to
+ * one workgroup, with the same result up to rounding. Host-only. */
+int cpapr_plan_set_team_wait(cpapr_plan* plan, int64_t ticks);
+
 /* Number of nonempty rows (segments) of mode `mode` (host query). */
 int64_t cpapr_plan_segments(const cpapr_plan* plan, int32_t mode);
 

@@ -87,6 +87,7 @@ def load():
         "cpapr_plan_destroy": (C.c_int, [vp]),
         "cpapr_plan_segments": (i64, [vp, i32]),
         "cpapr_plan_set_shape": (C.c_int, [vp, i32, i32]),
+        "cpapr_plan_set_team_wait": (C.c_int, [vp, i64]),
         "cpapr_plan_shape": (C.c_int, [vp, P(i32), P(i32)]),
         "cpapr_plan_batch_shape": (C.c_int, [vp, P(i32), P(i32)]),
         "cpapr_phi": (C.c_int, [vp, i32, vp, P(vp), dbl, vp, vp]),
@@ -132,7 +133,7 @@ def load():
 
 
 EXPORTED = ("cpapr_params_default", "cpapr_plan_workspace_size", "cpapr_plan_create", "cpapr_plan_destroy",
-            "cpapr_plan_segments", "cpapr_plan_set_shape", "cpapr_plan_shape",
+            "cpapr_plan_segments", "cpapr_plan_set_shape", "cpapr_plan_set_team_wait", "cpapr_plan_shape",
             "cpapr_plan_batch_shape", "cpapr_phi", "cpapr_phi_coo_workspace_size",
             "cpapr_phi_coo", "cpapr_phi_coo_noalloc", "cpapr_mu_inner", "cpapr_pqnr_inner",
             "cpapr_pdnr_inner", "cpapr_row_stats", "cpapr_solve", "cpapr_loglik",
@@ -211,6 +212,10 @@ def cpapr_plan_destroy(h):
 
 def cpapr_plan_set_shape(h, group: int, chunk: int):
     return _check(load().cpapr_plan_set_shape(h, group, chunk))
+
+
+def cpapr_plan_set_team_wait(h, ticks: int):
+    return _check(load().cpapr_plan_set_team_wait(h, ticks))
 
 
 def cpapr_plan_shape(h):

@@ -98,13 +98,17 @@ struct Layout {
     size_t mode_rows[CPAPR_MAX_MODES], mode_cidx[CPAPR_MAX_MODES], mode_vals[CPAPR_MAX_MODES];
     size_t mode_pk[CPAPR_MAX_MODES];  // packed records (N <= 3), size 0 otherwise
     size_t f32[CPAPR_MAX_MODES];
+    size_t mode_rp[CPAPR_MAX_MODES];
     size_t region2;
-    size_t B, phi_prev[CPAPR_MAX_MODES], partial, llpart, colsums, state, pqnr, pdnr, det_part, det_rows;
+    size_t B, phi_prev[CPAPR_MAX_MODES], partial, llpart, colsums, state, rs, hot, pqnr, pdnr, det_part, det_rows;
     size_t total;
 };
 
-Layout layout(int N, int64_t nnz, const int64_t* dims, int R, bool mixed, int method, bool det)
+Layout layout(int N, int64_t nnz, const int64_t* dims, int R, const cpapr_params* p)
 {
+    const bool mixed = p->precision == CPAPR_MIXED, det = p->deterministic != 0;
+    const int method = p->method;
+    const bool by_rows = cpapr::rows_supported(R, method);
     Layout L{};
     size_t off = 0;
     for (int n = 0; n < N; ++n) {
@@ -120,6 +124,10 @@ Layout layout(int N, int64_t nnz, const int64_t* dims, int R, bool mixed, int me
     for (int n = 0; n < N; ++n) {
         L.f32[n] = off;
         if (mixed) off += align256((size_t)dims[n] * R * 4);
+    }
+    for (int n = 0; n < N; ++n) {
+        L.mode_rp[n] = off;
+        if (by_rows) off += cpapr::rows_mode_bind(nullptr, nullptr, nnz, dims[n], R);
     }
     L.region2 = off;
     int64_t maxI = 0;
@@ -139,6 +147,10 @@ Layout layout(int N, int64_t nnz, const int64_t* dims, int R, bool mixed, int me
     s += align256((size_t)N * R * 8);
     L.state = off + s;
     s += align256(sizeof(cpapr::DevState));
+    L.rs = off + s;
+    if (by_rows) s += cpapr::rows_state_bind(nullptr, nullptr, nnz, maxI, R, p->tol > 0.0);
+    L.hot = off + s;
+    if (by_rows) s += cpapr::rows_hot_bind(nullptr, nullptr, N, nnz, dims, R);
     L.pqnr = off + s;
     if (method == CPAPR_METHOD_PQNR) s += cpapr::pqnr_bytes(maxI, R);
     L.pdnr = off + s;
@@ -197,6 +209,10 @@ Error enqueue_inner(cpapr_plan* P, int mode, double* B, const void* const* fac, 
 {
     const int64_t n = P->dims[mode] * (int64_t)P->R;
     const bool mixed = P->params.precision == CPAPR_MIXED;
+    // The rows' own loops (rows.hip) unless the caller chose the Phi launch: a
+    // shape of its own or a variant.
+    if (P->by_rows && P->shape_auto && P->params.variant <= CPAPR_VARIANT_SEGMENTED)
+        return cpapr::enqueue_inner_rows(P, mode, B, fac, Phi, s);
     const bool fused = !(P->params.tol > 0.0);
     const int* done = &P->state->done;
     Error e = cpapr::launch_fill(Phi, n, 0.0, done, s);
@@ -368,8 +384,7 @@ int cpapr_plan_workspace_size(const cpapr_coo* X, int32_t R, const cpapr_params*
         e = check_params(p, R, X->nmodes);
         if (e.code) return report(e);
         if (!bytes) return fail(CPAPR_EINVAL, "bytes is NULL");
-        *bytes = layout(X->nmodes, X->nnz, X->dims, R, p->precision == CPAPR_MIXED, p->method,
-                        p->deterministic != 0).total;
+        *bytes = layout(X->nmodes, X->nnz, X->dims, R, p).total;
         return CPAPR_OK;
     } catch (...) {
         return fail(CPAPR_EINVAL, "unexpected exception");
@@ -387,7 +402,7 @@ int cpapr_plan_create(const cpapr_coo* X, int32_t R, const cpapr_params* p, void
         e = check_params(p, R, X->nmodes);
         if (e.code) return report(e);
         const bool mixed = p->precision == CPAPR_MIXED;
-        const Layout L = layout(X->nmodes, X->nnz, X->dims, R, mixed, p->method, p->deterministic != 0);
+        const Layout L = layout(X->nmodes, X->nnz, X->dims, R, p);
         if (!ws) return fail(CPAPR_EWORKSPACE, "workspace is NULL");
         if (((uintptr_t)ws & 255) != 0) return fail(CPAPR_EWORKSPACE, "workspace must be 256-byte aligned");
         if (ws_bytes < L.total) return fail(CPAPR_EWORKSPACE, "workspace too small");
@@ -422,6 +437,14 @@ int cpapr_plan_create(const cpapr_coo* X, int32_t R, const cpapr_params* p, void
         P->det_tiles = cpapr::det_tile_capacity(X->nnz);
         int64_t maxI = 0;
         for (int m = 0; m < P->N; ++m) maxI = std::max(maxI, P->dims[m]);
+        P->by_rows = cpapr::rows_supported(R, p->method);
+        if (P->by_rows) {
+            for (int n = 0; n < P->N; ++n)
+                cpapr::rows_mode_bind(&P->mode[n].rp, w + L.mode_rp[n], X->nnz, P->dims[n], R);
+            P->team_wait = 5000000;  // 50 ms
+            cpapr::rows_state_bind(&P->rs, w + L.rs, X->nnz, maxI, R, p->tol > 0.0);
+            cpapr::rows_hot_bind(P, w + L.hot, P->N, X->nnz, P->dims, R);
+        }
         if (p->method == CPAPR_METHOD_PQNR) cpapr::pqnr_bind(&P->pq, w + L.pqnr, maxI, R);
         if (p->method == CPAPR_METHOD_PDNR) cpapr::pdnr_bind(&P->pd, w + L.pdnr, maxI, R);
 
@@ -438,6 +461,9 @@ int cpapr_plan_create(const cpapr_coo* X, int32_t R, const cpapr_params* p, void
             return fail(CPAPR_EUNSUPPORTED, "deterministic mode needs tiles of at least 128 nonzeros");
         }
         e = cpapr::launch_reset_state(P->state, true, true, s);
+        if (!e.code && P->by_rows)  // tickets start at zero (two per word of the fill)
+            e = cpapr::launch_fill((double*)P->rs.ticket, (P->rs.tickets + 1) / 2, 0.0, nullptr, s);
+        if (!e.code && P->by_rows) e = cpapr::rows_hot_build(P, s);
         if (e.code) {
             delete P;
             return report(e);
@@ -475,6 +501,14 @@ int cpapr_plan_set_shape(cpapr_plan* plan, int32_t group, int32_t chunk)
     plan->group = new_group;
     plan->chunk = new_chunk;
     plan->shape_auto = group == 0 && chunk == 0;
+    return CPAPR_OK;
+}
+
+int cpapr_plan_set_team_wait(cpapr_plan* plan, int64_t ticks)
+{
+    if (!plan) return fail(CPAPR_EINVAL, "plan is NULL");
+    if (ticks < 0) return fail(CPAPR_EINVAL, "ticks must be >= 0");
+    plan->team_wait = ticks;
     return CPAPR_OK;
 }
 

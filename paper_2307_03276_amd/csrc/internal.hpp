@@ -24,6 +24,14 @@ struct Error {
 constexpr int kViolSlots = 64;
 constexpr int kViolStride = 16;  // u64 words per slot (128 bytes)
 
+// MU inner loop row by row (rows.hip): iterations per chunk when a KKT stop may
+// end it, violation slots per iteration, row classes, ints of a mode's class counts.
+constexpr int kInnerChunk = 16;
+constexpr int kInnerSlots = 8;
+constexpr int kRowClasses = 20;
+constexpr int kLenBuckets = 128;  // row lengths: four buckets per octave
+constexpr int kRowMeta = 64 + 2 * kLenBuckets;
+
 // Device-side state block of one inner loop (lives in the plan workspace).
 struct DevState {
     unsigned long long viol[2][kViolSlots * kViolStride];  // per-parity slots, ordered bits of doubles >= 0
@@ -31,7 +39,7 @@ struct DevState {
     int done;                                               // inner loop of the current mode has stopped
     int updates;                                            // MU updates in the current inner loop
     int sweep_updates;                                      // MU updates in the current outer sweep
-    int pad;
+    int rerun;                                              // iteration of the chunk the rows are run again to (-1: none)
     long long total_updates;                                // MU updates since the last reset
     long long phi_evals;                                    // Phi computations since the last reset
     double ll;                                              // log-likelihood result
@@ -39,6 +47,7 @@ struct DevState {
     long long trial_evals;                                  // row solves: line-search passes since the last reset
     int pq_all_done;                                        // row solves: no row of the current mode is active
     int pq_idle;                                            // row solves: no row is in a line search
+    unsigned long long iv[kInnerChunk][kInnerSlots][16];    // KKT violation per iteration of a chunk (ordered bits)
 };
 
 // PQNR (projected quasi-Newton row solves): constants shared by every kernel.
@@ -94,6 +103,51 @@ struct PdnrState {
     int32_t* steps;     // per row: steps taken
 };
 
+// Rows of one mode by class (rows.hip).
+struct RowPlan {
+    int32_t* row_ptr;      // [I + 1] first sorted position of each row
+    int32_t* order;        // [I] rows by class
+    int32_t* chunk_begin;  // [heavy rows + 1] first chunk of each heavy row
+    int32_t* chunk_row;    // [chunks] heavy row of each chunk
+    int32_t* team_begin;   // [team rows + 1] first member of each team
+    int32_t* team_row;     // [members] team of each member
+    int32_t count[kRowClasses];
+    int32_t nmembers;           // members of the teams
+    bool use_teams;             // teams take the long rows but the longest; else all of them are heavy
+    int32_t nlong, nchunks_all; // long rows and their chunks
+    int32_t nchunks;            // chunks of the heavy rows
+    int32_t rows_in[kLenBuckets];   // rows per length bucket
+    int32_t nnz_in[kLenBuckets];    // their nonzeros
+    // Long rows' nonzeros again, each row's split by whether a second mode's
+    // coordinate is one of its hot rows (in order inside each part).
+    int32_t lead, hot, third;       // other modes: ordered by / hot rows kept in LDS / remaining one (-1); hot < 0: not built
+    int32_t nhot;                   // hot rows
+    uint32_t* s_lead;               // [nnz] offsets into the lead mode's factor
+    uint16_t* s_slot;               // [nnz] place among the hot rows (hot part)
+    uint32_t* s_hot;                // [nnz] offsets into the hot mode's factor (cold part)
+    uint32_t* s_third;              // [nnz] offsets (three other modes)
+    void* s_val;                    // [nnz] FP32 where every value is exact in it, else FP64
+    int4* entry;                    // pieces {long row, first, end, hot} of the parts
+    int32_t* entry_begin;           // [long rows + 1] first piece of each long row
+    int32_t* xlist;                 // [pieces] pieces by die
+    int32_t* xbegin;                // [kXcds + 1] first of each die
+    uint16_t* hot_id;               // [I] this mode's rows' places among its hot rows (kCold: none)
+    int32_t* hot_rows;              // [kMaxHot] this mode's hot rows
+};
+
+// Work buffers of the row-by-row inner loop (shared by the modes).
+struct RowState {
+    double* partial;       // [chunks x R] partial Phi rows of the heavy rows' chunks
+    double* team_part;     // [3 x members x R] partial rows of the teams' members
+    unsigned int* ticket;  // [tickets] next member, teams' arrivals, heavy rows' arrived chunks; zero between launches
+    int64_t tickets;
+    int* split;            // temporaries of the hot / cold split: [chunks] + [long rows] + [modes]
+    int cus;               // compute units of the device
+    double* hot_tab;       // the hot rows of the current inner loop's factor, in their places
+    double* B0;            // [maxI x R] the chunk's start (tol > 0)
+    double* hist;          // [2 kInnerChunk x heavy rows x R] heavy rows' B and Phi per iteration (tol > 0)
+};
+
 struct PlanMode {
     int32_t* rows;  // [nnz] sorted mode-n coordinates
     uint32_t* cofs;  // [(N-1) * nnz] the other modes' factor row offsets (coordinate x R), ascending m
@@ -104,6 +158,7 @@ struct PlanMode {
     // 2^24); nullptr otherwise.
     int4* pk;
     int64_t segments;
+    RowPlan rp;
 };
 
 constexpr int kMaxOther = CPAPR_MAX_MODES - 1;
@@ -192,6 +247,10 @@ struct cpapr_plan {
     bool shape_auto;                  // group and chunk both from the launch-policy model
     cpapr::PqnrState pq;              // PQNR row-solve state (method CPAPR_METHOD_PQNR only)
     cpapr::PdnrState pd;              // PDNR row-solve state (method CPAPR_METHOD_PDNR only)
+    cpapr::RowState rs;               // row-by-row inner loop (rows_supported)
+    bool by_rows;                     // its structures are there
+    bool exact32;                     // every value is exact in FP32
+    int64_t team_wait;                // clock ticks (10 ns) a team member waits for its team to start
     double* det_part;                 // deterministic mode: tile-end partial rows (nullptr: atomics)
     int32_t* det_rows;                // deterministic mode: their row ids
     int64_t det_tiles;                // tiles the buffers hold (launches with more tiles are refused)
@@ -251,6 +310,25 @@ struct BatchState {
 Error launch_batch_mu(const BatchMu* items, const int32_t* nitems_dev, const int64_t* total_dev, int max_slots,
                       unsigned long long* viol_spread, BatchState st, int grid, hipStream_t s);
 Error launch_batch_reset(BatchState st, int max_slots, hipStream_t s);
+
+// ---- MU inner loop row by row (rows.hip) ----
+bool rows_supported(int R, int method);
+// Bytes of a mode's row classes / of the inner loop's buffers, bound to `base`
+// unless r is nullptr (stops: tol > 0).
+size_t rows_mode_bind(RowPlan* r, char* base, int64_t nnz, int64_t dim, int R);
+size_t rows_state_bind(RowState* r, char* base, int64_t nnz, int64_t maxI, int R, bool stops);
+// Device part of a mode's row classes (meta: kRowMeta zeroed device ints), then
+// the host part from meta's host copy.
+Error rows_build(const cpapr_plan* P, int mode, int* meta, hipStream_t s);
+void rows_finish(cpapr_plan* P, int mode, const int* meta);
+// Long rows' nonzeros split by a second mode's hot rows, where that pays (after
+// every mode's rows_finish). Bytes bound to `base` unless P is nullptr.
+size_t rows_hot_bind(cpapr_plan* P, char* base, int N, int64_t nnz, const int64_t* dims, int R);
+Error rows_hot_build(cpapr_plan* P, hipStream_t s);
+// One MU inner loop of `mode` (lmax iterations or the KKT stop); B in/out, Phi
+// receives the last Phi. State and counters as the Phi / KKT / update launches
+// leave them.
+Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, hipStream_t s);
 
 // ---- elementwise and reduction kernels (mu.hip) ----
 Error launch_fill(double* p, int64_t n, double v, const int* done, hipStream_t s);

@@ -1,0 +1,2024 @@
+// The MU inner loop row by row. With the other factors fixed, row i of Phi
+// depends only on row i of B and on row i's nonzeros, so the iterations of a row
+// need no other row: a workgroup forms the pi rows of its rows' nonzeros once,
+// keeps them in registers and runs all the inner iterations
+//   m_k = b . pi_k,  phi = sum_k x_k / max(m_k, eps) pi_k,  b <- b .* phi
+// on them. The Phi kernel's limit is the gather of the other factors' rows
+// (every iteration again); here each row is gathered once per inner loop.
+//
+// The only coupling between rows is the KKT stop (one violation for the whole
+// mode). With tol > 0 the rows run a chunk of iterations speculatively and
+// record each iteration's violation; decide_kernel finds the first iteration
+// below tol, and if there is one the rows are run again from their saved start
+// to exactly that iteration (all on the device, no host round trip).
+//
+// Rows by length (a plan-time counting sort of the rows into classes):
+//  * up to K nonzeros: one group of G lanes per row (each lane holds C rank
+//    columns, R <= G * C, of up to K pi rows); 64 / G rows per wave;
+//  * longer: 2, 4, .. 64 / G groups of a wave, then 2 or 4 waves of a workgroup;
+//  * longer than 4 waves' registers: heavy rows. Their nonzeros are cut into
+//    chunks of one row each; every iteration gathers again (heavy_kernel), the
+//    last workgroup of a row to finish sums the chunks' partial rows in order
+//    and takes the MU step of that row.
+// Every sum has a fixed order, so results repeat bit for bit.
+#include <algorithm>
+#include <type_traits>
+
+#include "internal.hpp"
+
+namespace cpapr {
+namespace {
+
+inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+
+// x / m for finite m > 0: reciprocal estimate and one Newton step (the Phi
+// kernel's quotient, within a few ulps).
+__device__ __forceinline__ double div_pos(double x, double m)
+{
+    double r = __builtin_amdgcn_rcp(m);
+    r = __builtin_fma(r, __builtin_fma(-m, r, 1.0), r);
+    return x * r;
+}
+
+__device__ __forceinline__ double wave_max(double v)
+{
+    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
+    return v;
+}
+
+// quad_perm controls broadcasting lane j of each quad
+template <int J>
+__device__ __forceinline__ double quad_bcast(double v) { return dpp_f64<J * 0x55>(v); }
+template <int J>
+__device__ __forceinline__ uint32_t quad_bcast(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, J * 0x55, 0xF, 0xF, false);
+}
+
+// One block of four nonzeros of a lane group: every lane holds its C columns
+// of the four pi rows and of b, and the value x of the nonzero whose slot is
+// its lane's place in the quad. The four dot products are reduce-scattered
+// over the quad (7 instead of 8 adds, and every lane ends with one nonzero), summed
+// over the group's quads by mirrors, so that a lane divides once for the four,
+// and the four scales come back as quad broadcasts. A mirror pairs place i
+// with place 3 - i of another quad, so lanes of odd quads (G >= 8) hold the
+// block's nonzeros in reverse order; everything else is the same for all lanes.
+template <int G, int C>
+__device__ __forceinline__ void block4(const double (&pi)[4][C], double x, const double (&b)[C], double eps, bool odd1,
+                                       bool odd2, double (&acc)[C])
+{
+    double d[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        d[j] = b[0] * pi[j][0];
+#pragma unroll
+        for (int c = 1; c < C; ++c) d[j] = __builtin_fma(b[c], pi[j][c], d[j]);
+    }
+    const double a0 = (odd1 ? d[1] : d[0]) + dpp_f64<0xB1>(odd1 ? d[0] : d[1]);
+    const double a1 = (odd1 ? d[3] : d[2]) + dpp_f64<0xB1>(odd1 ? d[2] : d[3]);
+    double m = (odd2 ? a1 : a0) + dpp_f64<0x4E>(odd2 ? a0 : a1);
+    if constexpr (G >= 8) m += dpp_f64<0x141>(m);
+    if constexpr (G >= 16) m += dpp_f64<0x140>(m);
+    const double s = div_pos(x, __builtin_fmax(m, eps));
+    const double s0 = quad_bcast<0>(s), s1 = quad_bcast<1>(s), s2 = quad_bcast<2>(s), s3 = quad_bcast<3>(s);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        acc[c] = __builtin_fma(s0, pi[0][c], acc[c]);
+        acc[c] = __builtin_fma(s1, pi[1][c], acc[c]);
+        acc[c] = __builtin_fma(s2, pi[2][c], acc[c]);
+        acc[c] = __builtin_fma(s3, pi[3][c], acc[c]);
+    }
+}
+
+// Columns [colbase, colbase + C) of the row at element offset `off`.
+template <int C, typename L>
+__device__ __forceinline__ void load_cols(const L* fac, uint32_t off, int colbase, double (&v)[C])
+{
+    const L* f = fac + (uint64_t)off + colbase;
+#pragma unroll
+    for (int c = 0; c < C; ++c) v[c] = (double)f[c];
+}
+
+struct Entry {
+    int32_t block0;  // first workgroup of the class
+    int32_t row0;    // first position in `order`
+    int32_t count;   // rows
+    int32_t groups;  // lane groups per row (> 64 / G: several waves)
+};
+constexpr int kEntries = 16;
+
+struct ResArgs {
+    const uint32_t* cofs;
+    const double* vals;
+    const int32_t* row_ptr;
+    const int32_t* order;
+    const void* fac[kMaxOther];
+    double* B;
+    double* B0;     // saved start of the chunk (tol > 0), else nullptr
+    double* Phi;
+    DevState* st;
+    double* hist;        // heavy rows: B and Phi per iteration (restored on a stop)
+    int64_t nnz;
+    int64_t hist_stride;
+    double eps;
+    int R;
+    int NM1;
+    int n_it;       // iterations (rerun: read from the state)
+    int each;       // 1: record every iteration's violation, 0: the last one's
+    int nentries;
+    int heavy0, nheavy;  // positions of the heavy rows in `order` (team rows last)
+    int light_blocks;
+    // team rows: workgroups (members) of one row that meet after every iteration
+    int team_blocks;             // members of all teams
+    int team0;                   // first team's heavy row
+    const int32_t* team_begin;   // [teams + 1] first member of each team
+    const int32_t* team_row;     // [members] team of each member
+    double* team_part;           // [3 x members x R] members' partial rows, by iteration mod 3
+    unsigned int* team_count;    // [teams] arrivals (kAbandoned: the team never met); zero between launches
+    unsigned int* team_ticket;   // next member; zero between launches
+    long long team_wait;         // clock ticks a member waits for its team to meet
+    Entry entry[kEntries];
+};
+
+constexpr int kResBlock = 256;
+constexpr int kCountStride = 32;  // u32 words between counters: one 128-byte line each (their atomics and polls serialise per line)
+
+constexpr unsigned int kAbandoned = 0x80000000u;
+
+// Members of a team exchange their partial rows after every iteration: a
+// member stores its row in memory and reads everybody's, waiting for entries
+// that still hold kNotYet. Three buffers in turn: in iteration l a member
+// clears its row of l + 1 (read last in l - 2, which all have left) before it
+// computes, and stores its row of l once that has arrived, so whoever sees the
+// row of l never finds an old one in l + 1. One trip through memory per
+// iteration; counting the members in and then reading took three (teams of up
+// to 128 for all long rows of the 20M-nonzero three-way tensor: 1.34 against
+// 1.69 ms per inner loop; with the counters on one cache line 3.4 ms).
+//
+// First the members must be running at all: in iteration 0 they count
+// themselves in, their rows stored, and wait a bounded time for the team to be
+// complete. A member that gives up marks the team abandoned (only while it is
+// incomplete, so either all members meet or none); *last tells the last member to
+// arrive at an abandoned team.
+constexpr unsigned long long kNotYet = 0x7ff8a5a5c3c35a5aull;
+
+__device__ __forceinline__ bool team_meet(unsigned int* count, unsigned int T, long long wait, bool* last)
+{
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    unsigned int seen = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+    *last = seen == (kAbandoned | T);
+    const long long t0 = wall_clock64();
+    while (true) {
+        if (seen & kAbandoned) return false;
+        if (seen >= T) return true;
+        if (wall_clock64() - t0 > wait) {
+            unsigned int expect = seen;
+            if (__hip_atomic_compare_exchange_strong(count, &expect, seen | kAbandoned, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT))
+                return false;
+            seen = expect;
+            continue;
+        }
+        __builtin_amdgcn_s_sleep(1);
+        seen = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+template <int G, int C, int K, bool MIXED, bool TEAM>
+__device__ __forceinline__ void resident_rows(const ResArgs& a, int light, bool rerun, int n_it)
+{
+    using L = typename std::conditional<MIXED, float, double>::type;
+    constexpr int NG = 64 / G;     // lane groups per wave
+    constexpr int KB = K / 4;      // blocks of four nonzeros per lane group
+    constexpr int W = kResBlock / 64;
+    constexpr int RP = 4 * G;      // columns of a partial row, padded
+    __shared__ double red[2][W][RP];
+    __shared__ unsigned long long vmax[kInnerChunk];
+    __shared__ int sh_member, sh_ok, sh_last;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int gl = lane % G, g = lane / G;
+    const int R = a.R;
+    if (t < kInnerChunk) vmax[t] = 0ull;
+
+    int row, S, sub, WR, member = 0, h = 0;
+    int T = 1, nseg = 1;  // members of the team; pieces the row is taken in (an abandoned team's)
+    uint32_t p0, p1;
+    bool valid = true;
+    uint32_t seg0 = 0, seg1 = 0;  // the whole row, for an abandoned team
+    if constexpr (TEAM) {
+        // members in the order in which workgroups start, so that the oldest team is always the first to be complete
+        if (t == 0) {
+            sh_member = (int)__hip_atomic_fetch_add(a.team_ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            sh_last = 0;
+        }
+        __syncthreads();
+        member = __builtin_amdgcn_readfirstlane(sh_member);
+        h = a.team_row[member];
+        const int m0 = a.team_begin[h];
+        T = a.team_begin[h + 1] - m0;
+        row = a.order[a.heavy0 + a.team0 + h];
+        seg0 = (uint32_t)a.row_ptr[row];
+        seg1 = (uint32_t)a.row_ptr[row + 1];
+        const uint32_t per = ((seg1 - seg0 + T - 1) / T + 3) / 4 * 4;
+        p0 = seg0 + (uint32_t)(member - m0) * per;
+        p1 = min(p0 + per, seg1);
+        S = W * NG;
+        WR = W;
+        sub = wave * NG + g;
+    } else {
+        int e = 0;
+        while (e + 1 < a.nentries && light >= a.entry[e + 1].block0) ++e;
+        const int row0 = a.entry[e].row0, count = a.entry[e].count;
+        S = a.entry[e].groups;
+        WR = S > NG ? S / NG : 1;  // waves per row
+        const int local = light - a.entry[e].block0;
+        // position of this lane group's row in the class, and its place among the row's groups
+        int pos;
+        if (WR > 1) {
+            pos = local * (W / WR) + wave / WR;
+            sub = (wave % WR) * NG + g;
+        } else {
+            pos = (local * W + wave) * (NG / S) + g / S;
+            sub = g % S;
+        }
+        valid = pos < count;
+        row = a.order[row0 + (valid ? pos : count - 1)];
+        p0 = (uint32_t)a.row_ptr[row];
+        p1 = (uint32_t)a.row_ptr[row + 1];
+    }
+    bool lead = valid && sub == 0 && (!TEAM || p0 == seg0);  // writes the row
+
+    const int colbase = min(gl * C, R - C);
+    bool own[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) own[c] = colbase + c >= gl * C && colbase + c < R;
+    const bool odd1 = lane & 1, odd2 = lane & 2;
+    const int q = (lane & 3) ^ (G >= 8 && (lane & 4) ? 3 : 0);  // nonzero of the block this lane holds
+
+    double b[C];
+    {
+        const double* src = (rerun ? a.B0 : a.B) + (int64_t)row * R + colbase;
+#pragma unroll
+        for (int c = 0; c < C; ++c) b[c] = own[c] ? src[c] : 0.0;
+        if (!TEAM && !rerun && a.B0 != nullptr && lead)
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                if (own[c]) a.B0[(int64_t)row * R + colbase + c] = b[c];
+    }
+
+    // pi rows of [p0, p1): slots past the end repeat its last nonzero with value 0
+    double pi[KB][4][C];
+    double x[KB];
+    int nb = 0;  // blocks this wave runs (the longest of its rows)
+    auto gather = [&]() {
+        nb = ((int)(p1 - p0) + 4 * S - 1) / (4 * S);
+#pragma unroll
+        for (int o = G; o < 64; o <<= 1) nb = max(nb, __shfl_xor(nb, o));
+        nb = min(__builtin_amdgcn_readfirstlane(nb), KB);
+        uint32_t off[KB];
+        auto at = [&](int kb) { return p0 + (uint32_t)((kb * S + sub) * 4 + q); };
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            x[kb] = 0.0;
+            off[kb] = 0;
+            if (kb < nb) {
+                x[kb] = at(kb) < p1 ? a.vals[min(at(kb), p1 - 1)] : 0.0;
+                off[kb] = a.cofs[min(at(kb), p1 - 1)];
+            }
+        }
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int c = 0; c < C; ++c) pi[kb][j][c] = 1.0;
+        for (int m = 0; m < a.NM1; ++m) {
+            const L* fac = (const L*)a.fac[m];
+            uint32_t next[KB];
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)  // the next factor's offsets before this one's rows are used
+                next[kb] = kb < nb && m + 1 < a.NM1 ? a.cofs[(int64_t)(m + 1) * a.nnz + min(at(kb), p1 - 1)] : 0u;
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) {
+                if (kb < nb) {
+                    double f[4][C];
+                    load_cols<C>(fac, quad_bcast<0>(off[kb]), colbase, f[0]);
+                    load_cols<C>(fac, quad_bcast<1>(off[kb]), colbase, f[1]);
+                    load_cols<C>(fac, quad_bcast<2>(off[kb]), colbase, f[2]);
+                    load_cols<C>(fac, quad_bcast<3>(off[kb]), colbase, f[3]);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int c = 0; c < C; ++c) pi[kb][j][c] *= f[j][c];
+                }
+            }
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) off[kb] = next[kb];
+        }
+    };
+
+    double acc[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) acc[c] = 0.0;
+    __syncthreads();  // vmax is cleared
+    for (int l = 0; l < n_it; ++l) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) acc[c] = 0.0;
+        if (TEAM && T > 1 && wave == 0 && g == 0)
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                if (own[c])
+                    __hip_atomic_store((unsigned long long*)a.team_part +
+                                           ((int64_t)((l + 1) % 3) * a.team_blocks + member) * R + colbase + c,
+                                       kNotYet, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int sg = 0; sg < nseg; ++sg) {
+            if (TEAM && nseg > 1) {  // an abandoned team's row, piece by piece in every iteration
+                p0 = seg0 + (uint32_t)sg * (uint32_t)(K * NG * W);
+                p1 = min(p0 + (uint32_t)(K * NG * W), seg1);
+            }
+            if (l == 0 || (TEAM && nseg > 1)) gather();
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+                if (kb < nb) block4<G, C>(pi[kb], x[kb], b, a.eps, odd1, odd2, acc);
+        }
+        // the row's other lane groups of this wave
+#pragma unroll
+        for (int o = G; o < 64; o <<= 1)
+            if (o < G * S)
+#pragma unroll
+                for (int c = 0; c < C; ++c) acc[c] += __shfl_xor(acc[c], o);
+        if (WR > 1) {  // uniform over the workgroup
+            double(*rd)[RP] = red[l & 1];
+            if (g == 0)
+#pragma unroll
+                for (int c = 0; c < C; ++c) rd[wave][gl * C + c] = acc[c];
+            __syncthreads();
+            const int w0 = wave / WR * WR;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                double v = 0.0;
+                for (int w = 0; w < WR; ++w) v += rd[w0 + w][gl * C + c];
+                acc[c] = v;
+            }
+        }
+        if (TEAM && T > 1) {  // a team: the members' partial rows, summed by every member in the same order
+            double* part = a.team_part + (int64_t)(l % 3) * a.team_blocks * R;
+            if (wave == 0 && g == 0) {
+                __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the next meeting's row is cleared
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    if (own[c]) {
+                        // a value with the bits of "not there yet" can only be a NaN of the inputs
+                        const double v = acc[c] == acc[c] ? acc[c] : __builtin_nan("");
+                        __hip_atomic_store(&part[(int64_t)member * R + colbase + c], v, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                    }
+            }
+            if (l == 0) {
+                if (t == 0) {
+                    bool last = false;
+                    sh_ok = team_meet(a.team_count + h * kCountStride, (unsigned int)T, a.team_wait, &last);
+                    sh_last = last;
+                }
+                __syncthreads();
+                if (!__builtin_amdgcn_readfirstlane(sh_ok)) {
+                    // Nobody else works on this row: its last member does, alone.
+                    if (!__builtin_amdgcn_readfirstlane(sh_last)) return;
+                    __syncthreads();
+                    T = 1;
+                    lead = sub == 0;
+                    nseg = (int)((seg1 - seg0 + K * NG * W - 1) / (uint32_t)(K * NG * W));
+                    l = -1;
+                    continue;
+                }
+            }
+            const int m0 = a.team_begin[h];
+            const int c1 = lane % RP, k0 = wave * (64 / RP) + lane / RP;
+            constexpr int KS = W * (64 / RP);
+            double v = 0.0;
+            if (c1 < R) {
+                const double* src = part + (int64_t)m0 * R + c1;
+                for (int k = k0; k < T; k += 4 * KS) {
+                    unsigned long long u[4];
+                    bool wait;
+                    do {  // every member is running: its row comes
+                        wait = false;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            u[i] = k + i * KS < T ? __hip_atomic_load((const unsigned long long*)&src[(int64_t)(k + i * KS) * R],
+                                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                                  : 0ull;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) wait = wait || u[i] == kNotYet;
+                    } while (wait);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v += __longlong_as_double((long long)u[i]);
+                }
+            }
+#pragma unroll
+            for (int o = RP; o < 64; o <<= 1) v += __shfl_xor(v, o);
+            double(*rd)[RP] = red[(l & 1) ^ 1];
+            if (lane < RP) rd[wave][lane] = v;
+            __syncthreads();
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                double w = 0.0;
+#pragma unroll
+                for (int u = 0; u < W; ++u) w += rd[u][colbase + c];
+                acc[c] = w;
+            }
+            __syncthreads();
+        }
+        if (!rerun && (a.each || l + 1 == n_it)) {
+            double v = 0.0;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const double r = 1.0 - acc[c];
+                if (own[c]) v = fmax(v, fabs(b[c] < r ? b[c] : r));
+            }
+            v = wave_max(valid ? v : 0.0);
+            if (lane == 0) atomicMax(&vmax[a.each ? l : 0], (unsigned long long)__double_as_longlong(v));
+            if (TEAM && a.each && lead)
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    if (own[c]) {
+                        double* hist = a.hist + (int64_t)2 * l * a.hist_stride + (int64_t)(a.team0 + h) * R + colbase + c;
+                        hist[0] = b[c];
+                        hist[a.hist_stride] = acc[c];
+                    }
+        }
+        if (!rerun || l + 1 < n_it)
+#pragma unroll
+            for (int c = 0; c < C; ++c) b[c] *= acc[c];
+    }
+    if (lead)
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            if (own[c]) {
+                a.B[(int64_t)row * R + colbase + c] = b[c];
+                a.Phi[(int64_t)row * R + colbase + c] = acc[c];
+            }
+    if (!rerun) {
+        __syncthreads();
+        const int nv = a.each ? n_it : 1;
+        if (t < nv) atomicMax(&a.st->iv[t][blockIdx.x % kInnerSlots][0], vmax[t]);
+    }
+}
+
+// Two waves per SIMD: the pi rows take most of a lane's 256 registers.
+template <int G, int C, int K, bool MIXED>
+__global__ __launch_bounds__(kResBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void resident_kernel(ResArgs a)
+{
+    if (a.st->done) return;
+    // Team members and light workgroups alternate in launch order, so that a
+    // compute unit has light rows to work on while a team meets.
+    const int b = (int)blockIdx.x, both = min(a.team_blocks, a.light_blocks);
+    const bool team = b < 2 * both ? (b & 1) == 0 : a.team_blocks > a.light_blocks;
+    if (team)
+        resident_rows<G, C, K, MIXED, true>(a, 0, false, a.n_it);
+    else
+        resident_rows<G, C, K, MIXED, false>(a, b < 2 * both ? b >> 1 : b - a.team_blocks, false, a.n_it);
+}
+
+// After a stop at iteration st->rerun of the chunk: the light rows again from
+// their saved start to that iteration, the heavy rows from their history.
+template <int G, int C, int K, bool MIXED>
+__global__ __launch_bounds__(kResBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void rerun_kernel(ResArgs a)
+{
+    const int l = a.st->rerun;
+    if (l < 0) return;
+    if ((int)blockIdx.x < a.light_blocks) {
+        resident_rows<G, C, K, MIXED, false>(a, (int)blockIdx.x, true, l + 1);
+        return;
+    }
+    for (int64_t i = ((int64_t)blockIdx.x - a.light_blocks) * kResBlock + threadIdx.x; i < (int64_t)a.nheavy * a.R;
+         i += ((int64_t)gridDim.x - a.light_blocks) * kResBlock) {
+        const int64_t h = i / a.R, c = i % a.R;
+        const int64_t e = (int64_t)a.order[a.heavy0 + h] * a.R + c;
+        a.B[e] = a.hist[(2 * l) * a.hist_stride + i];
+        a.Phi[e] = a.hist[(2 * l + 1) * a.hist_stride + i];
+    }
+}
+
+struct HeavyArgs {
+    const uint32_t* cofs[kMaxOther];  // offsets into fac[m]
+    const double* vals;
+    const int32_t* row_ptr;
+    const int32_t* rows;         // heavy rows (in `order`)
+    const int32_t* chunk_begin;  // [nheavy + 1] first chunk of each heavy row
+    const int32_t* chunk_row;    // [chunks] heavy row of each chunk
+    const void* fac[kMaxOther];
+    double* B;
+    double* Phi;
+    double* partial;             // [chunks x R]
+    unsigned int* ticket;        // [nheavy], zero between launches
+    DevState* st;
+    double* hist;                // tol > 0: B, then (hist_stride on) Phi of this iteration, else nullptr
+    int64_t hist_stride;
+    int64_t nnz;
+    double eps;
+    int R;
+    int NM1;
+    int chunk;
+    int l;                       // violation slot of this iteration, -1: not recorded
+};
+
+// One iteration of the heavy rows: a workgroup per chunk of one row, so b is
+// loaded once and there is no row logic. A wave takes 4 * 64 / G consecutive
+// nonzeros per step, four per lane group, their gathers in flight together.
+template <int G, int C, int NM1, bool MIXED>
+__global__ __launch_bounds__(kBlock) void heavy_kernel(HeavyArgs a)
+{
+    using L = typename std::conditional<MIXED, float, double>::type;
+    constexpr int W = kBlock / 64;
+    constexpr int STEP = 4 * (64 / G);
+    __shared__ double red[W][G * C];
+    __shared__ double fin[kBlock];
+    __shared__ int last;
+    if (a.st->done) return;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int gl = lane % G, g = lane / G;
+    const int R = a.R;
+    const int ch = blockIdx.x;
+    const int h = a.chunk_row[ch];
+    const int row = a.rows[h];
+    const int c0 = a.chunk_begin[h], nch = a.chunk_begin[h + 1] - c0;
+    const uint32_t r1 = (uint32_t)a.row_ptr[row + 1];
+    const uint32_t p0 = (uint32_t)a.row_ptr[row] + (uint32_t)((ch - c0) * a.chunk);
+    const uint32_t p1 = min(p0 + (uint32_t)a.chunk, r1);
+    const uint32_t per = (uint32_t)((a.chunk / W + STEP - 1) / STEP * STEP);
+    const uint32_t w0 = p0 + (uint32_t)wave * per, w1 = min(w0 + per, p1);
+
+    const int colbase = min(gl * C, R - C);
+    const bool odd1 = lane & 1, odd2 = lane & 2;
+    const int q = (lane & 3) ^ (G >= 8 && (lane & 4) ? 3 : 0);
+    double b[C], acc[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const bool own = colbase + c >= gl * C && colbase + c < R;
+        b[c] = own ? a.B[(int64_t)row * R + colbase + c] : 0.0;
+        acc[c] = 0.0;
+    }
+    // Other modes: a.fac[0] is the one the row's nonzeros are ordered by. While a
+    // step's nonzeros all share that coordinate (a fiber of the row), its factor
+    // row multiplies b once instead of every nonzero, and is not gathered again:
+    //   m = (b .* a) . f,  phi += a .* (sum of s f),  f the other factors' product.
+    const int nm1 = NM1 > 0 ? NM1 : a.NM1;
+    constexpr int NOFF = NM1 > 0 ? NM1 : 1;
+    uint32_t off[NOFF];
+    double x = 0.0;
+    auto load_meta = [&](uint32_t base) {
+        const uint32_t p = base + (uint32_t)(g * 4 + q);
+        const uint32_t pc = min(p, w1 - 1);
+        x = __builtin_nontemporal_load(a.vals + pc);
+        if (p >= w1) x = 0.0;
+#pragma unroll
+        for (int m = 0; m < NOFF; ++m) off[m] = __builtin_nontemporal_load(a.cofs[m] + pc);
+    };
+    uint32_t cur = 0;
+    double arow[C], bw[C], tacc[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) arow[c] = bw[c] = tacc[c] = 0.0;
+    bool have = false;
+    if (w0 < w1) load_meta(w0);
+    for (uint32_t base = w0; base < w1; base += STEP) {
+        double pi[4][C];
+        const double xc = x;
+        const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)off[0]);
+        const bool fiber = NM1 != 1 && __ballot(off[0] != first) == 0ull;
+        if (fiber && (!have || first != cur)) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                acc[c] = __builtin_fma(arow[c], tacc[c], acc[c]);
+                tacc[c] = 0.0;
+            }
+            load_cols<C>((const L*)a.fac[0], first, colbase, arow);
+#pragma unroll
+            for (int c = 0; c < C; ++c) bw[c] = b[c] * arow[c];
+            cur = first;
+            have = true;
+        }
+        if constexpr (NM1 > 0) {
+            double f[NM1][4][C];
+            auto gather = [&](int m) {
+                const L* fac = (const L*)a.fac[m];
+                load_cols<C>(fac, quad_bcast<0>(off[m]), colbase, f[m][0]);
+                load_cols<C>(fac, quad_bcast<1>(off[m]), colbase, f[m][1]);
+                load_cols<C>(fac, quad_bcast<2>(off[m]), colbase, f[m][2]);
+                load_cols<C>(fac, quad_bcast<3>(off[m]), colbase, f[m][3]);
+            };
+#pragma unroll
+            for (int m = 1; m < NM1; ++m) gather(m);
+            if (fiber) {
+                if (base + STEP < w1) load_meta(base + STEP);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        pi[j][c] = f[NM1 - 1][j][c];
+#pragma unroll
+                        for (int m = 1; m < NM1 - 1; ++m) pi[j][c] *= f[m][j][c];
+                    }
+                block4<G, C>(pi, xc, bw, a.eps, odd1, odd2, tacc);
+            } else {
+                gather(0);
+                if (base + STEP < w1) load_meta(base + STEP);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        pi[j][c] = f[0][j][c];
+#pragma unroll
+                        for (int m = 1; m < NM1; ++m) pi[j][c] *= f[m][j][c];
+                    }
+                block4<G, C>(pi, xc, b, a.eps, odd1, odd2, acc);
+            }
+        } else {
+            const uint32_t pc = min(base + (uint32_t)(g * 4 + q), w1 - 1);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int c = 0; c < C; ++c) pi[j][c] = 1.0;
+            for (int m = fiber ? 1 : 0; m < nm1; ++m) {
+                const L* fac = (const L*)a.fac[m];
+                const uint32_t o = m == 0 ? off[0] : a.cofs[m][pc];
+                double f[4][C];
+                load_cols<C>(fac, quad_bcast<0>(o), colbase, f[0]);
+                load_cols<C>(fac, quad_bcast<1>(o), colbase, f[1]);
+                load_cols<C>(fac, quad_bcast<2>(o), colbase, f[2]);
+                load_cols<C>(fac, quad_bcast<3>(o), colbase, f[3]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int c = 0; c < C; ++c) pi[j][c] *= f[j][c];
+            }
+            if (base + STEP < w1) load_meta(base + STEP);
+            if (fiber)
+                block4<G, C>(pi, xc, bw, a.eps, odd1, odd2, tacc);
+            else
+                block4<G, C>(pi, xc, b, a.eps, odd1, odd2, acc);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) acc[c] = __builtin_fma(arow[c], tacc[c], acc[c]);
+    // lane groups, then waves, in a fixed order
+#pragma unroll
+    for (int o = G; o < 64; o <<= 1)
+#pragma unroll
+        for (int c = 0; c < C; ++c) acc[c] += __shfl_xor(acc[c], o);
+    if (g == 0)
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            if (colbase + c >= gl * C && colbase + c < R) red[wave][colbase + c] = acc[c];
+    __syncthreads();
+    // The partial row goes out past the L2 of this die (other dies' workgroups
+    // may finish the row); the ticket is taken once it has arrived.
+    if (t < R) {
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) v += red[w][t];
+        __hip_atomic_store(&a.partial[(int64_t)ch * R + t], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (t == 0) {
+        const unsigned int k = __hip_atomic_fetch_add(&a.ticket[h * kCountStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = k + 1 == (unsigned int)nch;
+    }
+    __syncthreads();
+    if (!last) return;
+    // this workgroup is the row's last: sum its chunks, kBlock / rp of them in parallel
+    int rp = 1;
+    while (rp < R) rp *= 2;
+    const int lanes = kBlock / rp, c = t % rp, jj = t / rp;
+    double v = 0.0;
+    if (c < R) {
+        const double* src = a.partial + (int64_t)c0 * R + c;
+        int k = jj;
+        for (; k + 7 * lanes < nch; k += 8 * lanes) {
+            double u[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                u[i] = __hip_atomic_load(&src[(int64_t)(k + i * lanes) * R], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v += u[i];
+        }
+        for (; k < nch; k += lanes)
+            v += __hip_atomic_load(&src[(int64_t)k * R], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    fin[t] = v;
+    __syncthreads();
+    for (int w = lanes / 2; w > 0; w >>= 1) {
+        if (jj < w) fin[t] += fin[t + w * rp];
+        __syncthreads();
+    }
+    double viol = 0.0;
+    if (t < R) {
+        const int64_t e = (int64_t)row * R + t;
+        const double phi = fin[t], bb = a.B[e], r = 1.0 - phi;
+        viol = fabs(bb < r ? bb : r);
+        a.Phi[e] = phi;
+        if (a.hist != nullptr) {
+            a.hist[(int64_t)h * R + t] = bb;
+            a.hist[a.hist_stride + (int64_t)h * R + t] = phi;
+        }
+        a.B[e] = bb * phi;
+    }
+    if (t == 0) a.ticket[h * kCountStride] = 0u;
+    if (a.l >= 0 && t < 64) {
+        viol = wave_max(viol);
+        if (t == 0) atomicMax(&a.st->iv[a.l][h % kInnerSlots][0], (unsigned long long)__double_as_longlong(viol));
+    }
+}
+
+// ---- heavy rows with a second factor's hot rows in LDS ----
+
+constexpr int kHotThreads = 1024;          // one workgroup per compute unit
+constexpr int kHotLds = 140 * 1024;        // bytes of hot rows (the workgroup's sums take up to 16 KB more)
+constexpr int kMaxHot = kHotLds / 8;       // (R = 1 with FP64 rows)
+constexpr uint16_t kCold = 0xffff;
+static_assert(kMaxHot < kCold, "places fit 16 bits");
+
+struct HotArgs {
+    const uint32_t *s_lead, *s_hot, *s_third;
+    const uint16_t* s_slot;
+    const void* s_val;
+    const int4* entry;
+    const int32_t *xlist, *xbegin;
+    const int32_t* rows;      // long rows (in `order`)
+    const uint4* tab;         // the hot rows, in their places
+    int tab_vecs;             // 16-byte words of them
+    const void *lead, *hot, *third;
+    const double* B;
+    double* partial;          // [pieces x R]
+    DevState* st;
+    int R;
+    double eps;
+};
+
+// A factor's hot rows in their places, once per inner loop.
+template <typename L>
+__global__ __launch_bounds__(kBlock) void hot_table_kernel(const L* __restrict__ fac, const int32_t* __restrict__ rows,
+                                                           int nhot, int R, L* __restrict__ tab)
+{
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i < nhot * R; i += gridDim.x * kBlock)
+        tab[i] = fac[(int64_t)rows[i / R] * R + i % R];
+}
+
+template <int C, typename L>
+__device__ __forceinline__ void load_lds(const L* tab, uint32_t at, double (&v)[C])
+{
+#pragma unroll
+    for (int c = 0; c < C; ++c) v[c] = (double)tab[at + c];
+}
+
+// The partial rows of one iteration of the heavy rows, by workgroups that stay
+// on their compute unit: each copies the hot rows of one factor to LDS once,
+// then its waves take pieces of rows in turn, each on its own. In a hot piece
+// every nonzero reads that factor from LDS; the gathers past L1 (the bound of
+// heavy_kernel) are left to the other factors. The pieces of a long row go to
+// the dies by their place in the row, and a die takes them in that order, so
+// that the rows of the leading factor it gathers at a time stay in its L2.
+template <int G, int C, bool THIRD, bool MIXED, typename V>
+__global__ __launch_bounds__(kHotThreads) void hot_kernel(HotArgs a)
+{
+    using L = typename std::conditional<MIXED, float, double>::type;
+    constexpr int W = kHotThreads / 64;
+    constexpr uint32_t STEP = 4 * (64 / G);
+    extern __shared__ double2 dyn[];
+    const L* tab = (const L*)dyn;
+    if (a.st->done) return;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int gl = lane % G, g = lane / G;
+    const int R = a.R;
+#pragma unroll 5
+    for (int i = t; i < a.tab_vecs; i += kHotThreads) ((uint4*)dyn)[i] = a.tab[i];
+    const int colbase = min(gl * C, R - C);
+    const bool odd1 = lane & 1, odd2 = lane & 2;
+    const int q = (lane & 3) ^ (G >= 8 && (lane & 4) ? 3 : 0);
+    __syncthreads();
+    const int die = (int)blockIdx.x % kXcds, nb = ((int)gridDim.x - die + kXcds - 1) / kXcds;  // workgroups of this die
+    const int k1 = a.xbegin[die + 1];
+    for (int k = a.xbegin[die] + wave * nb + (int)blockIdx.x / kXcds; k < k1; k += W * nb) {
+        const int e = a.xlist[k];
+        const int4 en = a.entry[e];
+        const int row = a.rows[en.x];
+        const uint32_t w0 = (uint32_t)en.y, w1 = (uint32_t)en.z;
+        double b[C], acc[C], arow[C], bw[C], tacc[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const bool own = colbase + c >= gl * C && colbase + c < R;
+            b[c] = own ? a.B[(int64_t)row * R + colbase + c] : 0.0;
+            acc[c] = arow[c] = bw[c] = tacc[c] = 0.0;
+        }
+        auto run = [&](auto hotpart) {
+            constexpr bool HOT = decltype(hotpart)::value;
+            uint32_t ol = 0, oh = 0, o3 = 0, cur = 0;
+            double x = 0.0;
+            bool have = false;
+            auto load_meta = [&](uint32_t base) {
+                const uint32_t p = base + (uint32_t)(g * 4 + q);
+                const uint32_t pc = min(p, w1 - 1);
+                x = (double)__builtin_nontemporal_load((const V*)a.s_val + pc);
+                if (p >= w1) x = 0.0;
+                ol = __builtin_nontemporal_load(a.s_lead + pc);
+                if constexpr (HOT)
+                    oh = (uint32_t)__builtin_nontemporal_load(a.s_slot + pc) * (uint32_t)R;
+                else
+                    oh = __builtin_nontemporal_load(a.s_hot + pc);
+                if constexpr (THIRD) o3 = __builtin_nontemporal_load(a.s_third + pc);
+            };
+            if (w0 < w1) load_meta(w0);
+            for (uint32_t base = w0; base < w1; base += STEP) {
+                const double xc = x;
+                const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)ol);
+                const bool fiber = __ballot(ol != first) == 0ull;
+                if (fiber && (!have || first != cur)) {
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        acc[c] = __builtin_fma(arow[c], tacc[c], acc[c]);
+                        tacc[c] = 0.0;
+                    }
+                    load_cols<C>((const L*)a.lead, first, colbase, arow);
+#pragma unroll
+                    for (int c = 0; c < C; ++c) bw[c] = b[c] * arow[c];
+                    cur = first;
+                    have = true;
+                }
+                double pi[4][C], f[4][C];
+                if constexpr (THIRD) {
+                    const L* fac = (const L*)a.third;
+                    load_cols<C>(fac, quad_bcast<0>(o3), colbase, f[0]);
+                    load_cols<C>(fac, quad_bcast<1>(o3), colbase, f[1]);
+                    load_cols<C>(fac, quad_bcast<2>(o3), colbase, f[2]);
+                    load_cols<C>(fac, quad_bcast<3>(o3), colbase, f[3]);
+                }
+                auto second = [&]() {
+                    if constexpr (HOT) {
+                        load_lds<C>(tab, quad_bcast<0>(oh) + colbase, pi[0]);
+                        load_lds<C>(tab, quad_bcast<1>(oh) + colbase, pi[1]);
+                        load_lds<C>(tab, quad_bcast<2>(oh) + colbase, pi[2]);
+                        load_lds<C>(tab, quad_bcast<3>(oh) + colbase, pi[3]);
+                    } else {
+                        const L* fac = (const L*)a.hot;
+                        load_cols<C>(fac, quad_bcast<0>(oh), colbase, pi[0]);
+                        load_cols<C>(fac, quad_bcast<1>(oh), colbase, pi[1]);
+                        load_cols<C>(fac, quad_bcast<2>(oh), colbase, pi[2]);
+                        load_cols<C>(fac, quad_bcast<3>(oh), colbase, pi[3]);
+                    }
+                };
+                auto times = [&]() {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int c = 0; c < C; ++c) pi[j][c] *= f[j][c];
+                };
+                if (fiber) {
+                    second();
+                    if (base + STEP < w1) load_meta(base + STEP);
+                    if constexpr (THIRD) times();
+                    block4<G, C>(pi, xc, bw, a.eps, odd1, odd2, tacc);
+                } else {
+                    second();
+                    if constexpr (THIRD) times();
+                    const L* fac = (const L*)a.lead;
+                    load_cols<C>(fac, quad_bcast<0>(ol), colbase, f[0]);
+                    load_cols<C>(fac, quad_bcast<1>(ol), colbase, f[1]);
+                    load_cols<C>(fac, quad_bcast<2>(ol), colbase, f[2]);
+                    load_cols<C>(fac, quad_bcast<3>(ol), colbase, f[3]);
+                    if (base + STEP < w1) load_meta(base + STEP);
+                    times();
+                    block4<G, C>(pi, xc, b, a.eps, odd1, odd2, acc);
+                }
+            }
+        };
+        if (en.w)
+            run(std::true_type{});
+        else
+            run(std::false_type{});
+#pragma unroll
+        for (int c = 0; c < C; ++c) acc[c] = __builtin_fma(arow[c], tacc[c], acc[c]);
+#pragma unroll
+        for (int o = G; o < 64; o <<= 1)
+#pragma unroll
+            for (int c = 0; c < C; ++c) acc[c] += __shfl_xor(acc[c], o);
+        if (g == 0)
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                if (colbase + c >= gl * C && colbase + c < R) a.partial[(int64_t)e * R + colbase + c] = acc[c];
+    }
+}
+
+struct HotStep {
+    const int32_t* entry_begin;
+    const int32_t* rows;
+    const double* partial;
+    double* B;
+    double* Phi;
+    DevState* st;
+    double* hist;
+    int64_t hist_stride;
+    int R;
+    int l;
+};
+
+// After hot_kernel: a workgroup per long row sums its pieces' partial rows and
+// takes the row's MU step.
+__global__ __launch_bounds__(512) void hot_step_kernel(HotStep a)
+{
+    __shared__ double sum[8][64];
+    if (a.st->done) return;
+    const int t = threadIdx.x, lane = t & 63, R = a.R, h = blockIdx.x;
+    const int e0 = a.entry_begin[h], ne = a.entry_begin[h + 1] - e0;
+    int rp = 1;
+    while (rp < R) rp *= 2;
+    const int lanes = 512 / rp, c = t % rp, jj = t / rp;
+    double v = 0.0;
+    if (c < R) {
+        const double* src = a.partial + (int64_t)e0 * R + c;
+        int k = jj;
+        for (; k + 15 * lanes < ne; k += 16 * lanes) {  // sixteen loads in flight: the longest row is a chain of them
+            double u[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) u[i] = src[(int64_t)(k + i * lanes) * R];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v += u[i];
+        }
+        for (; k < ne; k += lanes) v += src[(int64_t)k * R];
+    }
+    for (int o = rp; o < 64; o <<= 1) v += __shfl_xor(v, o);
+    if (lane < rp) sum[t >> 6][lane] = v;
+    __syncthreads();
+    if (t >= 64) return;
+    double viol = 0.0;
+    if (t < R) {
+        const int64_t x = (int64_t)a.rows[h] * R + t;
+        double phi = 0.0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) phi += sum[w][t];
+        const double b = a.B[x], r = 1.0 - phi;
+        viol = fabs(b < r ? b : r);
+        a.Phi[x] = phi;
+        if (a.hist != nullptr) {
+            a.hist[(int64_t)h * R + t] = b;
+            a.hist[a.hist_stride + (int64_t)h * R + t] = phi;
+        }
+        a.B[x] = b * phi;
+    }
+    if (a.l >= 0) {
+        viol = wave_max(viol);
+        if (t == 0) atomicMax(&a.st->iv[a.l][h % kInnerSlots][0], (unsigned long long)__double_as_longlong(viol));
+    }
+}
+
+// End of a chunk of n iterations: the first one whose violation is below tol
+// stops the inner loop (st->rerun tells rerun_kernel which), else all n count.
+__global__ __launch_bounds__(kBlock) void decide_kernel(DevState* st, int mode, int n, int each, double tol,
+                                                        unsigned int* team_ticket, unsigned int* team_count, int teams)
+{
+    __shared__ double v[kInnerChunk];
+    const int t = threadIdx.x;
+    for (int i = t; i < teams; i += kBlock) team_count[i * kCountStride] = 0u;
+    if (t == 0) *team_ticket = 0u;
+    if (st->done) {
+        if (t == 0) st->rerun = -1;
+        return;
+    }
+    if (t < kInnerChunk) {
+        unsigned long long m = 0ull;
+        for (int j = 0; j < kInnerSlots; ++j) {
+            const unsigned long long u = st->iv[t][j][0];
+            m = u > m ? u : m;
+            st->iv[t][j][0] = 0ull;
+        }
+        v[t] = __longlong_as_double((long long)m);
+    }
+    __syncthreads();
+    if (t != 0) return;
+    int stop = -1;
+    if (each)
+        for (int l = 0; l < n && stop < 0; ++l)
+            if (v[l] < tol) stop = l;
+    const int upd = stop >= 0 ? stop : n;
+    st->last_viol[mode] = v[stop >= 0 ? stop : each ? n - 1 : 0];
+    st->rerun = stop;
+    if (stop >= 0) st->done = 1;
+    st->updates += upd;
+    st->sweep_updates += upd;
+    st->total_updates += upd;
+    st->phi_evals += stop >= 0 ? stop + 1 : n;
+}
+
+// ---- plan: rows by class ----
+
+// Row classes of a launch shape: 0..KB blocks of four nonzeros for one lane
+// group, then 2, 4, .. NG groups of a wave, then 2 and 4 waves, then heavy rows
+// (more than kTeamMax workgroups' registers) and team rows.
+struct ClassShape {
+    int KB, NG;
+};
+
+__host__ __device__ inline int class_count(ClassShape c)
+{
+    int lg = 0;
+    while ((1 << lg) < c.NG) ++lg;
+    return c.KB + lg + 5;
+}
+
+__host__ __device__ inline int class_cap(ClassShape c) { return 4 * c.KB * c.NG * (kResBlock / 64); }
+
+// Most members of a team: a quarter of the 512 workgroups that fit the device,
+// so that a kernel on each of the process's four hardware queues still has a whole
+// team running.
+constexpr int kTeamMax = 128;
+constexpr int kTeamMembers = 256;
+
+__device__ __forceinline__ int class_of(ClassShape c, int len)
+{
+    const int K = 4 * c.KB;
+    if (len <= K) return (len + 3) / 4;
+    int id = c.KB, g = 1;
+    while (g < c.NG * (kResBlock / 64) && g * K < len) {
+        g *= 2;
+        ++id;
+    }
+    if (g * K >= len) return id;
+    return len > kTeamMax * class_cap(c) ? id + 1 : id + 2;
+}
+
+// Bucket of a row length > 0, four per octave (longer rows in later buckets).
+__device__ __forceinline__ int len_bucket(int len)
+{
+    const int e = 31 - __clz(len);
+    return 4 * e + (e >= 2 ? (len >> (e - 2)) & 3 : (len << (2 - e)) & 3);
+}
+
+// First sorted position of every row (row_ptr[rows] = nnz), by binary search.
+__global__ __launch_bounds__(kBlock) void row_ptr_kernel(const int32_t* __restrict__ rows, int64_t nnz, int64_t nrows,
+                                                         int32_t* __restrict__ row_ptr)
+{
+    for (int64_t r = blockIdx.x * (int64_t)kBlock + threadIdx.x; r <= nrows; r += (int64_t)gridDim.x * kBlock) {
+        int64_t lo = 0, hi = nnz;
+        while (lo < hi) {
+            const int64_t mid = lo + (hi - lo) / 2;
+            if (rows[mid] < r)
+                lo = mid + 1;
+            else
+                hi = mid;
+        }
+        row_ptr[r] = (int32_t)lo;
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void class_hist_kernel(const int32_t* __restrict__ row_ptr, int64_t nrows,
+                                                            ClassShape cs, int* __restrict__ meta)
+{
+    __shared__ int h[kRowClasses], hr[kLenBuckets], hn[kLenBuckets];
+    if (threadIdx.x < kRowClasses) h[threadIdx.x] = 0;
+    if (threadIdx.x < kLenBuckets) hr[threadIdx.x] = hn[threadIdx.x] = 0;
+    __syncthreads();
+    for (int64_t r = blockIdx.x * (int64_t)kBlock + threadIdx.x; r < nrows; r += (int64_t)gridDim.x * kBlock) {
+        const int len = row_ptr[r + 1] - row_ptr[r];
+        atomicAdd(&h[class_of(cs, len)], 1);
+        if (len > 0) {
+            atomicAdd(&hr[len_bucket(len)], 1);
+            atomicAdd(&hn[len_bucket(len)], len);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < kRowClasses && h[threadIdx.x]) atomicAdd(&meta[threadIdx.x], h[threadIdx.x]);
+    if (threadIdx.x < kLenBuckets && hr[threadIdx.x]) {
+        atomicAdd(&meta[64 + threadIdx.x], hr[threadIdx.x]);
+        atomicAdd(&meta[64 + kLenBuckets + threadIdx.x], hn[threadIdx.x]);
+    }
+}
+
+// Counting sort of the rows by class. meta: class counts, then the classes'
+// cursors (zero before). A workgroup reserves its share of every class at
+// once; the order inside a class does not matter to any row's result.
+__global__ __launch_bounds__(kBlock) void class_scatter_kernel(const int32_t* __restrict__ row_ptr, int64_t nrows,
+                                                               ClassShape cs, int* __restrict__ meta,
+                                                               int32_t* __restrict__ order)
+{
+    __shared__ int h[kRowClasses], base[kRowClasses];
+    for (int64_t r0 = blockIdx.x * (int64_t)kBlock; r0 < nrows; r0 += (int64_t)gridDim.x * kBlock) {
+        if (threadIdx.x < kRowClasses) h[threadIdx.x] = 0;
+        __syncthreads();
+        const int64_t r = r0 + threadIdx.x;
+        int id = -1, k = 0;
+        if (r < nrows) {
+            id = class_of(cs, row_ptr[r + 1] - row_ptr[r]);
+            k = atomicAdd(&h[id], 1);
+        }
+        __syncthreads();
+        if (threadIdx.x < kRowClasses) {
+            int b = 0;
+            for (int i = 0; i < (int)threadIdx.x; ++i) b += meta[i];
+            if (h[threadIdx.x]) b += atomicAdd(&meta[kRowClasses + threadIdx.x], h[threadIdx.x]);
+            base[threadIdx.x] = b;
+        }
+        __syncthreads();
+        if (id >= 0) order[base[id] + k] = (int32_t)r;
+        __syncthreads();
+    }
+}
+
+// Rows of one class cut into pieces of at most `piece` nonzeros: the prefix of
+// their counts (begin), the piece -> row map and the total. Block 0: the long rows'
+// chunks (and the longest class's share of them), block 1: the team rows' members.
+struct Pieces {
+    int cls, ncls, piece, max_rows, max_pieces;
+    int32_t *begin, *row;
+};
+
+__global__ __launch_bounds__(1024) void pieces_kernel(const int32_t* __restrict__ row_ptr,
+                                                      const int32_t* __restrict__ order, Pieces heavy, Pieces teams,
+                                                      int* __restrict__ meta)
+{
+    const Pieces a = blockIdx.x == 0 ? heavy : teams;
+    __shared__ int scan[1024];
+    const int t = threadIdx.x;
+    int row0 = 0;
+    for (int i = 0; i < a.cls; ++i) row0 += meta[i];
+    int nheavy = 0;
+    for (int i = 0; i < a.ncls; ++i) nheavy += meta[a.cls + i];
+    nheavy = min(nheavy, a.max_rows);
+    int run = 0;
+    for (int h0 = 0; h0 < nheavy; h0 += 1024) {
+        const int h = h0 + t;
+        int n = 0;
+        if (h < nheavy) {
+            const int r = order[row0 + h];
+            n = (row_ptr[r + 1] - row_ptr[r] + a.piece - 1) / a.piece;
+        }
+        scan[t] = n;
+        __syncthreads();
+        for (int o = 1; o < 1024; o <<= 1) {
+            const int v = t >= o ? scan[t - o] : 0;
+            __syncthreads();
+            scan[t] += v;
+            __syncthreads();
+        }
+        const int begin = run + scan[t] - n;
+        if (h < nheavy) a.begin[h] = begin;
+        run += scan[1023];
+        // the map: a wave per row
+        const int lane = t & 63, w0 = t & ~63;
+        for (int k = 0; k < 64; ++k) {
+            const int b0 = __shfl(begin, k), nk = __shfl(n, k);
+            for (int i = lane; i < nk; i += 64)
+                if (b0 + i < a.max_pieces) a.row[b0 + i] = h0 + w0 + k;
+        }
+        __syncthreads();
+    }
+    if (t == 0) {
+        a.begin[nheavy] = run;
+        meta[2 * kRowClasses + blockIdx.x] = run;
+        if (blockIdx.x == 0) meta[2 * kRowClasses + 2] = a.begin[min(meta[a.cls], nheavy)];
+    }
+}
+
+// ---- plan: the long rows' nonzeros by hot and cold ----
+
+// Places of a mode's hot rows: its rows in length buckets >= bucket, in any
+// order (at most kMaxHot by the choice of the bucket).
+__global__ __launch_bounds__(kBlock) void hot_rows_kernel(const int32_t* __restrict__ row_ptr, int64_t nrows, int bucket,
+                                                          int max_hot, int* __restrict__ counter,
+                                                          uint16_t* __restrict__ hot_id, int32_t* __restrict__ hot_rows)
+{
+    for (int64_t r = blockIdx.x * (int64_t)kBlock + threadIdx.x; r < nrows; r += (int64_t)gridDim.x * kBlock) {
+        const int len = row_ptr[r + 1] - row_ptr[r];
+        uint16_t id = kCold;
+        if (len > 0 && len_bucket(len) >= bucket) {
+            const int k = atomicAdd(counter, 1);
+            if (k < max_hot) {
+                id = (uint16_t)k;
+                hot_rows[k] = (int32_t)r;
+            }
+        }
+        hot_id[r] = id;
+    }
+}
+
+struct SplitArgs {
+    const int32_t *row_ptr, *rows, *chunk_begin, *chunk_row;
+    const uint32_t *lead, *hot, *third;  // the sorted copy's offsets
+    const double* vals;
+    const uint16_t* hot_id;
+    uint32_t *s_lead, *s_hot, *s_third;
+    uint16_t* s_slot;
+    void* s_val;
+    int exact32;
+    int* hot_before;   // [chunks] hot nonzeros of the chunk, then of the row's chunks before it
+    int* row_hot;      // [long rows] hot nonzeros
+    int chunk;
+    int piece;
+    int R;
+};
+
+__device__ __forceinline__ void chunk_range(const SplitArgs& a, int ch, int* h, uint32_t* p0, uint32_t* p1)
+{
+    *h = a.chunk_row[ch];
+    const int row = a.rows[*h];
+    *p0 = (uint32_t)a.row_ptr[row] + (uint32_t)((ch - a.chunk_begin[*h]) * a.chunk);
+    *p1 = min(*p0 + (uint32_t)a.chunk, (uint32_t)a.row_ptr[row + 1]);
+}
+
+__global__ __launch_bounds__(kBlock) void split_count_kernel(SplitArgs a)
+{
+    __shared__ int sum;
+    int h;
+    uint32_t p0, p1;
+    chunk_range(a, blockIdx.x, &h, &p0, &p1);
+    if (threadIdx.x == 0) sum = 0;
+    __syncthreads();
+    int n = 0;
+    for (uint32_t p = p0 + threadIdx.x; p < p1; p += kBlock) n += a.hot_id[a.hot[p] / (uint32_t)a.R] != kCold;
+    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+    if ((threadIdx.x & 63) == 0) atomicAdd(&sum, n);
+    __syncthreads();
+    if (threadIdx.x == 0) a.hot_before[blockIdx.x] = sum;
+}
+
+// A wave per long row: exclusive prefix of its chunks' hot counts.
+__global__ __launch_bounds__(64) void split_scan_kernel(SplitArgs a)
+{
+    const int h = blockIdx.x, lane = threadIdx.x;
+    const int c0 = a.chunk_begin[h], c1 = a.chunk_begin[h + 1];
+    int run = 0;
+    for (int c = c0; c < c1; c += 64) {
+        const int v = c + lane < c1 ? a.hot_before[c + lane] : 0;
+        int incl = v;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int u = __shfl_up(incl, o);
+            if (lane >= o) incl += u;
+        }
+        if (c + lane < c1) a.hot_before[c + lane] = run + incl - v;
+        run += __shfl(incl, 63);
+    }
+    if (lane == 0) a.row_hot[h] = run;
+}
+
+// Stable partition of a chunk's nonzeros into its row's hot and cold parts.
+__global__ __launch_bounds__(kBlock) void split_scatter_kernel(SplitArgs a)
+{
+    __shared__ int wsum[kBlock / 64];
+    int h;
+    uint32_t p0, p1;
+    chunk_range(a, blockIdx.x, &h, &p0, &p1);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t start = (uint32_t)a.row_ptr[a.rows[h]];
+    uint32_t hot_at = start + (uint32_t)a.hot_before[blockIdx.x];
+    uint32_t cold_at = start + (uint32_t)a.row_hot[h] + (p0 - start) - (uint32_t)a.hot_before[blockIdx.x];
+    for (uint32_t base = p0; base < p1; base += kBlock) {
+        const uint32_t p = base + threadIdx.x;
+        const bool in = p < p1;
+        uint32_t off = 0;
+        uint16_t id = kCold;
+        if (in) {
+            off = a.hot[p];
+            id = a.hot_id[off / (uint32_t)a.R];
+        }
+        const bool ishot = id != kCold;
+        const unsigned long long m = __ballot(ishot);
+        const int below = __popcll(m & ((1ull << lane) - 1ull));
+        if (lane == 0) wsum[wave] = __popcll(m);
+        __syncthreads();
+        int before = 0, total = 0;
+        for (int w = 0; w < kBlock / 64; ++w) {
+            if (w < wave) before += wsum[w];
+            total += wsum[w];
+        }
+        before += below;
+        if (in) {
+            const uint32_t to = ishot ? hot_at + before : cold_at + (threadIdx.x - before);
+            a.s_lead[to] = a.lead[p];
+            if (ishot)
+                a.s_slot[to] = id;
+            else
+                a.s_hot[to] = off;
+            if (a.third != nullptr) a.s_third[to] = a.third[p];
+            if (a.exact32)
+                ((float*)a.s_val)[to] = (float)a.vals[p];
+            else
+                ((double*)a.s_val)[to] = a.vals[p];
+        }
+        const uint32_t n = min((uint32_t)kBlock, p1 - base);
+        hot_at += total;
+        cold_at += n - total;
+        __syncthreads();
+    }
+}
+
+// Inclusive scan over 1024 threads; *total receives the sum.
+__device__ __forceinline__ int block_scan(int v, int* wsum, int* total)
+{
+    const int t = threadIdx.x, lane = t & 63;
+    int incl = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(incl, o);
+        if (lane >= o) incl += u;
+    }
+    if (lane == 63) wsum[t >> 6] = incl;
+    __syncthreads();
+    int before = 0, all = 0;
+    for (int w = 0; w < 16; ++w) {
+        if (w < (t >> 6)) before += wsum[w];
+        all += wsum[w];
+    }
+    __syncthreads();
+    *total = all;
+    return incl + before;
+}
+
+// Place of piece i of a part of np pieces of long row h among kPlaces: its
+// position in the part, or (fewer pieces than dies) turned by the row.
+constexpr int kPlaces = 256;
+static_assert(kPlaces % kXcds == 0, "whole places per die");
+__device__ __forceinline__ int piece_place(int i, int np, int h)
+{
+    const int at = (int)(((2 * (int64_t)i + 1) * kPlaces) / (2 * (int64_t)np));
+    return np >= kXcds ? at : (at + 53 * h) % kPlaces;
+}
+
+// Pieces of the long rows' hot and cold parts (row by row), and their lists by
+// die, in the order of their places (pass 0 counts the places' pieces, pass 1
+// lists them).
+__global__ __launch_bounds__(1024) void entries_kernel(SplitArgs a, int nlong, int max_entries, int4* __restrict__ entry,
+                                                       int32_t* __restrict__ entry_begin, int32_t* __restrict__ xlist,
+                                                       int32_t* __restrict__ xbegin)
+{
+    struct Row {
+        int begin, n, nh;
+        uint32_t p0, pm, p1;
+    };
+    __shared__ Row sh[1024];
+    __shared__ int wsum[16], place_n[kPlaces], place_at[kPlaces], many[1024], nmany;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (t < kPlaces) place_n[t] = 0;
+    __syncthreads();
+    for (int pass = 0; pass < 2; ++pass) {
+        int run = 0;
+        for (int h0 = 0; h0 < nlong; h0 += 1024) {
+            const int h = h0 + t;
+            int n = 0, nh = 0;
+            uint32_t p0 = 0, pm = 0, p1 = 0;
+            if (h < nlong) {
+                const int r = a.rows[h];
+                p0 = (uint32_t)a.row_ptr[r];
+                p1 = (uint32_t)a.row_ptr[r + 1];
+                pm = p0 + (uint32_t)a.row_hot[h];
+                nh = (int)((pm - p0 + a.piece - 1) / a.piece);
+                n = nh + (int)((p1 - pm + a.piece - 1) / a.piece);
+            }
+            int all;
+            const int begin = run + block_scan(n, wsum, &all) - n;
+            if (h < nlong && pass == 0) entry_begin[h] = min(begin, max_entries);
+            run += all;
+            sh[t] = {begin, n, nh, p0, pm, p1};
+            if (t == 0) nmany = 0;
+            __syncthreads();
+            if (n > 512) many[atomicAdd(&nmany, 1)] = t;
+            __syncthreads();
+            // Rows of many pieces by all waves, one row after the other, then a wave per row.
+            const int rows = min(1024, nlong - h0), nm = nmany;
+            for (int r = 0; r < nm + (rows - wave + 15) / 16; ++r) {
+                const bool all16 = r < nm;
+                const int k = all16 ? many[r] : wave + 16 * (r - nm);
+                if (!all16 && sh[k].n > 512) continue;
+                const int first = all16 ? wave * 64 : 0, step = all16 ? 1024 : 64;
+                const int b0 = sh[k].begin, nk = min(sh[k].n, max_entries - b0), nhk = sh[k].nh, hk = h0 + k;
+                const uint32_t q0 = sh[k].p0, qm = sh[k].pm, q1 = sh[k].p1;
+                for (int i0 = first; i0 < nk; i0 += step) {
+                    const int i = i0 + lane;
+                    const bool in = i < nk, hot = i < nhk;
+                    const int ip = hot ? i : i - nhk;
+                    const int d = in ? piece_place(ip, hot ? nhk : sh[k].n - nhk, hk) : -1;
+                    // neighbours of one place are counted together
+                    const int prev = __shfl_up(d, 1);
+                    const unsigned long long starts = __ballot(lane == 0 || d != prev);
+                    const int lead = 63 - __clzll(starts & (~0ull >> (63 - lane)));
+                    const unsigned long long after = lead < 63 ? starts >> (lead + 1) : 0ull;
+                    const int len = after ? __ffsll(after) : 64 - lead;
+                    int at = 0;
+                    if (in && lane == lead) at = atomicAdd(pass == 0 ? &place_n[d] : &place_at[d], len);
+                    at = __shfl(at, lead) + lane - lead;
+                    if (!in) continue;
+                    if (pass == 0) {
+                        const uint32_t lo = (hot ? q0 : qm) + (uint32_t)(ip * a.piece);
+                        entry[b0 + i] =
+                            make_int4(hk, (int)lo, (int)min(lo + (uint32_t)a.piece, hot ? qm : q1), hot ? 1 : 0);
+                    } else if (at < max_entries) {
+                        xlist[at] = b0 + i;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+        __syncthreads();
+        if (pass == 0 && t == 0) {
+            entry_begin[nlong] = min(run, max_entries);
+            int at = 0;
+            for (int d = 0; d < kPlaces; ++d) {
+                if (d % (kPlaces / kXcds) == 0) xbegin[d / (kPlaces / kXcds)] = at;
+                place_at[d] = at;
+                at += place_n[d];
+            }
+            xbegin[kXcds] = at;
+        }
+        __syncthreads();
+    }
+}
+
+// Launch shape of the resident rows by rank: lanes per row and columns per
+// lane so that few lanes idle, and as many nonzeros per lane group as leave the
+// pi rows within 160 of a lane's 256 registers.
+struct Shape {
+    int G, C, K;
+};
+
+bool row_shape(int R, Shape* s)
+{
+    if (R <= 4)
+        *s = {4, 1, 32};
+    else if (R <= 8)
+        *s = {4, 2, 32};
+    else if (R <= 12)
+        *s = {4, 3, 24};
+    else if (R <= 16)
+        *s = {4, 4, 20};
+    else if (R <= 24)
+        *s = {8, 3, 24};
+    else if (R <= 32)
+        *s = {8, 4, 20};
+    else if (R <= 48)
+        *s = {16, 3, 24};
+    else if (R <= 64)
+        *s = {16, 4, 20};
+    else
+        return false;
+    return true;
+}
+
+template <typename F>
+Error by_row_shape(const Shape& s, F&& f)
+{
+    using std::integral_constant;
+#define CPAPR_ROW(GG, CC, KK)                   if (s.G == GG && s.C == CC)                     return f(integral_constant<int, GG>{}, integral_constant<int, CC>{}, integral_constant<int, KK>{});
+    CPAPR_ROW(4, 1, 32)
+    CPAPR_ROW(4, 2, 32)
+    CPAPR_ROW(4, 3, 24)
+    CPAPR_ROW(4, 4, 20)
+    CPAPR_ROW(8, 3, 24)
+    CPAPR_ROW(8, 4, 20)
+    CPAPR_ROW(16, 3, 24)
+    CPAPR_ROW(16, 4, 20)
+#undef CPAPR_ROW
+    return {CPAPR_EUNSUPPORTED, "no resident-row kernel for this rank"};
+}
+
+ClassShape class_shape(const Shape& s) { return {s.K / 4, 64 / s.G}; }
+
+// Heavy rows' shape: the Phi kernel's lanes per nonzero (wider gathers), at
+// columns per lane that fit the rank.
+Shape heavy_shape(int R, bool mixed)
+{
+    if (R <= 4) return {4, 1, 0};
+    if (R <= 8) return {8, 1, 0};
+    if (R <= 16) return {4, 4, 0};
+    if (R <= 24) return {8, 3, 0};
+    if (R <= 32) return mixed ? Shape{8, 4, 0} : Shape{16, 2, 0};
+    if (R <= 48) return {16, 3, 0};
+    return {16, 4, 0};
+}
+
+template <bool MIXED, typename F>
+Error by_heavy_shape(const Shape& s, F&& f)
+{
+    using std::integral_constant;
+#define CPAPR_HVY(GG, CC)     if (s.G == GG && s.C == CC) return f(integral_constant<int, GG>{}, integral_constant<int, CC>{});
+    CPAPR_HVY(4, 1)
+    CPAPR_HVY(8, 1)
+    CPAPR_HVY(4, 4)
+    CPAPR_HVY(8, 3)
+    if constexpr (MIXED) {
+        CPAPR_HVY(8, 4)
+    } else {
+        CPAPR_HVY(16, 2)
+    }
+    CPAPR_HVY(16, 3)
+    CPAPR_HVY(16, 4)
+#undef CPAPR_HVY
+    return {CPAPR_EUNSUPPORTED, "no heavy-row kernel for this rank"};
+}
+
+// Nonzeros per heavy chunk: ~1000 chunks for a small tensor, 2048 for a large one.
+int heavy_chunk(int64_t nnz)
+{
+    int c = 256;
+    while (c < 2048 && (int64_t)c * 2 * 1024 <= nnz) c *= 2;
+    return c;
+}
+
+// Bounds on the rows longer than a workgroup's registers, the chunks of the
+// heavy ones and the members of the teams.
+int64_t max_long(int64_t nnz, const Shape& s) { return nnz / (class_cap(class_shape(s)) + 1); }
+int64_t max_chunks(int64_t nnz, const Shape& s)
+{
+    return nnz / heavy_chunk(nnz) + max_long(nnz, s);
+}
+// Nonzeros a wave of hot_kernel takes at a time: about eight pieces per wave,
+// so that the last round of pieces is a small part of the launch.
+int hot_piece(int64_t nnz)
+{
+    int c = 256;
+    while (c < 4096 && (int64_t)c * 2 * 32768 <= nnz) c *= 2;
+    return c;
+}
+int64_t max_entries(int64_t nnz, const Shape& s) { return nnz / hot_piece(nnz) + 2 * max_long(nnz, s); }
+int64_t max_partials(int64_t nnz, const Shape& s) { return std::max(max_chunks(nnz, s), max_entries(nnz, s)); }
+
+// Tensors whose long rows may be split by hot rows: three- and four-way ones of
+// at least 2^20 nonzeros (below, the launches weigh more than the gathers).
+bool hot_supported(int N, int64_t nnz, int R)
+{
+    Shape s;
+    return (N == 3 || N == 4) && nnz >= (1 << 20) && row_shape(R, &s);
+}
+int64_t max_members(int64_t nnz, const Shape& s) { return nnz / class_cap(class_shape(s)) + max_long(nnz, s); }
+
+}  // namespace
+
+bool rows_supported(int R, int method)
+{
+    Shape s;
+    return method == CPAPR_METHOD_MU && row_shape(R, &s);
+}
+
+size_t rows_mode_bind(RowPlan* r, char* base, int64_t nnz, int64_t dim, int R)
+{
+    Shape s;
+    if (!row_shape(R, &s)) return 0;
+    size_t at = 0;
+    auto take = [&](int64_t n) {
+        char* q = base != nullptr ? base + at : nullptr;
+        at += align256((size_t)n * 4);
+        return (int32_t*)q;
+    };
+    RowPlan o{};
+    o.row_ptr = take(dim + 1);
+    o.order = take(dim);
+    o.chunk_begin = take(max_long(nnz, s) + 1);
+    o.chunk_row = take(max_chunks(nnz, s) + 1);
+    o.team_begin = take(max_long(nnz, s) + 1);
+    o.team_row = take(max_members(nnz, s) + 1);
+    if (r != nullptr) *r = o;
+    return at;
+}
+
+size_t rows_state_bind(RowState* r, char* base, int64_t nnz, int64_t maxI, int R, bool stops)
+{
+    Shape s;
+    if (!row_shape(R, &s)) return 0;
+    const int64_t nl = max_long(nnz, s);
+    size_t at = 0;
+    auto take = [&](int64_t bytes) {
+        char* q = base != nullptr ? base + at : nullptr;
+        at += align256((size_t)bytes);
+        return q;
+    };
+    RowState o{};
+    o.partial = (double*)take(max_partials(nnz, s) * R * 8);
+    o.team_part = (double*)take(3 * max_members(nnz, s) * R * 8);
+    o.tickets = (1 + 2 * nl) * kCountStride;
+    o.ticket = (unsigned int*)take(o.tickets * 4);
+    o.split = (int*)take((max_chunks(nnz, s) + nl + CPAPR_MAX_MODES) * 4);
+    o.hot_tab = (double*)take(kHotLds);
+    if (stops) {
+        o.B0 = (double*)take(maxI * R * 8);
+        o.hist = (double*)take(2 * kInnerChunk * nl * R * 8);
+    }
+    if (r != nullptr) *r = o;
+    return at;
+}
+
+size_t rows_hot_bind(cpapr_plan* P, char* base, int N, int64_t nnz, const int64_t* dims, int R)
+{
+    if (!hot_supported(N, nnz, R)) return 0;
+    Shape s;
+    row_shape(R, &s);
+    size_t at = 0;
+    auto take = [&](int64_t bytes) {
+        char* q = base != nullptr ? base + at : nullptr;
+        at += align256((size_t)bytes);
+        return q;
+    };
+    for (int n = 0; n < N; ++n) {
+        uint32_t* lead = (uint32_t*)take(nnz * 4);
+        uint32_t* hot = (uint32_t*)take(nnz * 4);
+        uint32_t* third = N == 4 ? (uint32_t*)take(nnz * 4) : nullptr;
+        uint16_t* slot = (uint16_t*)take(nnz * 2);
+        void* val = take(nnz * 8);
+        int32_t* xlist = (int32_t*)take((max_entries(nnz, s) + 1) * 4);
+        int32_t* xbegin = (int32_t*)take((kXcds + 1) * 4);
+        int4* entry = (int4*)take((max_entries(nnz, s) + 1) * 16);
+        int32_t* begin = (int32_t*)take((max_long(nnz, s) + 1) * 4);
+        uint16_t* id = (uint16_t*)take(dims[n] * 2);
+        int32_t* rows = (int32_t*)take((int64_t)kMaxHot * 4);
+        if (P != nullptr) {
+            RowPlan& r = P->mode[n].rp;
+            r.s_lead = lead;
+            r.s_hot = hot;
+            r.s_third = third;
+            r.s_slot = slot;
+            r.s_val = val;
+            r.xlist = xlist;
+            r.xbegin = xbegin;
+            r.entry = entry;
+            r.entry_begin = begin;
+            r.hot_id = id;
+            r.hot_rows = rows;
+        }
+    }
+    return at;
+}
+
+Error rows_hot_build(cpapr_plan* P, hipStream_t s)
+{
+    int dev = 0;
+    CPAPR_HIP(hipGetDevice(&dev));
+    CPAPR_HIP(hipDeviceGetAttribute(&P->rs.cus, hipDeviceAttributeMultiprocessorCount, dev));
+    if (!hot_supported(P->N, P->nnz, P->R)) return {CPAPR_OK, ""};
+    Shape sh;
+    row_shape(P->R, &sh);
+    const int word = P->params.precision == CPAPR_MIXED ? 4 : 8;
+    const int fit = kHotLds / (P->R * word);
+    const int ncls = class_count(class_shape(sh));
+    // every mode's hot rows: as many of its longest length buckets as fit
+    int bucket[CPAPR_MAX_MODES], nhot[CPAPR_MAX_MODES];
+    double share[CPAPR_MAX_MODES];
+    bool made[CPAPR_MAX_MODES] = {};
+    for (int m = 0; m < P->N; ++m) {
+        const RowPlan& r = P->mode[m].rp;
+        bucket[m] = kLenBuckets;
+        nhot[m] = 0;
+        int64_t mass = 0;
+        while (bucket[m] > 0 && nhot[m] + r.rows_in[bucket[m] - 1] <= fit) {
+            --bucket[m];
+            nhot[m] += r.rows_in[bucket[m]];
+            mass += r.nnz_in[bucket[m]];
+        }
+        share[m] = (double)mass / (double)P->nnz;
+    }
+    int* counters = P->rs.split;
+    Error e = launch_fill((double*)counters, CPAPR_MAX_MODES / 2, 0.0, nullptr, s);
+    if (e.code) return e;
+    for (int n = 0; n < P->N; ++n) {
+        RowPlan& r = P->mode[n].rp;
+        if (r.use_teams || r.nchunks_all == 0) continue;
+        int lead = -1, hot = -1;
+        for (int m = 0; m < P->N; ++m)
+            if (m != n && (lead < 0 || P->dims[m] > P->dims[lead])) lead = m;
+        for (int m = 0; m < P->N; ++m)
+            if (m != n && m != lead && (hot < 0 || share[m] > share[hot])) hot = m;
+        if (share[hot] < 0.25) continue;
+        const RowPlan& rh = P->mode[hot].rp;
+        if (!made[hot]) {
+            hot_rows_kernel<<<(unsigned)std::min<int64_t>(cdiv(P->dims[hot], kBlock), 1024), kBlock, 0, s>>>(
+                rh.row_ptr, P->dims[hot], bucket[hot], nhot[hot], counters + hot, rh.hot_id, rh.hot_rows);
+            CPAPR_LAUNCHED();
+            made[hot] = true;
+        }
+        int first = 0;
+        for (int i = 0; i < ncls - 2; ++i) first += r.count[i];
+        SplitArgs a{};
+        a.row_ptr = r.row_ptr;
+        a.rows = r.order + first;
+        a.chunk_begin = r.chunk_begin;
+        a.chunk_row = r.chunk_row;
+        int third = -1;
+        for (int m = 0, k = 0; m < P->N; ++m) {
+            if (m == n) continue;
+            const uint32_t* c = P->mode[n].cofs + (int64_t)k++ * P->nnz;
+            if (m == lead)
+                a.lead = c;
+            else if (m == hot)
+                a.hot = c;
+            else {
+                a.third = c;
+                third = m;
+            }
+        }
+        a.vals = P->mode[n].vals;
+        a.hot_id = rh.hot_id;
+        a.s_lead = r.s_lead;
+        a.s_hot = r.s_hot;
+        a.s_third = r.s_third;
+        a.s_slot = r.s_slot;
+        a.s_val = r.s_val;
+        a.exact32 = P->exact32 ? 1 : 0;
+        a.hot_before = P->rs.split + CPAPR_MAX_MODES;
+        a.row_hot = a.hot_before + max_chunks(P->nnz, sh);
+        a.chunk = heavy_chunk(P->nnz);
+        a.piece = hot_piece(P->nnz);
+        a.R = P->R;
+        split_count_kernel<<<r.nchunks_all, kBlock, 0, s>>>(a);
+        CPAPR_LAUNCHED();
+        split_scan_kernel<<<r.nlong, 64, 0, s>>>(a);
+        CPAPR_LAUNCHED();
+        split_scatter_kernel<<<r.nchunks_all, kBlock, 0, s>>>(a);
+        CPAPR_LAUNCHED();
+        entries_kernel<<<1, 1024, 0, s>>>(a, r.nlong, (int)max_entries(P->nnz, sh), r.entry, r.entry_begin,
+                                           r.xlist, r.xbegin);
+        CPAPR_LAUNCHED();
+        auto allow = [&](auto M) -> Error {  // more than 64 KB of LDS is asked for
+            constexpr bool MX = decltype(M)::value;
+            return by_heavy_shape<MX>(heavy_shape(P->R, MX), [&](auto G, auto C) -> Error {
+                constexpr int GG = decltype(G)::value, CC = decltype(C)::value;
+                const void* f = third >= 0 ? P->exact32 ? (const void*)hot_kernel<GG, CC, true, MX, float>
+                                                        : (const void*)hot_kernel<GG, CC, true, MX, double>
+                                : P->exact32 ? (const void*)hot_kernel<GG, CC, false, MX, float>
+                                             : (const void*)hot_kernel<GG, CC, false, MX, double>;
+                CPAPR_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kHotLds));
+                return {CPAPR_OK, ""};
+            });
+        };
+        e = word == 4 ? allow(std::true_type{}) : allow(std::false_type{});
+        if (e.code) return e;
+        r.lead = lead;
+        r.hot = hot;
+        r.third = third;
+        r.nhot = nhot[hot];
+    }
+    return {CPAPR_OK, ""};
+}
+
+// Rows of one mode by class, from its sorted copy. meta: kRowMeta zeroed ints on
+// the device; rows_finish takes their host copy.
+Error rows_build(const cpapr_plan* P, int mode, int* meta, hipStream_t s)
+{
+    Shape sh;
+    if (!row_shape(P->R, &sh)) return {CPAPR_OK, ""};
+    const RowPlan& r = P->mode[mode].rp;
+    const int64_t nrows = P->dims[mode];
+    const ClassShape cs = class_shape(sh);
+    const unsigned grid = (unsigned)std::min<int64_t>(cdiv(nrows + 1, kBlock), 4096);
+    row_ptr_kernel<<<grid, kBlock, 0, s>>>(P->mode[mode].rows, P->nnz, nrows, r.row_ptr);
+    CPAPR_LAUNCHED();
+    class_hist_kernel<<<std::min(grid, 1024u), kBlock, 0, s>>>(r.row_ptr, nrows, cs, meta);
+    CPAPR_LAUNCHED();
+    class_scatter_kernel<<<std::min(grid, 1024u), kBlock, 0, s>>>(r.row_ptr, nrows, cs, meta, r.order);
+    CPAPR_LAUNCHED();
+    if (max_long(P->nnz, sh) > 0) {
+        const int n = class_count(cs), nl = (int)max_long(P->nnz, sh);
+        const Pieces heavy{n - 2, 2, heavy_chunk(P->nnz), nl, (int)max_chunks(P->nnz, sh), r.chunk_begin, r.chunk_row};
+        const Pieces teams{n - 1, 1, class_cap(cs), nl, (int)max_members(P->nnz, sh), r.team_begin, r.team_row};
+        pieces_kernel<<<2, 1024, 0, s>>>(r.row_ptr, r.order, heavy, teams, meta);
+        CPAPR_LAUNCHED();
+    }
+    return {CPAPR_OK, ""};
+}
+
+void rows_finish(cpapr_plan* P, int mode, const int* meta)
+{
+    Shape sh;
+    if (!row_shape(P->R, &sh)) return;
+    RowPlan& r = P->mode[mode].rp;
+    const int n = class_count(class_shape(sh));
+    for (int i = 0; i < kRowClasses; ++i) r.count[i] = i < n ? meta[i] : 0;
+    r.nlong = r.count[n - 2] + r.count[n - 1];
+    r.nchunks_all = meta[2 * kRowClasses];
+    r.nmembers = meta[2 * kRowClasses + 1];
+    // Teams where all their members fit the device at once (half of its 512
+    // workgroups, the light rows beside them): then an iteration costs one
+    // meeting instead of a launch (600k nonzeros: 92 us per inner loop of ten against
+    // 195). With more members than that the heavy kernels are faster.
+    r.use_teams = r.nmembers > 0 && r.nmembers <= kTeamMembers;
+    r.nchunks = r.use_teams ? meta[2 * kRowClasses + 2] : r.nchunks_all;
+    for (int i = 0; i < kLenBuckets; ++i) {
+        r.rows_in[i] = meta[64 + i];
+        r.nnz_in[i] = meta[64 + kLenBuckets + i];
+    }
+    r.hot = -1;
+    P->mode[mode].segments = P->dims[mode] - r.count[0];
+}
+
+Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, hipStream_t s)
+{
+    Shape sh;
+    if (!row_shape(P->R, &sh)) return {CPAPR_EUNSUPPORTED, "no resident-row kernel for this rank"};
+    const ClassShape cs = class_shape(sh);
+    const PlanMode& pm = P->mode[mode];
+    const RowPlan& r = pm.rp;
+    const bool mixed = P->params.precision == CPAPR_MIXED;
+    const bool each = P->params.tol > 0.0;
+    const int NG = cs.NG, W = kResBlock / 64;
+
+    ResArgs a{};
+    a.cofs = pm.cofs;
+    a.vals = pm.vals;
+    a.row_ptr = r.row_ptr;
+    a.order = r.order;
+    a.B = B;
+    a.Phi = Phi;
+    a.st = P->state;
+    a.nnz = P->nnz;
+    a.eps = P->params.eps;
+    a.R = P->R;
+    a.NM1 = P->N - 1;
+    a.each = each ? 1 : 0;
+    int j = 0;
+    for (int m = 0; m < P->N; ++m)
+        if (m != mode) a.fac[j++] = fac[m];
+    // classes in launch order: the longest rows first
+    const int ncls = class_count(cs), nlight = ncls - 2;
+    int begin[kRowClasses] = {}, at = 0;
+    for (int i = 0; i < ncls; ++i) {
+        begin[i] = at;
+        at += r.count[i];
+    }
+    int64_t blocks = 0;
+    for (int i = nlight - 1; i >= 0; --i) {
+        if (r.count[i] == 0) continue;
+        const int S = i <= cs.KB ? 1 : 1 << (i - cs.KB);
+        const int per = std::max(1, W * NG / S);  // rows per workgroup
+        a.entry[a.nentries++] = {(int32_t)blocks, begin[i], r.count[i], S};
+        blocks += cdiv(r.count[i], per);
+    }
+    if (blocks + a.team_blocks > 0x7fffffff) return {CPAPR_EUNSUPPORTED, "too many rows"};
+    a.light_blocks = (int)blocks;
+    a.heavy0 = begin[nlight];
+    a.team0 = r.count[nlight];
+    a.nheavy = r.count[nlight] + r.count[nlight + 1];
+    a.team_blocks = r.use_teams ? r.nmembers : 0;
+    a.team_begin = r.team_begin;
+    a.team_row = r.team_row;
+    a.team_part = P->rs.team_part;
+    a.team_ticket = P->rs.ticket;
+    a.team_count = P->rs.ticket + kCountStride;
+    a.team_wait = P->team_wait;
+    a.hist = P->rs.hist;
+    a.hist_stride = (int64_t)a.nheavy * P->R;
+    a.B0 = each ? P->rs.B0 : nullptr;
+
+    HeavyArgs h{};
+    h.vals = pm.vals;
+    h.row_ptr = r.row_ptr;
+    h.rows = r.order + a.heavy0;
+    h.chunk_begin = r.chunk_begin;
+    h.chunk_row = r.chunk_row;
+    // the mode the rows are ordered by (the largest other one, the first on ties) leads
+    int lead = 0, k = 0;
+    int64_t most = -1;
+    for (int m = 0; m < P->N; ++m)
+        if (m != mode) {
+            if (P->dims[m] > most) {
+                most = P->dims[m];
+                lead = k;
+            }
+            ++k;
+        }
+    for (int m = 0, at1 = 1; m < P->N - 1; ++m) {
+        const int to = m == lead ? 0 : at1++;
+        h.fac[to] = a.fac[m];
+        h.cofs[to] = pm.cofs + (int64_t)m * P->nnz;
+    }
+    h.B = B;
+    h.Phi = Phi;
+    h.partial = P->rs.partial;
+    h.ticket = P->rs.ticket + (1 + r.count[nlight + 1]) * kCountStride;
+    h.st = P->state;
+    h.hist_stride = a.hist_stride;
+    h.nnz = P->nnz;
+    h.eps = P->params.eps;
+    h.R = P->R;
+    h.NM1 = P->N - 1;
+    h.chunk = heavy_chunk(P->nnz);
+
+    const int lmax = P->params.lmax;
+    const int step = each ? kInnerChunk : lmax;
+    prof_begin(mode, s);  // one record per inner loop
+    for (int l0 = 0; l0 < lmax; l0 += step) {
+        const int n = std::min(step, lmax - l0);
+        Error e{CPAPR_OK, ""};
+        if (r.nchunks > 0 && r.hot >= 0) {
+            HotArgs k{};
+            k.s_lead = r.s_lead;
+            k.s_hot = r.s_hot;
+            k.s_third = r.s_third;
+            k.s_val = r.s_val;
+            k.s_slot = r.s_slot;
+            k.entry = r.entry;
+            k.xlist = r.xlist;
+            k.xbegin = r.xbegin;
+            k.rows = h.rows;
+            k.tab = (const uint4*)P->rs.hot_tab;
+            k.tab_vecs = (int)cdiv((int64_t)r.nhot * P->R * (mixed ? 4 : 8), 16);
+            k.lead = fac[r.lead];
+            k.hot = fac[r.hot];
+            k.third = r.third >= 0 ? fac[r.third] : nullptr;
+            k.B = B;
+            k.partial = h.partial;
+            k.st = P->state;
+            k.eps = h.eps;
+            k.R = P->R;
+            HotStep hs{r.entry_begin, h.rows, h.partial, B, Phi, P->state, nullptr, h.hist_stride, P->R, -1};
+            const size_t lds = (size_t)k.tab_vecs * 16;
+            if (l0 == 0) {
+                const int32_t* rows = P->mode[r.hot].rp.hot_rows;
+                const unsigned tg = (unsigned)cdiv((int64_t)r.nhot * P->R, kBlock);
+                if (mixed)
+                    hot_table_kernel<<<tg, kBlock, 0, s>>>((const float*)k.hot, rows, r.nhot, P->R, (float*)P->rs.hot_tab);
+                else
+                    hot_table_kernel<<<tg, kBlock, 0, s>>>((const double*)k.hot, rows, r.nhot, P->R, P->rs.hot_tab);
+                CPAPR_LAUNCHED();
+            }
+            for (int l = 0; l < n; ++l) {
+                auto launch = [&](auto M) -> Error {
+                    constexpr bool MX = decltype(M)::value;
+                    return by_heavy_shape<MX>(heavy_shape(P->R, mixed), [&](auto G, auto C) -> Error {
+                        constexpr int GG = decltype(G)::value, CC = decltype(C)::value;
+                        if (r.third >= 0 && P->exact32)
+                            hot_kernel<GG, CC, true, MX, float><<<P->rs.cus, kHotThreads, lds, s>>>(k);
+                        else if (r.third >= 0)
+                            hot_kernel<GG, CC, true, MX, double><<<P->rs.cus, kHotThreads, lds, s>>>(k);
+                        else if (P->exact32)
+                            hot_kernel<GG, CC, false, MX, float><<<P->rs.cus, kHotThreads, lds, s>>>(k);
+                        else
+                            hot_kernel<GG, CC, false, MX, double><<<P->rs.cus, kHotThreads, lds, s>>>(k);
+                        CPAPR_LAUNCHED();
+                        return {CPAPR_OK, ""};
+                    });
+                };
+                e = mixed ? launch(std::true_type{}) : launch(std::false_type{});
+                if (e.code) return e;
+                hs.l = each ? l : l + 1 == n ? 0 : -1;
+                hs.hist = each ? P->rs.hist + (int64_t)2 * l * h.hist_stride : nullptr;
+                hot_step_kernel<<<r.nlong, 512, 0, s>>>(hs);
+                CPAPR_LAUNCHED();
+            }
+        } else if (r.nchunks > 0) {
+            const Shape hs = heavy_shape(P->R, mixed);
+            for (int l = 0; l < n; ++l) {
+                h.l = each ? l : l + 1 == n ? 0 : -1;
+                h.hist = each ? P->rs.hist + (int64_t)2 * l * h.hist_stride : nullptr;
+                auto launch = [&](auto M) -> Error {
+                    constexpr bool MX = decltype(M)::value;
+                    return by_heavy_shape<MX>(hs, [&](auto G, auto C) -> Error {
+                        constexpr int GG = decltype(G)::value, CC = decltype(C)::value;
+                        const dim3 grid((unsigned)r.nchunks);
+                        switch (h.NM1) {
+                            case 1: heavy_kernel<GG, CC, 1, MX><<<grid, kBlock, 0, s>>>(h); break;
+                            case 2: heavy_kernel<GG, CC, 2, MX><<<grid, kBlock, 0, s>>>(h); break;
+                            case 3: heavy_kernel<GG, CC, 3, MX><<<grid, kBlock, 0, s>>>(h); break;
+                            default: heavy_kernel<GG, CC, 0, MX><<<grid, kBlock, 0, s>>>(h); break;
+                        }
+                        CPAPR_LAUNCHED();
+                        return {CPAPR_OK, ""};
+                    });
+                };
+                e = mixed ? launch(std::true_type{}) : launch(std::false_type{});
+                if (e.code) return e;
+            }
+        }
+        a.n_it = n;
+        auto light = [&](bool rerun) {
+            return by_row_shape(sh, [&](auto G, auto C, auto K) -> Error {
+                constexpr int GG = decltype(G)::value, CC = decltype(C)::value, KK = decltype(K)::value;
+                if (rerun) {
+                    const dim3 grid((unsigned)(blocks + cdiv((int64_t)a.nheavy * P->R, kResBlock)));
+                    if (mixed)
+                        rerun_kernel<GG, CC, KK, true><<<grid, kResBlock, 0, s>>>(a);
+                    else
+                        rerun_kernel<GG, CC, KK, false><<<grid, kResBlock, 0, s>>>(a);
+                } else if (mixed) {
+                    resident_kernel<GG, CC, KK, true><<<(unsigned)(blocks + a.team_blocks), kResBlock, 0, s>>>(a);
+                } else {
+                    resident_kernel<GG, CC, KK, false><<<(unsigned)(blocks + a.team_blocks), kResBlock, 0, s>>>(a);
+                }
+                CPAPR_LAUNCHED();
+                return {CPAPR_OK, ""};
+            });
+        };
+        if (blocks + a.team_blocks > 0) e = light(false);
+        if (e.code) return e;
+        decide_kernel<<<1, kBlock, 0, s>>>(P->state, mode, n, each ? 1 : 0, P->params.tol, P->rs.ticket,
+                                          P->rs.ticket + kCountStride, r.use_teams ? r.count[ncls - 1] : 0);
+        CPAPR_LAUNCHED();
+        if (each) e = light(true);
+        if (e.code) return e;
+    }
+    prof_end(s);
+    return {CPAPR_OK, ""};
+}
+
+}  // namespace cpapr

@@ -18,6 +18,7 @@
 // addresses. Stability keeps nonzeros of equal keys in input order, so plans
 // and Phi are deterministic.
 #include <algorithm>
+#include <cstring>
 
 #include "internal.hpp"
 
@@ -401,7 +402,7 @@ int64_t sort_scratch_bytes(int64_t nnz, int N)
     b += 4 * align256((size_t)nnz * 4);                     // keys/payload ping-pong
     b += align256((size_t)ncounts * 4);                     // histogram table
     b += align256((size_t)(cdiv(ntiles, kScanTiles) + 1) * kRadix * 4);  // offsets scan: group sums, digit bases
-    b += 256;                                                // flags / counters
+    b += align256(256 + CPAPR_MAX_MODES * kRowMeta * 4);     // flags / counters, row class counts
     b += align256(kSegPartials * 8);                         // segment-count partials
     return (int64_t)b;
 }
@@ -426,12 +427,13 @@ Error build_sorted(cpapr_plan* P, const cpapr_coo* X, char* scratch, hipStream_t
     int32_t* pb = (int32_t*)take((size_t)nnz * 4);
     int* counts = (int*)take((size_t)ncounts * 4);
     int* part = (int*)take((size_t)(cdiv(ntiles, kScanTiles) + 1) * kRadix * 4);
-    int* flags = (int*)take(256);
+    int* flags = (int*)take(256 + CPAPR_MAX_MODES * kRowMeta * 4);
+    int* meta = flags + 64;  // kRowMeta ints per mode
     unsigned long long* segc = (unsigned long long*)(flags + 8);
     unsigned long long* segpart = (unsigned long long*)take(kSegPartials * 8);
 
     // flags and segment counters start at zero (plain kernel-free path: a tiny fill)
-    CPAPR_HIP(hipMemsetAsync(flags, 0, 256, s));
+    CPAPR_HIP(hipMemsetAsync(flags, 0, 256 + CPAPR_MAX_MODES * kRowMeta * 4, s));
     if (nnz > 0) {
         DimsArg d{};
         for (int m = 0; m < N; ++m) d.d[m] = P->dims[m];
@@ -446,6 +448,7 @@ Error build_sorted(cpapr_plan* P, const cpapr_coo* X, char* scratch, hipStream_t
     CPAPR_HIP(hipStreamSynchronize(s));
     if (hflags & 1) return {CPAPR_EINDEX, "a coordinate lies outside its mode's range"};
     if (hflags & 2) return {CPAPR_EVALUE, "a tensor value is not finite and positive"};
+    P->exact32 = !(hflags & 4);
     if (hflags & 4)  // some value is not exact in FP32: the kernels read the arrays
         for (int n = 0; n < N; ++n) P->mode[n].pk = nullptr;
 
@@ -454,6 +457,10 @@ Error build_sorted(cpapr_plan* P, const cpapr_coo* X, char* scratch, hipStream_t
         PlanMode& pm = P->mode[n];
         if (nnz == 0) {
             pm.segments = 0;
+            if (P->by_rows) {
+                Error e = rows_build(P, n, meta + n * kRowMeta, s);
+                if (e.code) return e;
+            }
             continue;
         }
         // LSD passes over the low `bits` bits of the keys in (kin, pin); outputs
@@ -505,17 +512,27 @@ Error build_sorted(cpapr_plan* P, const cpapr_coo* X, char* scratch, hipStream_t
             gather_sorted_kernel<16><<<grid_for(nnz), kBlock, 0, s>>>(rec, nnz, N, n, pin, P->R, pm.rows, pm.cofs,
                                                                       pm.vals, pm.pk);
         CPAPR_LAUNCHED();
+        if (P->by_rows) {  // counts the segments too
+            Error e = rows_build(P, n, meta + n * kRowMeta, s);
+            if (e.code) return e;
+            continue;
+        }
         const int gseg = std::min(grid_for(nnz), kSegPartials);
         count_segments_kernel<<<gseg, kBlock, 0, s>>>(pm.rows, nnz, segpart);
         CPAPR_LAUNCHED();
         sum_partials_kernel<<<1, kBlock, 0, s>>>(segpart, gseg, segc + n);
         CPAPR_LAUNCHED();
     }
-    unsigned long long hseg[CPAPR_MAX_MODES] = {};
-    CPAPR_HIP(hipMemcpyAsync(hseg, segc, sizeof(unsigned long long) * N, hipMemcpyDeviceToHost, s));
+    int host[64 + CPAPR_MAX_MODES * kRowMeta];
+    CPAPR_HIP(hipMemcpyAsync(host, flags, sizeof(int) * (64 + N * kRowMeta), hipMemcpyDeviceToHost, s));
     CPAPR_HIP(hipStreamSynchronize(s));
-    for (int n = 0; n < N; ++n)
-        if (only < 0 || n == only) P->mode[n].segments = (int64_t)hseg[n];
+    for (int n = 0; n < N; ++n) {
+        if (only >= 0 && n != only) continue;
+        unsigned long long seg;
+        std::memcpy(&seg, host + 8 + 2 * n, sizeof(seg));
+        P->mode[n].segments = (int64_t)seg;
+        if (P->by_rows) rows_finish(P, n, host + 64 + n * kRowMeta);
+    }
     return {CPAPR_OK, ""};
 }
 

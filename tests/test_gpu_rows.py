@@ -1,0 +1,126 @@
+"""The row-by-row MU inner loop against the oracle, at row lengths around every
+class of row (lane groups, waves, workgroups, teams of workgroups, heavy rows),
+every launch shape by rank, both precisions, fixed schedules and KKT stops."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2307_03276_amd import cpapr, synth
+from tests.gpu_util import assert_parity, dev, host
+
+pytestmark = pytest.mark.gpu
+# FP64: rows of up to 2e5 summed terms (error growth about sqrt(n) u) over a few
+# multiplicative steps stay far below the library's parity gate; mixed: the
+# factors' FP32 storage (6e-8 relative) enters every product N - 1 times and
+# every step once
+TOL64, TOL32 = 1e-12, 1e-5
+
+
+def _tensor(lengths, others, seed, skew=0.0):
+    """Mode 0 has rows of the given lengths; the other coordinates are random
+    (skew > 0: Zipf, so rows have long fibers and hot coordinates)."""
+    rng = np.random.default_rng(seed)
+    lengths = np.asarray(lengths)
+    nnz = int(lengths.sum())
+    idx = np.empty((1 + len(others), nnz), np.int32)
+    idx[0] = np.repeat(np.arange(lengths.size), lengths)
+    for m, d in enumerate(others):
+        if skew > 0:
+            p = np.arange(1, d + 1) ** -skew
+            idx[1 + m] = rng.permutation(d)[rng.choice(d, nnz, p=p / p.sum())]
+        else:
+            idx[1 + m] = rng.integers(0, d, nnz)
+    o = rng.permutation(nnz)
+    vals = 1.0 + rng.poisson(2.0, nnz)
+    return synth.SparseTensor((lengths.size, *others), np.ascontiguousarray(idx[:, o]), vals.astype(np.float64))
+
+
+def _check(X, R, lmax, tol=0.0, precision=cpapr.CPAPR_FP64, wait=None, seed=3, mode=0):
+    M = synth.random_model(seed, X.dims, R)
+    Bh = M.factors[mode] * M.lam
+    P = cpapr.Plan.from_tensor(X, R, lmax=lmax, tol=tol, precision=precision)
+    if wait is not None:
+        cpapr.cpapr_plan_set_team_wait(P.handle, wait)
+    B = dev(Bh)
+    phi, st = P.mu_inner(mode, B, [dev(a) for a in M.factors])
+    Bo, Po, hist, nup = oracle.mu_inner(X, mode, Bh, M.factors, lmax=lmax, tau=tol)
+    t = TOL64 if precision == cpapr.CPAPR_FP64 else TOL32
+    assert_parity(host(B), Bo, t, f"B R={R}", elementwise=precision == cpapr.CPAPR_FP64)
+    assert_parity(host(phi), Po, t, f"Phi R={R}", elementwise=precision == cpapr.CPAPR_FP64)
+    assert st["inner_iters"] == nup and st["phi_evals"] == nup + st["converged"]
+    assert P.segments(mode) == np.unique(X.idx[mode]).size
+    P.close()
+    return hist
+
+
+EDGES = [0, 1, 3, 4, 5, 19, 20, 21, 24, 25, 32, 33, 40, 41, 63, 64, 65, 80, 81, 160, 161, 319, 320, 321, 384, 385,
+         639, 640, 641, 1279, 1280, 1281, 1536, 1537, 2048, 2049, 3000, 0, 0]
+
+
+@pytest.mark.parametrize("R", [1, 2, 3, 4, 5, 8, 9, 10, 12, 13, 16, 17, 24, 25, 32, 33, 40, 48, 49, 63, 64])
+def test_row_lengths_at_every_rank(R):
+    _check(_tensor(EDGES, (37, 29), 10 + R), R, 3)
+
+
+@pytest.mark.parametrize("others", [(50,), (41, 31, 17), (23, 17, 13, 11), (11, 9, 8, 7, 6, 5, 4)])
+@pytest.mark.parametrize("precision", [cpapr.CPAPR_FP64, cpapr.CPAPR_MIXED])
+def test_mode_counts(others, precision):
+    _check(_tensor(EDGES, others, 40 + len(others)), 10, 3, precision=precision)
+    _check(_tensor(EDGES, others, 50 + len(others)), 32, 2, precision=precision)
+
+
+@pytest.mark.parametrize("R,longest", [(16, 170_000), (40, 45_000)])
+@pytest.mark.parametrize("wait", [None, 0])
+def test_teams_and_heavy_rows(R, longest, wait):
+    """Rows of several workgroups, one longer than the largest team; with no wait
+    for a team to start, its rows are left to one workgroup."""
+    X = _tensor([longest, 5_000, 1_300, 20_000, 7, 0, 700], (200, 150), 7)
+    _check(X, R, 4, wait=wait)
+
+
+@pytest.mark.parametrize("wait", [None, 0])
+@pytest.mark.parametrize("big", [False, True])
+def test_stop_at_every_iteration(big, wait):
+    """KKT stops before, inside and after the first chunk of iterations, with
+    light rows, team rows and (big) heavy rows restored from their history."""
+    X = _tensor(EDGES + [6_000] + ([200_000] if big else []), (60, 45), 9)
+    hist = _check(X, 16, 20, seed=5, wait=wait)
+    low = np.minimum.accumulate(hist)
+    for l in (0, 1, 7, 15, 16, 18):
+        _check(X, 16, 20, tol=float(low[l]) * (1 + 1e-9), seed=5, wait=wait)
+
+
+@pytest.mark.parametrize("R,others,precision,frac", [
+    (16, (900, 700), cpapr.CPAPR_FP64, False), (10, (3000, 2500), cpapr.CPAPR_MIXED, False),
+    (32, (800, 60, 30), cpapr.CPAPR_FP64, True), (64, (500, 400), cpapr.CPAPR_FP64, True),
+    (24, (3000, 300, 200), cpapr.CPAPR_MIXED, False), (5, (40000, 30000), cpapr.CPAPR_FP64, True)])
+def test_heavy_rows_split_by_hot_coordinates(R, others, precision, frac):
+    """Over 2^20 nonzeros, most in rows longer than a workgroup's registers:
+    their nonzeros run by hot and cold parts, values exact in FP32 or not."""
+    rng = np.random.default_rng(1)
+    lengths = np.concatenate([[420_000, 160_000], rng.integers(1_500, 12_000, 90), EDGES])
+    X = _tensor(lengths, others, 20 + R, skew=1.1)
+    if frac:
+        X = synth.SparseTensor(X.dims, X.idx, X.vals + 0.1)
+    hist = _check(X, R, 3, precision=precision)
+    _check(X, R, 3, tol=float(min(hist[:2])) * (1 + 1e-5), precision=precision)
+
+
+def test_empty_tensor_and_repeat():
+    X = synth.SparseTensor((7, 5, 4), np.zeros((3, 0), np.int32), np.zeros(0))
+    P = cpapr.Plan.from_tensor(X, 6, lmax=3, tol=0.0)
+    M = synth.random_model(2, X.dims, 6)
+    B = dev(M.factors[0])
+    phi, st = P.mu_inner(0, B, [dev(a) for a in M.factors])
+    assert not host(B).any() and not host(phi).any() and P.segments(0) == 0
+    P.close()
+    X = _tensor(EDGES + [30_000], (60, 45), 9)  # no atomics: every run gives the same bits
+    M = synth.random_model(4, X.dims, 16)
+    P = cpapr.Plan.from_tensor(X, 16, lmax=5, tol=0.0)
+    out = []
+    for _ in range(3):
+        B = dev(M.factors[0] * M.lam)
+        P.mu_inner(0, B, [dev(a) for a in M.factors])
+        out.append(host(B))
+    assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
+    P.close()
