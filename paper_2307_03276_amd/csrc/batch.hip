@@ -36,7 +36,8 @@ struct HostSlot {
 
 struct Layout {
     size_t slots, tile_map, class_off, class_ntiles, copies, ncopies, copy_total;
-    size_t mu, nmu, mu_total, viol, st_done, st_updates, st_viol, st_hold, counters, total;
+    size_t mu, nmu, mu_total, viol, st_done, st_updates, st_viol, st_hold, counters;
+    size_t row_items, row_prefix, row_iv, row_rerun, row_tickets, row_copies, nrow_copies, row_copy_total, total;
 };
 
 Layout layout(int max_slots, int64_t max_tiles)
@@ -75,6 +76,22 @@ Layout layout(int max_slots, int64_t max_tiles)
     off += align256(4 * (size_t)max_slots);
     L.counters = off;
     off += align256(4 * (size_t)cpapr::kBatchCounters * cpapr::kCounterStride);
+    L.row_items = off;
+    off += align256(cpapr::rows_batch_item_bytes() * (size_t)max_slots);
+    L.row_prefix = off;
+    off += align256(4 * 3 * ((size_t)max_slots + cpapr::kRowShapes));
+    L.row_iv = off;
+    off += align256(8 * (size_t)cpapr::kBatchInnerSlots * cpapr::kInnerChunk * max_slots);
+    L.row_rerun = off;
+    off += align256(4 * (size_t)max_slots);
+    L.row_tickets = off;
+    off += align256(4 * (size_t)cpapr::kRowShapes * cpapr::kCounterStride);
+    L.row_copies = off;
+    off += align256(sizeof(BatchCopy) * (size_t)max_slots * CPAPR_MAX_MODES);
+    L.nrow_copies = off;
+    off += 256;
+    L.row_copy_total = off;
+    off += 256;
     L.total = off;
     return L;
 }
@@ -123,10 +140,18 @@ struct cpapr_batch {
     bool skip_held = false;             // held slots are left out of the launches at commit
     int grid_cache[kMaxClasses] = {};   // persistent grid per class
     int copy_grid = 0;
+    // Inner loops row by row (every running slot's plan allows it): per launch
+    // shape its slots' descriptors; nrows slots in all, 0: the Phi / KKT / update launches.
+    cpapr::RowsBatch rows[cpapr::kRowShapes] = {};
+    int nrows = 0;
+    bool row_stops = false;             // some slot has a KKT tolerance
+    int row_copies = 0;                 // FP32 factor copies to refresh first
+    std::vector<int> row_grids;         // grid sizes of the row launches (baked into a captured graph)
     struct Graph {
         hipGraphExec_t exec = nullptr;
         std::vector<int> classes;  // classes captured
         std::vector<int64_t> tiles;  // per-class tile counts captured (grid launches)
+        std::vector<int> row_grids;  // the same of the row launches (inner loops)
         int lmax = 0;              // inner iterations captured (0: Phi only)
     } graph_run, graph_inner;
 };
@@ -181,6 +206,38 @@ Error enqueue_mu(cpapr_batch* b, hipStream_t s)
     return cpapr::launch_batch_mu(b->d_mu, b->d_nmu, b->d_mu_total, b->max_slots, b->d_viol, b->st, b->copy_grid, s);
 }
 
+// Inner loops row by row (after the state is cleared), in chunks of iterations
+// as the single-plan loop's.
+Error enqueue_rows(cpapr_batch* b, int lmax, hipStream_t s)
+{
+    char* w = b->ws;
+    Error e = ensure_grids(b);
+    if (e.code) return e;
+    if (b->row_copies > 0) {
+        e = cpapr::launch_batch_elementwise((const BatchCopy*)(w + b->L.row_copies), (const int32_t*)(w + b->L.nrow_copies),
+                                            (const int64_t*)(w + b->L.row_copy_total), b->st.done, b->d_counters,
+                                            b->copy_grid, s);
+        if (e.code) return e;
+    }
+    for (int l0 = 0; l0 < lmax; l0 += cpapr::kInnerChunk) {
+        const int n = std::min(cpapr::kInnerChunk, lmax - l0);
+        for (int c = 0; c < cpapr::kRowShapes; ++c)
+            if (b->rows[c].n > 0) {
+                e = cpapr::launch_rows_batch(c, b->rows[c], n, false, s);
+                if (e.code) return e;
+            }
+        e = cpapr::launch_rows_batch_decide(w + b->L.row_items, b->nrows, b->st, (int32_t*)(w + b->L.row_rerun), n,
+                                            (unsigned int*)(w + b->L.row_tickets), s);
+        if (e.code) return e;
+        for (int c = 0; c < cpapr::kRowShapes; ++c)
+            if (b->rows[c].n > 0 && b->row_stops) {
+                e = cpapr::launch_rows_batch(c, b->rows[c], n, true, s);
+                if (e.code) return e;
+            }
+    }
+    return {CPAPR_OK, ""};
+}
+
 // lmax == 0: clear the per-slot state and compute Phi for every slot.
 // lmax > 0: clear it and run lmax x {Phi, KKT, MU update} with per-slot stops.
 Error enqueue_sequence(cpapr_batch* b, int lmax, hipStream_t s)
@@ -188,6 +245,7 @@ Error enqueue_sequence(cpapr_batch* b, int lmax, hipStream_t s)
     Error e = cpapr::launch_batch_reset(b->st, b->max_slots, s);
     if (e.code) return e;
     if (lmax == 0) return enqueue_phi(b, b->classes, s);
+    if (b->nrows > 0) return enqueue_rows(b, lmax, s);
     for (int l = 0; l < lmax; ++l) {
         e = enqueue_phi(b, b->classes, s);
         if (e.code) return e;
@@ -206,6 +264,7 @@ int run_sequence(cpapr_batch* b, cpapr_batch::Graph& g, int lmax, bool use_graph
     for (int c : b->classes)
         if (std::find(g.classes.begin(), g.classes.end(), c) == g.classes.end()) covered = false;
     if (!b->persistent && g.tiles != b->class_tiles) covered = false;  // grid sizes are baked into the graph
+    if (lmax > 0 && g.row_grids != b->row_grids) covered = false;
     if (covered) {
         if (hipGraphLaunch(g.exec, s) != hipSuccess) return fail(CPAPR_EHIP, "hipGraphLaunch failed");
         return CPAPR_OK;
@@ -237,6 +296,7 @@ int run_sequence(cpapr_batch* b, cpapr_batch::Graph& g, int lmax, bool use_graph
     }
     g.classes = b->classes;
     g.tiles = b->class_tiles;
+    g.row_grids = b->row_grids;
     g.lmax = lmax;
     return CPAPR_OK;
 }
@@ -466,7 +526,98 @@ int cpapr_batch_commit(cpapr_batch* batch, void* stream)
         if (hipMemcpyAsync(b->st.hold, b->hold.data(), 4 * (size_t)b->max_slots, hipMemcpyHostToDevice, s) !=
             hipSuccess)
             return fail(CPAPR_EHIP, "upload of the hold flags failed");
+        // inner loops row by row: every slot's plan allows it, and no plan's buffers serve two slots
+        std::vector<int> shape_of(b->max_slots, -1);
+        std::vector<const cpapr_plan*> seen;
+        bool by_rows = nmu > 0;
+        for (int i = 0; i < b->max_slots && by_rows; ++i) {
+            const HostSlot& h = b->slots[i];
+            if (!h.set || (b->skip_held && b->hold[i])) continue;
+            shape_of[i] = cpapr::rows_batch_shape(h.plan, h.mode);
+            by_rows = shape_of[i] >= 0;
+            seen.push_back(h.plan);
+        }
+        std::sort(seen.begin(), seen.end());
+        by_rows = by_rows && std::adjacent_find(seen.begin(), seen.end()) == seen.end();
+        std::vector<char> items;
+        std::vector<int32_t> prefix;
+        std::vector<BatchCopy> rcopies;
+        int64_t rcopy_total = 0;
+        std::vector<int> grids;
+        int nrows = 0;
+        bool row_stops = false;
+        cpapr::RowsBatch rows[cpapr::kRowShapes] = {};
+        char* w = b->ws;
+        const size_t ib = cpapr::rows_batch_item_bytes();
+        for (int c = 0; c < cpapr::kRowShapes && by_rows; ++c) {
+            cpapr::RowsBatch& rb = rows[c];
+            rb.items = w + b->L.row_items + (size_t)nrows * ib;
+            rb.ticket = (unsigned int*)(w + b->L.row_tickets) + c * cpapr::kCounterStride;
+            std::vector<int32_t> pl{0}, pa{0}, pm{0};
+            for (int i = 0; i < b->max_slots; ++i) {
+                if (shape_of[i] != c) continue;
+                const HostSlot& h = b->slots[i];
+                const cpapr_plan* P = h.plan;
+                const void* fac[CPAPR_MAX_MODES] = {};
+                for (int m = 0; m < P->N; ++m) {
+                    if (m == h.mode) continue;
+                    fac[m] = h.A[m];
+                    if (P->params.precision == CPAPR_MIXED) {
+                        fac[m] = P->f32[m];
+                        if (!(h.flags & CPAPR_BATCH_F32_CURRENT)) {
+                            BatchCopy cp{h.A[m], P->f32[m], P->dims[m] * (int64_t)P->R, rcopy_total, 1, -1};
+                            rcopies.push_back(cp);
+                            rcopy_total += cp.n;
+                        }
+                    }
+                }
+                items.resize(items.size() + ib);
+                int light = 0, again = 0, members = 0;
+                cpapr::rows_batch_item(P, h.mode, h.B, fac, h.Phi, i, b->st.done + i,
+                                       (int32_t*)(w + b->L.row_rerun) + i,
+                                       (unsigned long long*)(w + b->L.row_iv) +
+                                           (size_t)i * cpapr::kBatchInnerSlots * cpapr::kInnerChunk,
+                                       items.data() + items.size() - ib, &light, &again, &members);
+                pl.push_back(pl.back() + light);
+                pa.push_back(pa.back() + again);
+                pm.push_back(pm.back() + members);
+                row_stops = row_stops || P->params.tol > 0.0;
+                ++rb.n;
+                ++nrows;
+            }
+            rb.nlight = pl.back();
+            rb.nagain = pa.back();
+            rb.nmembers = pm.back();
+            int32_t* d = (int32_t*)(w + b->L.row_prefix);
+            for (auto* v : {&pl, &pa, &pm}) {
+                (v == &pl ? rb.light : v == &pa ? rb.again : rb.members) = d + prefix.size();
+                prefix.insert(prefix.end(), v->begin(), v->end());
+            }
+            grids.insert(grids.end(), {rb.n, rb.nlight, rb.nagain, rb.nmembers});
+        }
+        const int32_t nrcopies = (int32_t)rcopies.size();
+        if (by_rows) {
+            grids.push_back(nrows);
+            grids.push_back(nrcopies > 0);
+            grids.push_back(row_stops);
+            if (hipMemcpyAsync(w + b->L.row_items, items.data(), items.size(), hipMemcpyHostToDevice, s) != hipSuccess ||
+                hipMemcpyAsync(w + b->L.row_prefix, prefix.data(), 4 * prefix.size(), hipMemcpyHostToDevice, s) !=
+                    hipSuccess ||
+                (nrcopies > 0 && hipMemcpyAsync(w + b->L.row_copies, rcopies.data(), sizeof(BatchCopy) * rcopies.size(),
+                                                hipMemcpyHostToDevice, s) != hipSuccess) ||
+                hipMemcpyAsync(w + b->L.nrow_copies, &nrcopies, 4, hipMemcpyHostToDevice, s) != hipSuccess ||
+                hipMemcpyAsync(w + b->L.row_copy_total, &rcopy_total, 8, hipMemcpyHostToDevice, s) != hipSuccess)
+                return fail(CPAPR_EHIP, "upload of the row lists failed");
+            const cpapr::Error e = cpapr::launch_fill((double*)(w + b->L.row_iv), (int64_t)(b->L.row_copies - b->L.row_iv) / 8,
+                                                      0.0, nullptr, s);  // violations and tickets start at zero
+            if (e.code) return report(e);
+        }
         if (hipStreamSynchronize(s) != hipSuccess) return fail(CPAPR_EHIP, "stream synchronisation failed");
+        std::copy(std::begin(rows), std::end(rows), std::begin(b->rows));
+        b->nrows = by_rows ? nrows : 0;
+        b->row_copies = nrcopies;
+        b->row_stops = row_stops;
+        b->row_grids = grids;
         b->classes = classes;
         b->class_tiles.assign(cnt.begin(), cnt.end());
         b->committed = true;

@@ -27,7 +27,8 @@ constexpr int kViolStride = 16;  // u64 words per slot (128 bytes)
 // MU inner loop row by row (rows.hip): iterations per chunk when a KKT stop may
 // end it, violation slots per iteration, row classes, ints of a mode's class counts.
 constexpr int kInnerChunk = 16;
-constexpr int kInnerSlots = 8;
+constexpr int kInnerSlots = 64;
+constexpr int kBatchInnerSlots = 8;  // per batch slot
 constexpr int kRowClasses = 20;
 constexpr int kLenBuckets = 128;  // row lengths: four buckets per octave
 constexpr int kRowMeta = 64 + 2 * kLenBuckets;
@@ -47,7 +48,7 @@ struct DevState {
     long long trial_evals;                                  // row solves: line-search passes since the last reset
     int pq_all_done;                                        // row solves: no row of the current mode is active
     int pq_idle;                                            // row solves: no row is in a line search
-    unsigned long long iv[kInnerChunk][kInnerSlots][16];    // KKT violation per iteration of a chunk (ordered bits)
+    unsigned long long iv[kInnerSlots][kInnerChunk];        // KKT violation per iteration of a chunk (ordered bits)
 };
 
 // PQNR (projected quasi-Newton row solves): constants shared by every kernel.
@@ -286,6 +287,25 @@ Error launch_phi(const cpapr_plan* P, int mode, const double* B, const void* con
                  double eps, double* Phi, const int* done, hipStream_t s);
 Error launch_mttkrp(const cpapr_plan* P, int mode, const double* const* A, double* M, hipStream_t s);
 
+// ---- batched inner loops row by row (rows.hip; host side in batch.hip) ----
+constexpr int kRowShapes = 16;  // launch shapes by rank and precision
+// Whether a batch slot of this plan can run row by row, and as which shape (-1: not).
+int rows_batch_shape(const cpapr_plan* P, int mode);
+size_t rows_batch_item_bytes();
+// Device-side descriptor of one slot (written to `out`), its workgroups without
+// and with the rows restored after a stop, and its team members.
+void rows_batch_item(const cpapr_plan* P, int mode, const double* B, const void* const* fac, double* Phi, int slot,
+                     const int32_t* done, int32_t* rerun, unsigned long long* iv, void* out, int* light, int* again,
+                     int* members);
+// One shape's slots of a batch (descriptors and the prefixes of their workgroups, on the device).
+struct RowsBatch {
+    const void* items;
+    const int32_t *light, *again, *members;  // [n + 1] prefixes
+    int n, nlight, nagain, nmembers;         // slots and totals
+    unsigned int* ticket;                    // next team member; zero between launches
+};
+Error launch_rows_batch(int shape, const RowsBatch& b, int n_it, bool again, hipStream_t s);
+
 // ---- batched Phi (phi.hip; host side in batch.hip) ----
 int batch_class_count();
 int batch_class_of(int G, int RPL, int NM1, bool mixed);  // -1: no batched kernel for this shape
@@ -310,6 +330,9 @@ struct BatchState {
 Error launch_batch_mu(const BatchMu* items, const int32_t* nitems_dev, const int64_t* total_dev, int max_slots,
                       unsigned long long* viol_spread, BatchState st, int grid, hipStream_t s);
 Error launch_batch_reset(BatchState st, int max_slots, hipStream_t s);
+// End of n iterations of a row-by-row batch (all its slots' descriptors): stops, counters, tickets.
+Error launch_rows_batch_decide(const void* items, int n, BatchState st, int32_t* rerun, int n_it, unsigned int* tickets,
+                               hipStream_t s);
 
 // ---- MU inner loop row by row (rows.hip) ----
 bool rows_supported(int R, int method);

@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kBlock) void to_f32_kernel(const double* __restrict
 __global__ __launch_bounds__(kBlock) void reset_state_kernel(DevState* st, int new_sweep, int all)
 {
     for (int i = threadIdx.x; i < 2 * kViolSlots * kViolStride; i += kBlock) (&st->viol[0][0])[i] = 0ull;
-    for (int i = threadIdx.x; i < kInnerChunk * kInnerSlots; i += kBlock) st->iv[i / kInnerSlots][i % kInnerSlots][0] = 0ull;
+    for (int i = threadIdx.x; i < kInnerChunk * kInnerSlots; i += kBlock) (&st->iv[0][0])[i] = 0ull;
     if (threadIdx.x == 0) {
         st->done = 0;
         st->rerun = -1;

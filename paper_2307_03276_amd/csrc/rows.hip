@@ -22,6 +22,7 @@
 //    and takes the MU step of that row.
 // Every sum has a fixed order, so results repeat bit for bit.
 #include <algorithm>
+#include <cstring>
 #include <type_traits>
 
 #include "internal.hpp"
@@ -125,7 +126,13 @@ struct ResArgs {
     double* B;
     double* B0;     // saved start of the chunk (tol > 0), else nullptr
     double* Phi;
-    DevState* st;
+    const int32_t* done;       // the inner loop has stopped: no work
+    const int32_t* rerun;      // iteration to run again to (-1: none)
+    unsigned long long* iv;    // [iv_slots x kInnerChunk] violations
+    int iv_slots;
+    int slot;                  // batch slot
+    int teams;                 // team rows that run as teams
+    double tol;
     double* hist;        // heavy rows: B and Phi per iteration (restored on a stop)
     int64_t nnz;
     int64_t hist_stride;
@@ -194,7 +201,7 @@ __device__ __forceinline__ bool team_meet(unsigned int* count, unsigned int T, l
 }
 
 template <int G, int C, int K, bool MIXED, bool TEAM>
-__device__ __forceinline__ void resident_rows(const ResArgs& a, int light, bool rerun, int n_it)
+__device__ __forceinline__ void resident_rows(const ResArgs& a, int at, bool rerun, int n_it)
 {
     using L = typename std::conditional<MIXED, float, double>::type;
     constexpr int NG = 64 / G;     // lane groups per wave
@@ -203,7 +210,7 @@ __device__ __forceinline__ void resident_rows(const ResArgs& a, int light, bool 
     constexpr int RP = 4 * G;      // columns of a partial row, padded
     __shared__ double red[2][W][RP];
     __shared__ unsigned long long vmax[kInnerChunk];
-    __shared__ int sh_member, sh_ok, sh_last;
+    __shared__ int sh_ok, sh_last;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int gl = lane % G, g = lane / G;
     const int R = a.R;
@@ -215,13 +222,7 @@ __device__ __forceinline__ void resident_rows(const ResArgs& a, int light, bool 
     bool valid = true;
     uint32_t seg0 = 0, seg1 = 0;  // the whole row, for an abandoned team
     if constexpr (TEAM) {
-        // members in the order in which workgroups start, so that the oldest team is always the first to be complete
-        if (t == 0) {
-            sh_member = (int)__hip_atomic_fetch_add(a.team_ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            sh_last = 0;
-        }
-        __syncthreads();
-        member = __builtin_amdgcn_readfirstlane(sh_member);
+        member = at;
         h = a.team_row[member];
         const int m0 = a.team_begin[h];
         T = a.team_begin[h + 1] - m0;
@@ -236,11 +237,11 @@ __device__ __forceinline__ void resident_rows(const ResArgs& a, int light, bool 
         sub = wave * NG + g;
     } else {
         int e = 0;
-        while (e + 1 < a.nentries && light >= a.entry[e + 1].block0) ++e;
+        while (e + 1 < a.nentries && at >= a.entry[e + 1].block0) ++e;
         const int row0 = a.entry[e].row0, count = a.entry[e].count;
         S = a.entry[e].groups;
         WR = S > NG ? S / NG : 1;  // waves per row
-        const int local = light - a.entry[e].block0;
+        const int local = at - a.entry[e].block0;
         // position of this lane group's row in the class, and its place among the row's groups
         int pos;
         if (WR > 1) {
@@ -470,7 +471,38 @@ __device__ __forceinline__ void resident_rows(const ResArgs& a, int light, bool 
     if (!rerun) {
         __syncthreads();
         const int nv = a.each ? n_it : 1;
-        if (t < nv) atomicMax(&a.st->iv[t][blockIdx.x % kInnerSlots][0], vmax[t]);
+        if (t < nv) atomicMax(&a.iv[blockIdx.x % a.iv_slots * kInnerChunk + t], vmax[t]);
+    }
+}
+
+// Next team member: members in the order in which workgroups start, so that the
+// oldest team is always the first to be complete.
+__device__ __forceinline__ int next_member(unsigned int* ticket)
+{
+    __shared__ int sh;
+    if (threadIdx.x == 0) sh = (int)__hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(sh);
+}
+
+// Team members and light workgroups alternate in launch order, so that a
+// compute unit has light rows to work on while a team meets. Returns whether
+// workgroup b is a team's; *light: its place among the light ones.
+__device__ __forceinline__ bool team_turn(int b, int members, int lights, int* light)
+{
+    const int both = min(members, lights);
+    *light = b < 2 * both ? b >> 1 : b - members;
+    return b < 2 * both ? (b & 1) == 0 : members > lights;
+}
+
+// Heavy and team rows from their history after a stop at iteration l.
+__device__ __forceinline__ void restore_rows(const ResArgs& a, int l, int at, int blocks)
+{
+    for (int64_t i = (int64_t)at * kResBlock + threadIdx.x; i < (int64_t)a.nheavy * a.R; i += (int64_t)blocks * kResBlock) {
+        const int64_t h = i / a.R, c = i % a.R;
+        const int64_t e = (int64_t)a.order[a.heavy0 + h] * a.R + c;
+        a.B[e] = a.hist[(2 * l) * a.hist_stride + i];
+        a.Phi[e] = a.hist[(2 * l + 1) * a.hist_stride + i];
     }
 }
 
@@ -478,35 +510,70 @@ __device__ __forceinline__ void resident_rows(const ResArgs& a, int light, bool 
 template <int G, int C, int K, bool MIXED>
 __global__ __launch_bounds__(kResBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void resident_kernel(ResArgs a)
 {
-    if (a.st->done) return;
-    // Team members and light workgroups alternate in launch order, so that a
-    // compute unit has light rows to work on while a team meets.
-    const int b = (int)blockIdx.x, both = min(a.team_blocks, a.light_blocks);
-    const bool team = b < 2 * both ? (b & 1) == 0 : a.team_blocks > a.light_blocks;
-    if (team)
-        resident_rows<G, C, K, MIXED, true>(a, 0, false, a.n_it);
+    if (*a.done) return;
+    int light;
+    if (team_turn((int)blockIdx.x, a.team_blocks, a.light_blocks, &light))
+        resident_rows<G, C, K, MIXED, true>(a, next_member(a.team_ticket), false, a.n_it);
     else
-        resident_rows<G, C, K, MIXED, false>(a, b < 2 * both ? b >> 1 : b - a.team_blocks, false, a.n_it);
+        resident_rows<G, C, K, MIXED, false>(a, light, false, a.n_it);
 }
 
-// After a stop at iteration st->rerun of the chunk: the light rows again from
-// their saved start to that iteration, the heavy rows from their history.
+// After a stop at iteration *rerun of the chunk: the light rows again from
+// their saved start to that iteration, the others from their history.
 template <int G, int C, int K, bool MIXED>
 __global__ __launch_bounds__(kResBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void rerun_kernel(ResArgs a)
 {
-    const int l = a.st->rerun;
+    const int l = *a.rerun;
     if (l < 0) return;
-    if ((int)blockIdx.x < a.light_blocks) {
+    if ((int)blockIdx.x < a.light_blocks)
         resident_rows<G, C, K, MIXED, false>(a, (int)blockIdx.x, true, l + 1);
-        return;
+    else
+        restore_rows(a, l, (int)blockIdx.x - a.light_blocks, (int)gridDim.x - a.light_blocks);
+}
+
+// Item of `n` (prefix [n + 1] of counts) that holds place `at`: one load per
+// thread instead of a chain of them (called by the whole workgroup).
+__device__ __forceinline__ int item_at(const int32_t* __restrict__ prefix, int n, int at)
+{
+    int found = 0;
+    for (int i0 = 0; i0 < n; i0 += kResBlock) {
+        const int i = i0 + (int)threadIdx.x;
+        found += __syncthreads_count(i < n && prefix[i] <= at);
     }
-    for (int64_t i = ((int64_t)blockIdx.x - a.light_blocks) * kResBlock + threadIdx.x; i < (int64_t)a.nheavy * a.R;
-         i += ((int64_t)gridDim.x - a.light_blocks) * kResBlock) {
-        const int64_t h = i / a.R, c = i % a.R;
-        const int64_t e = (int64_t)a.order[a.heavy0 + h] * a.R + c;
-        a.B[e] = a.hist[(2 * l) * a.hist_stride + i];
-        a.Phi[e] = a.hist[(2 * l + 1) * a.hist_stride + i];
+    return __builtin_amdgcn_readfirstlane(found - 1);
+}
+
+// The same for the slots of a batch that share a launch shape.
+template <int G, int C, int K, bool MIXED>
+__global__ __launch_bounds__(kResBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void batch_resident_kernel(
+    const ResArgs* __restrict__ items, const int32_t* __restrict__ lights, const int32_t* __restrict__ members, int n,
+    int nlight, int nmembers, unsigned int* ticket, int n_it)
+{
+    int light;
+    if (team_turn((int)blockIdx.x, nmembers, nlight, &light)) {
+        const int m = next_member(ticket);
+        const int i = item_at(members, n, m);
+        if (*items[i].done) return;
+        resident_rows<G, C, K, MIXED, true>(items[i], m - members[i], false, n_it);
+    } else {
+        const int i = item_at(lights, n, light);
+        if (*items[i].done) return;
+        resident_rows<G, C, K, MIXED, false>(items[i], light - lights[i], false, n_it);
     }
+}
+
+template <int G, int C, int K, bool MIXED>
+__global__ __launch_bounds__(kResBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void batch_rerun_kernel(
+    const ResArgs* __restrict__ items, const int32_t* __restrict__ blocks, int n)
+{
+    const int i = item_at(blocks, n, (int)blockIdx.x);
+    const int l = *items[i].rerun;
+    if (l < 0) return;
+    const int at = (int)blockIdx.x - blocks[i], light = items[i].light_blocks;
+    if (at < light)
+        resident_rows<G, C, K, MIXED, false>(items[i], at, true, l + 1);
+    else
+        restore_rows(items[i], l, at - light, blocks[i + 1] - blocks[i] - light);
 }
 
 struct HeavyArgs {
@@ -736,7 +803,7 @@ __global__ __launch_bounds__(kBlock) void heavy_kernel(HeavyArgs a)
     if (t == 0) a.ticket[h * kCountStride] = 0u;
     if (a.l >= 0 && t < 64) {
         viol = wave_max(viol);
-        if (t == 0) atomicMax(&a.st->iv[a.l][h % kInnerSlots][0], (unsigned long long)__double_as_longlong(viol));
+        if (t == 0) atomicMax(&a.st->iv[h % kInnerSlots][a.l], (unsigned long long)__double_as_longlong(viol));
     }
 }
 
@@ -976,16 +1043,35 @@ __global__ __launch_bounds__(512) void hot_step_kernel(HotStep a)
     }
     if (a.l >= 0) {
         viol = wave_max(viol);
-        if (t == 0) atomicMax(&a.st->iv[a.l][h % kInnerSlots][0], (unsigned long long)__double_as_longlong(viol));
+        if (t == 0) atomicMax(&a.st->iv[h % kInnerSlots][a.l], (unsigned long long)__double_as_longlong(viol));
     }
 }
 
-// End of a chunk of n iterations: the first one whose violation is below tol
-// stops the inner loop (st->rerun tells rerun_kernel which), else all n count.
+// End of a chunk of n iterations (one workgroup): the largest violation of each
+// iteration, the slots cleared; the first iteration below tol stops the inner
+// loop. Returns that iteration or -1, *viol the last violation that counts (thread 0).
+__device__ __forceinline__ int decide(unsigned long long* iv, int slots, int n, bool each, double tol, double* viol)
+{
+    __shared__ unsigned long long v[kInnerChunk];
+    const int t = threadIdx.x;
+    if (t < kInnerChunk) v[t] = 0ull;
+    __syncthreads();
+    for (int i = t; i < slots * kInnerChunk; i += kBlock) {
+        if (iv[i]) atomicMax(&v[i % kInnerChunk], iv[i]);
+        iv[i] = 0ull;
+    }
+    __syncthreads();
+    int stop = -1;
+    if (each)
+        for (int l = 0; l < n && stop < 0; ++l)
+            if (__longlong_as_double((long long)v[l]) < tol) stop = l;
+    *viol = __longlong_as_double((long long)v[stop >= 0 ? stop : each ? n - 1 : 0]);
+    return stop;
+}
+
 __global__ __launch_bounds__(kBlock) void decide_kernel(DevState* st, int mode, int n, int each, double tol,
                                                         unsigned int* team_ticket, unsigned int* team_count, int teams)
 {
-    __shared__ double v[kInnerChunk];
     const int t = threadIdx.x;
     for (int i = t; i < teams; i += kBlock) team_count[i * kCountStride] = 0u;
     if (t == 0) *team_ticket = 0u;
@@ -993,29 +1079,39 @@ __global__ __launch_bounds__(kBlock) void decide_kernel(DevState* st, int mode, 
         if (t == 0) st->rerun = -1;
         return;
     }
-    if (t < kInnerChunk) {
-        unsigned long long m = 0ull;
-        for (int j = 0; j < kInnerSlots; ++j) {
-            const unsigned long long u = st->iv[t][j][0];
-            m = u > m ? u : m;
-            st->iv[t][j][0] = 0ull;
-        }
-        v[t] = __longlong_as_double((long long)m);
-    }
-    __syncthreads();
+    double viol;
+    const int stop = decide(&st->iv[0][0], kInnerSlots, n, each != 0, tol, &viol);
     if (t != 0) return;
-    int stop = -1;
-    if (each)
-        for (int l = 0; l < n && stop < 0; ++l)
-            if (v[l] < tol) stop = l;
     const int upd = stop >= 0 ? stop : n;
-    st->last_viol[mode] = v[stop >= 0 ? stop : each ? n - 1 : 0];
+    st->last_viol[mode] = viol;
     st->rerun = stop;
     if (stop >= 0) st->done = 1;
     st->updates += upd;
     st->sweep_updates += upd;
     st->total_updates += upd;
     st->phi_evals += stop >= 0 ? stop + 1 : n;
+}
+
+// A workgroup per slot of a batch.
+__global__ __launch_bounds__(kBlock) void batch_decide_kernel(const ResArgs* __restrict__ items, BatchState st,
+                                                              int32_t* __restrict__ rerun, int n,
+                                                              unsigned int* __restrict__ tickets)
+{
+    const ResArgs& a = items[blockIdx.x];
+    const int t = threadIdx.x, slot = a.slot;
+    for (int i = t; i < a.teams; i += kBlock) a.team_count[i * kCountStride] = 0u;
+    if (blockIdx.x == 0 && t < kRowShapes) tickets[t * kCountStride] = 0u;
+    if (st.done[slot]) {
+        if (t == 0) rerun[slot] = -1;
+        return;
+    }
+    double viol;
+    const int stop = decide(a.iv, a.iv_slots, n, a.each != 0, a.tol, &viol);
+    if (t != 0) return;
+    st.viol[slot] = viol;
+    st.updates[slot] += stop >= 0 ? stop : n;
+    rerun[slot] = stop;
+    if (stop >= 0) st.done[slot] = 1;
 }
 
 // ---- plan: rows by class ----
@@ -1812,17 +1908,17 @@ void rows_finish(cpapr_plan* P, int mode, const int* meta)
     P->mode[mode].segments = P->dims[mode] - r.count[0];
 }
 
-Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, hipStream_t s)
+namespace {
+
+// Operands of the resident rows of one mode (without its flags).
+void res_args(const cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, bool teams, ResArgs* out)
 {
     Shape sh;
-    if (!row_shape(P->R, &sh)) return {CPAPR_EUNSUPPORTED, "no resident-row kernel for this rank"};
+    row_shape(P->R, &sh);
     const ClassShape cs = class_shape(sh);
     const PlanMode& pm = P->mode[mode];
     const RowPlan& r = pm.rp;
-    const bool mixed = P->params.precision == CPAPR_MIXED;
-    const bool each = P->params.tol > 0.0;
     const int NG = cs.NG, W = kResBlock / 64;
-
     ResArgs a{};
     a.cofs = pm.cofs;
     a.vals = pm.vals;
@@ -1830,12 +1926,12 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
     a.order = r.order;
     a.B = B;
     a.Phi = Phi;
-    a.st = P->state;
     a.nnz = P->nnz;
     a.eps = P->params.eps;
     a.R = P->R;
     a.NM1 = P->N - 1;
-    a.each = each ? 1 : 0;
+    a.tol = P->params.tol;
+    a.each = P->params.tol > 0.0 ? 1 : 0;
     int j = 0;
     for (int m = 0; m < P->N; ++m)
         if (m != mode) a.fac[j++] = fac[m];
@@ -1852,14 +1948,14 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
         const int S = i <= cs.KB ? 1 : 1 << (i - cs.KB);
         const int per = std::max(1, W * NG / S);  // rows per workgroup
         a.entry[a.nentries++] = {(int32_t)blocks, begin[i], r.count[i], S};
-        blocks += cdiv(r.count[i], per);
+        blocks += cdiv(r.count[i], per);  // < 2^31 rows
     }
-    if (blocks + a.team_blocks > 0x7fffffff) return {CPAPR_EUNSUPPORTED, "too many rows"};
     a.light_blocks = (int)blocks;
     a.heavy0 = begin[nlight];
     a.team0 = r.count[nlight];
     a.nheavy = r.count[nlight] + r.count[nlight + 1];
-    a.team_blocks = r.use_teams ? r.nmembers : 0;
+    a.team_blocks = teams ? r.nmembers : 0;
+    a.teams = teams ? r.count[nlight + 1] : 0;
     a.team_begin = r.team_begin;
     a.team_row = r.team_row;
     a.team_part = P->rs.team_part;
@@ -1868,7 +1964,91 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
     a.team_wait = P->team_wait;
     a.hist = P->rs.hist;
     a.hist_stride = (int64_t)a.nheavy * P->R;
-    a.B0 = each ? P->rs.B0 : nullptr;
+    a.B0 = a.each ? P->rs.B0 : nullptr;
+    *out = a;
+}
+
+}  // namespace
+
+// A batch slot can run row by row when its plan's single inner loop would, and
+// no row is longer than the largest team.
+int rows_batch_shape(const cpapr_plan* P, int mode)
+{
+    Shape sh;
+    if (!P->by_rows || !P->shape_auto || P->params.variant > CPAPR_VARIANT_SEGMENTED || !row_shape(P->R, &sh)) return -1;
+    if (P->mode[mode].rp.count[class_count(class_shape(sh)) - 2] > 0) return -1;
+    const int mixed = P->params.precision == CPAPR_MIXED ? 1 : 0;
+    return 2 * (P->R <= 16 ? (P->R - 1) / 4 : P->R <= 32 ? 4 + (P->R - 17) / 8 : 6 + (P->R - 33) / 16) + mixed;
+}
+
+size_t rows_batch_item_bytes() { return sizeof(ResArgs); }
+
+void rows_batch_item(const cpapr_plan* P, int mode, const double* B, const void* const* fac, double* Phi, int slot,
+                     const int32_t* done, int32_t* rerun, unsigned long long* iv, void* out, int* light, int* again,
+                     int* members)
+{
+    ResArgs a;
+    res_args(P, mode, const_cast<double*>(B), fac, Phi, true, &a);
+    a.slot = slot;
+    a.done = done;
+    a.rerun = rerun;
+    a.iv = iv;
+    a.iv_slots = kBatchInnerSlots;
+    *light = a.light_blocks;
+    *again = a.light_blocks + (int)cdiv((int64_t)a.nheavy * P->R, kResBlock);
+    *members = a.team_blocks;
+    std::memcpy(out, &a, sizeof(a));
+}
+
+Error launch_rows_batch(int shape, const RowsBatch& b, int n_it, bool again, hipStream_t s)
+{
+    const Shape shapes[kRowShapes / 2] = {{4, 1, 32}, {4, 2, 32}, {4, 3, 24}, {4, 4, 20},
+                                          {8, 3, 24}, {8, 4, 20}, {16, 3, 24}, {16, 4, 20}};
+    return by_row_shape(shapes[shape / 2], [&](auto G, auto C, auto K) -> Error {
+        constexpr int GG = decltype(G)::value, CC = decltype(C)::value, KK = decltype(K)::value;
+        const ResArgs* items = (const ResArgs*)b.items;
+        const unsigned grid = (unsigned)(again ? b.nagain : b.nlight + b.nmembers);
+        if (grid == 0) return {CPAPR_OK, ""};
+        if (again && shape % 2)
+            batch_rerun_kernel<GG, CC, KK, true><<<grid, kResBlock, 0, s>>>(items, b.again, b.n);
+        else if (again)
+            batch_rerun_kernel<GG, CC, KK, false><<<grid, kResBlock, 0, s>>>(items, b.again, b.n);
+        else if (shape % 2)
+            batch_resident_kernel<GG, CC, KK, true><<<grid, kResBlock, 0, s>>>(items, b.light, b.members, b.n, b.nlight,
+                                                                              b.nmembers, b.ticket, n_it);
+        else
+            batch_resident_kernel<GG, CC, KK, false><<<grid, kResBlock, 0, s>>>(items, b.light, b.members, b.n, b.nlight,
+                                                                               b.nmembers, b.ticket, n_it);
+        CPAPR_LAUNCHED();
+        return {CPAPR_OK, ""};
+    });
+}
+
+Error launch_rows_batch_decide(const void* items, int n, BatchState st, int32_t* rerun, int n_it, unsigned int* tickets,
+                               hipStream_t s)
+{
+    batch_decide_kernel<<<(unsigned)n, kBlock, 0, s>>>((const ResArgs*)items, st, rerun, n_it, tickets);
+    CPAPR_LAUNCHED();
+    return {CPAPR_OK, ""};
+}
+
+Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, hipStream_t s)
+{
+    Shape sh;
+    if (!row_shape(P->R, &sh)) return {CPAPR_EUNSUPPORTED, "no resident-row kernel for this rank"};
+    const PlanMode& pm = P->mode[mode];
+    const RowPlan& r = pm.rp;
+    const bool mixed = P->params.precision == CPAPR_MIXED;
+    const bool each = P->params.tol > 0.0;
+    const int ncls = class_count(class_shape(sh)), nlight = ncls - 2;
+    ResArgs a;
+    res_args(P, mode, B, fac, Phi, r.use_teams, &a);
+    a.done = &P->state->done;
+    a.rerun = &P->state->rerun;
+    a.iv = &P->state->iv[0][0];
+    a.iv_slots = kInnerSlots;
+    const int64_t blocks = a.light_blocks;
+    if (blocks + a.team_blocks > 0x7fffffff) return {CPAPR_EUNSUPPORTED, "too many rows"};
 
     HeavyArgs h{};
     h.vals = pm.vals;
@@ -2011,8 +2191,8 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
         };
         if (blocks + a.team_blocks > 0) e = light(false);
         if (e.code) return e;
-        decide_kernel<<<1, kBlock, 0, s>>>(P->state, mode, n, each ? 1 : 0, P->params.tol, P->rs.ticket,
-                                          P->rs.ticket + kCountStride, r.use_teams ? r.count[ncls - 1] : 0);
+        decide_kernel<<<1, kBlock, 0, s>>>(P->state, mode, n, each ? 1 : 0, P->params.tol, a.team_ticket,
+                                          a.team_count, a.teams);
         CPAPR_LAUNCHED();
         if (each) e = light(true);
         if (e.code) return e;

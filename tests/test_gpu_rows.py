@@ -124,3 +124,52 @@ def test_empty_tensor_and_repeat():
         out.append(host(B))
     assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
     P.close()
+
+
+@pytest.mark.parametrize("use_graph", [False, True])
+def test_batch_slots_row_by_row(use_graph):
+    """A batch whose slots all run row by row: every launch shape and precision,
+    light and team rows, a fixed schedule and stops in and after the first chunk,
+    slots held, run again after a commit with other slots."""
+    import torch
+    stream = torch.cuda.Stream()
+    rng = np.random.default_rng(4)
+    with torch.cuda.stream(stream):
+        items = []
+        for i, R in enumerate([2, 6, 10, 16, 20, 32, 40, 64, 16, 10]):
+            X = _tensor(EDGES + ([9_000] if i % 2 else []), (60, 45) if i % 3 else (30, 20, 10), 60 + i)
+            M = synth.random_model(60 + i, X.dims, R)
+            Bh = M.factors[0] * M.lam
+            hist = oracle.mu_inner(X, 0, Bh, M.factors, lmax=20)[2]
+            at = [0, 3, 14, 17, None][i % 5]
+            tol = 0.0 if at is None else float(np.minimum.accumulate(hist)[at]) * (1 + 1e-5)
+            prec = cpapr.CPAPR_MIXED if i >= 8 else cpapr.CPAPR_FP64
+            P = cpapr.Plan.from_tensor(X, R, lmax=20, tol=tol, precision=prec)
+            items.append((X, M, P, Bh, tol, prec, [dev(a) for a in M.factors], dev(Bh), dev(np.zeros_like(Bh))))
+        b = cpapr.Batch(len(items), sum(it[2].tiles() for it in items) + 1)
+        for i, (X, M, P, Bh, tol, prec, A, B, Phi) in enumerate(items):
+            b.set(i, P, 0, B, A, Phi)
+        b.commit()
+        for turn in range(4):
+            held = set()
+            if turn == 2:
+                held = {1, 4}
+                b.hold([i in held for i in range(len(items))])
+            if turn == 3:
+                b.hold([0] * len(items))
+                b.clear(0)
+                b.commit()
+            for it in items:
+                it[7].copy_(dev(it[3]))
+            b.inner(20, use_graph=use_graph)
+            viol, upd, done = b.status()
+            for i, (X, M, P, Bh, tol, prec, A, B, Phi) in enumerate(items):
+                if i in held or (turn == 3 and i == 0):
+                    assert np.array_equal(host(B), Bh)
+                    continue
+                Bo, Po, hist, nup = oracle.mu_inner(X, 0, Bh, M.factors, lmax=20, tau=tol)
+                t, el = (TOL64, True) if prec == cpapr.CPAPR_FP64 else (TOL32, False)
+                assert upd[i] == nup and done[i] == (1 if nup < 20 else 0)
+                assert_parity(host(B), Bo, t, f"B slot {i}", elementwise=el)
+                assert_parity(host(Phi), Po, t, f"Phi slot {i}", elementwise=el)
+        b.close()
