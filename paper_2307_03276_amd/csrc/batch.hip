@@ -219,8 +219,9 @@ Error enqueue_rows(cpapr_batch* b, int lmax, hipStream_t s)
                                             b->copy_grid, s);
         if (e.code) return e;
     }
-    for (int l0 = 0; l0 < lmax; l0 += cpapr::kInnerChunk) {
-        const int n = std::min(cpapr::kInnerChunk, lmax - l0);
+    const int step = cpapr::inner_step(lmax);
+    for (int l0 = 0; l0 < lmax; l0 += step) {
+        const int n = std::min(step, lmax - l0);
         for (int c = 0; c < cpapr::kRowShapes; ++c)
             if (b->rows[c].n > 0) {
                 e = cpapr::launch_rows_batch(c, b->rows[c], n, false, s);
@@ -245,7 +246,7 @@ Error enqueue_sequence(cpapr_batch* b, int lmax, hipStream_t s)
     Error e = cpapr::launch_batch_reset(b->st, b->max_slots, s);
     if (e.code) return e;
     if (lmax == 0) return enqueue_phi(b, b->classes, s);
-    if (b->nrows > 0) return enqueue_rows(b, lmax, s);
+    if (b->nrows > 0 && lmax > 1) return enqueue_rows(b, lmax, s);
     for (int l = 0; l < lmax; ++l) {
         e = enqueue_phi(b, b->classes, s);
         if (e.code) return e;

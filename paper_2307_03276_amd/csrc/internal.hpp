@@ -29,25 +29,35 @@ constexpr int kViolStride = 16;  // u64 words per slot (128 bytes)
 constexpr int kInnerChunk = 16;
 constexpr int kInnerSlots = 64;
 constexpr int kBatchInnerSlots = 8;  // per batch slot
+// Iterations per chunk of an inner loop of lmax: equal shares of at most kInnerChunk.
+inline int inner_step(int lmax)
+{
+    const int chunks = (lmax + kInnerChunk - 1) / kInnerChunk;
+    return (lmax + chunks - 1) / chunks;
+}
 constexpr int kRowClasses = 20;
 constexpr int kLenBuckets = 128;  // row lengths: four buckets per octave
 constexpr int kRowMeta = 64 + 2 * kLenBuckets;
 
+// Results a call reads back, in one transfer.
+struct DevResults {
+    double last_viol[CPAPR_MAX_MODES];  // last KKT violation seen per mode
+    int done;                           // inner loop of the current mode has stopped
+    int updates;                        // MU updates in the current inner loop
+    int sweep_updates;                  // MU updates in the current outer sweep
+    int rerun;                          // iteration of the chunk the rows are run again to (-1: none)
+    long long total_updates;            // MU updates since the last reset
+    long long phi_evals;                // Phi computations since the last reset
+    double ll;                          // log-likelihood result
+    long long row_steps;                // row solves: steps summed over rows since the last reset
+    long long trial_evals;              // row solves: line-search passes since the last reset
+};
+
 // Device-side state block of one inner loop (lives in the plan workspace).
-struct DevState {
-    unsigned long long viol[2][kViolSlots * kViolStride];  // per-parity slots, ordered bits of doubles >= 0
-    double last_viol[CPAPR_MAX_MODES];                      // last KKT violation seen per mode
-    int done;                                               // inner loop of the current mode has stopped
-    int updates;                                            // MU updates in the current inner loop
-    int sweep_updates;                                      // MU updates in the current outer sweep
-    int rerun;                                              // iteration of the chunk the rows are run again to (-1: none)
-    long long total_updates;                                // MU updates since the last reset
-    long long phi_evals;                                    // Phi computations since the last reset
-    double ll;                                              // log-likelihood result
-    long long row_steps;                                    // row solves: steps summed over rows since the last reset
-    long long trial_evals;                                  // row solves: line-search passes since the last reset
+struct DevState : DevResults {
     int pq_all_done;                                        // row solves: no row of the current mode is active
     int pq_idle;                                            // row solves: no row is in a line search
+    unsigned long long viol[2][kViolSlots * kViolStride];   // per-parity slots, ordered bits of doubles >= 0
     unsigned long long iv[kInnerSlots][kInnerChunk];        // KKT violation per iteration of a chunk (ordered bits)
 };
 
@@ -403,6 +413,10 @@ Error launch_loglik(const cpapr_plan* P, const double* lam, const double* const*
 Error launch_loglik_terms(const cpapr_plan* P, const double* B, const double* const* A, double eps, double* partial,
                           int* nparts, hipStream_t s);
 int64_t loglik_partials(int64_t nnz);
+// The whole log-likelihood (into the state) where loglik_fused_supported: the
+// terms and every factor's column sums in one launch, then one reduction.
+bool loglik_fused_supported(int R);
+Error launch_loglik_fused(const cpapr_plan* P, const double* lam, const double* const* A, double eps, hipStream_t s);
 
 // ---- transient Phi without a plan (api.hip) ----
 // Workspace bytes of a transient Phi for N modes and nnz nonzeros.

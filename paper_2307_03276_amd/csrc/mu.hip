@@ -493,6 +493,7 @@ Error launch_normalize(const double* B, const double* lam, double* A, float* A32
 Error launch_loglik(const cpapr_plan* P, const double* lam, const double* const* A, double eps, hipStream_t s)
 {
     const int N = P->N, R = P->R;
+    if (loglik_fused_supported(R)) return launch_loglik_fused(P, lam, A, eps, s);
     for (int m = 0; m < N; ++m) {
         Error e = launch_colsum(A[m], P->dims[m], R, P->partial, P->colsums + (int64_t)m * R, s);
         if (e.code) return e;

@@ -1137,6 +1137,7 @@ __host__ __device__ inline int class_cap(ClassShape c) { return 4 * c.KB * c.NG 
 // team running.
 constexpr int kTeamMax = 128;
 constexpr int kTeamMembers = 256;
+constexpr int kSpreadBlocks = 256;  // one workgroup per compute unit
 
 __device__ __forceinline__ int class_of(ClassShape c, int len)
 {
@@ -1911,7 +1912,8 @@ void rows_finish(cpapr_plan* P, int mode, const int* meta)
 namespace {
 
 // Operands of the resident rows of one mode (without its flags).
-void res_args(const cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, bool teams, ResArgs* out)
+void res_args(const cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, bool teams, int max_spread,
+              ResArgs* out)
 {
     Shape sh;
     row_shape(P->R, &sh);
@@ -1942,14 +1944,29 @@ void res_args(const cpapr_plan* P, int mode, double* B, const void* const* fac, 
         begin[i] = at;
         at += r.count[i];
     }
+    // A tensor too small to fill the device spreads its rows over more lane
+    // groups (fewer nonzeros per group one after the other), up to `spread` times.
     int64_t blocks = 0;
-    for (int i = nlight - 1; i >= 0; --i) {
-        if (r.count[i] == 0) continue;
-        const int S = i <= cs.KB ? 1 : 1 << (i - cs.KB);
-        const int per = std::max(1, W * NG / S);  // rows per workgroup
-        a.entry[a.nentries++] = {(int32_t)blocks, begin[i], r.count[i], S};
-        blocks += cdiv(r.count[i], per);  // < 2^31 rows
+    auto list = [&](int spread) {
+        blocks = 0;
+        a.nentries = 0;
+        for (int i = nlight - 1; i >= 0; --i) {
+            if (r.count[i] == 0) continue;
+            const int nb = i <= cs.KB ? i : cs.KB;  // blocks of four nonzeros per lane group
+            int S = i <= cs.KB ? 1 : 1 << (i - cs.KB);
+            for (int f = 1; f < spread && f < nb && S < W * NG; f *= 2) S *= 2;
+            const int per = std::max(1, W * NG / S);  // rows per workgroup
+            a.entry[a.nentries++] = {(int32_t)blocks, begin[i], r.count[i], S};
+            blocks += cdiv(r.count[i], per);  // < 2^31 rows
+        }
+    };
+    int spread = 1;
+    while (spread < max_spread) {
+        list(2 * spread);
+        if (blocks > kSpreadBlocks) break;
+        spread *= 2;
     }
+    list(spread);
     a.light_blocks = (int)blocks;
     a.heavy0 = begin[nlight];
     a.team0 = r.count[nlight];
@@ -1970,6 +1987,235 @@ void res_args(const cpapr_plan* P, int mode, double* B, const void* const* fac, 
 
 }  // namespace
 
+// ---- log-likelihood ----
+
+namespace {
+
+constexpr int kSumParts = 128;  // column-sum workgroups per factor
+
+struct LoglikArgs {
+    const int32_t* rows;
+    const uint32_t* cofs;
+    const double* vals;
+    const double* fac[CPAPR_MAX_MODES];  // mode 0's factor, then the others'
+    const double* all[CPAPR_MAX_MODES];  // every mode's factor, for the column sums
+    int64_t dims[CPAPR_MAX_MODES];
+    const double* lam;
+    double* part;     // [term workgroups] sums of terms
+    double* sums;     // [N x parts x R] column sums
+    int64_t nnz;
+    double eps;
+    int R, N;
+    int parts;        // column-sum workgroups per factor
+    int per;          // nonzeros per wave
+};
+
+// x log(max(m, eps)) over the nonzeros of mode 0's copy, m = sum_r lambda_r
+// prod_m A(m)[i_m, r]: four nonzeros per lane group, their sums
+// reduce-scattered over the quad as in block4, so that a lane takes one
+// logarithm for the four (an all-reduce with the logarithm in every lane
+// spent 150 us on 5M three-way nonzeros at R = 16, Phi on the same tensor 85).
+// While all nonzeros of a step lie in one row, that row is loaded once. The
+// first workgroups sum the factors' columns.
+template <int G, int C, int NM1>
+__global__ __launch_bounds__(kBlock) void loglik_kernel(LoglikArgs a)
+{
+    constexpr int W = kBlock / 64;
+    constexpr uint32_t STEP = 4 * (64 / G);
+    __shared__ double sh[kBlock];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int R = a.R;
+    if ((int)blockIdx.x < a.N * a.parts) {
+        const int m = (int)blockIdx.x / a.parts, part = (int)blockIdx.x % a.parts;
+        const int64_t per = (a.dims[m] + a.parts - 1) / a.parts;
+        const int64_t r0 = part * per, r1 = min(r0 + per, a.dims[m]);
+        const int Q = kBlock / R, c = t % R, q = t / R;
+        double s = 0.0;
+        if (q < Q) {
+#pragma unroll 8
+            for (int64_t i = r0 + q; i < r1; i += Q) s += a.all[m][i * R + c];
+        }
+        sh[t] = q < Q ? s : 0.0;
+        __syncthreads();
+        if (t < R) {
+            double tot = 0.0;
+            for (int k = 0; k < Q; ++k) tot += sh[k * R + t];
+            a.sums[((int64_t)m * a.parts + part) * R + t] = tot;
+        }
+        return;
+    }
+    const int blk = (int)blockIdx.x - a.N * a.parts;
+    const int gl = lane % G, g = lane / G;
+    const int64_t p0 = ((int64_t)blk * W + wave) * a.per;
+    const uint32_t w0 = (uint32_t)min(p0, a.nnz), w1 = (uint32_t)min(p0 + a.per, a.nnz);
+    const int colbase = min(gl * C, R - C);
+    const bool odd1 = lane & 1, odd2 = lane & 2;
+    const int q = (lane & 3) ^ (G >= 8 && (lane & 4) ? 3 : 0);
+    double lam[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) lam[c] = colbase + c >= gl * C && colbase + c < R ? a.lam[colbase + c] : 0.0;
+    uint32_t off[NM1 > 0 ? NM1 : 1];
+    uint32_t row = 0;
+    double x = 0.0;
+    auto load_meta = [&](uint32_t base) {
+        const uint32_t p = base + (uint32_t)(g * 4 + q), pc = min(p, w1 - 1);
+        x = a.vals[pc];
+        if (p >= w1) x = 0.0;
+        row = (uint32_t)a.rows[pc] * (uint32_t)R;
+        if constexpr (NM1 > 0)
+#pragma unroll
+            for (int m = 0; m < NM1; ++m) off[m] = a.cofs[(int64_t)m * a.nnz + pc];
+    };
+    double ll = 0.0;
+    if (w0 < w1) load_meta(w0);
+    for (uint32_t base = w0; base < w1; base += STEP) {
+        const double xc = x;
+        const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)row);
+        const bool one = __ballot(row != first) == 0ull;
+        double pi[4][C], f[4][C];
+        auto times = [&](const double* fac, uint32_t o) {
+            load_cols<C>(fac, quad_bcast<0>(o), colbase, f[0]);
+            load_cols<C>(fac, quad_bcast<1>(o), colbase, f[1]);
+            load_cols<C>(fac, quad_bcast<2>(o), colbase, f[2]);
+            load_cols<C>(fac, quad_bcast<3>(o), colbase, f[3]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int c = 0; c < C; ++c) pi[j][c] *= f[j][c];
+        };
+        if (one) {
+            load_cols<C>(a.fac[0], first, colbase, f[0]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int c = 0; c < C; ++c) pi[j][c] = f[0][c] * lam[c];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int c = 0; c < C; ++c) pi[j][c] = lam[c];
+            times(a.fac[0], row);
+        }
+        if constexpr (NM1 > 0) {
+#pragma unroll
+            for (int m = 0; m < NM1; ++m) times(a.fac[1 + m], off[m]);
+        } else {
+            const uint32_t pc = min(base + (uint32_t)(g * 4 + q), w1 - 1);
+            for (int m = 0; m < a.N - 1; ++m) times(a.fac[1 + m], a.cofs[(int64_t)m * a.nnz + pc]);
+        }
+        if (base + STEP < w1) load_meta(base + STEP);
+        double d[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            d[j] = pi[j][0];
+#pragma unroll
+            for (int c = 1; c < C; ++c) d[j] += pi[j][c];
+        }
+        const double a0 = (odd1 ? d[1] : d[0]) + dpp_f64<0xB1>(odd1 ? d[0] : d[1]);
+        const double a1 = (odd1 ? d[3] : d[2]) + dpp_f64<0xB1>(odd1 ? d[2] : d[3]);
+        double m = (odd2 ? a1 : a0) + dpp_f64<0x4E>(odd2 ? a0 : a1);
+        if constexpr (G >= 8) m += dpp_f64<0x141>(m);
+        if constexpr (G >= 16) m += dpp_f64<0x140>(m);
+        ll += xc * log(__builtin_fmax(m, a.eps));
+    }
+    if (gl >= 4) ll = 0.0;  // the group's other quads hold the same nonzeros
+    for (int o = 32; o > 0; o >>= 1) ll += __shfl_xor(ll, o);
+    if (lane == 0) sh[wave] = ll;
+    __syncthreads();
+    if (t == 0) a.part[blk] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
+}
+
+// Terms minus the model's mass sum_r lambda_r prod_m (column sums).
+__global__ __launch_bounds__(1024) void loglik_sum_kernel(const double* __restrict__ part, int nparts,
+                                                          const double* __restrict__ sums, int sum_parts,
+                                                          const double* __restrict__ lam, int N, int R, DevState* st)
+{
+    __shared__ double sh[1024];
+    __shared__ double mass[CPAPR_MAX_MODES * 64];
+    const int t = threadIdx.x;
+    // the columns of all factors, 1024 / (N R) threads each
+    const int cols = N * R, Q = max(1, 1024 / cols);
+    for (int c0 = 0; c0 < cols; c0 += 1024) {
+        const int c = c0 + t % min(cols, 1024), q = t / min(cols, 1024);
+        double s = 0.0;
+        if (q < Q && c < cols) {
+            const double* src = sums + (int64_t)(c / R) * sum_parts * R + c % R;
+#pragma unroll 4
+            for (int k = q; k < sum_parts; k += Q) s += src[(int64_t)k * R];
+        }
+        sh[t] = s;
+        __syncthreads();
+        if (q == 0 && c < cols) {
+            double tot = 0.0;
+            for (int k = 0; k < Q; ++k) tot += sh[k * min(cols, 1024) + t];
+            mass[c] = tot;
+        }
+        __syncthreads();
+    }
+    double v = 0.0;
+#pragma unroll 4
+    for (int k = t; k < nparts; k += 1024) v += part[k];
+    if (t < R) {
+        double p = lam[t];
+        for (int m = 0; m < N; ++m) p *= mass[m * R + t];
+        v -= p;
+    }
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if ((t & 63) == 0) sh[t >> 6] = v;
+    __syncthreads();
+    if (t == 0) {
+        double s = 0.0;
+        for (int w = 0; w < 16; ++w) s += sh[w];
+        st->ll = s;
+    }
+}
+
+}  // namespace
+
+bool loglik_fused_supported(int R) { return R <= 64; }
+
+Error launch_loglik_fused(const cpapr_plan* P, const double* lam, const double* const* A, double eps, hipStream_t s)
+{
+    LoglikArgs a{};
+    a.rows = P->mode[0].rows;
+    a.cofs = P->mode[0].cofs;
+    a.vals = P->mode[0].vals;
+    for (int m = 0; m < P->N; ++m) {
+        a.fac[m] = a.all[m] = A[m];
+        a.dims[m] = P->dims[m];
+    }
+    a.lam = lam;
+    a.part = P->llpart;
+    a.sums = P->partial;
+    a.nnz = P->nnz;
+    a.eps = eps;
+    a.R = P->R;
+    a.N = P->N;
+    a.parts = std::min(kSumParts, kPartials / P->N);
+    // 128 nonzeros per wave (512 per partial sum) at least; about 4096 waves
+    int64_t per = 128;
+    while (per < 2048 && per * 2 * 4096 <= P->nnz) per *= 2;
+    a.per = (int)per;
+    const int64_t blocks = cdiv(P->nnz, per * (kBlock / 64));
+    const dim3 grid((unsigned)(blocks + (int64_t)a.N * a.parts));
+    Shape sh = heavy_shape(P->R, false);
+    Error e = by_heavy_shape<false>(sh, [&](auto G, auto C) -> Error {
+        constexpr int GG = decltype(G)::value, CC = decltype(C)::value;
+        switch (P->N) {
+            case 2: loglik_kernel<GG, CC, 1><<<grid, kBlock, 0, s>>>(a); break;
+            case 3: loglik_kernel<GG, CC, 2><<<grid, kBlock, 0, s>>>(a); break;
+            case 4: loglik_kernel<GG, CC, 3><<<grid, kBlock, 0, s>>>(a); break;
+            default: loglik_kernel<GG, CC, 0><<<grid, kBlock, 0, s>>>(a); break;
+        }
+        CPAPR_LAUNCHED();
+        return {CPAPR_OK, ""};
+    });
+    if (e.code) return e;
+    loglik_sum_kernel<<<1, 1024, 0, s>>>(P->llpart, (int)blocks, P->partial, a.parts, lam, P->N, P->R, P->state);
+    CPAPR_LAUNCHED();
+    return {CPAPR_OK, ""};
+}
+
 // A batch slot can run row by row when its plan's single inner loop would, and
 // no row is longer than the largest team.
 int rows_batch_shape(const cpapr_plan* P, int mode)
@@ -1988,7 +2234,7 @@ void rows_batch_item(const cpapr_plan* P, int mode, const double* B, const void*
                      int* members)
 {
     ResArgs a;
-    res_args(P, mode, const_cast<double*>(B), fac, Phi, true, &a);
+    res_args(P, mode, const_cast<double*>(B), fac, Phi, true, 1, &a);  // the batch fills the device
     a.slot = slot;
     a.done = done;
     a.rerun = rerun;
@@ -2042,7 +2288,7 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
     const bool each = P->params.tol > 0.0;
     const int ncls = class_count(class_shape(sh)), nlight = ncls - 2;
     ResArgs a;
-    res_args(P, mode, B, fac, Phi, r.use_teams, &a);
+    res_args(P, mode, B, fac, Phi, r.use_teams, 8, &a);
     a.done = &P->state->done;
     a.rerun = &P->state->rerun;
     a.iv = &P->state->iv[0][0];
@@ -2085,7 +2331,7 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
     h.chunk = heavy_chunk(P->nnz);
 
     const int lmax = P->params.lmax;
-    const int step = each ? kInnerChunk : lmax;
+    const int step = each ? inner_step(lmax) : lmax;
     prof_begin(mode, s);  // one record per inner loop
     for (int l0 = 0; l0 < lmax; l0 += step) {
         const int n = std::min(step, lmax - l0);

@@ -517,17 +517,18 @@ Error build_sorted(cpapr_plan* P, const cpapr_coo* X, char* scratch, hipStream_t
             if (e.code) return e;
             continue;
         }
+        if (only >= 0) continue;  // a transient Phi has no use for the segment count
         const int gseg = std::min(grid_for(nnz), kSegPartials);
         count_segments_kernel<<<gseg, kBlock, 0, s>>>(pm.rows, nnz, segpart);
         CPAPR_LAUNCHED();
         sum_partials_kernel<<<1, kBlock, 0, s>>>(segpart, gseg, segc + n);
         CPAPR_LAUNCHED();
     }
+    if (only >= 0) return {CPAPR_OK, ""};
     int host[64 + CPAPR_MAX_MODES * kRowMeta];
     CPAPR_HIP(hipMemcpyAsync(host, flags, sizeof(int) * (64 + N * kRowMeta), hipMemcpyDeviceToHost, s));
     CPAPR_HIP(hipStreamSynchronize(s));
     for (int n = 0; n < N; ++n) {
-        if (only >= 0 && n != only) continue;
         unsigned long long seg;
         std::memcpy(&seg, host + 8 + 2 * n, sizeof(seg));
         P->mode[n].segments = (int64_t)seg;
