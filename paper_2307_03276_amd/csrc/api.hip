@@ -108,7 +108,7 @@ Layout layout(int N, int64_t nnz, const int64_t* dims, int R, const cpapr_params
 {
     const bool mixed = p->precision == CPAPR_MIXED, det = p->deterministic != 0;
     const int method = p->method;
-    const bool by_rows = cpapr::rows_supported(R, method);
+    const bool by_rows = cpapr::rows_supported(R);
     Layout L{};
     size_t off = 0;
     for (int n = 0; n < N; ++n) {
@@ -150,7 +150,7 @@ Layout layout(int N, int64_t nnz, const int64_t* dims, int R, const cpapr_params
     L.rs = off + s;
     if (by_rows) s += cpapr::rows_state_bind(nullptr, nullptr, nnz, maxI, R, p->tol > 0.0);
     L.hot = off + s;
-    if (by_rows) s += cpapr::rows_hot_bind(nullptr, nullptr, N, nnz, dims, R);
+    if (by_rows && method == CPAPR_METHOD_MU) s += cpapr::rows_hot_bind(nullptr, nullptr, N, nnz, dims, R);
     L.pqnr = off + s;
     if (method == CPAPR_METHOD_PQNR) s += cpapr::pqnr_bytes(maxI, R);
     L.pdnr = off + s;
@@ -201,6 +201,15 @@ Error phi_factors(cpapr_plan* P, int mode, const double* const* A, const void** 
     return {CPAPR_OK, ""};
 }
 
+// Whether the MU inner loop runs row by row (rows.hip): unless the caller chose
+// the Phi launch (a shape of its own or a variant). One iteration alone gathers
+// once either way, and the Phi kernel does that faster (8M uniform nonzeros, R =
+// 32: 224 against 394 us).
+bool runs_by_rows(const cpapr_plan* P)
+{
+    return P->by_rows && P->shape_auto && P->params.variant <= CPAPR_VARIANT_SEGMENTED && P->params.lmax > 1;
+}
+
 // One inner loop (Algorithm 1): zero Phi, then lmax x {Phi, KKT, MU update},
 // all gated by the device-side `done` flag. No host synchronisation. With a
 // fixed schedule (tol <= 0) nothing depends on the violation before the
@@ -209,11 +218,7 @@ Error enqueue_inner(cpapr_plan* P, int mode, double* B, const void* const* fac, 
 {
     const int64_t n = P->dims[mode] * (int64_t)P->R;
     const bool mixed = P->params.precision == CPAPR_MIXED;
-    // The rows' own loops (rows.hip) unless the caller chose the Phi launch: a
-    // shape of its own or a variant.
-    // One iteration alone gathers once either way, and the Phi kernel does that
-    // faster (8M uniform nonzeros, R = 32: 224 against 394 us).
-    if (P->by_rows && P->shape_auto && P->params.variant <= CPAPR_VARIANT_SEGMENTED && P->params.lmax > 1)
+    if (runs_by_rows(P))
         return cpapr::enqueue_inner_rows(P, mode, B, fac, Phi, s);
     const bool fused = !(P->params.tol > 0.0);
     const int* done = &P->state->done;
@@ -431,13 +436,13 @@ int cpapr_plan_create(const cpapr_coo* X, int32_t R, const cpapr_params* p, void
         P->det_tiles = cpapr::det_tile_capacity(X->nnz);
         int64_t maxI = 0;
         for (int m = 0; m < P->N; ++m) maxI = std::max(maxI, P->dims[m]);
-        P->by_rows = cpapr::rows_supported(R, p->method);
+        P->by_rows = cpapr::rows_supported(R);
         if (P->by_rows) {
             for (int n = 0; n < P->N; ++n)
                 cpapr::rows_mode_bind(&P->mode[n].rp, w + L.mode_rp[n], X->nnz, P->dims[n], R);
             P->team_wait = 5000000;  // 50 ms
             cpapr::rows_state_bind(&P->rs, w + L.rs, X->nnz, maxI, R, p->tol > 0.0);
-            cpapr::rows_hot_bind(P, w + L.hot, P->N, X->nnz, P->dims, R);
+            if (p->method == CPAPR_METHOD_MU) cpapr::rows_hot_bind(P, w + L.hot, P->N, X->nnz, P->dims, R);
         }
         if (p->method == CPAPR_METHOD_PQNR) cpapr::pqnr_bind(&P->pq, w + L.pqnr, maxI, R);
         if (p->method == CPAPR_METHOD_PDNR) cpapr::pdnr_bind(&P->pd, w + L.pdnr, maxI, R);
@@ -717,19 +722,28 @@ int cpapr_solve(cpapr_plan* plan, double* lambda, double* const* A, cpapr_stats*
         for (; k <= P->params.kmax; ++k) {
             for (int n = 0; n < N; ++n) {
                 const int64_t In = P->dims[n];
-                e = cpapr::launch_reset_state(P->state, n == 0, false, s);
-                if (e.code) return report(e);
+                const bool rows = runs_by_rows(P);
+                if (!rows) {
+                    e = cpapr::launch_reset_state(P->state, n == 0, false, s);
+                    if (e.code) return report(e);
+                }
                 const int32_t method = P->params.method;
                 e = cpapr::launch_shift_scale(A[n], P->phi_prev[n], lambda, P->B, In, R, P->params.kappa,
-                                              P->params.kappa_tol, k > 1, s);
+                                              P->params.kappa_tol, k > 1, s, rows ? P->state : nullptr, n == 0);
                 if (e.code) return report(e);
                 e = method == CPAPR_METHOD_PQNR   ? cpapr::enqueue_pqnr_inner(P, n, P->B, fac, P->phi_prev[n], s)
                     : method == CPAPR_METHOD_PDNR ? cpapr::enqueue_pdnr_inner(P, n, P->B, fac, P->phi_prev[n], s)
                                                   : enqueue_inner(P, n, P->B, fac, P->phi_prev[n], s);
                 if (e.code) return report(e);
+                float* a32 = mixed ? P->f32[n] : nullptr;
+                if (cpapr::colnorm_small(In, R)) {
+                    e = cpapr::launch_colnorm_small(P->B, lambda, A[n], a32, In, R, s);
+                    if (e.code) return report(e);
+                    continue;
+                }
                 e = cpapr::launch_colsum(P->B, In, R, P->partial, lambda, s);
                 if (e.code) return report(e);
-                e = cpapr::launch_normalize(P->B, lambda, A[n], mixed ? P->f32[n] : nullptr, In, R, s);
+                e = cpapr::launch_normalize(P->B, lambda, A[n], a32, In, R, s);
                 if (e.code) return report(e);
             }
             if (tol > 0.0) {

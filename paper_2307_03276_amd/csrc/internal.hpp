@@ -345,7 +345,7 @@ Error launch_rows_batch_decide(const void* items, int n, BatchState st, int32_t*
                                hipStream_t s);
 
 // ---- MU inner loop row by row (rows.hip) ----
-bool rows_supported(int R, int method);
+bool rows_supported(int R);
 // Bytes of a mode's row classes / of the inner loop's buffers, bound to `base`
 // unless r is nullptr (stops: tol > 0).
 size_t rows_mode_bind(RowPlan* r, char* base, int64_t nnz, int64_t dim, int R);
@@ -362,6 +362,11 @@ Error rows_hot_build(cpapr_plan* P, hipStream_t s);
 // receives the last Phi. State and counters as the Phi / KKT / update launches
 // leave them.
 Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, hipStream_t s);
+// The four-trial line-search sums of launch_delta4, row by row (R >= 4, the
+// plan's rows by class): column k of `out` for rows with live[row] == 1, other
+// entries are left alone.
+Error launch_delta4_rows(const cpapr_plan* P, int mode, const double* B, const double* D, const int32_t* live,
+                         const void* const* fac, double eps, double* out, const int* skip, hipStream_t s);
 
 // ---- elementwise and reduction kernels (mu.hip) ----
 Error launch_fill(double* p, int64_t n, double v, const int* done, hipStream_t s);
@@ -401,7 +406,11 @@ Error launch_kkt_fold(DevState* st, int l, int mode, hipStream_t s);
 Error launch_mu_update(double* B, double* Phi, int64_t n, DevState* st, int l, int mode, double tol, bool zero_phi,
                        hipStream_t s);
 Error launch_shift_scale(double* A, const double* phi_prev, const double* lam, double* B, int64_t I, int R,
-                         double kappa, double kappa_tol, bool shift, hipStream_t s);
+                         double kappa, double kappa_tol, bool shift, hipStream_t s, DevState* st = nullptr,
+                         bool new_sweep = false);  // st: also begins a row-by-row inner loop (launch_reset_state otherwise)
+// lambda and the normalised factor of a small matrix in one launch.
+bool colnorm_small(int64_t I, int R);
+Error launch_colnorm_small(const double* B, double* lam, double* A, float* A32, int64_t I, int R, hipStream_t s);
 Error launch_colsum(const double* M, int64_t I, int R, double* partial, double* out, hipStream_t s);
 Error launch_normalize(const double* B, const double* lam, double* A, float* A32, int64_t I, int R,
                        hipStream_t s);

@@ -198,8 +198,14 @@ __global__ __launch_bounds__(kBlock) void shift_scale_kernel(double* __restrict_
                                                              const double* __restrict__ phi_prev,
                                                              const double* __restrict__ lam, double* __restrict__ B,
                                                              int64_t n, int R, double kappa, double kappa_tol,
-                                                             int shift)
+                                                             int shift, DevState* st, int new_sweep)
 {
+    if (st != nullptr && blockIdx.x == 0 && threadIdx.x == 0) {  // a new inner loop begins
+        st->done = 0;
+        st->rerun = -1;
+        st->updates = 0;
+        if (new_sweep) st->sweep_updates = 0;
+    }
     for (int64_t e = blockIdx.x * (int64_t)kBlock + threadIdx.x; e < n; e += (int64_t)gridDim.x * kBlock) {
         double a = A[e];
         if (shift && a < kappa_tol && phi_prev[e] > 1.0) {
@@ -264,6 +270,47 @@ __global__ __launch_bounds__(kBlock) void normalize_kernel(const double* __restr
         A[e] = a;
         if (A32) A32[e] = (float)a;
     }
+}
+
+// lambda = column sums of B and A = B Lambda^-1 of a matrix of up to 8192
+// entries, in one workgroup: one launch instead of three that each wait for
+// the one before (100 x 10: 3 us against 2.6 + 1.8 + 2.3 and their gaps).
+__global__ __launch_bounds__(1024) void colnorm_small_kernel(const double* __restrict__ B, double* __restrict__ lam,
+                                                             double* __restrict__ A, float* __restrict__ A32, int n, int R)
+{
+    __shared__ double sm[1024], tot[CPAPR_MAX_RANK];
+    const int t = threadIdx.x, Q = 1024 / R, c = t % R, q = t / R, step = Q * R;
+    double v[8], s = 0.0;  // n <= 8192, at least 768 threads at work: up to eleven passes; the first eight stay here
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = 0.0;
+    if (q < Q) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (t + k * step < n) v[k] = B[t + k * step];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s += v[k];
+        for (int i = t + 8 * step; i < n; i += step) s += B[i];
+    }
+    sm[t] = q < Q ? s : 0.0;
+    __syncthreads();
+    if (t < R) {
+        double a = 0.0;
+        for (int k = 0; k < Q; ++k) a += sm[k * R + t];
+        tot[t] = a;
+        lam[t] = a;
+    }
+    __syncthreads();
+    if (q >= Q) return;
+    const double l = tot[c];
+    auto put = [&](int i, double b) {
+        const double a = l > 0.0 ? b / l : 0.0;
+        A[i] = a;
+        if (A32) A32[i] = (float)a;
+    };
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        if (t + k * step < n) put(t + k * step, v[k]);
+    for (int i = t + 8 * step; i < n; i += step) put(i, B[i]);
 }
 
 __global__ __launch_bounds__(kBlock) void loglik_final_kernel(const double* __restrict__ partial, int nparts,
@@ -460,11 +507,20 @@ Error launch_kkt_fold(DevState* st, int l, int mode, hipStream_t s)
 }
 
 Error launch_shift_scale(double* A, const double* phi_prev, const double* lam, double* B, int64_t I, int R,
-                         double kappa, double kappa_tol, bool shift, hipStream_t s)
+                         double kappa, double kappa_tol, bool shift, hipStream_t s, DevState* st, bool new_sweep)
 {
     const int64_t n = I * R;
     shift_scale_kernel<<<grid_for(n, 4096), kBlock, 0, s>>>(A, phi_prev, lam, B, n, R, kappa, kappa_tol,
-                                                            shift ? 1 : 0);
+                                                            shift ? 1 : 0, st, new_sweep ? 1 : 0);
+    CPAPR_LAUNCHED();
+    return {CPAPR_OK, ""};
+}
+
+bool colnorm_small(int64_t I, int R) { return I * R <= 8192; }
+
+Error launch_colnorm_small(const double* B, double* lam, double* A, float* A32, int64_t I, int R, hipStream_t s)
+{
+    colnorm_small_kernel<<<1, 1024, 0, s>>>(B, lam, A, A32, (int)(I * R), R);
     CPAPR_LAUNCHED();
     return {CPAPR_OK, ""};
 }

@@ -80,6 +80,19 @@ __device__ __forceinline__ double seg_sum(double v)
     return v;
 }
 
+// 1 / sqrt(x), x > 0 and finite: the hardware estimate and two Newton steps
+// (each squares the error, so the second leaves the roundings).
+__device__ __forceinline__ double rsqrt_pos(double x)
+{
+    double r = __builtin_amdgcn_rsq(x);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const double e = __builtin_fma(-x * r, r, 1.0);
+        r = __builtin_fma(0.5 * r, e, r);
+    }
+    return r;
+}
+
 __device__ __forceinline__ double wave_sum(double v) { return seg_sum<64>(v); }
 
 __device__ __forceinline__ double wave_max(double v)
@@ -234,9 +247,12 @@ __device__ __forceinline__ void hess_tiles(const HessArgs& a)
 #pragma unroll
             for (int t = 0; t < NT; ++t) mk = __builtin_fma(bv[t], pi[t], mk);
             mk = seg_sum<16>(mk);
+            // 1 / max(m, eps) by the Phi kernel's estimate and Newton step, once for both quotients
             const double mm = mk > a.eps ? mk : a.eps;
-            const double sc = x / mm;
-            const double w = sc / mm;
+            double rm = __builtin_amdgcn_rcp(mm);
+            rm = __builtin_fma(rm, __builtin_fma(-mm, rm, 1.0), rm);
+            const double sc = x * rm;
+            const double w = sc * rm;
             int rk[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) rk[k] = __builtin_amdgcn_readlane(row, 16 * k);
@@ -406,9 +422,11 @@ __global__ __launch_bounds__(64 * begin_waves<RM>()) void pdnr_begin_kernel(RowA
                     ok = false;
                     break;
                 }
-                const double lkk = sqrt(piv);
-                const double lik = lane == k ? lkk : M[k] / lkk;
-                M[k] = lik;
+                // The diagonal place keeps 1 / L[k][k]: the substitutions multiply by it
+                // (a square root and 3 RM divisions, one after the other, were most of this kernel).
+                const double inv = rsqrt_pos(piv);
+                const double lik = M[k] * inv;
+                M[k] = lane == k ? inv : lik;
                 if (lane < RM) lcol[k][lane] = lik;
                 wave_sync();
 #pragma unroll
@@ -419,7 +437,7 @@ __global__ __launch_bounds__(64 * begin_waves<RM>()) void pdnr_begin_kernel(RowA
                 double z = fre ? -g : 0.0;
 #pragma unroll
                 for (int j = 0; j < RM; ++j) {
-                    const double yj = lane_value(z, j) / lane_value(M[j], j);
+                    const double yj = lane_value(z, j) * lane_value(M[j], j);
                     if (lane > j)
                         z = __builtin_fma(-M[j], yj, z);
                     else if (lane == j)
@@ -427,7 +445,7 @@ __global__ __launch_bounds__(64 * begin_waves<RM>()) void pdnr_begin_kernel(RowA
                 }
 #pragma unroll
                 for (int j = RM - 1; j >= 0; --j) {
-                    const double dj = lane_value(z, j) / lane_value(M[j], j);
+                    const double dj = lane_value(z, j) * lane_value(M[j], j);
                     if (lane < j)
                         z = __builtin_fma(-lcol[lane][j], dj, z);
                     else if (lane == j)
@@ -511,9 +529,9 @@ __global__ __launch_bounds__(64) void pdnr_begin16_kernel(RowArgs a)
     for (int k = 0; k < RM; ++k) {
         const double piv = __shfl(M[k], sb + k);
         ok = ok && piv > 0.0;
-        const double lkk = sqrt(piv > 0.0 ? piv : 1.0);
-        const double lik = s == k ? lkk : M[k] / lkk;
-        M[k] = lik;
+        const double inv = rsqrt_pos(piv > 0.0 ? piv : 1.0);  // as in pdnr_begin_kernel
+        const double lik = M[k] * inv;
+        M[k] = s == k ? inv : lik;
         lcol[k][s] = lik;
         wave_sync();
 #pragma unroll
@@ -522,7 +540,7 @@ __global__ __launch_bounds__(64) void pdnr_begin16_kernel(RowArgs a)
     double z = fre ? -g : 0.0;
 #pragma unroll
     for (int j = 0; j < RM; ++j) {
-        const double yj = __shfl(z, sb + j) / __shfl(M[j], sb + j);
+        const double yj = __shfl(z, sb + j) * __shfl(M[j], sb + j);
         if (s > j)
             z = __builtin_fma(-M[j], yj, z);
         else if (s == j)
@@ -530,7 +548,7 @@ __global__ __launch_bounds__(64) void pdnr_begin16_kernel(RowArgs a)
     }
 #pragma unroll
     for (int j = RM - 1; j >= 0; --j) {
-        const double dj = __shfl(z, sb + j) / __shfl(M[j], sb + j);
+        const double dj = __shfl(z, sb + j) * __shfl(M[j], sb + j);
         if (s < j)
             z = __builtin_fma(-lcol[s][j], dj, z);
         else if (s == j)
@@ -886,9 +904,13 @@ Error enqueue_pdnr_inner(cpapr_plan* P, int mode, double* B, const void* const* 
         }
         if (e.code) return e;
         if (R >= kPdnrTrials) {  // all trials in one line-search pass
-            e = launch_fill(P->pd.T, n, 0.0, idle, s);
-            if (e.code) return e;
-            e = launch_delta4(P, mode, B, P->pd.Dd, P->pd.status, fac, P->params.eps, P->pd.T, idle, s);
+            if (P->by_rows && P->shape_auto) {
+                e = launch_delta4_rows(P, mode, B, P->pd.Dd, P->pd.status, fac, P->params.eps, P->pd.T, idle, s);
+            } else {
+                e = launch_fill(P->pd.T, n, 0.0, idle, s);
+                if (e.code) return e;
+                e = launch_delta4(P, mode, B, P->pd.Dd, P->pd.status, fac, P->params.eps, P->pd.T, idle, s);
+            }
             if (e.code) return e;
             pdnr_flags_kernel<<<1, 64, 0, s>>>(st, 0);
             CPAPR_LAUNCHED();

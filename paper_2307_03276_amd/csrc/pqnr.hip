@@ -554,9 +554,13 @@ Error enqueue_pqnr_inner(cpapr_plan* P, int mode, double* B, const void* const* 
         });
         if (e.code) return e;
         if (R >= kPqnrTrials) {  // all trials in one line-search pass
-            e = launch_fill(P->pq.T, n, 0.0, idle, s);
-            if (e.code) return e;
-            e = launch_delta4(P, mode, B, P->pq.Dd, P->pq.status, fac, P->params.eps, P->pq.T, idle, s);
+            if (P->by_rows && P->shape_auto) {
+                e = launch_delta4_rows(P, mode, B, P->pq.Dd, P->pq.status, fac, P->params.eps, P->pq.T, idle, s);
+            } else {
+                e = launch_fill(P->pq.T, n, 0.0, idle, s);
+                if (e.code) return e;
+                e = launch_delta4(P, mode, B, P->pq.Dd, P->pq.status, fac, P->params.eps, P->pq.T, idle, s);
+            }
             if (e.code) return e;
             pqnr_flags_kernel<<<1, 64, 0, s>>>(st, 0);
             CPAPR_LAUNCHED();

@@ -109,6 +109,47 @@ __device__ __forceinline__ void load_cols(const L* fac, uint32_t off, int colbas
     for (int c = 0; c < C; ++c) v[c] = (double)f[c];
 }
 
+// Sum of the two values v of lanes i and i ^ 16 (i ^ 32), in both.
+__device__ __forceinline__ double sum_xor16(double v)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ __forceinline__ double sum_xor32(double v)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
+// Place among its group's columns of a lane: groups with an odd number hold
+// them in reverse, so that the mirrors below pair equal columns.
+template <int G>
+__device__ __forceinline__ int column_lane(int lane)
+{
+    if constexpr (G == 4) return (lane & 3) ^ (lane & 4 ? 3 : 0);
+    if constexpr (G == 8) return (lane & 7) ^ (lane & 8 ? 7 : 0);
+    return lane % G;
+}
+
+// Sum over the S lane groups (aligned, S a power of two up to 64 / G) of one
+// row, every lane receiving its column's total, on the vector unit alone
+// (shuffles through LDS made this most of a short iteration).
+template <int G>
+__device__ __forceinline__ double sum_groups(double v, int S)
+{
+    if constexpr (G == 4) {
+        if (S >= 2) v += dpp_f64<0x141>(v);
+        if (S >= 4) v += dpp_f64<0x140>(v);
+    }
+    if constexpr (G == 8)
+        if (S >= 2) v += dpp_f64<0x140>(v);
+    if (S * G >= 32) v = sum_xor16(v);
+    if (S * G >= 64) v = sum_xor32(v);
+    return v;
+}
+
 struct Entry {
     int32_t block0;  // first workgroup of the class
     int32_t row0;    // first position in `order`
@@ -212,7 +253,7 @@ __device__ __forceinline__ void resident_rows(const ResArgs& a, int at, bool rer
     __shared__ unsigned long long vmax[kInnerChunk];
     __shared__ int sh_ok, sh_last;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int gl = lane % G, g = lane / G;
+    const int gl = column_lane<G>(lane), g = lane / G;
     const int R = a.R;
     if (t < kInnerChunk) vmax[t] = 0ull;
 
@@ -353,10 +394,7 @@ __device__ __forceinline__ void resident_rows(const ResArgs& a, int at, bool rer
         }
         // the row's other lane groups of this wave
 #pragma unroll
-        for (int o = G; o < 64; o <<= 1)
-            if (o < G * S)
-#pragma unroll
-                for (int c = 0; c < C; ++c) acc[c] += __shfl_xor(acc[c], o);
+        for (int c = 0; c < C; ++c) acc[c] = sum_groups<G>(acc[c], S);
         if (WR > 1) {  // uniform over the workgroup
             double(*rd)[RP] = red[l & 1];
             if (g == 0)
@@ -425,8 +463,8 @@ __device__ __forceinline__ void resident_rows(const ResArgs& a, int at, bool rer
                     for (int i = 0; i < 4; ++i) v += __longlong_as_double((long long)u[i]);
                 }
             }
-#pragma unroll
-            for (int o = RP; o < 64; o <<= 1) v += __shfl_xor(v, o);
+            if constexpr (RP <= 16) v = sum_xor16(v);
+            if constexpr (RP <= 32) v = sum_xor32(v);
             double(*rd)[RP] = red[(l & 1) ^ 1];
             if (lane < RP) rd[wave][lane] = v;
             __syncthreads();
@@ -1052,13 +1090,20 @@ __global__ __launch_bounds__(512) void hot_step_kernel(HotStep a)
 // loop. Returns that iteration or -1, *viol the last violation that counts (thread 0).
 __device__ __forceinline__ int decide(unsigned long long* iv, int slots, int n, bool each, double tol, double* viol)
 {
-    __shared__ unsigned long long v[kInnerChunk];
-    const int t = threadIdx.x;
-    if (t < kInnerChunk) v[t] = 0ull;
-    __syncthreads();
+    static_assert(kInnerChunk == 16 && kBlock == 256, "sixteen threads per iteration");
+    __shared__ unsigned long long part[16][kInnerChunk], v[kInnerChunk];
+    const int t = threadIdx.x, l0 = t % kInnerChunk;
+    unsigned long long m = 0ull;
     for (int i = t; i < slots * kInnerChunk; i += kBlock) {
-        if (iv[i]) atomicMax(&v[i % kInnerChunk], iv[i]);
-        iv[i] = 0ull;
+        const unsigned long long u = iv[i];
+        m = u > m ? u : m;
+        if (u) iv[i] = 0ull;
+    }
+    part[t / kInnerChunk][l0] = m;
+    __syncthreads();
+    if (t < kInnerChunk) {
+        for (int k = 1; k < 16; ++k) m = part[k][t] > m ? part[k][t] : m;
+        v[t] = m;
     }
     __syncthreads();
     int stop = -1;
@@ -1655,10 +1700,10 @@ int64_t max_members(int64_t nnz, const Shape& s) { return nnz / class_cap(class_
 
 }  // namespace
 
-bool rows_supported(int R, int method)
+bool rows_supported(int R)
 {
     Shape s;
-    return method == CPAPR_METHOD_MU && row_shape(R, &s);
+    return row_shape(R, &s);
 }
 
 size_t rows_mode_bind(RowPlan* r, char* base, int64_t nnz, int64_t dim, int R)
@@ -1754,7 +1799,7 @@ Error rows_hot_build(cpapr_plan* P, hipStream_t s)
     int dev = 0;
     CPAPR_HIP(hipGetDevice(&dev));
     CPAPR_HIP(hipDeviceGetAttribute(&P->rs.cus, hipDeviceAttributeMultiprocessorCount, dev));
-    if (!hot_supported(P->N, P->nnz, P->R)) return {CPAPR_OK, ""};
+    if (P->params.method != CPAPR_METHOD_MU || !hot_supported(P->N, P->nnz, P->R)) return {CPAPR_OK, ""};
     Shape sh;
     row_shape(P->R, &sh);
     const int word = P->params.precision == CPAPR_MIXED ? 4 : 8;
@@ -1913,14 +1958,14 @@ namespace {
 
 // Operands of the resident rows of one mode (without its flags).
 void res_args(const cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, bool teams, int max_spread,
-              ResArgs* out)
+              ResArgs* out, int ng = 0)
 {
     Shape sh;
     row_shape(P->R, &sh);
     const ClassShape cs = class_shape(sh);
     const PlanMode& pm = P->mode[mode];
     const RowPlan& r = pm.rp;
-    const int NG = cs.NG, W = kResBlock / 64;
+    const int NG = ng > 0 ? ng : cs.NG, W = kResBlock / 64;  // ng: lane groups per wave of another launch
     ResArgs a{};
     a.cofs = pm.cofs;
     a.vals = pm.vals;
@@ -1953,7 +1998,7 @@ void res_args(const cpapr_plan* P, int mode, double* B, const void* const* fac, 
         for (int i = nlight - 1; i >= 0; --i) {
             if (r.count[i] == 0) continue;
             const int nb = i <= cs.KB ? i : cs.KB;  // blocks of four nonzeros per lane group
-            int S = i <= cs.KB ? 1 : 1 << (i - cs.KB);
+            int S = std::min(i <= cs.KB ? 1 : 1 << (i - cs.KB), W * NG);
             for (int f = 1; f < spread && f < nb && S < W * NG; f *= 2) S *= 2;
             const int per = std::max(1, W * NG / S);  // rows per workgroup
             a.entry[a.nentries++] = {(int32_t)blocks, begin[i], r.count[i], S};
@@ -1986,6 +2031,267 @@ void res_args(const cpapr_plan* P, int mode, double* B, const void* const* fac, 
 }
 
 }  // namespace
+
+// ---- line search of the row solves ----
+
+namespace {
+
+struct LsArgs {
+    ResArgs r;  // sorted copy, rows by class, factors
+    const double* D;
+    const int32_t* live;
+    double* T;
+    const int* skip;
+    const int32_t *chunk_begin, *chunk_row;
+    double* partial;  // [chunks x 4]
+    int chunk, nchunks;
+};
+
+// Four trial steps delta_k = max(b + alpha_k d, 0) - b, alpha = 1, 1/2, 1/4, 1/8
+// of every live row: sums over its nonzeros of x log1p(dm_k / m), m = b . pi,
+// dm_k = delta_k . pi (see delta_ratio in phi.hip for the cases at the floor).
+// A row belongs to its lane groups alone, so b and the trial steps are formed
+// once and four nonzeros go through the five dot products together, each
+// reduce-scattered over the quad: a lane ends with all five of one nonzero. The
+// group's quads share the four trials, so every lane takes 16 / G logarithms
+// for the block instead of a fifth of the all-reduces and the quotients of
+// every nonzero in every lane (the same sums by the Phi tile code: 1545 us on
+// 20M nonzeros at R = 16).
+template <int G, int C, int NM1>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(C >= 3 ? 3 : 4))) void ls_rows_kernel(LsArgs a)
+{
+    constexpr int NG = 64 / G, W = kBlock / 64;
+    constexpr int NQ = G / 4;                       // quads per lane group
+    constexpr int TPQ = NQ >= 4 ? 1 : 4 / NQ;       // trials per quad
+    __shared__ double red[W][4];
+    if (*a.skip) return;
+    const ResArgs& r = a.r;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int gl = lane % G, g = lane / G, qi = gl / 4;
+    const int R = r.R;
+    const bool odd1 = lane & 1, odd2 = lane & 2;
+    const int q = (lane & 3) ^ (G >= 8 && (lane & 4) ? 3 : 0);
+    int row, S, sub, WR;
+    uint32_t p0, p1;
+    bool valid = true;
+    const bool heavy = (int)blockIdx.x < a.nchunks;
+    if (heavy) {
+        const int h = a.chunk_row[blockIdx.x];
+        row = r.order[r.heavy0 + h];
+        p0 = (uint32_t)r.row_ptr[row] + (uint32_t)(((int)blockIdx.x - a.chunk_begin[h]) * a.chunk);
+        p1 = min(p0 + (uint32_t)a.chunk, (uint32_t)r.row_ptr[row + 1]);
+        S = W * NG;
+        WR = W;
+        sub = wave * NG + g;
+    } else {
+        const int at = (int)blockIdx.x - a.nchunks;
+        int e = 0;
+        while (e + 1 < r.nentries && at >= r.entry[e + 1].block0) ++e;
+        const int row0 = r.entry[e].row0, count = r.entry[e].count;
+        S = r.entry[e].groups;
+        WR = S > NG ? S / NG : 1;
+        const int local = at - r.entry[e].block0;
+        int pos;
+        if (WR > 1) {
+            pos = local * (W / WR) + wave / WR;
+            sub = (wave % WR) * NG + g;
+        } else {
+            pos = (local * W + wave) * (NG / S) + g / S;
+            sub = g % S;
+        }
+        valid = pos < count;
+        row = r.order[row0 + (valid ? pos : count - 1)];
+        p0 = (uint32_t)r.row_ptr[row];
+        p1 = (uint32_t)r.row_ptr[row + 1];
+    }
+    valid = valid && a.live[row] == 1;
+    if (!valid) p1 = p0;
+    const int colbase = min(gl * C, R - C);
+    double b[C], dk[4][C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const bool own = colbase + c >= gl * C && colbase + c < R;
+        const int64_t e = (int64_t)row * R + colbase + c;
+        b[c] = own && valid ? r.B[e] : 0.0;
+        const double d = own && valid ? a.D[e] : 0.0;
+        double alpha = 1.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k, alpha *= 0.5) {
+            const double nb = b[c] + alpha * d;
+            dk[k][c] = (nb > 0.0 ? nb : 0.0) - b[c];
+        }
+    }
+    // dot products of the four nonzeros with u, the lane's nonzero's total
+    auto dots = [&](const double (&pi)[4][C], const double (&u)[C]) {
+        double d[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            d[j] = u[0] * pi[j][0];
+#pragma unroll
+            for (int c = 1; c < C; ++c) d[j] = __builtin_fma(u[c], pi[j][c], d[j]);
+        }
+        const double a0 = (odd1 ? d[1] : d[0]) + dpp_f64<0xB1>(odd1 ? d[0] : d[1]);
+        const double a1 = (odd1 ? d[3] : d[2]) + dpp_f64<0xB1>(odd1 ? d[2] : d[3]);
+        double m = (odd2 ? a1 : a0) + dpp_f64<0x4E>(odd2 ? a0 : a1);
+        if constexpr (G >= 8) m += dpp_f64<0x141>(m);
+        if constexpr (G >= 16) m += dpp_f64<0x140>(m);
+        return m;
+    };
+    double sum[TPQ];
+#pragma unroll
+    for (int k = 0; k < TPQ; ++k) sum[k] = 0.0;
+    constexpr int NOFF = NM1 > 0 ? NM1 : 1;
+    uint32_t off[NOFF];
+    double x = 0.0;
+    auto load_meta = [&](uint32_t base) {
+        const uint32_t p = base + (uint32_t)q, pc = min(p, p1 - 1);
+        x = r.vals[pc];
+        if (p >= p1) x = 0.0;
+#pragma unroll
+        for (int m = 0; m < NOFF; ++m) off[m] = r.cofs[(int64_t)m * r.nnz + pc];
+    };
+    const uint32_t step = (uint32_t)S * 4u;
+    uint32_t base = p0 + (uint32_t)sub * 4u;
+    if (base < p1) load_meta(base);
+    for (; base < p1; base += step) {
+        const double xc = x;
+        double pi[4][C];
+        const double* fac = (const double*)r.fac[0];
+        load_cols<C>(fac, quad_bcast<0>(off[0]), colbase, pi[0]);
+        load_cols<C>(fac, quad_bcast<1>(off[0]), colbase, pi[1]);
+        load_cols<C>(fac, quad_bcast<2>(off[0]), colbase, pi[2]);
+        load_cols<C>(fac, quad_bcast<3>(off[0]), colbase, pi[3]);
+        const int nm1 = NM1 > 0 ? NM1 : r.NM1;
+#pragma unroll
+        for (int m = 1; m < nm1; ++m) {
+            uint32_t o;
+            if constexpr (NM1 > 0)
+                o = off[m];
+            else
+                o = r.cofs[(int64_t)m * r.nnz + min(base + (uint32_t)q, p1 - 1)];
+            const double* f2 = (const double*)r.fac[m];
+            double f[4][C];
+            load_cols<C>(f2, quad_bcast<0>(o), colbase, f[0]);
+            load_cols<C>(f2, quad_bcast<1>(o), colbase, f[1]);
+            load_cols<C>(f2, quad_bcast<2>(o), colbase, f[2]);
+            load_cols<C>(f2, quad_bcast<3>(o), colbase, f[3]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int c = 0; c < C; ++c) pi[j][c] *= f[j][c];
+        }
+        const bool there = base + (uint32_t)q < p1;
+        if (base + step < p1) load_meta(base + step);
+        const double m = dots(pi, b);
+        double dm[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) dm[k] = dots(pi, dk[k]);
+#pragma unroll
+        for (int k = 0; k < TPQ; ++k) {
+            double d;
+            if constexpr (NQ == 1)
+                d = dm[k];
+            else if constexpr (NQ == 2)
+                d = qi ? dm[2 + k] : dm[k];
+            else
+                d = qi & 2 ? (qi & 1 ? dm[3] : dm[2]) : (qi & 1 ? dm[1] : dm[0]);
+            const double m1 = m + d;
+            double term;
+            if (m > r.eps && m1 > r.eps)
+                term = xc * log1p(div_pos(d, m));
+            else
+                term = m > r.eps ? -__builtin_inf() : xc * (log(m1 > r.eps ? m1 : r.eps) - log(r.eps));
+            sum[k] += there ? term : 0.0;
+        }
+    }
+    // the quad's nonzeros, the row's other lane groups, its other waves
+#pragma unroll
+    for (int k = 0; k < TPQ; ++k) {
+        sum[k] += dpp_f64<0xB1>(sum[k]);
+        sum[k] += dpp_f64<0x4E>(sum[k]);
+#pragma unroll
+        for (int o = G; o < 64; o <<= 1)
+            if (o < G * S) sum[k] += __shfl_xor(sum[k], o);
+    }
+    if (WR > 1) {
+        if (g == 0 && (gl & 3) == 0)
+#pragma unroll
+            for (int k = 0; k < TPQ; ++k)
+                if (qi * TPQ + k < 4) red[wave][qi * TPQ + k] = sum[k];
+        __syncthreads();
+        const int w0 = wave / WR * WR;
+        if (sub / NG == 0 && lane < 4) {
+            double v = 0.0;
+            for (int w = 0; w < WR; ++w) v += red[w0 + w][lane];
+            if (heavy)
+                a.partial[(int64_t)blockIdx.x * 4 + lane] = v;
+            else if (valid)
+                a.T[(int64_t)row * R + lane] = v;
+        }
+        return;
+    }
+    if (valid && sub == 0 && (gl & 3) == 0)
+#pragma unroll
+        for (int k = 0; k < TPQ; ++k) a.T[(int64_t)row * R + qi * TPQ + k] = sum[k];
+}
+
+// Long rows: the sums of their chunks, a wave per row.
+__global__ __launch_bounds__(64) void ls_fold_kernel(LsArgs a)
+{
+    if (*a.skip) return;
+    const int h = blockIdx.x, lane = threadIdx.x, k = lane & 3;
+    const int row = a.r.order[a.r.heavy0 + h];
+    const int c0 = a.chunk_begin[h], c1 = a.chunk_begin[h + 1];
+    double v = 0.0;
+#pragma unroll 8
+    for (int c = c0 + lane / 4; c < c1; c += 16) v += a.partial[(int64_t)c * 4 + k];
+    for (int o = 4; o < 64; o <<= 1) v += __shfl_xor(v, o);
+    if (lane < 4 && a.live[row] == 1) a.T[(int64_t)row * a.r.R + lane] = v;
+}
+
+}  // namespace
+
+Error launch_delta4_rows(const cpapr_plan* P, int mode, const double* B, const double* D, const int32_t* live,
+                         const void* const* fac, double eps, double* out, const int* skip, hipStream_t s)
+{
+    const RowPlan& rp = P->mode[mode].rp;
+    LsArgs a{};
+    // few columns per lane: a lane holds five vectors of them beside the pi rows
+    const Shape sh = P->R > 8 && P->R <= 16 ? Shape{8, 2, 0} : heavy_shape(P->R, false);
+    res_args(P, mode, const_cast<double*>(B), fac, nullptr, false, 8, &a.r, 64 / sh.G);
+    a.r.eps = eps;
+    a.D = D;
+    a.live = live;
+    a.T = out;
+    a.skip = skip;
+    a.chunk_begin = rp.chunk_begin;
+    a.chunk_row = rp.chunk_row;
+    a.partial = P->rs.partial;
+    a.chunk = heavy_chunk(P->nnz);
+    a.nchunks = rp.nchunks_all;
+    const int64_t blocks = (int64_t)a.nchunks + a.r.light_blocks;
+    if (blocks == 0) return {CPAPR_OK, ""};
+    if (blocks > 0x7fffffff) return {CPAPR_EUNSUPPORTED, "too many rows"};
+    const dim3 grid((unsigned)blocks);
+    auto launch = [&](auto G, auto C) -> Error {
+        constexpr int GG = decltype(G)::value, CC = decltype(C)::value;
+        switch (a.r.NM1) {
+            case 1: ls_rows_kernel<GG, CC, 1><<<grid, kBlock, 0, s>>>(a); break;
+            case 2: ls_rows_kernel<GG, CC, 2><<<grid, kBlock, 0, s>>>(a); break;
+            case 3: ls_rows_kernel<GG, CC, 3><<<grid, kBlock, 0, s>>>(a); break;
+            default: ls_rows_kernel<GG, CC, 0><<<grid, kBlock, 0, s>>>(a); break;
+        }
+        CPAPR_LAUNCHED();
+        return {CPAPR_OK, ""};
+    };
+    using std::integral_constant;
+    Error e = sh.G == 8 && sh.C == 2 ? launch(integral_constant<int, 8>{}, integral_constant<int, 2>{})
+                                       : by_heavy_shape<false>(sh, launch);
+    if (e.code || a.nchunks == 0) return e;
+    ls_fold_kernel<<<rp.nlong, 64, 0, s>>>(a);
+    CPAPR_LAUNCHED();
+    return {CPAPR_OK, ""};
+}
 
 // ---- log-likelihood ----
 
@@ -2221,7 +2527,8 @@ Error launch_loglik_fused(const cpapr_plan* P, const double* lam, const double* 
 int rows_batch_shape(const cpapr_plan* P, int mode)
 {
     Shape sh;
-    if (!P->by_rows || !P->shape_auto || P->params.variant > CPAPR_VARIANT_SEGMENTED || !row_shape(P->R, &sh)) return -1;
+    if (!P->by_rows || P->params.method != CPAPR_METHOD_MU || !P->shape_auto ||
+        P->params.variant > CPAPR_VARIANT_SEGMENTED || !row_shape(P->R, &sh)) return -1;
     if (P->mode[mode].rp.count[class_count(class_shape(sh)) - 2] > 0) return -1;
     const int mixed = P->params.precision == CPAPR_MIXED ? 1 : 0;
     return 2 * (P->R <= 16 ? (P->R - 1) / 4 : P->R <= 32 ? 4 + (P->R - 17) / 8 : 6 + (P->R - 33) / 16) + mixed;

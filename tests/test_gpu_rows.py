@@ -173,3 +173,33 @@ def test_batch_slots_row_by_row(use_graph):
                 assert_parity(host(B), Bo, t, f"B slot {i}", elementwise=el)
                 assert_parity(host(Phi), Po, t, f"Phi slot {i}", elementwise=el)
         b.close()
+
+
+@pytest.mark.parametrize("R,others", [(4, (37, 29)), (8, (37, 29)), (10, (41, 31, 17)), (16, (60, 45)),
+                                      (24, (23, 17, 13, 11)), (32, (41, 31, 17)), (48, (37, 29)), (64, (50,))])
+def test_line_search_by_rows(R, others, lmax=2):
+    """Row solves (line-search sums row by row) at every launch shape, with rows
+    of every class, a long one cut into chunks, empty rows, and values not exact
+    in FP32: iterates in lockstep with the oracle's. Two steps: from the third on
+    PQNR divides by curvature s.y, differences of gradients that cancel on
+    these nearly solved rows (the general line-search pass, taken by a plan with
+    an explicit shape, is off by 4e-12 there too)."""
+    X = _tensor(EDGES + [30_000], others, 80 + R)
+    X = synth.SparseTensor(X.dims, X.idx, X.vals + 0.25)
+    M = synth.random_model(81, X.dims, R)
+    Bh = M.factors[0] * M.lam
+    for method, run, ref in ((cpapr.CPAPR_METHOD_PQNR, "pqnr_inner", oracle.pqnr_inner),
+                             (cpapr.CPAPR_METHOD_PDNR, "pdnr_inner", oracle.pdnr_inner)):
+        P = cpapr.Plan.from_tensor(X, R, lmax=lmax, tol=0.0, method=method)
+        B = dev(Bh)
+        st = getattr(P, run)(0, B, [dev(a) for a in M.factors])
+        Bo, info = ref(X, 0, Bh, M.factors, lmax=lmax)[:2]
+        # the damped solve's condition bound (see the PDNR tests), never below the parity gate
+        tol = TOL64 if method == cpapr.CPAPR_METHOD_PQNR else max(TOL64, 1.2e-16 * (1 + R * 4.0 ** (lmax - 1) / 1e-3))
+        assert_parity(host(B), Bo, tol, f"{run} R={R}", elementwise=False)
+        P.set_shape(*P.shape())
+        B2 = dev(Bh)
+        st2 = getattr(P, run)(0, B2, [dev(a) for a in M.factors])
+        assert st["row_steps"] == st2["row_steps"] and st["trial_evals"] == st2["trial_evals"]
+        assert_parity(host(B2), host(B), tol, f"{run} R={R} against the general pass", elementwise=False)
+        P.close()
