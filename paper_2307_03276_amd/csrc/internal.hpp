@@ -362,6 +362,8 @@ Error rows_hot_build(cpapr_plan* P, hipStream_t s);
 // receives the last Phi. State and counters as the Phi / KKT / update launches
 // leave them.
 Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, hipStream_t s);
+// Nonzeros per chunk of a long row.
+int heavy_chunk(int64_t nnz);
 // The four-trial line-search sums of launch_delta4, row by row (R >= 4, the
 // plan's rows by class): column k of `out` for rows with live[row] == 1, other
 // entries are left alone.

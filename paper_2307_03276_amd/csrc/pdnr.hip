@@ -212,7 +212,7 @@ __device__ __forceinline__ void hess_tiles(const HessArgs& a)
             if (a.status[myrow] == kConverged) myrow = -1;
 #pragma unroll
             for (int m = 0; m < NMAX; ++m)
-                if (m < a.NM1) myc[m] = (int)a.cofs[(int64_t)m * a.nnz + base + lane];
+                if (NMAX <= 3 || m < a.NM1) myc[m] = (int)a.cofs[(int64_t)m * a.nnz + base + lane];
             myx = a.vals[base + lane];
         }
         for (int u0 = 0; u0 < cnt; u0 += 4) {
@@ -239,7 +239,7 @@ __device__ __forceinline__ void hess_tiles(const HessArgs& a)
                     double p = a.fac[0][(uint64_t)(uint32_t)c[0] + col];
 #pragma unroll
                     for (int m = 1; m < NMAX; ++m)
-                        if (m < a.NM1) p *= a.fac[m][(uint64_t)(uint32_t)c[m] + col];
+                        if (NMAX <= 3 || m < a.NM1) p *= a.fac[m][(uint64_t)(uint32_t)c[m] + col];
                     pi[t] = p;
                 }
             }
@@ -339,6 +339,18 @@ __global__ void pdnr_flags_kernel(DevState* st, int before_begin)
         } else {
             if (!st->pq_idle) st->trial_evals += 1;
         }
+        st->pq_idle = 1;
+    }
+}
+
+// pdnr_flags_kernel before the rows decide, for a pass whose rows themselves read
+// whether there is work: that answer is kept in st->rerun.
+__global__ void pdnr_row_flags_kernel(DevState* st)
+{
+    if (threadIdx.x == 0) {
+        st->rerun = st->pq_all_done;
+        if (!st->pq_all_done) st->phi_evals += 1;
+        st->pq_all_done = 1;
         st->pq_idle = 1;
     }
 }
@@ -573,6 +585,373 @@ __global__ __launch_bounds__(64) void pdnr_begin16_kernel(RowArgs a)
         a.d.trials[i] = 0;
         a.d.status[i] = kSearching;
         a.st->pq_idle = 0;
+    }
+}
+
+// ---- 17 <= R <= 32: Hessian and Newton step of a row in one wave ----
+//
+// H of a short row never leaves the compute unit: the wave that owns the row
+// accumulates it on the matrix cores, keeps it in LDS, solves the Newton system
+// and leaves the four trials' quadratic terms (delta_k . H delta_k) for the
+// accept kernel. Through memory a row's R^2 + R words were written, read twice
+// and cleared in every iteration (5M four-way nonzeros in 40k rows, R = 32: the
+// three kernels took 823 + 343 + 173 us, now 299 + 370 + 15). Rows longer than
+// a workgroup's share (RowPlan's long rows) are still accumulated in memory, a
+// workgroup per chunk of one row, and solved from there. One wave per short row
+// bounds this: 16 nonzeros' gathers in flight, then a chain of 32 pivots.
+
+constexpr int kRowU = 4;  // rounds of four nonzeros gathered together
+
+// H (blocks on and above the diagonal) and the Phi row of nonzeros [p0, p1) of
+// one row, b in bv as in hess_tiles.
+template <int NT, int NMAX>  // NMAX: other modes, exactly
+__device__ __forceinline__ void hess_row(const HessArgs& a, const double (&bv)[NT], uint32_t p0, uint32_t p1,
+                                         f64x4 (&acc)[NT][NT], double (&ph)[NT])
+{
+    const int lane = threadIdx.x & 63, s = lane & 15, q = lane >> 4;
+    const int R = a.R;
+#pragma unroll
+    for (int ta = 0; ta < NT; ++ta) {
+        ph[ta] = 0.0;
+#pragma unroll
+        for (int tb = 0; tb < NT; ++tb) acc[ta][tb] = f64x4{0.0, 0.0, 0.0, 0.0};
+    }
+    double x[kRowU];
+    uint32_t off[kRowU][NMAX];
+    auto load_meta = [&](uint32_t base) {
+#pragma unroll
+        for (int u = 0; u < kRowU; ++u) {
+            const uint32_t p = base + (uint32_t)(4 * u + q), pc = min(p, p1 - 1);
+            x[u] = a.vals[pc];
+            if (p >= p1) x[u] = 0.0;
+#pragma unroll
+            for (int m = 0; m < NMAX; ++m)
+                off[u][m] = a.cofs[(int64_t)m * a.nnz + pc];
+        }
+    };
+    if (p0 < p1) load_meta(p0);
+    for (uint32_t base = p0; base < p1; base += 4 * kRowU) {
+        double pi[kRowU][NT], xc[kRowU];
+        // every gather of the block before any of them is used (a branch per mode
+        // between them made each wait for the last: 576 us for the long rows)
+#pragma unroll
+        for (int u = 0; u < kRowU; ++u) {
+            xc[u] = x[u];
+            double f[NMAX][NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int m = 0; m < NMAX; ++m)
+                    f[m][t] = a.fac[m][(uint64_t)off[u][m] + min(16 * t + s, R - 1)];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                double p = f[0][t];
+#pragma unroll
+                for (int m = 1; m < NMAX; ++m) p *= f[m][t];
+                pi[u][t] = 16 * t + s < R ? p : 0.0;
+            }
+        }
+        if (base + 4 * kRowU < p1) load_meta(base + 4 * kRowU);
+#pragma unroll
+        for (int u = 0; u < kRowU; ++u) {
+            double mk = 0.0;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) mk = __builtin_fma(bv[t], pi[u][t], mk);
+            mk = seg_sum<16>(mk);
+            const double mm = mk > a.eps ? mk : a.eps;
+            double rm = __builtin_amdgcn_rcp(mm);
+            rm = __builtin_fma(rm, __builtin_fma(-mm, rm, 1.0), rm);
+            const double sc = xc[u] * rm;
+            const double w = sc * rm;
+#pragma unroll
+            for (int ta = 0; ta < NT; ++ta) {
+                const double av = w * pi[u][ta];
+#pragma unroll
+                for (int tb = ta; tb < NT; ++tb)
+                    acc[ta][tb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, pi[u][tb], acc[ta][tb], 0, 0, 0);
+                ph[ta] = __builtin_fma(sc, pi[u][ta], ph[ta]);
+            }
+        }
+    }
+}
+
+template <int NT>
+__device__ __forceinline__ void row_b(const HessArgs& a, int64_t row, double (&bv)[NT])
+{
+    const int s = threadIdx.x & 15;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) bv[t] = 16 * t + s < a.R ? a.B[row * a.R + 16 * t + s] : 0.0;
+}
+
+struct LongRows {
+    const int32_t* rows;  // long rows
+    const int32_t *row_ptr, *chunk_begin, *chunk_row;
+    int chunk;
+};
+
+// The long rows' H and Phi row are cleared before each pass.
+__global__ __launch_bounds__(kBlock) void pdnr_long_clear_kernel(HessArgs a, LongRows lr)
+{
+    if (*a.skip) return;
+    double* hp = a.HP + (int64_t)lr.rows[blockIdx.x] * a.hp_stride;
+    for (int64_t e = threadIdx.x; e < a.hp_stride; e += kBlock) hp[e] = 0.0;
+}
+
+// Long rows: a workgroup per chunk.
+template <int NMAX>
+__global__ __launch_bounds__(kBlock) void pdnr_long_kernel(HessArgs a, LongRows lr)
+{
+    constexpr int NT = 2;
+    if (*a.skip) return;
+    const int h = lr.chunk_row[blockIdx.x], row = lr.rows[h];
+    if (a.status[row] == kConverged) return;
+    __shared__ double sum[32][33], phs[32];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, s = lane & 15, q = lane >> 4;
+    const uint32_t c0 = (uint32_t)lr.row_ptr[row] + (uint32_t)(((int)blockIdx.x - lr.chunk_begin[h]) * lr.chunk);
+    const uint32_t c1 = min(c0 + (uint32_t)lr.chunk, (uint32_t)lr.row_ptr[row + 1]);
+    const uint32_t per = (uint32_t)lr.chunk / (kBlock / 64);
+    const uint32_t p0 = min(c0 + (uint32_t)wave * per, c1), p1 = min(p0 + per, c1);
+    double bv[NT], ph[NT];
+    f64x4 acc[NT][NT];
+    row_b<NT>(a, row, bv);
+    hess_row<NT, NMAX>(a, bv, p0, p1, acc, ph);
+    // the waves' sums one after the other, then one atomic per entry and chunk
+    // (same-address atomics serialise; one row can have most of the nonzeros)
+    for (int w = 0; w < kBlock / 64; ++w) {
+        if (wave == w) {
+#pragma unroll
+            for (int ta = 0; ta < NT; ++ta)
+#pragma unroll
+                for (int tb = ta; tb < NT; ++tb)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        double& e = sum[16 * ta + 4 * v + q][16 * tb + s];
+                        e = w == 0 ? acc[ta][tb][v] : e + acc[ta][tb][v];
+                    }
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                double tot = ph[t];
+                tot += __shfl_xor(tot, 16);
+                tot += __shfl_xor(tot, 32);
+                if (q == 0) phs[16 * t + s] = w == 0 ? tot : phs[16 * t + s] + tot;
+            }
+        }
+        __syncthreads();
+    }
+    double* base = a.HP + (int64_t)row * a.hp_stride;
+    const int R = a.R;
+    for (int e = threadIdx.x; e < 32 * 32; e += kBlock) {
+        const int r = e / 32, c = e % 32;
+        if (r <= c && c < R) unsafeAtomicAdd(base + r * R + c, sum[r][c]);  // H is symmetric: on and above the diagonal
+    }
+    if (threadIdx.x < R) unsafeAtomicAdd(base + R * R + threadIdx.x, phs[threadIdx.x]);
+}
+
+// The rows' decisions of pdnr_begin_kernel, for the lane's Phi entry and H on and
+// below the diagonal of sm (padding included); the Cholesky factor's columns
+// go above it, so that a wave needs one matrix of LDS. The four trials'
+// delta_k . H delta_k go to Dt.
+__device__ __forceinline__ void newton_row(const RowArgs& a, int64_t i, double (*sm)[33], double ph)
+{
+    constexpr int RM = 32;
+    const int lane = threadIdx.x & 63;
+    auto h_at = [&](int r, int c) { return c <= r ? sm[r][c] : sm[c][r]; };
+    const int R = a.R;
+    const bool on = lane < R;
+    double b = 0.0, g = 0.0;
+    if (on) {
+        b = a.B[i * R + lane];
+        g = 1.0 - ph;
+        a.phi[i * R + lane] = ph;
+        a.d.G[i * R + lane] = g;
+    }
+    const double viol = wave_max(on ? fabs(b < g ? b : g) : 0.0);
+    if (lane == 0) a.d.viol[i] = viol;
+    if (a.tau > 0.0 && viol < a.tau) {
+        if (lane == 0) a.d.status[i] = kConverged;
+        return;
+    }
+    if (lane == 0) a.st->pq_all_done = 0;
+    const bool fre = on && !(g > 0.0 && b <= kPdnrHeld);
+    const unsigned long long fmask = __ballot(fre);
+    const int nf = __popcll(fmask);
+    double d = -g;  // held entries (and every entry when no entry is free)
+    bool newton = nf == 0;
+    const int lr = min(lane, RM - 1);
+    if (nf > 0) {
+        const double trace = wave_sum(fre ? sm[lr][lr] : 0.0);
+        if (trace > 0.0) {
+            const double damp = a.d.mu[i] * (trace / nf);
+            double M[RM];
+#pragma unroll
+            for (int j = 0; j < RM; ++j) {
+                const bool fj = (fmask >> j) & 1ull;
+                M[j] = fre ? (fj ? h_at(lr, j) : 0.0) + (j == lane ? damp : 0.0) : (j == lane ? 1.0 : 0.0);
+            }
+            bool ok = true;
+#pragma unroll
+            for (int k = 0; k < RM; ++k) {
+                const double piv = lane_value(M[k], k);
+                if (!(piv > 0.0)) {
+                    ok = false;
+                    break;
+                }
+                const double inv = rsqrt_pos(piv);  // kept in the diagonal place, as in pdnr_begin_kernel
+                const double lik = M[k] * inv;
+                M[k] = lane == k ? inv : lik;
+                if (lane > k && lane < RM) sm[k][lane] = lik;
+                wave_sync();
+#pragma unroll
+                for (int j = k + 1; j < RM; ++j) M[j] = __builtin_fma(-lik, sm[k][j], M[j]);
+            }
+            if (ok) {
+                double z = fre ? -g : 0.0;
+#pragma unroll
+                for (int j = 0; j < RM; ++j) {
+                    const double yj = lane_value(z, j) * lane_value(M[j], j);
+                    if (lane > j)
+                        z = __builtin_fma(-M[j], yj, z);
+                    else if (lane == j)
+                        z = yj;
+                }
+#pragma unroll
+                for (int j = RM - 1; j >= 0; --j) {
+                    const double dj = lane_value(z, j) * lane_value(M[j], j);
+                    if (lane < j)
+                        z = __builtin_fma(-sm[lr][j], dj, z);
+                    else if (lane == j)
+                        z = dj;
+                }
+                if (fre) d = z;
+                newton = true;
+            }
+        }
+    }
+    if (newton) newton = wave_sum(on ? g * d : 0.0) < 0.0;
+    if (!newton) d = -b * g;
+    if (on) a.d.Dd[i * R + lane] = d;
+    // the trials' quadratic terms
+    double dl[kPdnrTrials], hd[kPdnrTrials];
+    double alpha = 1.0;
+#pragma unroll
+    for (int k = 0; k < kPdnrTrials; ++k, alpha *= 0.5) {
+        const double nb = b + alpha * d;
+        dl[k] = on ? (nb > 0.0 ? nb : 0.0) - b : 0.0;
+        hd[k] = 0.0;
+    }
+    for (int j = 0; j < R; ++j) {
+        const double hj = h_at(lr, j);
+#pragma unroll
+        for (int k = 0; k < kPdnrTrials; ++k) hd[k] = __builtin_fma(hj, lane_value(dl[k], j), hd[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < kPdnrTrials; ++k) {
+        const double quad = wave_sum(on ? dl[k] * hd[k] : 0.0);
+        if (lane == 0) a.d.Dt[i * R + k] = quad;
+    }
+    if (lane == 0) {
+        a.d.trials[i] = 0;
+        a.d.status[i] = kSearching;
+        a.st->pq_idle = 0;
+    }
+}
+
+// A wave per row: the long rows from memory first, then the others, longest first.
+template <int NMAX>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void pdnr_row_kernel(HessArgs h, RowArgs a, LongRows lr, const int32_t* __restrict__ order,
+                                                      int nlong, int nshort, const int* skip)
+{
+    constexpr int NT = 2, RM = 32;
+    __shared__ double sm[RM][RM + 1], phs[RM];
+    if (*skip) return;
+    const int lane = threadIdx.x & 63, s = lane & 15, q = lane >> 4;
+    const int R = a.R;
+    const bool islong = (int)blockIdx.x < nlong;
+    const int64_t i = islong ? lr.rows[blockIdx.x] : order[nshort - 1 - ((int)blockIdx.x - nlong)];
+    if (a.d.status[i] == kConverged) return;
+    if (islong) {
+        const double* hp = h.HP + i * h.hp_stride;
+        for (int e = lane; e < RM * RM; e += 64) {
+            const int r = e / RM, c = e % RM;
+            if (c <= r) sm[r][c] = r < R ? hp[c * R + r] : 0.0;  // stored on and above the diagonal
+        }
+        if (lane < RM) phs[lane] = lane < R ? hp[R * R + lane] : 0.0;
+    } else {
+        double bv[NT], ph[NT];
+        f64x4 acc[NT][NT];
+        row_b<NT>(h, i, bv);
+        hess_row<NT, NMAX>(h, bv, (uint32_t)lr.row_ptr[i], (uint32_t)lr.row_ptr[i + 1], acc, ph);
+#pragma unroll
+        for (int ta = 0; ta < NT; ++ta)
+#pragma unroll
+            for (int tb = ta; tb < NT; ++tb)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int r = 16 * ta + 4 * v + q, c = 16 * tb + s;
+                    if (r <= c) sm[c][r] = acc[ta][tb][v];
+                }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            double tot = ph[t];
+            tot += __shfl_xor(tot, 16);
+            tot += __shfl_xor(tot, 32);
+            if (q == 0) phs[16 * t + s] = tot;
+        }
+    }
+    wave_sync();
+    newton_row(a, i, sm, phs[min(lane, RM - 1)]);
+}
+
+// pdnr_accept4_kernel after pdnr_row_kernel: the quadratic terms are in Dt.
+__global__ __launch_bounds__(kBlock) void pdnr_accept_row_kernel(RowArgs a)
+{
+    constexpr int SEG = 32;  // two rows per wave
+    const int lane = threadIdx.x & 63, s = lane & (SEG - 1);
+    const int64_t i = (int64_t)blockIdx.x * (kBlock / SEG) + threadIdx.x / SEG;
+    const bool live = i < a.rows && a.d.status[i] == kSearching;
+    const int R = a.R;
+    const bool on = live && s < R;
+    double b = 0.0, g = 0.0, d = 0.0;
+    if (on) {
+        b = a.B[i * R + s];
+        g = a.d.G[i * R + s];
+        d = a.d.Dd[i * R + s];
+    }
+    bool accept = false;
+    double delta = 0.0, pred = 0.0, df = 0.0, alpha = 1.0;
+#pragma unroll
+    for (int k = 0; k < kPdnrTrials; ++k, alpha *= 0.5) {
+        double dl = 0.0;
+        if (on) {
+            const double nb = b + alpha * d;
+            dl = (nb > 0.0 ? nb : 0.0) - b;
+        }
+        const double gd = seg_sum<SEG>(g * dl);
+        const double dfk = seg_sum<SEG>(dl) - (live ? a.d.T[i * R + k] : 0.0);
+        if (live && !accept && gd < 0.0 && dfk <= kPdnrSigma * gd) {
+            accept = true;
+            delta = dl;
+            df = dfk;
+            pred = -(gd + 0.5 * a.d.Dt[i * R + k]);
+        }
+    }
+    if (!live) return;
+    double mu = a.d.mu[i];
+    if (accept) {
+        const double rho = pred > 0.0 ? -df / pred : 0.0;
+        if (rho < 0.25)
+            mu = fmin(mu * kPdnrMuStep, kPdnrMuMax);
+        else if (rho > 0.75)
+            mu = fmax(mu / kPdnrMuStep, kPdnrMuMin);
+    } else {
+        delta = -b * g;  // the MU step
+        mu = fmin(mu * kPdnrMuStep, kPdnrMuMax);
+    }
+    if (on) a.B[i * R + s] = b + delta;
+    if (s == 0) {
+        a.d.mu[i] = mu;
+        a.d.steps[i] += 1;
+        a.d.status[i] = kActive;
     }
 }
 
@@ -824,6 +1203,52 @@ void pdnr_bind(PdnrState* d, char* base, int64_t maxI, int R)
     d->steps = (int32_t*)take(align256((size_t)maxI * 4));
 }
 
+namespace {
+
+// One iteration of the rows with pdnr_row_kernel.
+Error enqueue_row_step(cpapr_plan* P, int mode, const HessArgs& h, const RowArgs& ra, double* B, const void* const* fac,
+                       hipStream_t s)
+{
+    const RowPlan& rp = P->mode[mode].rp;
+    DevState* st = P->state;
+    const int nshort = (int)(P->dims[mode] - rp.nlong);
+    const LongRows lr{rp.order + nshort, rp.row_ptr, rp.chunk_begin, rp.chunk_row, heavy_chunk(P->nnz)};
+    prof_begin(mode, s);
+    if (rp.nlong > 0) {
+        pdnr_long_clear_kernel<<<rp.nlong, kBlock, 0, s>>>(h, lr);
+        CPAPR_LAUNCHED();
+        switch (h.NM1) {
+            case 1: pdnr_long_kernel<1><<<rp.nchunks_all, kBlock, 0, s>>>(h, lr); break;
+            case 2: pdnr_long_kernel<2><<<rp.nchunks_all, kBlock, 0, s>>>(h, lr); break;
+            case 3: pdnr_long_kernel<3><<<rp.nchunks_all, kBlock, 0, s>>>(h, lr); break;
+            default: return {CPAPR_EUNSUPPORTED, "more than three other modes"};
+        }
+        CPAPR_LAUNCHED();
+    }
+    // the rows read the flag that says the last pass left work; the flags kernel then resets it
+    int* skip = &st->rerun;  // unused by the row solves: this iteration's copy of the flag
+    pdnr_row_flags_kernel<<<1, 64, 0, s>>>(st);
+    CPAPR_LAUNCHED();
+    const dim3 grid((unsigned)P->dims[mode]);
+    switch (h.NM1) {
+        case 1: pdnr_row_kernel<1><<<grid, 64, 0, s>>>(h, ra, lr, rp.order, rp.nlong, nshort, skip); break;
+        case 2: pdnr_row_kernel<2><<<grid, 64, 0, s>>>(h, ra, lr, rp.order, rp.nlong, nshort, skip); break;
+        case 3: pdnr_row_kernel<3><<<grid, 64, 0, s>>>(h, ra, lr, rp.order, rp.nlong, nshort, skip); break;
+        default: return {CPAPR_EUNSUPPORTED, "more than three other modes"};
+    }
+    CPAPR_LAUNCHED();
+    prof_end(s);
+    Error e = launch_delta4_rows(P, mode, B, P->pd.Dd, P->pd.status, fac, P->params.eps, P->pd.T, &st->pq_idle, s);
+    if (e.code) return e;
+    pdnr_flags_kernel<<<1, 64, 0, s>>>(st, 0);
+    CPAPR_LAUNCHED();
+    pdnr_accept_row_kernel<<<(unsigned)((P->dims[mode] + kBlock / 32 - 1) / (kBlock / 32)), kBlock, 0, s>>>(ra);
+    CPAPR_LAUNCHED();
+    return {CPAPR_OK, ""};
+}
+
+}  // namespace
+
 Error enqueue_pdnr_inner(cpapr_plan* P, int mode, double* B, const void* const* fac, double* phi, hipStream_t s)
 {
     const int64_t rows = P->dims[mode];
@@ -861,10 +1286,20 @@ Error enqueue_pdnr_inner(cpapr_plan* P, int mode, double* B, const void* const* 
     const int zgrid = (int)std::min<int64_t>(std::max<int64_t>((rows + kBlock - 1) / kBlock, 1), 4096);
     pdnr_reset_kernel<<<zgrid, kBlock, 0, s>>>(P->pd, rows, st);
     CPAPR_LAUNCHED();
-    Error e = launch_fill(P->pd.HP, rows * P->pd.hp_stride, 0.0, nullptr, s);
+    // 17 <= R <= 32 and up to four modes: below, four rows share a wave's Newton
+    // step (pdnr_begin16_kernel); with more modes the gathers of a block do not
+    // fit the registers beside the accumulators.
+    const bool by_row = P->by_rows && P->shape_auto && R > 16 && R <= 32 && P->N <= 4;
+    Error e{CPAPR_OK, ""};
+    if (!by_row) e = launch_fill(P->pd.HP, rows * P->pd.hp_stride, 0.0, nullptr, s);
     if (e.code) return e;
     RowArgs ra{B, phi, rows, R, P->params.tol, P->pd, st};
     for (int l = 0; l < P->params.lmax; ++l) {
+        if (by_row) {
+            e = enqueue_row_step(P, mode, h, ra, B, fac, s);
+            if (e.code) return e;
+            continue;
+        }
         prof_begin(mode, s);
         e = by_tile(std::max(rm, 16), [&](auto RM) -> Error {
             constexpr int T = decltype(RM)::value < 16 ? 16 : decltype(RM)::value;

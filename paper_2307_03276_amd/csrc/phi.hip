@@ -1036,17 +1036,22 @@ Error dispatch_seg_n(int G, int RPL, const PhiArgs& a, dim3 grid, hipStream_t s)
     CPAPR_SEG_CASE(32, 1)
     CPAPR_SEG_CASE(64, 1)
     CPAPR_SEG_CASE(64, 2)
+    CPAPR_SEG_CASE(64, 3)
     CPAPR_SEG_CASE(64, 4)
     CPAPR_SEG_CASE(8, 2)
     CPAPR_SEG_CASE(16, 2)
+    CPAPR_SEG_CASE(8, 3)
+    CPAPR_SEG_CASE(16, 3)
     if constexpr (NM1 <= 3) {
         CPAPR_SEG_CASE(8, 4)
         CPAPR_SEG_CASE(16, 4)
     }
     if constexpr (NM1 <= 3 && KIND != kLoglik) {
         CPAPR_SEG_CASE(4, 2)
+        CPAPR_SEG_CASE(4, 3)
         CPAPR_SEG_CASE(4, 4)
         CPAPR_SEG_CASE(32, 2)
+        CPAPR_SEG_CASE(32, 3)
         CPAPR_SEG_CASE(32, 4)
     }
 #undef CPAPR_SEG_CASE
@@ -1056,7 +1061,7 @@ Error dispatch_seg_n(int G, int RPL, const PhiArgs& a, dim3 grid, hipStream_t s)
 // Shapes the reduce-scatter tile is built for: 8 or 16 lanes per nonzero, up
 // to 8 gathered words per lane and nonzero (its Q rounds keep them in
 // registers).
-bool xr_shape_supported(int G, int RPL, int NM1) { return (G == 8 || G == 16) && NM1 * RPL <= 8; }
+bool xr_shape_supported(int G, int RPL, int NM1) { return (G == 8 || G == 16) && RPL != 3 && NM1 * RPL <= 8; }
 
 template <bool MIXED>
 Error dispatch_xr(int G, int RPL, const PhiArgs& a, hipStream_t s)
@@ -1121,18 +1126,23 @@ Error dispatch_atomic(int G, int RPL, const PhiArgs& a, hipStream_t s)
     }
     CPAPR_AT_CASE(4, 1)
     CPAPR_AT_CASE(4, 2)
+    CPAPR_AT_CASE(4, 3)
     CPAPR_AT_CASE(4, 4)
     CPAPR_AT_CASE(8, 1)
     CPAPR_AT_CASE(8, 2)
+    CPAPR_AT_CASE(8, 3)
     CPAPR_AT_CASE(8, 4)
     CPAPR_AT_CASE(16, 1)
     CPAPR_AT_CASE(16, 2)
+    CPAPR_AT_CASE(16, 3)
     CPAPR_AT_CASE(16, 4)
     CPAPR_AT_CASE(32, 1)
     CPAPR_AT_CASE(32, 2)
+    CPAPR_AT_CASE(32, 3)
     CPAPR_AT_CASE(32, 4)
     CPAPR_AT_CASE(64, 1)
     CPAPR_AT_CASE(64, 2)
+    CPAPR_AT_CASE(64, 3)
     CPAPR_AT_CASE(64, 4)
 #undef CPAPR_AT_CASE
     return {CPAPR_EUNSUPPORTED, "no atomic Phi kernel for this shape"};
@@ -1188,7 +1198,11 @@ int resolve_group(int R, int requested, int nm1)
     if (R <= 4) return 4;
     if (R <= 8) return 8;
     if (R <= 16) return 8;
+    // 17..24: three columns on 8 lanes, one lane in four or fewer idle; 16 lanes
+    // of two left 7 of 16 idle at R = 17 and re-read the row's end with them
+    if (R <= 24) return 8;
     if (R <= 32) return nm1 <= 3 ? 8 : 16;
+    if (R <= 48 && nm1 > 3) return 16;
     if (R <= 64) return nm1 <= 3 ? 16 : 64;
     return 64;
 }
@@ -1197,18 +1211,17 @@ bool phi_shape_supported(int group, int rpl, int nmodes_other)
 {
     if (nmodes_other < 1 || nmodes_other > kMaxOther) return false;
     if (group != 4 && group != 8 && group != 16 && group != 32 && group != 64) return false;
-    if (rpl != 1 && rpl != 2 && rpl != 4) return false;
+    if (rpl < 1 || rpl > 4) return false;
     if (rpl == 1 || group == 64) return true;
     if (nmodes_other <= 3) return true;
-    return rpl == 2 && (group == 8 || group == 16);  // N >= 5: the default shapes only
+    return rpl <= 3 && (group == 8 || group == 16);  // N >= 5: the default shapes only
 }
 
 int rank_block(int R, int group)
 {
     const int need = (R + group - 1) / group;
     if (need <= 1) return 1;
-    if (need <= 2) return 2;
-    if (need <= 4) return 4;
+    if (need <= 4) return need;
     return -1;
 }
 
@@ -1269,7 +1282,7 @@ void model_shape(const ModelIn& m, int* tile, int* group)
 {
     const int g0 = resolve_group(m.R, 0, m.nm1);
     int tb = 512, gb = g0;  // a large tensor's shape
-    if (m.R > 16 && m.R <= 32 && m.nm1 <= 3) {
+    if (m.R > 24 && m.R <= 32 && m.nm1 <= 3) {
         if (m.mixed) {
             tb = 1024;
         } else if (group16_ok(m)) {
@@ -1397,9 +1410,9 @@ Error launch_delta4(const cpapr_plan* P, int mode, const double* B, const double
     int G = P->group;
     int RPL = rank_block(P->R, G);
     PhiArgs a = make_args(P, mode, B, fac, eps, out, skip);
-    // Four rank columns per lane hold 16 trial-step words per lane: such shapes
+    // Three or four rank columns per lane hold 12 or 16 trial-step words per lane: such shapes
     // take twice the lanes per nonzero for this pass, on the same tiles.
-    if (RPL == 4 && G <= 32 && phi_shape_supported(2 * G, rank_block(P->R, 2 * G), P->N - 1)) {
+    if (RPL >= 3 && G <= 32 && phi_shape_supported(2 * G, rank_block(P->R, 2 * G), P->N - 1)) {
         G *= 2;
         RPL = rank_block(P->R, G);
         a.L *= 2;
@@ -1470,7 +1483,8 @@ constexpr BatchShape kBatchShapes[] = {
 #define CPAPR_BS(GG, RR)                                                                              \
     {GG, RR, 1, false}, {GG, RR, 2, false}, {GG, RR, 3, false}, {GG, RR, 1, true}, {GG, RR, 2, true}, \
         {GG, RR, 3, true}
-    CPAPR_BS(4, 1), CPAPR_BS(8, 1), CPAPR_BS(8, 2), CPAPR_BS(8, 4), CPAPR_BS(16, 1), CPAPR_BS(16, 2), CPAPR_BS(16, 4)
+    CPAPR_BS(4, 1), CPAPR_BS(8, 1), CPAPR_BS(8, 2), CPAPR_BS(8, 4), CPAPR_BS(16, 1), CPAPR_BS(16, 2), CPAPR_BS(16, 4),
+    CPAPR_BS(8, 3), CPAPR_BS(16, 3)
 #undef CPAPR_BS
 };
 
@@ -1501,6 +1515,7 @@ Error launch_phi_batch(int cls, const BatchSlot* slots, const int32_t* tile_map,
     CPAPR_BL(GG, RR, 1, false) CPAPR_BL(GG, RR, 2, false) CPAPR_BL(GG, RR, 3, false)                 \
     CPAPR_BL(GG, RR, 1, true) CPAPR_BL(GG, RR, 2, true) CPAPR_BL(GG, RR, 3, true)
     CPAPR_BL6(4, 1) CPAPR_BL6(8, 1) CPAPR_BL6(8, 2) CPAPR_BL6(8, 4) CPAPR_BL6(16, 1) CPAPR_BL6(16, 2) CPAPR_BL6(16, 4)
+    CPAPR_BL6(8, 3) CPAPR_BL6(16, 3)
 #undef CPAPR_BL6
 #undef CPAPR_BL
     return {CPAPR_EUNSUPPORTED, "no batched Phi kernel for this shape"};

@@ -1663,6 +1663,8 @@ Error by_heavy_shape(const Shape& s, F&& f)
     return {CPAPR_EUNSUPPORTED, "no heavy-row kernel for this rank"};
 }
 
+}  // namespace
+
 // Nonzeros per heavy chunk: ~1000 chunks for a small tensor, 2048 for a large one.
 int heavy_chunk(int64_t nnz)
 {
@@ -1670,6 +1672,8 @@ int heavy_chunk(int64_t nnz)
     while (c < 2048 && (int64_t)c * 2 * 1024 <= nnz) c *= 2;
     return c;
 }
+
+namespace {
 
 // Bounds on the rows longer than a workgroup's registers, the chunks of the
 // heavy ones and the members of the teams.

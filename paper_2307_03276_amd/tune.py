@@ -29,10 +29,7 @@ CHUNKS = (2, 4, 8, 16, 32, 64)
 
 def rank_block(R: int, G: int) -> int:
     need = -(-R // G)
-    for r in (1, 2, 4):
-        if need <= r:
-            return r
-    return -1
+    return need if need <= 4 else -1
 
 
 def shape_candidates(R: int, nmodes: int) -> List[Tuple[int, int]]:

@@ -1,0 +1,54 @@
+"""Phi, MTTKRP, row solves and batches at ranks that take three columns per lane
+(lane groups of 8 and 16 by default, 4 to 64 by choice), against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2307_03276_amd import cpapr, synth
+from tests.gpu_util import assert_parity, dev, host
+
+pytestmark = pytest.mark.gpu
+TOL64, TOLMIX = 1e-12, 1e-6  # the library's parity gates
+
+
+@pytest.mark.parametrize("R,group", [(17, 0), (20, 0), (23, 0), (24, 0), (33, 0), (47, 0), (48, 0), (9, 4), (12, 4),
+                                     (17, 8), (24, 8), (41, 16), (65, 32), (96, 32), (130, 64), (192, 64)])
+@pytest.mark.parametrize("dims", [(500, 90), (500, 90, 40), (300, 60, 40, 20), (200, 60, 40, 20, 10)])
+def test_phi_three_columns_per_lane(R, group, dims):
+    if group in (4, 32) and len(dims) == 5:
+        pytest.skip("no kernel for this lane group at five modes")
+    X = synth.random_tensor(R, dims, 9_001, zipf=(1.3, 1.1) + (None,) * (len(dims) - 2))
+    X = synth.SparseTensor(X.dims, X.idx, X.vals * 0.75 + 0.01)
+    M = synth.random_model(3, X.dims, R)
+    A = [dev(a) for a in M.factors]
+    for prec, tol in ((cpapr.CPAPR_FP64, TOL64), (cpapr.CPAPR_MIXED, TOLMIX)):
+        P = cpapr.Plan.from_tensor(X, R, group=group, precision=prec)
+        for n in (0, len(dims) - 1):
+            Bh = M.factors[n] * M.lam
+            assert_parity(host(P.phi(n, dev(Bh), A)), oracle.phi(X, n, Bh, M.factors), tol, f"Phi mode {n}")
+            if prec == cpapr.CPAPR_FP64:
+                assert_parity(host(P.mttkrp(n, A)), oracle.mttkrp(X, n, M.factors), tol, f"MTTKRP mode {n}")
+        P.close()
+
+
+@pytest.mark.parametrize("R,group", [(20, 8), (40, 16)])
+def test_batch_and_atomic_three_columns(R, group):
+    import torch
+    X = synth.random_tensor(R, (400, 80, 50), 20_000, zipf=(1.2, None, None))
+    M = synth.random_model(5, X.dims, R)
+    A = [dev(a) for a in M.factors]
+    Bh = M.factors[0] * M.lam
+    ref = oracle.phi(X, 0, Bh, M.factors)
+    P = cpapr.Plan.from_tensor(X, R, group=group)
+    Phi = torch.zeros((400, R), dtype=torch.float64, device="cuda")
+    b = cpapr.Batch(1, P.tiles() + 1)
+    b.set(0, P, 0, dev(Bh), A, Phi)
+    b.commit()
+    b.run()
+    assert_parity(host(Phi), ref, TOL64, "batched Phi")
+    b.close()
+    for variant in (cpapr.CPAPR_VARIANT_ATOMIC, cpapr.CPAPR_VARIANT_XR):
+        Q = cpapr.Plan.from_tensor(X, R, group=group, variant=variant)
+        assert_parity(host(Q.phi(0, dev(Bh), A)), ref, TOL64, "variant")
+        Q.close()
+    P.close()
