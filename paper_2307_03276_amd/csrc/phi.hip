@@ -1198,10 +1198,8 @@ int resolve_group(int R, int requested, int nm1)
     if (R <= 4) return 4;
     if (R <= 8) return 8;
     if (R <= 16) return 8;
-    // 17..24: three columns on 8 lanes, one lane in four or fewer idle; 16 lanes
-    // of two left 7 of 16 idle at R = 17 and re-read the row's end with them
-    if (R <= 24) return 8;
     if (R <= 32) return nm1 <= 3 ? 8 : 16;
+    // three columns on 16 lanes; one on 64 left a quarter to half of them idle
     if (R <= 48 && nm1 > 3) return 16;
     if (R <= 64) return nm1 <= 3 ? 16 : 64;
     return 64;
@@ -1243,7 +1241,14 @@ int resolve_chunk(int group, int requested)
 //  * a large tensor's shape: 512-nonzero tiles with lanes by rank, except
 //    17 <= R <= 32 with up to four modes: 16 lanes x 2 columns on 256-nonzero
 //    tiles in FP64, 8 lanes x 4 columns on 1024-nonzero tiles with FP32-stored
-//    factors (half the gathered words per lane); and 5 <= R <= 16 with packed
+//    factors (half the gathered words per lane; three columns up to R = 24).
+//    At 17 <= R <= 24 the FP64 tiles hold 512 nonzeros for three modes and 256
+//    for more, on 16 lanes at every mode count; with FP32-stored factors 8
+//    lanes x 3 columns take 1024 for up to four modes, 512 for more (R = 24,
+//    8 x 3 on 512 / 1024 against 16 x 2 on 256 / 512 nonzeros, us: 3-way 20M
+//    nonzeros FP64 460 / 462 / 470 / 437, mixed 406 / 364 / 474 / 431; 4-way
+//    16M FP64 1092 / 1179 / 1029 / 1063; 5-way 12.9M FP64 488 / 515 / 461 /
+//    476, mixed 333 / 347 / 453 / 465); and 5 <= R <= 16 with packed
 //    nonzero records (one load per staged nonzero): 1024-nonzero tiles, the
 //    tile's merge and row flushes weighing more against the cheaper nonzeros
 //    (-10 % at zipf3 against 512);
@@ -1280,9 +1285,12 @@ bool group16_ok(const ModelIn& m)
 // (tile nonzeros, lanes per nonzero)
 void model_shape(const ModelIn& m, int* tile, int* group)
 {
-    const int g0 = resolve_group(m.R, 0, m.nm1);
+    const bool three = m.R > 16 && m.R <= 24;  // three columns fill 8 lanes
+    const int g0 = three ? (m.mixed ? 8 : 16) : resolve_group(m.R, 0, m.nm1);
     int tb = 512, gb = g0;  // a large tensor's shape
-    if (m.R > 24 && m.R <= 32 && m.nm1 <= 3) {
+    if (three && !m.mixed) {
+        tb = m.nm1 <= 2 ? 512 : 256;
+    } else if (m.R > 16 && m.R <= 32 && m.nm1 <= 3) {
         if (m.mixed) {
             tb = 1024;
         } else if (group16_ok(m)) {
