@@ -108,7 +108,7 @@ Layout layout(int N, int64_t nnz, const int64_t* dims, int R, const cpapr_params
 {
     const bool mixed = p->precision == CPAPR_MIXED, det = p->deterministic != 0;
     const int method = p->method;
-    const bool by_rows = cpapr::rows_supported(R);
+    const bool by_rows = cpapr::rows_supported(R, nnz);
     Layout L{};
     size_t off = 0;
     for (int n = 0; n < N; ++n) {
@@ -160,7 +160,7 @@ Layout layout(int N, int64_t nnz, const int64_t* dims, int R, const cpapr_params
     if (det) s += align256((size_t)2 * cap * R * 8);
     L.det_rows = off + s;
     if (det) s += align256((size_t)2 * cap * 4);
-    s = std::max(s, (size_t)cpapr::sort_scratch_bytes(nnz, N));
+    s = std::max(s, (size_t)cpapr::sort_scratch_bytes(nnz, N, by_rows));
     L.total = off + s;
     return L;
 }
@@ -214,11 +214,12 @@ bool runs_by_rows(const cpapr_plan* P)
 // all gated by the device-side `done` flag. No host synchronisation. With a
 // fixed schedule (tol <= 0) nothing depends on the violation before the
 // update, so KKT and update are one pass over B and Phi.
-Error enqueue_inner(cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, hipStream_t s)
+// rows: runs_by_rows, and the caller holds the plan's row buffers.
+Error enqueue_inner(cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, bool rows, hipStream_t s)
 {
     const int64_t n = P->dims[mode] * (int64_t)P->R;
     const bool mixed = P->params.precision == CPAPR_MIXED;
-    if (runs_by_rows(P))
+    if (rows)
         return cpapr::enqueue_inner_rows(P, mode, B, fac, Phi, s);
     const bool fused = !(P->params.tol > 0.0);
     const int* done = &P->state->done;
@@ -292,7 +293,7 @@ TransientLayout transient_layout(int N, int64_t nnz)
     L.vals = off;
     off += align256((size_t)nnz * 8);
     L.scratch = off;
-    off += (size_t)cpapr::sort_scratch_bytes(nnz, N);
+    off += (size_t)cpapr::sort_scratch_bytes(nnz, N, false);
     L.total = off;
     return L;
 }
@@ -406,6 +407,7 @@ int cpapr_plan_create(const cpapr_coo* X, int32_t R, const cpapr_params* p, void
         if (((uintptr_t)ws & 255) != 0) return fail(CPAPR_EWORKSPACE, "workspace must be 256-byte aligned");
         if (ws_bytes < L.total) return fail(CPAPR_EWORKSPACE, "workspace too small");
 
+        auto owner = std::make_shared<cpapr::RowOwner>(nullptr);
         cpapr_plan* P = new (std::nothrow) cpapr_plan();
         if (!P) return fail(CPAPR_EINVAL, "out of host memory");
         char* w = (char*)ws;
@@ -436,7 +438,8 @@ int cpapr_plan_create(const cpapr_coo* X, int32_t R, const cpapr_params* p, void
         P->det_tiles = cpapr::det_tile_capacity(X->nnz);
         int64_t maxI = 0;
         for (int m = 0; m < P->N; ++m) maxI = std::max(maxI, P->dims[m]);
-        P->by_rows = cpapr::rows_supported(R);
+        P->by_rows = cpapr::rows_supported(R, X->nnz);
+        P->row_owner = std::move(owner);
         if (P->by_rows) {
             for (int n = 0; n < P->N; ++n)
                 cpapr::rows_mode_bind(&P->mode[n].rp, w + L.mode_rp[n], X->nnz, P->dims[n], R);
@@ -586,7 +589,8 @@ int cpapr_mu_inner(cpapr_plan* plan, int32_t mode, double* B, const double* cons
         if (e.code) return report(e);
         e = cpapr::launch_reset_state(plan->state, true, true, s);
         if (e.code) return report(e);
-        e = enqueue_inner(plan, mode, B, fac, Phi_last, s);
+        const cpapr::RowClaim claim(plan->row_owner.get(), &claim);
+        e = enqueue_inner(plan, mode, B, fac, Phi_last, claim.ok && runs_by_rows(plan), s);
         if (e.code) return report(e);
         HostState h{};
         e = read_state(plan, &h, s);
@@ -719,10 +723,11 @@ int cpapr_solve(cpapr_plan* plan, double* lambda, double* const* A, cpapr_stats*
         e = cpapr::launch_reset_state(P->state, true, true, s);
         if (e.code) return report(e);
         int k = 1, converged = 0;
+        const cpapr::RowClaim claim(P->row_owner.get(), &claim);
+        const bool rows = claim.ok && runs_by_rows(P);
         for (; k <= P->params.kmax; ++k) {
             for (int n = 0; n < N; ++n) {
                 const int64_t In = P->dims[n];
-                const bool rows = runs_by_rows(P);
                 if (!rows) {
                     e = cpapr::launch_reset_state(P->state, n == 0, false, s);
                     if (e.code) return report(e);
@@ -733,7 +738,7 @@ int cpapr_solve(cpapr_plan* plan, double* lambda, double* const* A, cpapr_stats*
                 if (e.code) return report(e);
                 e = method == CPAPR_METHOD_PQNR   ? cpapr::enqueue_pqnr_inner(P, n, P->B, fac, P->phi_prev[n], s)
                     : method == CPAPR_METHOD_PDNR ? cpapr::enqueue_pdnr_inner(P, n, P->B, fac, P->phi_prev[n], s)
-                                                  : enqueue_inner(P, n, P->B, fac, P->phi_prev[n], s);
+                                                  : enqueue_inner(P, n, P->B, fac, P->phi_prev[n], rows, s);
                 if (e.code) return report(e);
                 float* a32 = mixed ? P->f32[n] : nullptr;
                 if (cpapr::colnorm_small(In, R)) {

@@ -146,6 +146,13 @@ struct cpapr_batch {
     int nrows = 0;
     bool row_stops = false;             // some slot has a KKT tolerance
     int row_copies = 0;                 // FP32 factor copies to refresh first
+    std::vector<std::shared_ptr<cpapr::RowOwner>> owned;  // of the listed plans' row buffers
+    void release_rows()
+    {
+        for (auto& o : owned) o->store(nullptr);
+        owned.clear();
+    }
+    ~cpapr_batch() { release_rows(); }
     std::vector<int> row_grids;         // grid sizes of the row launches (baked into a captured graph)
     struct Graph {
         hipGraphExec_t exec = nullptr;
@@ -527,19 +534,19 @@ int cpapr_batch_commit(cpapr_batch* batch, void* stream)
         if (hipMemcpyAsync(b->st.hold, b->hold.data(), 4 * (size_t)b->max_slots, hipMemcpyHostToDevice, s) !=
             hipSuccess)
             return fail(CPAPR_EHIP, "upload of the hold flags failed");
-        // inner loops row by row: every slot's plan allows it, and no plan's buffers serve two slots
+        // inner loops row by row: every slot's plan allows it, and no plan's buffers serve two slots or owners
+        b->release_rows();
         std::vector<int> shape_of(b->max_slots, -1);
-        std::vector<const cpapr_plan*> seen;
         bool by_rows = nmu > 0;
         for (int i = 0; i < b->max_slots && by_rows; ++i) {
             const HostSlot& h = b->slots[i];
             if (!h.set || (b->skip_held && b->hold[i])) continue;
             shape_of[i] = cpapr::rows_batch_shape(h.plan, h.mode);
-            by_rows = shape_of[i] >= 0;
-            seen.push_back(h.plan);
+            const void* none = nullptr;
+            by_rows = shape_of[i] >= 0 && h.plan->row_owner->compare_exchange_strong(none, b);
+            if (by_rows) b->owned.push_back(h.plan->row_owner);
         }
-        std::sort(seen.begin(), seen.end());
-        by_rows = by_rows && std::adjacent_find(seen.begin(), seen.end()) == seen.end();
+        if (!by_rows) b->release_rows();
         std::vector<char> items;
         std::vector<int32_t> prefix;
         std::vector<BatchCopy> rcopies;

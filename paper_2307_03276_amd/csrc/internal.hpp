@@ -3,7 +3,9 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
+#include <memory>
 #include <string>
 
 #include "../../include/cpapr.h"
@@ -159,6 +161,30 @@ struct RowState {
     double* hist;          // [2 kInnerChunk x heavy rows x R] heavy rows' B and Phi per iteration (tol > 0)
 };
 
+// Who runs inner loops in a plan's row buffers (RowState): a batch from the
+// commit that lists the plan to its next commit or its end, a single inner loop
+// or solve for its duration. Whoever finds them taken runs the general launches,
+// which share nothing: a plan may be in several batches, on several streams.
+// The plan and its batches hold it jointly, so either may end first.
+using RowOwner = std::atomic<const void*>;
+
+struct RowClaim {
+    RowOwner* owner = nullptr;
+    const void* who;
+    bool ok;
+    RowClaim(RowOwner* o, const void* w) : owner(o), who(w)
+    {
+        const void* none = nullptr;
+        ok = o->compare_exchange_strong(none, w);
+    }
+    ~RowClaim()
+    {
+        if (ok) owner->store(nullptr);
+    }
+    RowClaim(const RowClaim&) = delete;
+    RowClaim& operator=(const RowClaim&) = delete;
+};
+
 struct PlanMode {
     int32_t* rows;  // [nnz] sorted mode-n coordinates
     uint32_t* cofs;  // [(N-1) * nnz] the other modes' factor row offsets (coordinate x R), ascending m
@@ -260,6 +286,7 @@ struct cpapr_plan {
     cpapr::PdnrState pd;              // PDNR row-solve state (method CPAPR_METHOD_PDNR only)
     cpapr::RowState rs;               // row-by-row inner loop (rows_supported)
     bool by_rows;                     // its structures are there
+    std::shared_ptr<cpapr::RowOwner> row_owner;
     bool exact32;                     // every value is exact in FP32
     int64_t team_wait;                // clock ticks (10 ns) a team member waits for its team to start
     double* det_part;                 // deterministic mode: tile-end partial rows (nullptr: atomics)
@@ -272,7 +299,7 @@ namespace cpapr {
 constexpr int kPartials = 512;   // blocks of the two-level deterministic column sums
 
 // ---- plan construction (sort.hip) ----
-int64_t sort_scratch_bytes(int64_t nnz, int N);
+int64_t sort_scratch_bytes(int64_t nnz, int N, bool rows);
 // Validates coordinates/values, then builds the sorted copies of every mode
 // (only >= 0: of that mode alone).
 Error build_sorted(cpapr_plan* P, const cpapr_coo* X, char* scratch, hipStream_t s, int only = -1);
@@ -345,7 +372,7 @@ Error launch_rows_batch_decide(const void* items, int n, BatchState st, int32_t*
                                hipStream_t s);
 
 // ---- MU inner loop row by row (rows.hip) ----
-bool rows_supported(int R);
+bool rows_supported(int R, int64_t nnz);
 // Bytes of a mode's row classes / of the inner loop's buffers, bound to `base`
 // unless r is nullptr (stops: tol > 0).
 size_t rows_mode_bind(RowPlan* r, char* base, int64_t nnz, int64_t dim, int R);

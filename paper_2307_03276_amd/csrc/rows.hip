@@ -1704,10 +1704,13 @@ int64_t max_members(int64_t nnz, const Shape& s) { return nnz / class_cap(class_
 
 }  // namespace
 
-bool rows_supported(int R)
+// Up to 2^30 nonzeros: positions are 32-bit with room for a step past the end,
+// and the structures below (up to 45 bytes per nonzero beyond a plan without
+// them, which takes 168 GB there) stay within the device's memory.
+bool rows_supported(int R, int64_t nnz)
 {
     Shape s;
-    return row_shape(R, &s);
+    return nnz <= (int64_t(1) << 30) && row_shape(R, &s);
 }
 
 size_t rows_mode_bind(RowPlan* r, char* base, int64_t nnz, int64_t dim, int R)

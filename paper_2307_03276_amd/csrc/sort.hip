@@ -393,7 +393,10 @@ Error pass_offsets(int* counts, int ntiles, int* part, hipStream_t s)
 
 }  // namespace
 
-int64_t sort_scratch_bytes(int64_t nnz, int N)
+// Counters of one sort: flags and segment counts, then for a plan the row class counts of its modes.
+static size_t sort_counter_bytes(bool rows) { return 256 + (rows ? (size_t)CPAPR_MAX_MODES * kRowMeta * 4 : 0); }
+
+int64_t sort_scratch_bytes(int64_t nnz, int N, bool rows)
 {
     const int64_t ntiles = cdiv(nnz > 0 ? nnz : 1, kSortTile);
     const int64_t ncounts = ntiles * kRadix;
@@ -402,7 +405,7 @@ int64_t sort_scratch_bytes(int64_t nnz, int N)
     b += 4 * align256((size_t)nnz * 4);                     // keys/payload ping-pong
     b += align256((size_t)ncounts * 4);                     // histogram table
     b += align256((size_t)(cdiv(ntiles, kScanTiles) + 1) * kRadix * 4);  // offsets scan: group sums, digit bases
-    b += align256(256 + CPAPR_MAX_MODES * kRowMeta * 4);     // flags / counters, row class counts
+    b += align256(sort_counter_bytes(rows));                // flags / counters
     b += align256(kSegPartials * 8);                         // segment-count partials
     return (int64_t)b;
 }
@@ -427,13 +430,13 @@ Error build_sorted(cpapr_plan* P, const cpapr_coo* X, char* scratch, hipStream_t
     int32_t* pb = (int32_t*)take((size_t)nnz * 4);
     int* counts = (int*)take((size_t)ncounts * 4);
     int* part = (int*)take((size_t)(cdiv(ntiles, kScanTiles) + 1) * kRadix * 4);
-    int* flags = (int*)take(256 + CPAPR_MAX_MODES * kRowMeta * 4);
+    int* flags = (int*)take(sort_counter_bytes(P->by_rows));
     int* meta = flags + 64;  // kRowMeta ints per mode
     unsigned long long* segc = (unsigned long long*)(flags + 8);
     unsigned long long* segpart = (unsigned long long*)take(kSegPartials * 8);
 
     // flags and segment counters start at zero (plain kernel-free path: a tiny fill)
-    CPAPR_HIP(hipMemsetAsync(flags, 0, 256 + CPAPR_MAX_MODES * kRowMeta * 4, s));
+    CPAPR_HIP(hipMemsetAsync(flags, 0, sort_counter_bytes(P->by_rows), s));
     if (nnz > 0) {
         DimsArg d{};
         for (int m = 0; m < N; ++m) d.d[m] = P->dims[m];
@@ -526,7 +529,7 @@ Error build_sorted(cpapr_plan* P, const cpapr_coo* X, char* scratch, hipStream_t
     }
     if (only >= 0) return {CPAPR_OK, ""};
     int host[64 + CPAPR_MAX_MODES * kRowMeta];
-    CPAPR_HIP(hipMemcpyAsync(host, flags, sizeof(int) * (64 + N * kRowMeta), hipMemcpyDeviceToHost, s));
+    CPAPR_HIP(hipMemcpyAsync(host, flags, sizeof(int) * (64 + (P->by_rows ? N * kRowMeta : 0)), hipMemcpyDeviceToHost, s));
     CPAPR_HIP(hipStreamSynchronize(s));
     for (int n = 0; n < N; ++n) {
         unsigned long long seg;

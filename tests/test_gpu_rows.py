@@ -203,3 +203,41 @@ def test_line_search_by_rows(R, others, lmax=2):
         assert st["row_steps"] == st2["row_steps"] and st["trial_evals"] == st2["trial_evals"]
         assert_parity(host(B2), host(B), tol, f"{run} R={R} against the general pass", elementwise=False)
         P.close()
+
+
+def test_plan_in_two_batches_and_a_single_loop():
+    """One plan listed by two batches that run on streams of their own, and run by
+    a single inner loop meanwhile; the batches then end before and after the plan."""
+    import torch
+    X = _tensor(EDGES + [9_000], (60, 45), 91)
+    M = synth.random_model(91, X.dims, 10)
+    Bh = M.factors[0] * M.lam
+    Bo, Po, _, nup = oracle.mu_inner(X, 0, Bh, M.factors, lmax=20)
+    P = cpapr.Plan.from_tensor(X, 10, lmax=20)
+    A = [dev(a) for a in M.factors]
+    runs = []
+    for _ in range(2):
+        s = torch.cuda.Stream()
+        b = cpapr.Batch(1, P.tiles() + 1)
+        B, Phi = dev(Bh), dev(np.zeros_like(Bh))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s):
+            b.set(0, P, 0, B, A, Phi)
+            b.commit()
+        runs.append((s, b, B, Phi))
+    for s, b, B, Phi in runs:
+        with torch.cuda.stream(s):
+            b.inner(20)
+    single = dev(Bh)
+    phi, st = P.mu_inner(0, single, A)
+    torch.cuda.synchronize()
+    for B, Phi in [(single, phi)] + [r[2:] for r in runs]:
+        assert_parity(host(B), Bo, TOL64, "B")
+        assert_parity(host(Phi), Po, TOL64, "Phi")
+    assert st["inner_iters"] == nup
+    runs[0][1].close()
+    single = dev(Bh)
+    P.mu_inner(0, single, A)
+    assert_parity(host(single), Bo, TOL64, "B")
+    P.close()
+    runs[1][1].close()
