@@ -1239,16 +1239,19 @@ int resolve_chunk(int group, int requested)
 // device), the rank and the precision; the modes of one tensor, and uniform
 // against Zipf rows at equal size, preferred the same shape.
 //  * a large tensor's shape: 512-nonzero tiles with lanes by rank, except
-//    17 <= R <= 32 with up to four modes: 16 lanes x 2 columns on 256-nonzero
-//    tiles in FP64, 8 lanes x 4 columns on 1024-nonzero tiles with FP32-stored
-//    factors (half the gathered words per lane; three columns up to R = 24).
-//    At 17 <= R <= 24 the FP64 tiles hold 512 nonzeros for three modes and 256
-//    for more, on 16 lanes at every mode count; with FP32-stored factors 8
-//    lanes x 3 columns take 1024 for up to four modes, 512 for more (R = 24,
-//    8 x 3 on 512 / 1024 against 16 x 2 on 256 / 512 nonzeros, us: 3-way 20M
-//    nonzeros FP64 460 / 462 / 470 / 437, mixed 406 / 364 / 474 / 431; 4-way
-//    16M FP64 1092 / 1179 / 1029 / 1063; 5-way 12.9M FP64 488 / 515 / 461 /
-//    476, mixed 333 / 347 / 453 / 465); and 5 <= R <= 16 with packed
+//    17 <= R <= 32: in FP64 16 lanes x 2 columns at every mode count, on 512
+//    nonzeros for up to three modes from 3 * 2^20 nonzeros on (24 tiles per
+//    compute unit; 1.85M uniform nonzeros, R = 24: 75.7 on 512 against 73.5 us
+//    on 256) and 256 else; with FP32-stored factors (half
+//    the gathered words per lane) 8 lanes x 3 or 4 columns, on 1024 for up to
+//    four modes and 512 for more (from five modes on four columns no longer
+//    fit: 16 x 2). Measured, 8 lanes on 512 / 1024 against 16 lanes on 256 /
+//    512 nonzeros, us: R = 24, 3-way 20M nonzeros FP64 460 / 462 / 470 / 437,
+//    mixed 406 / 364 / 474 / 431; 4-way 16M FP64 1092 / 1179 / 1029 / 1063;
+//    5-way 12.9M FP64 488 / 515 / 461 / 476, mixed 333 / 347 / 453 / 465; R =
+//    32 FP64, 3-way 20M 482 / 461 / 475 / 445, 3-way 4M 108 / 103 / 101 / 90,
+//    4-way 16M 1216 / 1312 / 1156 / 1192;
+//    and 5 <= R <= 16 with packed
 //    nonzero records (one load per staged nonzero): 1024-nonzero tiles, the
 //    tile's merge and row flushes weighing more against the cheaper nonzeros
 //    (-10 % at zipf3 against 512);
@@ -1285,18 +1288,13 @@ bool group16_ok(const ModelIn& m)
 // (tile nonzeros, lanes per nonzero)
 void model_shape(const ModelIn& m, int* tile, int* group)
 {
-    const bool three = m.R > 16 && m.R <= 24;  // three columns fill 8 lanes
-    const int g0 = three ? (m.mixed ? 8 : 16) : resolve_group(m.R, 0, m.nm1);
-    int tb = 512, gb = g0;  // a large tensor's shape
-    if (three && !m.mixed) {
-        tb = m.nm1 <= 2 ? 512 : 256;
-    } else if (m.R > 16 && m.R <= 32 && m.nm1 <= 3) {
-        if (m.mixed) {
-            tb = 1024;
-        } else if (group16_ok(m)) {
-            tb = 256;
-            gb = 16;
-        }
+    const bool wide = m.R > 16 && m.R <= 32;
+    const int g0 = !wide ? resolve_group(m.R, 0, m.nm1) : m.mixed && (m.nm1 <= 3 || m.R <= 24) ? 8 : 16;
+    int tb = 512;  // a large tensor's tile
+    if (wide && !m.mixed) {
+        tb = m.nm1 <= 2 && m.nnz >= (3 << 20) ? 512 : 256;
+    } else if (wide && m.nm1 <= 3) {
+        tb = 1024;
     } else if (m.packed && m.R > 4 && m.R <= 16) {
         tb = 1024;  // one load per staged nonzero: the tile's fixed costs weigh more
     }
@@ -1305,7 +1303,7 @@ void model_shape(const ModelIn& m, int* tile, int* group)
     if (m.det && t < 128) t = 128;
     if (t >= tb) {
         *tile = tb;
-        *group = gb;
+        *group = g0;
     } else if (t <= 128) {
         *tile = (int)t;
         *group = group16_ok(m) ? 16 : g0;
