@@ -1336,7 +1336,9 @@ void batch_shape(const cpapr_plan* P, int* group, int* chunk)
         return;
     }
     ModelIn m = model_in(P);
-    m.nnz = int64_t(1) << 40;  // the batch fills the device, not this slot
+    // the batch fills the device, not this slot: every rank's large tile, short of
+    // the 512 nonzeros that only pay where one tensor alone has the tiles
+    m.nnz = (3 << 20) - 1;
     m.det = false;             // batched launches take no tile-end buffers
     int t;
     model_shape(m, &t, group);
