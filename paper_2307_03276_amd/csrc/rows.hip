@@ -849,7 +849,7 @@ __global__ __launch_bounds__(kBlock) void heavy_kernel(HeavyArgs a)
 
 constexpr int kHotThreads = 1024;          // one workgroup per compute unit
 constexpr int kHotLds = 140 * 1024;        // bytes of hot rows (the workgroup's sums take up to 16 KB more)
-constexpr int kMaxHot = kHotLds / 8;       // (R = 1 with FP64 rows)
+constexpr int kMaxHot = kHotLds / 8;       // places of hot rows, at every rank and width
 constexpr uint16_t kCold = 0xffff;
 static_assert(kMaxHot < kCold, "places fit 16 bits");
 
@@ -1332,7 +1332,7 @@ __global__ __launch_bounds__(1024) void pieces_kernel(const int32_t* __restrict_
 // ---- plan: the long rows' nonzeros by hot and cold ----
 
 // Places of a mode's hot rows: its rows in length buckets >= bucket, in any
-// order (at most kMaxHot by the choice of the bucket).
+// order. max_hot: their number, at most kMaxHot (hot_rows holds no more).
 __global__ __launch_bounds__(kBlock) void hot_rows_kernel(const int32_t* __restrict__ row_ptr, int64_t nrows, int bucket,
                                                           int max_hot, int* __restrict__ counter,
                                                           uint16_t* __restrict__ hot_id, int32_t* __restrict__ hot_rows)
@@ -1810,7 +1810,7 @@ Error rows_hot_build(cpapr_plan* P, hipStream_t s)
     Shape sh;
     row_shape(P->R, &sh);
     const int word = P->params.precision == CPAPR_MIXED ? 4 : 8;
-    const int fit = kHotLds / (P->R * word);
+    const int fit = std::min(kHotLds / (P->R * word), kMaxHot);
     const int ncls = class_count(class_shape(sh));
     // every mode's hot rows: as many of its longest length buckets as fit
     int bucket[CPAPR_MAX_MODES], nhot[CPAPR_MAX_MODES];

@@ -106,6 +106,13 @@ def test_heavy_rows_split_by_hot_coordinates(R, others, precision, frac):
     _check(X, R, 3, tol=float(min(hist[:2])) * (1 + 1e-5), precision=precision)
 
 
+def test_hot_rows_at_rank_one():
+    """Rank 1 with FP32-stored factors: more rows of the second factor would fit
+    the LDS (35,840) than a plan has places for (17,920)."""
+    X = _tensor([21_500] * 50, (30_000, 25_000), 33)
+    _check(X, 1, 2, precision=cpapr.CPAPR_MIXED)
+
+
 def test_empty_tensor_and_repeat():
     X = synth.SparseTensor((7, 5, 4), np.zeros((3, 0), np.int32), np.zeros(0))
     P = cpapr.Plan.from_tensor(X, 6, lmax=3, tol=0.0)
