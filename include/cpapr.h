@@ -365,6 +365,10 @@ int cpapr_batch_create(int32_t max_slots, int64_t max_tiles, void* ws, size_t ws
 #define CPAPR_BATCH_SKIP_HELD 2
 int cpapr_batch_create2(int32_t max_slots, int64_t max_tiles, int32_t flags, void* ws, size_t ws_bytes,
                         cpapr_batch** out);
+/* Waits for the batch's queued inner loops (cpapr_batch_inner) that use their
+ * plans' row buffers; cpapr_batch_commit does too. A batch holds these buffers
+ * from its first inner loop of more than one iteration until then; other callers
+ * of the same plans run the general launches meanwhile. */
 int cpapr_batch_destroy(cpapr_batch* batch);
 
 /* Set slot `slot` (host-side only). B device [I_mode x R]; A host array of the

@@ -589,12 +589,13 @@ int cpapr_mu_inner(cpapr_plan* plan, int32_t mode, double* B, const double* cons
         if (e.code) return report(e);
         e = cpapr::launch_reset_state(plan->state, true, true, s);
         if (e.code) return report(e);
-        const cpapr::RowClaim claim(plan->row_owner.get(), &claim);
+        cpapr::RowClaim claim(plan->row_owner.get(), s);
         e = enqueue_inner(plan, mode, B, fac, Phi_last, claim.ok && runs_by_rows(plan), s);
         if (e.code) return report(e);
         HostState h{};
         e = read_state(plan, &h, s);
         if (e.code) return report(e);
+        claim.queued = false;
         if (out) {
             out->outer_iters = 0;
             out->converged = h.done;
@@ -723,7 +724,7 @@ int cpapr_solve(cpapr_plan* plan, double* lambda, double* const* A, cpapr_stats*
         e = cpapr::launch_reset_state(P->state, true, true, s);
         if (e.code) return report(e);
         int k = 1, converged = 0;
-        const cpapr::RowClaim claim(P->row_owner.get(), &claim);
+        cpapr::RowClaim claim(P->row_owner.get(), s);
         const bool rows = claim.ok && runs_by_rows(P);
         for (; k <= P->params.kmax; ++k) {
             for (int n = 0; n < N; ++n) {
@@ -769,6 +770,7 @@ int cpapr_solve(cpapr_plan* plan, double* lambda, double* const* A, cpapr_stats*
         HostState h{};
         e = read_state(P, &h, s);
         if (e.code) return report(e);
+        claim.queued = false;
         if (out) {
             out->outer_iters = k;
             out->converged = converged;

@@ -146,19 +146,55 @@ struct cpapr_batch {
     int nrows = 0;
     bool row_stops = false;             // some slot has a KKT tolerance
     int row_copies = 0;                 // FP32 factor copies to refresh first
-    std::vector<std::shared_ptr<cpapr::RowOwner>> owned;  // of the listed plans' row buffers
+    // The listed plans' row buffers: claimed by the first inner loop that uses
+    // them, given back by the next commit or the end of the batch, after the loops
+    // queued meanwhile have ended (row_used follows the last of them).
+    std::vector<std::shared_ptr<cpapr::RowOwner>> row_owners;
+    bool owns_rows = false;
+    bool use_rows = false;              // this inner loop runs row by row
+    bool row_untracked = false;         // a loop was queued that row_used does not follow
+    hipEvent_t row_used = nullptr;
+    bool claim_rows()
+    {
+        if (owns_rows) return true;
+        size_t n = 0;
+        const void* none = nullptr;
+        while (n < row_owners.size() && row_owners[n]->compare_exchange_strong(none, this)) ++n;
+        owns_rows = n == row_owners.size();
+        if (!owns_rows)
+            while (n > 0) row_owners[--n]->store(nullptr);
+        return owns_rows;
+    }
+    void follow_rows(hipStream_t s)
+    {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        const bool free = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+        if (!free || (row_used == nullptr && hipEventCreateWithFlags(&row_used, hipEventDisableTiming) != hipSuccess) ||
+            hipEventRecord(row_used, s) != hipSuccess)
+            row_untracked = true;
+    }
     void release_rows()
     {
-        for (auto& o : owned) o->store(nullptr);
-        owned.clear();
+        if (!owns_rows) return;
+        if (row_untracked)
+            hipDeviceSynchronize();
+        else if (row_used != nullptr)
+            hipEventSynchronize(row_used);
+        for (auto& o : row_owners) o->store(nullptr);
+        owns_rows = row_untracked = false;
     }
-    ~cpapr_batch() { release_rows(); }
+    ~cpapr_batch()
+    {
+        release_rows();
+        if (row_used != nullptr) hipEventDestroy(row_used);
+    }
     std::vector<int> row_grids;         // grid sizes of the row launches (baked into a captured graph)
     struct Graph {
         hipGraphExec_t exec = nullptr;
         std::vector<int> classes;  // classes captured
         std::vector<int64_t> tiles;  // per-class tile counts captured (grid launches)
         std::vector<int> row_grids;  // the same of the row launches (inner loops)
+        bool rows = false;           // captured row by row
         int lmax = 0;              // inner iterations captured (0: Phi only)
     } graph_run, graph_inner;
 };
@@ -253,7 +289,7 @@ Error enqueue_sequence(cpapr_batch* b, int lmax, hipStream_t s)
     Error e = cpapr::launch_batch_reset(b->st, b->max_slots, s);
     if (e.code) return e;
     if (lmax == 0) return enqueue_phi(b, b->classes, s);
-    if (b->nrows > 0 && lmax > 1) return enqueue_rows(b, lmax, s);
+    if (b->use_rows) return enqueue_rows(b, lmax, s);
     for (int l = 0; l < lmax; ++l) {
         e = enqueue_phi(b, b->classes, s);
         if (e.code) return e;
@@ -272,7 +308,7 @@ int run_sequence(cpapr_batch* b, cpapr_batch::Graph& g, int lmax, bool use_graph
     for (int c : b->classes)
         if (std::find(g.classes.begin(), g.classes.end(), c) == g.classes.end()) covered = false;
     if (!b->persistent && g.tiles != b->class_tiles) covered = false;  // grid sizes are baked into the graph
-    if (lmax > 0 && g.row_grids != b->row_grids) covered = false;
+    if (lmax > 0 && (g.rows != b->use_rows || (g.rows && g.row_grids != b->row_grids))) covered = false;
     if (covered) {
         if (hipGraphLaunch(g.exec, s) != hipSuccess) return fail(CPAPR_EHIP, "hipGraphLaunch failed");
         return CPAPR_OK;
@@ -305,6 +341,7 @@ int run_sequence(cpapr_batch* b, cpapr_batch::Graph& g, int lmax, bool use_graph
     g.classes = b->classes;
     g.tiles = b->class_tiles;
     g.row_grids = b->row_grids;
+    g.rows = b->use_rows;
     g.lmax = lmax;
     return CPAPR_OK;
 }
@@ -534,19 +571,21 @@ int cpapr_batch_commit(cpapr_batch* batch, void* stream)
         if (hipMemcpyAsync(b->st.hold, b->hold.data(), 4 * (size_t)b->max_slots, hipMemcpyHostToDevice, s) !=
             hipSuccess)
             return fail(CPAPR_EHIP, "upload of the hold flags failed");
-        // inner loops row by row: every slot's plan allows it, and no plan's buffers serve two slots or owners
+        // inner loops row by row: every slot's plan allows it, and no plan's buffers serve two slots
         b->release_rows();
+        b->row_owners.clear();
         std::vector<int> shape_of(b->max_slots, -1);
         bool by_rows = nmu > 0;
         for (int i = 0; i < b->max_slots && by_rows; ++i) {
             const HostSlot& h = b->slots[i];
             if (!h.set || (b->skip_held && b->hold[i])) continue;
             shape_of[i] = cpapr::rows_batch_shape(h.plan, h.mode);
-            const void* none = nullptr;
-            by_rows = shape_of[i] >= 0 && h.plan->row_owner->compare_exchange_strong(none, b);
-            if (by_rows) b->owned.push_back(h.plan->row_owner);
+            by_rows = shape_of[i] >= 0;
+            if (by_rows) b->row_owners.push_back(h.plan->row_owner);
         }
-        if (!by_rows) b->release_rows();
+        std::sort(b->row_owners.begin(), b->row_owners.end());
+        if (std::adjacent_find(b->row_owners.begin(), b->row_owners.end()) != b->row_owners.end()) by_rows = false;
+        if (!by_rows) b->row_owners.clear();
         std::vector<char> items;
         std::vector<int32_t> prefix;
         std::vector<BatchCopy> rcopies;
@@ -684,6 +723,7 @@ int cpapr_batch_run(cpapr_batch* batch, int32_t use_graph, void* stream)
     try {
         if (!batch) return fail(CPAPR_EINVAL, "batch is NULL");
         if (!batch->committed) return fail(CPAPR_EINVAL, "batch not committed since the last change");
+        batch->use_rows = false;
         return run_sequence(batch, batch->graph_run, 0, use_graph != 0, (hipStream_t)stream);
     } catch (...) {
         return fail(CPAPR_EINVAL, "unexpected exception");
@@ -696,7 +736,11 @@ int cpapr_batch_inner(cpapr_batch* batch, int32_t lmax, int32_t use_graph, void*
         if (!batch) return fail(CPAPR_EINVAL, "batch is NULL");
         if (lmax < 1 || lmax > CPAPR_MAX_LMAX) return fail(CPAPR_EINVAL, "lmax must be in [1, 4096]");
         if (!batch->committed) return fail(CPAPR_EINVAL, "batch not committed since the last change");
-        return run_sequence(batch, batch->graph_inner, lmax, use_graph != 0, (hipStream_t)stream);
+        // one iteration alone gathers once either way
+        batch->use_rows = batch->nrows > 0 && lmax > 1 && batch->claim_rows();
+        const int rc = run_sequence(batch, batch->graph_inner, lmax, use_graph != 0, (hipStream_t)stream);
+        if (batch->use_rows) batch->follow_rows((hipStream_t)stream);
+        return rc;
     } catch (...) {
         return fail(CPAPR_EINVAL, "unexpected exception");
     }

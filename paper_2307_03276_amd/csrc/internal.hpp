@@ -161,25 +161,28 @@ struct RowState {
     double* hist;          // [2 kInnerChunk x heavy rows x R] heavy rows' B and Phi per iteration (tol > 0)
 };
 
-// Who runs inner loops in a plan's row buffers (RowState): a batch from the
-// commit that lists the plan to its next commit or its end, a single inner loop
-// or solve for its duration. Whoever finds them taken runs the general launches,
-// which share nothing: a plan may be in several batches, on several streams.
+// Who runs inner loops in a plan's row buffers (RowState): a batch from its first
+// inner loop to its next commit or its end, a single inner loop or solve for its
+// duration. They are given back only when the device has done with them. Whoever
+// finds them taken runs the general launches, which share nothing: a plan may be
+// in several batches, on several streams.
 // The plan and its batches hold it jointly, so either may end first.
 using RowOwner = std::atomic<const void*>;
 
 struct RowClaim {
-    RowOwner* owner = nullptr;
-    const void* who;
-    bool ok;
-    RowClaim(RowOwner* o, const void* w) : owner(o), who(w)
+    RowOwner* owner;
+    hipStream_t stream;
+    bool ok, queued = true;  // queued: the stream was not waited for (the call failed half-way)
+    RowClaim(RowOwner* o, hipStream_t s) : owner(o), stream(s)
     {
         const void* none = nullptr;
-        ok = o->compare_exchange_strong(none, w);
+        ok = o->compare_exchange_strong(none, this);
     }
     ~RowClaim()
     {
-        if (ok) owner->store(nullptr);
+        if (!ok) return;
+        if (queued) hipStreamSynchronize(stream);
+        owner->store(nullptr);
     }
     RowClaim(const RowClaim&) = delete;
     RowClaim& operator=(const RowClaim&) = delete;

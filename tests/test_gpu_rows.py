@@ -248,3 +248,42 @@ def test_plan_in_two_batches_and_a_single_loop():
     assert_parity(host(single), Bo, TOL64, "B")
     P.close()
     runs[1][1].close()
+
+
+def test_row_buffers_come_back_when_the_device_is_done():
+    """A batch that ends (or commits) with its inner loop still queued keeps the
+    plan's row buffers until the loop is done; a batch that only ran Phi never
+    takes them, so a single loop takes its usual path (bit for bit)."""
+    import torch
+    X = _tensor(EDGES + [9_000, 30_000], (60, 45), 92)
+    M = synth.random_model(92, X.dims, 10)
+    Bh = M.factors[0] * M.lam
+    P = cpapr.Plan.from_tensor(X, 10, lmax=20, tol=0.0)
+    A = [dev(a) for a in M.factors]
+    alone = dev(Bh)
+    P.mu_inner(0, alone, A)
+    assert_parity(host(alone), oracle.mu_inner(X, 0, Bh, M.factors, lmax=20, tau=0.0)[0], TOL64, "B")
+    s = torch.cuda.Stream()
+    b = cpapr.Batch(1, P.tiles() + 1)
+    B, Phi = dev(Bh), dev(np.zeros_like(Bh))
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        b.set(0, P, 0, B, A, Phi)
+        b.commit()
+        b.run()
+    single = dev(Bh)
+    P.mu_inner(0, single, A)
+    torch.cuda.synchronize()
+    assert torch.equal(single, alone)
+    for end in ("commit", "close"):
+        with torch.cuda.stream(s):
+            B.copy_(dev(Bh))
+            torch.cuda._sleep(50_000_000)  # some 20 ms: the loop is still queued when the batch ends
+            b.inner(20)
+        getattr(b, end)()
+        single = dev(Bh)
+        P.mu_inner(0, single, A)
+        torch.cuda.synchronize()
+        assert torch.equal(single, alone)
+        assert_parity(host(B), host(alone), TOL64, "B of the batch")
+    P.close()
