@@ -202,12 +202,15 @@ Error phi_factors(cpapr_plan* P, int mode, const double* const* A, const void** 
 }
 
 // Whether the MU inner loop runs row by row (rows.hip): unless the caller chose
-// the Phi launch (a shape of its own or a variant). One iteration alone gathers
-// once either way, and the Phi kernel does that faster (8M uniform nonzeros, R =
-// 32: 224 against 394 us).
+// the Phi launch (a shape of its own or a variant), or asked for sums that repeat
+// bit for bit: a team's row is summed in other pieces when its members do not all
+// start in time, and a plan whose row buffers a batch holds takes the general
+// launches. One iteration alone gathers once either way, and the Phi kernel does
+// that faster (8M uniform nonzeros, R = 32: 224 against 394 us).
 bool runs_by_rows(const cpapr_plan* P)
 {
-    return P->by_rows && P->shape_auto && P->params.variant <= CPAPR_VARIANT_SEGMENTED && P->params.lmax > 1;
+    return P->by_rows && P->shape_auto && P->params.variant <= CPAPR_VARIANT_SEGMENTED && P->params.lmax > 1 &&
+           !P->params.deterministic;
 }
 
 // One inner loop (Algorithm 1): zero Phi, then lmax x {Phi, KKT, MU update},

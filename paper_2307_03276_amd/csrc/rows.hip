@@ -20,7 +20,9 @@
 //    chunks of one row each; every iteration gathers again (heavy_kernel), the
 //    last workgroup of a row to finish sums the chunks' partial rows in order
 //    and takes the MU step of that row.
-// Every sum has a fixed order, so results repeat bit for bit.
+// Every sum has a fixed order, so results repeat bit for bit while the same path
+// is taken: the row of a team whose members were not all running in time is summed
+// by one workgroup, in other pieces.
 #include <algorithm>
 #include <cstring>
 #include <type_traits>

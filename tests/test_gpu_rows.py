@@ -287,3 +287,36 @@ def test_row_buffers_come_back_when_the_device_is_done():
         assert torch.equal(single, alone)
         assert_parity(host(B), host(alone), TOL64, "B of the batch")
     P.close()
+
+
+def test_deterministic_plans_repeat_bit_for_bit():
+    """deterministic = 1: the same bits whether or not teams of workgroups could
+    meet, and whether or not a batch runs inner loops of the plan."""
+    import torch
+    X = _tensor(EDGES + [9_000, 30_000], (60, 45), 93)
+    M = synth.random_model(93, X.dims, 10)
+    Bh = M.factors[0] * M.lam
+    Bo = oracle.mu_inner(X, 0, Bh, M.factors, lmax=6, tau=0.0)[0]
+    A = [dev(a) for a in M.factors]
+    P = cpapr.Plan.from_tensor(X, 10, lmax=6, tol=0.0, deterministic=1)
+
+    def loop():
+        B = dev(Bh)
+        P.mu_inner(0, B, A)
+        lam, F = dev(M.lam), [dev(a) for a in M.factors]
+        P.solve(lam, F)
+        return [B, lam, *F]
+
+    first = loop()
+    assert_parity(host(first[0]), Bo, TOL64, "B")
+    cpapr.cpapr_plan_set_team_wait(P.handle, 0)
+    for again in (loop(), loop()):
+        assert all(torch.equal(x, y) for x, y in zip(first, again))
+    b = cpapr.Batch(1, P.tiles() + 1)
+    B, Phi = dev(Bh), dev(np.zeros_like(Bh))
+    b.set(0, P, 0, B, A, Phi)
+    b.commit()
+    b.inner(6)
+    assert all(torch.equal(x, y) for x, y in zip(first, loop()))
+    b.close()
+    P.close()
