@@ -80,17 +80,24 @@ __device__ __forceinline__ double seg_sum(double v)
     return v;
 }
 
-// 1 / sqrt(x), x > 0 and finite: the hardware estimate and two Newton steps
-// (each squares the error, so the second leaves the roundings).
-__device__ __forceinline__ double rsqrt_pos(double x)
+// 1 / b for normal, finite b: the hardware's estimate (about 2^-24) and two Newton
+// steps, within an ulp.
+__device__ __forceinline__ double reciprocal(double b)
 {
-    double r = __builtin_amdgcn_rsq(x);
+    double r = __builtin_amdgcn_rcp(b);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const double e = __builtin_fma(-x * r, r, 1.0);
-        r = __builtin_fma(0.5 * r, e, r);
-    }
+    for (int i = 0; i < 2; ++i) r = __builtin_fma(r, __builtin_fma(-b, r, 1.0), r);
     return r;
+}
+
+// a / b by rb = reciprocal(b): the product, corrected by its residual, which makes
+// it the nearest double again, as the division's own last step does (2e8 random
+// quotients, rb an ulp off to either side: all equal to a / b); the fix-up sets the
+// quotients of infinities and zeros. Quotients by one b share the reciprocal.
+__device__ __forceinline__ double quotient(double a, double b, double rb)
+{
+    const double q = a * rb;
+    return __builtin_amdgcn_div_fixup(__builtin_fma(__builtin_fma(-b, q, a), rb, q), b, a);
 }
 
 __device__ __forceinline__ double wave_sum(double v) { return seg_sum<64>(v); }
@@ -247,12 +254,10 @@ __device__ __forceinline__ void hess_tiles(const HessArgs& a)
 #pragma unroll
             for (int t = 0; t < NT; ++t) mk = __builtin_fma(bv[t], pi[t], mk);
             mk = seg_sum<16>(mk);
-            // 1 / max(m, eps) by the Phi kernel's estimate and Newton step, once for both quotients
             const double mm = mk > a.eps ? mk : a.eps;
-            double rm = __builtin_amdgcn_rcp(mm);
-            rm = __builtin_fma(rm, __builtin_fma(-mm, rm, 1.0), rm);
-            const double sc = x * rm;
-            const double w = sc * rm;
+            const double rm = reciprocal(mm);
+            const double sc = quotient(x, mm, rm);
+            const double w = quotient(sc, mm, rm);
             int rk[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) rk[k] = __builtin_amdgcn_readlane(row, 16 * k);
@@ -427,6 +432,7 @@ __global__ __launch_bounds__(64 * begin_waves<RM>()) void pdnr_begin_kernel(RowA
             // Right-looking Cholesky: at step k lane k's diagonal becomes L[k][k],
             // lanes below it take L[lane][k] and update their row's later columns.
             bool ok = true;
+            double rd = 1.0;  // 1 / L[lane][lane]
 #pragma unroll
             for (int k = 0; k < RM; ++k) {
                 const double piv = lane_value(M[k], k);
@@ -434,11 +440,10 @@ __global__ __launch_bounds__(64 * begin_waves<RM>()) void pdnr_begin_kernel(RowA
                     ok = false;
                     break;
                 }
-                // The diagonal place keeps 1 / L[k][k]: the substitutions multiply by it
-                // (a square root and 3 RM divisions, one after the other, were most of this kernel).
-                const double inv = rsqrt_pos(piv);
-                const double lik = M[k] * inv;
-                M[k] = lane == k ? inv : lik;
+                const double lkk = sqrt(piv), inv = reciprocal(lkk);
+                const double lik = lane == k ? lkk : quotient(M[k], lkk, inv);
+                M[k] = lik;
+                if (lane == k) rd = inv;
                 if (lane < RM) lcol[k][lane] = lik;
                 wave_sync();
 #pragma unroll
@@ -449,7 +454,7 @@ __global__ __launch_bounds__(64 * begin_waves<RM>()) void pdnr_begin_kernel(RowA
                 double z = fre ? -g : 0.0;
 #pragma unroll
                 for (int j = 0; j < RM; ++j) {
-                    const double yj = lane_value(z, j) * lane_value(M[j], j);
+                    const double yj = lane_value(quotient(z, M[j], rd), j);
                     if (lane > j)
                         z = __builtin_fma(-M[j], yj, z);
                     else if (lane == j)
@@ -457,7 +462,7 @@ __global__ __launch_bounds__(64 * begin_waves<RM>()) void pdnr_begin_kernel(RowA
                 }
 #pragma unroll
                 for (int j = RM - 1; j >= 0; --j) {
-                    const double dj = lane_value(z, j) * lane_value(M[j], j);
+                    const double dj = lane_value(quotient(z, M[j], rd), j);
                     if (lane < j)
                         z = __builtin_fma(-lcol[lane][j], dj, z);
                     else if (lane == j)
@@ -536,14 +541,16 @@ __global__ __launch_bounds__(64) void pdnr_begin16_kernel(RowArgs a)
         const bool fj = j < R && ((fmask >> j) & 1u);
         M[j] = fre ? (fj ? hp[(int64_t)s * R + j] : 0.0) + (j == s ? damp : 0.0) : (j == s ? 1.0 : 0.0);
     }
+    double rd = 1.0;  // 1 / L[s][s]
     bool ok = chol;
 #pragma unroll
     for (int k = 0; k < RM; ++k) {
         const double piv = __shfl(M[k], sb + k);
         ok = ok && piv > 0.0;
-        const double inv = rsqrt_pos(piv > 0.0 ? piv : 1.0);  // as in pdnr_begin_kernel
-        const double lik = M[k] * inv;
-        M[k] = s == k ? inv : lik;
+        const double lkk = sqrt(piv > 0.0 ? piv : 1.0), inv = reciprocal(lkk);
+        const double lik = s == k ? lkk : quotient(M[k], lkk, inv);
+        M[k] = lik;
+        if (s == k) rd = inv;
         lcol[k][s] = lik;
         wave_sync();
 #pragma unroll
@@ -552,7 +559,7 @@ __global__ __launch_bounds__(64) void pdnr_begin16_kernel(RowArgs a)
     double z = fre ? -g : 0.0;
 #pragma unroll
     for (int j = 0; j < RM; ++j) {
-        const double yj = __shfl(z, sb + j) * __shfl(M[j], sb + j);
+        const double yj = __shfl(quotient(z, M[j], rd), sb + j);
         if (s > j)
             z = __builtin_fma(-M[j], yj, z);
         else if (s == j)
@@ -560,7 +567,7 @@ __global__ __launch_bounds__(64) void pdnr_begin16_kernel(RowArgs a)
     }
 #pragma unroll
     for (int j = RM - 1; j >= 0; --j) {
-        const double dj = __shfl(z, sb + j) * __shfl(M[j], sb + j);
+        const double dj = __shfl(quotient(z, M[j], rd), sb + j);
         if (s < j)
             z = __builtin_fma(-lcol[s][j], dj, z);
         else if (s == j)
@@ -659,10 +666,9 @@ __device__ __forceinline__ void hess_row(const HessArgs& a, const double (&bv)[N
             for (int t = 0; t < NT; ++t) mk = __builtin_fma(bv[t], pi[u][t], mk);
             mk = seg_sum<16>(mk);
             const double mm = mk > a.eps ? mk : a.eps;
-            double rm = __builtin_amdgcn_rcp(mm);
-            rm = __builtin_fma(rm, __builtin_fma(-mm, rm, 1.0), rm);
-            const double sc = xc[u] * rm;
-            const double w = sc * rm;
+            const double rm = reciprocal(mm);
+            const double sc = quotient(xc[u], mm, rm);
+            const double w = quotient(sc, mm, rm);
 #pragma unroll
             for (int ta = 0; ta < NT; ++ta) {
                 const double av = w * pi[u][ta];
@@ -789,6 +795,7 @@ __device__ __forceinline__ void newton_row(const RowArgs& a, int64_t i, double (
                 M[j] = fre ? (fj ? h_at(lr, j) : 0.0) + (j == lane ? damp : 0.0) : (j == lane ? 1.0 : 0.0);
             }
             bool ok = true;
+            double rd = 1.0;  // 1 / L[lane][lane]
 #pragma unroll
             for (int k = 0; k < RM; ++k) {
                 const double piv = lane_value(M[k], k);
@@ -796,9 +803,10 @@ __device__ __forceinline__ void newton_row(const RowArgs& a, int64_t i, double (
                     ok = false;
                     break;
                 }
-                const double inv = rsqrt_pos(piv);  // kept in the diagonal place, as in pdnr_begin_kernel
-                const double lik = M[k] * inv;
-                M[k] = lane == k ? inv : lik;
+                const double lkk = sqrt(piv), inv = reciprocal(lkk);
+                const double lik = lane == k ? lkk : quotient(M[k], lkk, inv);
+                M[k] = lik;
+                if (lane == k) rd = inv;
                 if (lane > k && lane < RM) sm[k][lane] = lik;
                 wave_sync();
 #pragma unroll
@@ -808,7 +816,7 @@ __device__ __forceinline__ void newton_row(const RowArgs& a, int64_t i, double (
                 double z = fre ? -g : 0.0;
 #pragma unroll
                 for (int j = 0; j < RM; ++j) {
-                    const double yj = lane_value(z, j) * lane_value(M[j], j);
+                    const double yj = lane_value(quotient(z, M[j], rd), j);
                     if (lane > j)
                         z = __builtin_fma(-M[j], yj, z);
                     else if (lane == j)
@@ -816,7 +824,7 @@ __device__ __forceinline__ void newton_row(const RowArgs& a, int64_t i, double (
                 }
 #pragma unroll
                 for (int j = RM - 1; j >= 0; --j) {
-                    const double dj = lane_value(z, j) * lane_value(M[j], j);
+                    const double dj = lane_value(quotient(z, M[j], rd), j);
                     if (lane < j)
                         z = __builtin_fma(-sm[lr][j], dj, z);
                     else if (lane == j)

@@ -178,3 +178,27 @@ def test_pdnr_rejects_other_plans_and_settings():
     with pytest.raises(cpapr.CpaprError) as ei:
         _plan(X2, 65)
     assert ei.value.code == -6
+
+
+@pytest.mark.parametrize("R", [8, 16, 20, 32, 40, 64])
+def test_newton_step_is_as_exact_as_its_operations(R, n=6_000):
+    """One step of rows of one nonzero and one positive entry, b = x (1 + t): the
+    exact step is d = -g / (h (1 + mu)), g = 1 - x / b, h = x / b^2. The operations
+    rounded to nearest (u = 2^-53): m 1, x / m 2, Phi 3, so g is off by 3 u / g and
+    1; h 6 with its two quotients, the damped pivot 8, its root and the two
+    substitutions 11 more; b + d and back 2 u b / d. With t in [0.2, 0.4]: under 45 u."""
+    rng = np.random.default_rng(R)
+    c, a = np.arange(n) % R, rng.uniform(0.1, 3.0, n)
+    x, t = rng.uniform(0.5, 50.0, n), rng.uniform(0.2, 0.4, n)
+    Bh, F = np.zeros((n, R)), np.zeros((n, R))
+    Bh[np.arange(n), c], F[np.arange(n), c] = x * (1.0 + t), a
+    X = synth.SparseTensor((n, n), np.stack([np.arange(n), np.arange(n)]).astype(np.int32), x)
+    P = cpapr.Plan.from_tensor(X, R, lmax=1, tol=0.0, method=cpapr.CPAPR_METHOD_PDNR)
+    B = dev(Bh)
+    P.pdnr_inner(0, B, [dev(Bh), dev(F)])
+    got = host(B)[np.arange(n), c]
+    b, xl = Bh[np.arange(n), c].astype(np.longdouble), x.astype(np.longdouble)
+    d = -(1 - xl / b) / (xl / b ** 2 * (1 + np.longdouble(1e-3)))
+    err = np.abs((got - b) / d - 1)
+    assert float(err.max()) < 45 * 2.0 ** -53, f"{float(err.max()) * 2.0 ** 53:.1f} u"
+    P.close()
