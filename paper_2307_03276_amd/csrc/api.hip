@@ -222,13 +222,16 @@ Error enqueue_inner(cpapr_plan* P, int mode, double* B, const void* const* fac, 
 {
     const int64_t n = P->dims[mode] * (int64_t)P->R;
     const bool mixed = P->params.precision == CPAPR_MIXED;
-    if (rows)
-        return cpapr::enqueue_inner_rows(P, mode, B, fac, Phi, s);
+    const bool first = rows && cpapr::rows_first_alone(P, mode);  // the first iteration here, the others row by row
+    if (rows && !first) return cpapr::enqueue_inner_rows(P, mode, B, fac, Phi, P->params.lmax, s);
     const bool fused = !(P->params.tol > 0.0);
     const int* done = &P->state->done;
-    Error e = cpapr::launch_fill(Phi, n, 0.0, done, s);
+    Error e{CPAPR_OK, ""};
+    if (first) e = cpapr::launch_reset_state(P->state, false, false, s);  // the violation slots
     if (e.code) return e;
-    const int lmax = P->params.lmax;
+    e = cpapr::launch_fill(Phi, n, 0.0, done, s);
+    if (e.code) return e;
+    const int lmax = first ? 1 : P->params.lmax;
     for (int l = 0; l < lmax; ++l) {
         e = cpapr::launch_phi(P, mode, B, fac, mixed, P->params.eps, Phi, done, s);
         if (e.code) return e;
@@ -242,6 +245,7 @@ Error enqueue_inner(cpapr_plan* P, int mode, double* B, const void* const* fac, 
         }
         if (e.code) return e;
     }
+    if (first) return cpapr::enqueue_inner_rows(P, mode, B, fac, Phi, P->params.lmax - 1, s);
     if (fused && lmax > 0) return cpapr::launch_kkt_fold(P->state, lmax - 1, mode, s);
     return {CPAPR_OK, ""};
 }
@@ -599,6 +603,7 @@ int cpapr_mu_inner(cpapr_plan* plan, int32_t mode, double* B, const double* cons
         e = read_state(plan, &h, s);
         if (e.code) return report(e);
         claim.queued = false;
+        if (claim.ok && runs_by_rows(plan)) plan->expect[mode] = (int)h.phi_evals;
         if (out) {
             out->outer_iters = 0;
             out->converged = h.done;
@@ -756,12 +761,11 @@ int cpapr_solve(cpapr_plan* plan, double* lambda, double* const* A, cpapr_stats*
                 if (e.code) return report(e);
             }
             if (tol > 0.0) {
-                int sweep = 0;
-                if (hipMemcpyAsync(&sweep, &P->state->sweep_updates, sizeof(int), hipMemcpyDeviceToHost, s) !=
-                        hipSuccess ||
-                    hipStreamSynchronize(s) != hipSuccess)
-                    return fail(CPAPR_EHIP, "reading the sweep status failed");
-                if (sweep == 0) {
+                HostState h{};
+                e = read_state(P, &h, s);
+                if (e.code) return report(e);
+                for (int n = 0; rows && n < N; ++n) P->expect[n] = std::min(h.mode_updates[n] + 1, P->params.lmax);
+                if (h.sweep_updates == 0) {
                     converged = 1;
                     break;
                 }

@@ -145,6 +145,7 @@ struct cpapr_batch {
     cpapr::RowsBatch rows[cpapr::kRowShapes] = {};
     int nrows = 0;
     bool row_stops = false;             // some slot has a KKT tolerance
+    int row_chunk = cpapr::kInnerChunk; // iterations per chunk at most
     int row_copies = 0;                 // FP32 factor copies to refresh first
     // The listed plans' row buffers: claimed by the first inner loop that uses
     // them, given back by the next commit or the end of the batch, after the loops
@@ -262,7 +263,7 @@ Error enqueue_rows(cpapr_batch* b, int lmax, hipStream_t s)
                                             b->copy_grid, s);
         if (e.code) return e;
     }
-    const int step = cpapr::inner_step(lmax);
+    const int step = cpapr::inner_step(lmax, b->row_chunk);
     for (int l0 = 0; l0 < lmax; l0 += step) {
         const int n = std::min(step, lmax - l0);
         for (int c = 0; c < cpapr::kRowShapes; ++c)
@@ -593,6 +594,7 @@ int cpapr_batch_commit(cpapr_batch* batch, void* stream)
         std::vector<int> grids;
         int nrows = 0;
         bool row_stops = false;
+        int row_chunk = cpapr::kInnerChunk;
         cpapr::RowsBatch rows[cpapr::kRowShapes] = {};
         char* w = b->ws;
         const size_t ib = cpapr::rows_batch_item_bytes();
@@ -629,6 +631,7 @@ int cpapr_batch_commit(cpapr_batch* batch, void* stream)
                 pa.push_back(pa.back() + again);
                 pm.push_back(pm.back() + members);
                 row_stops = row_stops || P->params.tol > 0.0;
+                row_chunk = std::min(row_chunk, cpapr::rows_batch_chunk(P, h.mode));
                 ++rb.n;
                 ++nrows;
             }
@@ -647,6 +650,7 @@ int cpapr_batch_commit(cpapr_batch* batch, void* stream)
             grids.push_back(nrows);
             grids.push_back(nrcopies > 0);
             grids.push_back(row_stops);
+            grids.push_back(row_chunk);
             if (hipMemcpyAsync(w + b->L.row_items, items.data(), items.size(), hipMemcpyHostToDevice, s) != hipSuccess ||
                 hipMemcpyAsync(w + b->L.row_prefix, prefix.data(), 4 * prefix.size(), hipMemcpyHostToDevice, s) !=
                     hipSuccess ||
@@ -664,6 +668,7 @@ int cpapr_batch_commit(cpapr_batch* batch, void* stream)
         b->nrows = by_rows ? nrows : 0;
         b->row_copies = nrcopies;
         b->row_stops = row_stops;
+        b->row_chunk = row_chunk;
         b->row_grids = grids;
         b->classes = classes;
         b->class_tiles.assign(cnt.begin(), cnt.end());

@@ -31,11 +31,11 @@ constexpr int kViolStride = 16;  // u64 words per slot (128 bytes)
 constexpr int kInnerChunk = 16;
 constexpr int kInnerSlots = 64;
 constexpr int kBatchInnerSlots = 8;  // per batch slot
-// Iterations per chunk of an inner loop of lmax: equal shares of at most kInnerChunk.
-inline int inner_step(int lmax)
+// Iterations per chunk of an inner loop of lmax: equal shares of at most `most`.
+inline int inner_step(int lmax, int most = kInnerChunk)
 {
-    const int chunks = (lmax + kInnerChunk - 1) / kInnerChunk;
-    return (lmax + chunks - 1) / chunks;
+    const int chunks = (lmax + most - 1) / most;
+    return chunks > 0 ? (lmax + chunks - 1) / chunks : 0;
 }
 constexpr int kRowClasses = 20;
 constexpr int kLenBuckets = 128;  // row lengths: four buckets per octave
@@ -53,12 +53,14 @@ struct DevResults {
     double ll;                          // log-likelihood result
     long long row_steps;                // row solves: steps summed over rows since the last reset
     long long trial_evals;              // row solves: line-search passes since the last reset
+    int mode_updates[CPAPR_MAX_MODES];  // MU updates in the last inner loop of each mode (row by row)
 };
 
 // Device-side state block of one inner loop (lives in the plan workspace).
 struct DevState : DevResults {
     int pq_all_done;                                        // row solves: no row of the current mode is active
     int pq_idle;                                            // row solves: no row is in a line search
+    int halt;                                               // the chunk's heavy rows need no further iteration
     unsigned long long viol[2][kViolSlots * kViolStride];   // per-parity slots, ordered bits of doubles >= 0
     unsigned long long iv[kInnerSlots][kInnerChunk];        // KKT violation per iteration of a chunk (ordered bits)
 };
@@ -157,8 +159,12 @@ struct RowState {
     int* split;            // temporaries of the hot / cold split: [chunks] + [long rows] + [modes]
     int cus;               // compute units of the device
     double* hot_tab;       // the hot rows of the current inner loop's factor, in their places
-    double* B0;            // [maxI x R] the chunk's start (tol > 0)
-    double* hist;          // [2 kInnerChunk x heavy rows x R] heavy rows' B and Phi per iteration (tol > 0)
+    // tol > 0: what a stop goes back to
+    double* B0;            // [maxI x R] light rows at the chunk's start
+    double* B1;            // [maxI x R] and before the chunk's last update
+    double* hist;          // heavy rows' B and Phi of their last iteration, then the team rows' of every iteration
+    int64_t hist_n;        // its doubles
+    unsigned int* finished;  // heavy rows that are done with an iteration; zero between launches
 };
 
 // Who runs inner loops in a plan's row buffers (RowState): a batch from its first
@@ -292,6 +298,7 @@ struct cpapr_plan {
     std::shared_ptr<cpapr::RowOwner> row_owner;
     bool exact32;                     // every value is exact in FP32
     int64_t team_wait;                // clock ticks (10 ns) a team member waits for its team to start
+    int expect[CPAPR_MAX_MODES];      // iterations the last inner loop of each mode computed before its stop (0: none ran)
     double* det_part;                 // deterministic mode: tile-end partial rows (nullptr: atomics)
     int32_t* det_rows;                // deterministic mode: their row ids
     int64_t det_tiles;                // tiles the buffers hold (launches with more tiles are refused)
@@ -334,6 +341,8 @@ int rows_batch_shape(const cpapr_plan* P, int mode);
 size_t rows_batch_item_bytes();
 // Device-side descriptor of one slot (written to `out`), its workgroups without
 // and with the rows restored after a stop, and its team members.
+// Iterations a chunk of such a slot may take (its team rows' history).
+int rows_batch_chunk(const cpapr_plan* P, int mode);
 void rows_batch_item(const cpapr_plan* P, int mode, const double* B, const void* const* fac, double* Phi, int slot,
                      const int32_t* done, int32_t* rerun, unsigned long long* iv, void* out, int* light, int* again,
                      int* members);
@@ -388,10 +397,13 @@ void rows_finish(cpapr_plan* P, int mode, const int* meta);
 // every mode's rows_finish). Bytes bound to `base` unless P is nullptr.
 size_t rows_hot_bind(cpapr_plan* P, char* base, int N, int64_t nnz, const int64_t* dims, int R);
 Error rows_hot_build(cpapr_plan* P, hipStream_t s);
-// One MU inner loop of `mode` (lmax iterations or the KKT stop); B in/out, Phi
-// receives the last Phi. State and counters as the Phi / KKT / update launches
-// leave them.
-Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, hipStream_t s);
+// The (last) lmax iterations of an MU inner loop of `mode`, or to the KKT stop; B
+// in/out, Phi receives the last Phi. State and counters as the Phi / KKT / update
+// launches leave them.
+Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, int lmax,
+                         hipStream_t s);
+// Whether the loop's first iteration runs by the Phi / KKT / update launches.
+bool rows_first_alone(const cpapr_plan* P, int mode);
 // Nonzeros per chunk of a long row.
 int heavy_chunk(int64_t nnz);
 // The four-trial line-search sums of launch_delta4, row by row (R >= 4, the

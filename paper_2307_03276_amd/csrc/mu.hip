@@ -48,6 +48,7 @@ __global__ __launch_bounds__(kBlock) void reset_state_kernel(DevState* st, int n
     for (int i = threadIdx.x; i < kInnerChunk * kInnerSlots; i += kBlock) (&st->iv[0][0])[i] = 0ull;
     if (threadIdx.x == 0) {
         st->done = 0;
+        st->halt = 0;
         st->rerun = -1;
         st->updates = 0;
         if (new_sweep) st->sweep_updates = 0;
@@ -202,6 +203,7 @@ __global__ __launch_bounds__(kBlock) void shift_scale_kernel(double* __restrict_
 {
     if (st != nullptr && blockIdx.x == 0 && threadIdx.x == 0) {  // a new inner loop begins
         st->done = 0;
+        st->halt = 0;
         st->rerun = -1;
         st->updates = 0;
         if (new_sweep) st->sweep_updates = 0;

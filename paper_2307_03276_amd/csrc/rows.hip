@@ -7,10 +7,14 @@
 // (every iteration again); here each row is gathered once per inner loop.
 //
 // The only coupling between rows is the KKT stop (one violation for the whole
-// mode). With tol > 0 the rows run a chunk of iterations speculatively and
-// record each iteration's violation; decide_kernel finds the first iteration
-// below tol, and if there is one the rows are run again from their saved start
-// to exactly that iteration (all on the device, no host round trip).
+// mode). With tol > 0 the light and team rows run a chunk of iterations
+// speculatively and record each iteration's violation; the heavy rows, for which
+// every iteration costs the gathers again, follow one iteration at a time and
+// halt at the first one whose violation over all rows is below tol. decide_kernel
+// finds that iteration, and if there is one the others go back to it: by a copy
+// if it was the chunk's last, else the light rows run again from their saved
+// start and the team rows are taken from their history (all on the device, no
+// host round trip).
 //
 // Rows by length (a plan-time counting sort of the rows into classes):
 //  * up to K nonzeros: one group of G lanes per row (each lane holds C rank
@@ -168,6 +172,7 @@ struct ResArgs {
     const void* fac[kMaxOther];
     double* B;
     double* B0;     // saved start of the chunk (tol > 0), else nullptr
+    double* B1;     // b before the chunk's last update (tol > 0)
     double* Phi;
     const int32_t* done;       // the inner loop has stopped: no work
     const int32_t* rerun;      // iteration to run again to (-1: none)
@@ -176,16 +181,16 @@ struct ResArgs {
     int slot;                  // batch slot
     int teams;                 // team rows that run as teams
     double tol;
-    double* hist;        // heavy rows: B and Phi per iteration (restored on a stop)
+    double* heavy_hist;  // heavy rows: B, then Phi of their last iteration (restored on a stop)
+    double* hist;        // team rows: B and Phi per iteration
     int64_t nnz;
-    int64_t hist_stride;
     double eps;
     int R;
     int NM1;
     int n_it;       // iterations (rerun: read from the state)
     int each;       // 1: record every iteration's violation, 0: the last one's
     int nentries;
-    int heavy0, nheavy;  // positions of the heavy rows in `order` (team rows last)
+    int heavy0, nheavy;  // positions of the heavy rows in `order`, the rows that run as teams last
     int light_blocks;
     // team rows: workgroups (members) of one row that meet after every iteration
     int team_blocks;             // members of all teams
@@ -492,10 +497,15 @@ __device__ __forceinline__ void resident_rows(const ResArgs& a, int at, bool rer
 #pragma unroll
                 for (int c = 0; c < C; ++c)
                     if (own[c]) {
-                        double* hist = a.hist + (int64_t)2 * l * a.hist_stride + (int64_t)(a.team0 + h) * R + colbase + c;
+                        const int64_t n = (int64_t)a.teams * R;
+                        double* hist = a.hist + 2 * l * n + (int64_t)h * R + colbase + c;
                         hist[0] = b[c];
-                        hist[a.hist_stride] = acc[c];
+                        hist[n] = acc[c];
                     }
+            if (!TEAM && a.B1 != nullptr && lead && n_it > 1 && l + 1 == n_it)
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    if (own[c]) a.B1[(int64_t)row * R + colbase + c] = b[c];
         }
         if (!rerun || l + 1 < n_it)
 #pragma unroll
@@ -538,12 +548,38 @@ __device__ __forceinline__ bool team_turn(int b, int members, int lights, int* l
 // Heavy and team rows from their history after a stop at iteration l.
 __device__ __forceinline__ void restore_rows(const ResArgs& a, int l, int at, int blocks)
 {
-    for (int64_t i = (int64_t)at * kResBlock + threadIdx.x; i < (int64_t)a.nheavy * a.R; i += (int64_t)blocks * kResBlock) {
-        const int64_t h = i / a.R, c = i % a.R;
-        const int64_t e = (int64_t)a.order[a.heavy0 + h] * a.R + c;
-        a.B[e] = a.hist[(2 * l) * a.hist_stride + i];
-        a.Phi[e] = a.hist[(2 * l + 1) * a.hist_stride + i];
+    const int64_t nh = (int64_t)(a.nheavy - a.teams) * a.R, nt = (int64_t)a.teams * a.R;
+    for (int64_t i = (int64_t)at * kResBlock + threadIdx.x; i < nh + nt; i += (int64_t)blocks * kResBlock) {
+        const int64_t e = (int64_t)a.order[a.heavy0 + i / a.R] * a.R + i % a.R;
+        const double* hist = i < nh ? a.heavy_hist + i : a.hist + 2 * l * nt + (i - nh);
+        a.B[e] = hist[0];
+        a.Phi[e] = hist[i < nh ? nh : nt];
     }
+}
+
+// The light rows back to before the chunk's last update, after a stop there
+// (Phi is that iteration's already).
+__device__ __forceinline__ void restore_last(const ResArgs& a, int n_it, int at)
+{
+    const double* src = n_it == 1 ? a.B0 : a.B1;
+    for (int64_t i = (int64_t)at * kResBlock + threadIdx.x; i < (int64_t)a.heavy0 * a.R;
+         i += (int64_t)a.light_blocks * kResBlock) {
+        const int64_t e = (int64_t)a.order[i / a.R] * a.R + i % a.R;
+        a.B[e] = src[e];
+    }
+}
+
+// After a stop at iteration l of n_it: block `at` of the light rows' or, after
+// them, of the others'.
+template <int G, int C, int K, bool MIXED>
+__device__ __forceinline__ void back_to(const ResArgs& a, int l, int n_it, int at, int blocks)
+{
+    if (at >= a.light_blocks)
+        restore_rows(a, l, at - a.light_blocks, blocks - a.light_blocks);
+    else if (l + 1 == n_it)
+        restore_last(a, n_it, at);
+    else
+        resident_rows<G, C, K, MIXED, false>(a, at, true, l + 1);
 }
 
 // Two waves per SIMD: the pi rows take most of a lane's 256 registers.
@@ -558,17 +594,13 @@ __global__ __launch_bounds__(kResBlock) __attribute__((amdgpu_waves_per_eu(2, 2)
         resident_rows<G, C, K, MIXED, false>(a, light, false, a.n_it);
 }
 
-// After a stop at iteration *rerun of the chunk: the light rows again from
-// their saved start to that iteration, the others from their history.
+// After a stop at iteration *rerun of the chunk: all rows back to it.
 template <int G, int C, int K, bool MIXED>
 __global__ __launch_bounds__(kResBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void rerun_kernel(ResArgs a)
 {
     const int l = *a.rerun;
     if (l < 0) return;
-    if ((int)blockIdx.x < a.light_blocks)
-        resident_rows<G, C, K, MIXED, false>(a, (int)blockIdx.x, true, l + 1);
-    else
-        restore_rows(a, l, (int)blockIdx.x - a.light_blocks, (int)gridDim.x - a.light_blocks);
+    back_to<G, C, K, MIXED>(a, l, a.n_it, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // Item of `n` (prefix [n + 1] of counts) that holds place `at`: one load per
@@ -604,16 +636,40 @@ __global__ __launch_bounds__(kResBlock) __attribute__((amdgpu_waves_per_eu(2, 2)
 
 template <int G, int C, int K, bool MIXED>
 __global__ __launch_bounds__(kResBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void batch_rerun_kernel(
-    const ResArgs* __restrict__ items, const int32_t* __restrict__ blocks, int n)
+    const ResArgs* __restrict__ items, const int32_t* __restrict__ blocks, int n, int n_it)
 {
     const int i = item_at(blocks, n, (int)blockIdx.x);
     const int l = *items[i].rerun;
     if (l < 0) return;
-    const int at = (int)blockIdx.x - blocks[i], light = items[i].light_blocks;
-    if (at < light)
-        resident_rows<G, C, K, MIXED, false>(items[i], at, true, l + 1);
-    else
-        restore_rows(items[i], l, at - light, blocks[i + 1] - blocks[i] - light);
+    back_to<G, C, K, MIXED>(items[i], l, n_it, (int)blockIdx.x - blocks[i], blocks[i + 1] - blocks[i]);
+}
+
+// A heavy row has added its violation of iteration l to the slots (one wave; lane
+// 0 did): the last of the nrows rows knows the iteration's violation over all
+// rows of the mode and halts the chunk's further heavy iterations if it is below
+// tol. The counters are spread (one row after the other on a single one would
+// take longer than the rows' sums) and are zero again afterwards.
+__device__ __forceinline__ void row_finished(DevState* st, unsigned int* finished, int h, int nrows, int l, double tol)
+{
+    static_assert(kInnerSlots == 64, "a slot per lane");
+    int last = 0;
+    if ((threadIdx.x & 63) == 0) {
+        __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const int slot = h % kInnerSlots;
+        unsigned int* c = finished + (1 + slot) * kCountStride;
+        const unsigned int n = (unsigned int)((nrows - slot + kInnerSlots - 1) / kInnerSlots);
+        if (__hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == n) {
+            __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            last = __hip_atomic_fetch_add(finished, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
+                   (unsigned int)min(nrows, kInnerSlots);
+            if (last) __hip_atomic_store(finished, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    if (!__builtin_amdgcn_readfirstlane(last)) return;
+    const double v = wave_max(__longlong_as_double((long long)__hip_atomic_load(
+        &st->iv[threadIdx.x & 63][l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
+    if ((threadIdx.x & 63) == 0 && v < tol)
+        __hip_atomic_store(&st->halt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 struct HeavyArgs {
@@ -629,10 +685,11 @@ struct HeavyArgs {
     double* partial;             // [chunks x R]
     unsigned int* ticket;        // [nheavy], zero between launches
     DevState* st;
-    double* hist;                // tol > 0: B, then (hist_stride on) Phi of this iteration, else nullptr
-    int64_t hist_stride;
+    double* hist;                // tol > 0: B, then Phi of this iteration, else nullptr
+    unsigned int* finished;      // counters of row_finished
     int64_t nnz;
-    double eps;
+    double eps, tol;
+    int nrows;                   // heavy rows
     int R;
     int NM1;
     int chunk;
@@ -651,7 +708,7 @@ __global__ __launch_bounds__(kBlock) void heavy_kernel(HeavyArgs a)
     __shared__ double red[W][G * C];
     __shared__ double fin[kBlock];
     __shared__ int last;
-    if (a.st->done) return;
+    if (a.st->done || a.st->halt) return;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int gl = lane % G, g = lane / G;
     const int R = a.R;
@@ -836,7 +893,7 @@ __global__ __launch_bounds__(kBlock) void heavy_kernel(HeavyArgs a)
         a.Phi[e] = phi;
         if (a.hist != nullptr) {
             a.hist[(int64_t)h * R + t] = bb;
-            a.hist[a.hist_stride + (int64_t)h * R + t] = phi;
+            a.hist[(int64_t)(a.nrows + h) * R + t] = phi;
         }
         a.B[e] = bb * phi;
     }
@@ -844,6 +901,7 @@ __global__ __launch_bounds__(kBlock) void heavy_kernel(HeavyArgs a)
     if (a.l >= 0 && t < 64) {
         viol = wave_max(viol);
         if (t == 0) atomicMax(&a.st->iv[h % kInnerSlots][a.l], (unsigned long long)__double_as_longlong(viol));
+        if (a.hist != nullptr) row_finished(a.st, a.finished, h, a.nrows, a.l, a.tol);
     }
 }
 
@@ -903,7 +961,7 @@ __global__ __launch_bounds__(kHotThreads) void hot_kernel(HotArgs a)
     constexpr uint32_t STEP = 4 * (64 / G);
     extern __shared__ double2 dyn[];
     const L* tab = (const L*)dyn;
-    if (a.st->done) return;
+    if (a.st->done || a.st->halt) return;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int gl = lane % G, g = lane / G;
     const int R = a.R;
@@ -1033,7 +1091,9 @@ struct HotStep {
     double* Phi;
     DevState* st;
     double* hist;
-    int64_t hist_stride;
+    unsigned int* finished;
+    double tol;
+    int nrows;
     int R;
     int l;
 };
@@ -1043,7 +1103,7 @@ struct HotStep {
 __global__ __launch_bounds__(512) void hot_step_kernel(HotStep a)
 {
     __shared__ double sum[8][64];
-    if (a.st->done) return;
+    if (a.st->done || a.st->halt) return;
     const int t = threadIdx.x, lane = t & 63, R = a.R, h = blockIdx.x;
     const int e0 = a.entry_begin[h], ne = a.entry_begin[h + 1] - e0;
     int rp = 1;
@@ -1077,13 +1137,14 @@ __global__ __launch_bounds__(512) void hot_step_kernel(HotStep a)
         a.Phi[x] = phi;
         if (a.hist != nullptr) {
             a.hist[(int64_t)h * R + t] = b;
-            a.hist[a.hist_stride + (int64_t)h * R + t] = phi;
+            a.hist[(int64_t)(a.nrows + h) * R + t] = phi;
         }
         a.B[x] = b * phi;
     }
     if (a.l >= 0) {
         viol = wave_max(viol);
         if (t == 0) atomicMax(&a.st->iv[h % kInnerSlots][a.l], (unsigned long long)__double_as_longlong(viol));
+        if (a.hist != nullptr) row_finished(a.st, a.finished, h, a.nrows, a.l, a.tol);
     }
 }
 
@@ -1121,9 +1182,15 @@ __global__ __launch_bounds__(kBlock) void decide_kernel(DevState* st, int mode, 
 {
     const int t = threadIdx.x;
     for (int i = t; i < teams; i += kBlock) team_count[i * kCountStride] = 0u;
-    if (t == 0) *team_ticket = 0u;
+    if (t == 0) {
+        *team_ticket = 0u;
+        st->halt = 0;
+    }
     if (st->done) {
-        if (t == 0) st->rerun = -1;
+        if (t == 0) {
+            st->rerun = -1;
+            st->mode_updates[mode] = st->updates;
+        }
         return;
     }
     double viol;
@@ -1137,6 +1204,7 @@ __global__ __launch_bounds__(kBlock) void decide_kernel(DevState* st, int mode, 
     st->sweep_updates += upd;
     st->total_updates += upd;
     st->phi_evals += stop >= 0 ? stop + 1 : n;
+    st->mode_updates[mode] = st->updates;
 }
 
 // A workgroup per slot of a batch.
@@ -1704,6 +1772,21 @@ bool hot_supported(int N, int64_t nnz, int R)
 }
 int64_t max_members(int64_t nnz, const Shape& s) { return nnz / class_cap(class_shape(s)) + max_long(nnz, s); }
 
+// Doubles of the long rows' history (tol > 0). A single loop keeps one iteration of
+// its heavy rows, or, where it runs teams, kInnerChunk iterations of theirs (at
+// most kTeamMembers / 2 rows: a team has two members or more) and one of the rows
+// too long for a team. In a batch all long rows are teams: kInnerChunk iterations
+// of theirs while that is no more than a double per nonzero, else the batch takes
+// shorter chunks (R = 64, every row just longer than a workgroup's registers:
+// one iteration takes 3.2 bytes per nonzero).
+int64_t hist_doubles(int64_t nnz, const Shape& s, int R)
+{
+    const int64_t nl = max_long(nnz, s), row = 2 * (int64_t)R;
+    const int64_t longest = nnz / ((int64_t)kTeamMax * class_cap(class_shape(s)) + 1);
+    const int64_t single = std::max(nl * row, (longest + std::min<int64_t>(nl, kTeamMembers / 2) * kInnerChunk) * row);
+    return std::max(single, std::min(nl * row * kInnerChunk, nnz));
+}
+
 }  // namespace
 
 // Up to 2^30 nonzeros: positions are 32-bit with room for a step past the end,
@@ -1750,13 +1833,16 @@ size_t rows_state_bind(RowState* r, char* base, int64_t nnz, int64_t maxI, int R
     RowState o{};
     o.partial = (double*)take(max_partials(nnz, s) * R * 8);
     o.team_part = (double*)take(3 * max_members(nnz, s) * R * 8);
-    o.tickets = (1 + 2 * nl) * kCountStride;
+    o.tickets = (1 + 2 * nl + 1 + kInnerSlots) * kCountStride;
     o.ticket = (unsigned int*)take(o.tickets * 4);
+    o.finished = o.ticket + (1 + 2 * nl) * kCountStride;
     o.split = (int*)take((max_chunks(nnz, s) + nl + CPAPR_MAX_MODES) * 4);
     o.hot_tab = (double*)take(kHotLds);
     if (stops) {
         o.B0 = (double*)take(maxI * R * 8);
-        o.hist = (double*)take(2 * kInnerChunk * nl * R * 8);
+        o.B1 = (double*)take(maxI * R * 8);
+        o.hist_n = hist_doubles(nnz, s, R);
+        o.hist = (double*)take(o.hist_n * 8);
     }
     if (r != nullptr) *r = o;
     return at;
@@ -2033,9 +2119,10 @@ void res_args(const cpapr_plan* P, int mode, double* B, const void* const* fac, 
     a.team_ticket = P->rs.ticket;
     a.team_count = P->rs.ticket + kCountStride;
     a.team_wait = P->team_wait;
-    a.hist = P->rs.hist;
-    a.hist_stride = (int64_t)a.nheavy * P->R;
+    a.heavy_hist = P->rs.hist;
+    a.hist = P->rs.hist + 2 * (int64_t)(a.nheavy - a.teams) * P->R;
     a.B0 = a.each ? P->rs.B0 : nullptr;
+    a.B1 = a.each ? P->rs.B1 : nullptr;
     *out = a;
 }
 
@@ -2543,6 +2630,13 @@ int rows_batch_shape(const cpapr_plan* P, int mode)
     return 2 * (P->R <= 16 ? (P->R - 1) / 4 : P->R <= 32 ? 4 + (P->R - 17) / 8 : 6 + (P->R - 33) / 16) + mixed;
 }
 
+int rows_batch_chunk(const cpapr_plan* P, int mode)
+{
+    const int64_t per = 2 * (int64_t)P->mode[mode].rp.nlong * P->R;
+    if (!(P->params.tol > 0.0) || per == 0) return kInnerChunk;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(kInnerChunk, P->rs.hist_n / per));
+}
+
 size_t rows_batch_item_bytes() { return sizeof(ResArgs); }
 
 void rows_batch_item(const cpapr_plan* P, int mode, const double* B, const void* const* fac, double* Phi, int slot,
@@ -2572,9 +2666,9 @@ Error launch_rows_batch(int shape, const RowsBatch& b, int n_it, bool again, hip
         const unsigned grid = (unsigned)(again ? b.nagain : b.nlight + b.nmembers);
         if (grid == 0) return {CPAPR_OK, ""};
         if (again && shape % 2)
-            batch_rerun_kernel<GG, CC, KK, true><<<grid, kResBlock, 0, s>>>(items, b.again, b.n);
+            batch_rerun_kernel<GG, CC, KK, true><<<grid, kResBlock, 0, s>>>(items, b.again, b.n, n_it);
         else if (again)
-            batch_rerun_kernel<GG, CC, KK, false><<<grid, kResBlock, 0, s>>>(items, b.again, b.n);
+            batch_rerun_kernel<GG, CC, KK, false><<<grid, kResBlock, 0, s>>>(items, b.again, b.n, n_it);
         else if (shape % 2)
             batch_resident_kernel<GG, CC, KK, true><<<grid, kResBlock, 0, s>>>(items, b.light, b.members, b.n, b.nlight,
                                                                               b.nmembers, b.ticket, n_it);
@@ -2594,7 +2688,33 @@ Error launch_rows_batch_decide(const void* items, int n, BatchState st, int32_t*
     return {CPAPR_OK, ""};
 }
 
-Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, hipStream_t s)
+// What light rows compute past a stop is lost, and after a stop before the chunk's
+// last iteration they gather again. From 2^20 nonzeros on, where that outweighs a
+// launch or two, the first chunk is as long as the mode's last loop of this plan ran
+// (the modes of a solve stop early in sweep after sweep once they have
+// converged). Only the schedule depends on it, not the results.
+// 8M uniform three-way nonzeros, R = 32, lmax = 10, stops at the first / second /
+// sixth iteration: one chunk of all 1393 / 1395 / 1558 us, the Phi launches alone
+// 443 / 659 / 1544, this 291 / 553 / 778; without a stop 1010 / 2427 / 1026. 20M
+// nonzeros, Zipf rows, R = 16, stop at the first: 1905 / 471 / 381 (heavy rows ran
+// all ten iterations).
+static bool schedule_by_last(const cpapr_plan* P)
+{
+    return P->params.tol > 0.0 && P->nnz >= (int64_t(1) << 20);
+}
+
+// A loop that is expected to stop at its first iteration, or of which nothing is
+// known yet, takes that one by the Phi launches, as one iteration alone does.
+bool rows_first_alone(const cpapr_plan* P, int mode) { return schedule_by_last(P) && P->expect[mode] <= 1; }
+
+static int first_chunk(const cpapr_plan* P, int mode, int lmax)
+{
+    const int e = P->expect[mode];
+    return !schedule_by_last(P) || e <= 1 || e >= lmax ? inner_step(lmax) : std::min(e, kInnerChunk);
+}
+
+Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, int lmax,
+                         hipStream_t s)
 {
     Shape sh;
     if (!row_shape(P->R, &sh)) return {CPAPR_EUNSUPPORTED, "no resident-row kernel for this rank"};
@@ -2639,19 +2759,41 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
     h.partial = P->rs.partial;
     h.ticket = P->rs.ticket + (1 + r.count[nlight + 1]) * kCountStride;
     h.st = P->state;
-    h.hist_stride = a.hist_stride;
+    h.hist = each ? a.heavy_hist : nullptr;
+    h.finished = P->rs.finished;
+    h.nrows = a.nheavy - a.teams;
+    h.tol = P->params.tol;
     h.nnz = P->nnz;
     h.eps = P->params.eps;
     h.R = P->R;
     h.NM1 = P->N - 1;
     h.chunk = heavy_chunk(P->nnz);
 
-    const int lmax = P->params.lmax;
-    const int step = each ? inner_step(lmax) : lmax;
-    prof_begin(mode, s);  // one record per inner loop
-    for (int l0 = 0; l0 < lmax; l0 += step) {
-        const int n = std::min(step, lmax - l0);
+    prof_begin(mode, s);  // one record for all iterations
+    int n = each ? first_chunk(P, mode, lmax) : lmax;
+    for (int l0 = 0; l0 < lmax; l0 += n, n = inner_step(lmax - l0)) {
         Error e{CPAPR_OK, ""};
+        a.n_it = n;
+        auto light = [&](bool rerun) {
+            return by_row_shape(sh, [&](auto G, auto C, auto K) -> Error {
+                constexpr int GG = decltype(G)::value, CC = decltype(C)::value, KK = decltype(K)::value;
+                if (rerun) {
+                    const dim3 grid((unsigned)(blocks + cdiv((int64_t)a.nheavy * P->R, kResBlock)));
+                    if (mixed)
+                        rerun_kernel<GG, CC, KK, true><<<grid, kResBlock, 0, s>>>(a);
+                    else
+                        rerun_kernel<GG, CC, KK, false><<<grid, kResBlock, 0, s>>>(a);
+                } else if (mixed) {
+                    resident_kernel<GG, CC, KK, true><<<(unsigned)(blocks + a.team_blocks), kResBlock, 0, s>>>(a);
+                } else {
+                    resident_kernel<GG, CC, KK, false><<<(unsigned)(blocks + a.team_blocks), kResBlock, 0, s>>>(a);
+                }
+                CPAPR_LAUNCHED();
+                return {CPAPR_OK, ""};
+            });
+        };
+        if (blocks + a.team_blocks > 0) e = light(false);
+        if (e.code) return e;
         if (r.nchunks > 0 && r.hot >= 0) {
             HotArgs k{};
             k.s_lead = r.s_lead;
@@ -2673,7 +2815,7 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
             k.st = P->state;
             k.eps = h.eps;
             k.R = P->R;
-            HotStep hs{r.entry_begin, h.rows, h.partial, B, Phi, P->state, nullptr, h.hist_stride, P->R, -1};
+            HotStep hs{r.entry_begin, h.rows, h.partial, B, Phi, P->state, h.hist, h.finished, h.tol, h.nrows, P->R, -1};
             const size_t lds = (size_t)k.tab_vecs * 16;
             if (l0 == 0) {
                 const int32_t* rows = P->mode[r.hot].rp.hot_rows;
@@ -2704,7 +2846,6 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
                 e = mixed ? launch(std::true_type{}) : launch(std::false_type{});
                 if (e.code) return e;
                 hs.l = each ? l : l + 1 == n ? 0 : -1;
-                hs.hist = each ? P->rs.hist + (int64_t)2 * l * h.hist_stride : nullptr;
                 hot_step_kernel<<<r.nlong, 512, 0, s>>>(hs);
                 CPAPR_LAUNCHED();
             }
@@ -2712,7 +2853,6 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
             const Shape hs = heavy_shape(P->R, mixed);
             for (int l = 0; l < n; ++l) {
                 h.l = each ? l : l + 1 == n ? 0 : -1;
-                h.hist = each ? P->rs.hist + (int64_t)2 * l * h.hist_stride : nullptr;
                 auto launch = [&](auto M) -> Error {
                     constexpr bool MX = decltype(M)::value;
                     return by_heavy_shape<MX>(hs, [&](auto G, auto C) -> Error {
@@ -2732,27 +2872,6 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
                 if (e.code) return e;
             }
         }
-        a.n_it = n;
-        auto light = [&](bool rerun) {
-            return by_row_shape(sh, [&](auto G, auto C, auto K) -> Error {
-                constexpr int GG = decltype(G)::value, CC = decltype(C)::value, KK = decltype(K)::value;
-                if (rerun) {
-                    const dim3 grid((unsigned)(blocks + cdiv((int64_t)a.nheavy * P->R, kResBlock)));
-                    if (mixed)
-                        rerun_kernel<GG, CC, KK, true><<<grid, kResBlock, 0, s>>>(a);
-                    else
-                        rerun_kernel<GG, CC, KK, false><<<grid, kResBlock, 0, s>>>(a);
-                } else if (mixed) {
-                    resident_kernel<GG, CC, KK, true><<<(unsigned)(blocks + a.team_blocks), kResBlock, 0, s>>>(a);
-                } else {
-                    resident_kernel<GG, CC, KK, false><<<(unsigned)(blocks + a.team_blocks), kResBlock, 0, s>>>(a);
-                }
-                CPAPR_LAUNCHED();
-                return {CPAPR_OK, ""};
-            });
-        };
-        if (blocks + a.team_blocks > 0) e = light(false);
-        if (e.code) return e;
         decide_kernel<<<1, kBlock, 0, s>>>(P->state, mode, n, each ? 1 : 0, P->params.tol, a.team_ticket,
                                           a.team_count, a.teams);
         CPAPR_LAUNCHED();

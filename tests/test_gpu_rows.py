@@ -320,3 +320,61 @@ def test_deterministic_plans_repeat_bit_for_bit():
     assert all(torch.equal(x, y) for x, y in zip(first, loop()))
     b.close()
     P.close()
+
+
+@pytest.mark.parametrize("R,others,precision", [(16, (900, 700), cpapr.CPAPR_FP64), (24, (40, 30, 20, 10), cpapr.CPAPR_MIXED),
+                                                (10, (700, 500, 90), cpapr.CPAPR_FP64)])
+def test_stops_of_large_tensors(R, others, precision, lmax=5):
+    """From 2^20 nonzeros on the first chunk is as long as the mode's last loop,
+    and heavy rows halt at the stop: stops before, at and after the end of a
+    chunk, for a new plan and for one whose last loop stopped elsewhere."""
+    rng = np.random.default_rng(2)
+    lengths = np.concatenate([[420_000, 160_000], rng.integers(1_500, 12_000, 90), EDGES])
+    X = _tensor(lengths, others, 120 + R, skew=1.1)
+    M = synth.random_model(7, X.dims, R)
+    Bh, A = M.factors[0] * M.lam, [dev(a) for a in M.factors]
+    steps = [Bh]
+    for l in range(1, lmax + 1):
+        steps.append(oracle.mu_inner(X, 0, Bh, M.factors, lmax=l, tau=0.0)[0])
+    hist = oracle.mu_inner(X, 0, Bh, M.factors, lmax=lmax, tau=0.0)[2]
+    low = np.minimum.accumulate(hist)
+    t, el = (TOL64, True) if precision == cpapr.CPAPR_FP64 else (TOL32, False)
+    for l in range(lmax + 1):
+        tol = float(low[l]) * (1 + 1e-4) if l < lmax else float(low[-1]) * 0.5
+        stop = next((k for k in range(lmax) if hist[k] < tol), lmax)
+        P = cpapr.Plan.from_tensor(X, R, lmax=lmax, tol=tol, precision=precision)
+        for turn in range(3):
+            if turn == 2 and stop > 0:  # the last loop ended earlier: one that starts near its end
+                B = dev(steps[stop])
+                P.mu_inner(0, B, A)
+            B = dev(Bh)
+            phi, st = P.mu_inner(0, B, A)
+            assert st["inner_iters"] == stop and st["phi_evals"] == min(stop + 1, lmax)
+            assert_parity(host(B), steps[stop], t, f"B, stop at {stop}, turn {turn}", elementwise=el)
+        P.close()
+
+
+def test_batch_of_rows_just_longer_than_a_workgroups_registers():
+    """Such rows' history bounds the iterations of a batch's chunks (R = 64: 6 of
+    the 16); a stop in each chunk, and one slot with a fixed schedule."""
+    X = _tensor([330] * 300, (37, 29), 17)
+    M = synth.random_model(17, X.dims, 64)
+    Bh, A = M.factors[0] * M.lam, [dev(a) for a in M.factors]
+    hist = oracle.mu_inner(X, 0, Bh, M.factors, lmax=20, tau=0.0)[2]
+    low = np.minimum.accumulate(hist)
+    slots = []
+    for l in (0, 3, 5, 6, 9, 15, 19, None):
+        tol = 0.0 if l is None else float(low[l]) * (1 + 1e-6)
+        slots.append((cpapr.Plan.from_tensor(X, 64, lmax=20, tol=tol), tol, dev(Bh), dev(np.zeros_like(Bh))))
+    b = cpapr.Batch(len(slots), sum(P.tiles() for P, *_ in slots) + 1)
+    for i, (P, _, B, Phi) in enumerate(slots):
+        b.set(i, P, 0, B, A, Phi)
+    b.commit()
+    b.inner(20)
+    _, upd, _ = b.status()
+    for i, (P, tol, B, Phi) in enumerate(slots):
+        Bo, Po, _, nup = oracle.mu_inner(X, 0, Bh, M.factors, lmax=20, tau=tol)
+        assert upd[i] == nup
+        assert_parity(host(B), Bo, TOL64, f"B slot {i}")
+        assert_parity(host(Phi), Po, TOL64, f"Phi slot {i}")
+    b.close()
