@@ -472,7 +472,7 @@ int cpapr_plan_create(const cpapr_coo* X, int32_t R, const cpapr_params* p, void
         e = cpapr::launch_reset_state(P->state, true, true, s);
         if (!e.code && P->by_rows)  // tickets start at zero (two per word of the fill)
             e = cpapr::launch_fill((double*)P->rs.ticket, (P->rs.tickets + 1) / 2, 0.0, nullptr, s);
-        if (!e.code && P->by_rows) e = cpapr::rows_hot_build(P, s);
+        if (!e.code && P->by_rows) e = cpapr::rows_hot_choose(P);
         if (e.code) {
             delete P;
             return report(e);

@@ -135,8 +135,10 @@ struct RowPlan {
     int32_t nnz_in[kLenBuckets];    // their nonzeros
     // Long rows' nonzeros again, each row's split by whether a second mode's
     // coordinate is one of its hot rows (in order inside each part).
-    int32_t lead, hot, third;       // other modes: ordered by / hot rows kept in LDS / remaining one (-1); hot < 0: not built
-    int32_t nhot;                   // hot rows
+    int32_t lead, hot, third;       // other modes: ordered by / hot rows kept in LDS / remaining one (-1); hot < 0: no split
+    bool split_made;                // the first inner loop of the mode makes the split
+    int32_t bucket, nhot;           // this mode's own hot rows: its rows in length buckets >= bucket, their number
+    bool hot_made;                  // and their places
     uint32_t* s_lead;               // [nnz] offsets into the lead mode's factor
     uint16_t* s_slot;               // [nnz] place among the hot rows (hot part)
     uint32_t* s_hot;                // [nnz] offsets into the hot mode's factor (cold part)
@@ -393,10 +395,11 @@ size_t rows_state_bind(RowState* r, char* base, int64_t nnz, int64_t maxI, int R
 // the host part from meta's host copy.
 Error rows_build(const cpapr_plan* P, int mode, int* meta, hipStream_t s);
 void rows_finish(cpapr_plan* P, int mode, const int* meta);
-// Long rows' nonzeros split by a second mode's hot rows, where that pays (after
-// every mode's rows_finish). Bytes bound to `base` unless P is nullptr.
+// Long rows' nonzeros split by a second mode's hot rows, where that pays. Bytes
+// bound to `base` unless P is nullptr.
 size_t rows_hot_bind(cpapr_plan* P, char* base, int N, int64_t nnz, const int64_t* dims, int R);
-Error rows_hot_build(cpapr_plan* P, hipStream_t s);
+// The modes' choices (after every mode's rows_finish; host only).
+Error rows_hot_choose(cpapr_plan* P);
 // The (last) lmax iterations of an MU inner loop of `mode`, or to the KKT stop; B
 // in/out, Phi receives the last Phi. State and counters as the Phi / KKT / update
 // launches leave them.

@@ -1889,36 +1889,28 @@ size_t rows_hot_bind(cpapr_plan* P, char* base, int N, int64_t nnz, const int64_
     return at;
 }
 
-Error rows_hot_build(cpapr_plan* P, hipStream_t s)
+Error rows_hot_choose(cpapr_plan* P)
 {
     int dev = 0;
     CPAPR_HIP(hipGetDevice(&dev));
     CPAPR_HIP(hipDeviceGetAttribute(&P->rs.cus, hipDeviceAttributeMultiprocessorCount, dev));
     if (P->params.method != CPAPR_METHOD_MU || !hot_supported(P->N, P->nnz, P->R)) return {CPAPR_OK, ""};
-    Shape sh;
-    row_shape(P->R, &sh);
     const int word = P->params.precision == CPAPR_MIXED ? 4 : 8;
     const int fit = std::min(kHotLds / (P->R * word), kMaxHot);
-    const int ncls = class_count(class_shape(sh));
     // every mode's hot rows: as many of its longest length buckets as fit
-    int bucket[CPAPR_MAX_MODES], nhot[CPAPR_MAX_MODES];
     double share[CPAPR_MAX_MODES];
-    bool made[CPAPR_MAX_MODES] = {};
     for (int m = 0; m < P->N; ++m) {
-        const RowPlan& r = P->mode[m].rp;
-        bucket[m] = kLenBuckets;
-        nhot[m] = 0;
+        RowPlan& r = P->mode[m].rp;
+        r.bucket = kLenBuckets;
+        r.nhot = 0;
         int64_t mass = 0;
-        while (bucket[m] > 0 && nhot[m] + r.rows_in[bucket[m] - 1] <= fit) {
-            --bucket[m];
-            nhot[m] += r.rows_in[bucket[m]];
-            mass += r.nnz_in[bucket[m]];
+        while (r.bucket > 0 && r.nhot + r.rows_in[r.bucket - 1] <= fit) {
+            --r.bucket;
+            r.nhot += r.rows_in[r.bucket];
+            mass += r.nnz_in[r.bucket];
         }
         share[m] = (double)mass / (double)P->nnz;
     }
-    int* counters = P->rs.split;
-    Error e = launch_fill((double*)counters, CPAPR_MAX_MODES / 2, 0.0, nullptr, s);
-    if (e.code) return e;
     for (int n = 0; n < P->N; ++n) {
         RowPlan& r = P->mode[n].rp;
         if (r.use_teams || r.nchunks_all == 0) continue;
@@ -1928,74 +1920,82 @@ Error rows_hot_build(cpapr_plan* P, hipStream_t s)
         for (int m = 0; m < P->N; ++m)
             if (m != n && m != lead && (hot < 0 || share[m] > share[hot])) hot = m;
         if (share[hot] < 0.25) continue;
-        const RowPlan& rh = P->mode[hot].rp;
-        if (!made[hot]) {
-            hot_rows_kernel<<<(unsigned)std::min<int64_t>(cdiv(P->dims[hot], kBlock), 1024), kBlock, 0, s>>>(
-                rh.row_ptr, P->dims[hot], bucket[hot], nhot[hot], counters + hot, rh.hot_id, rh.hot_rows);
-            CPAPR_LAUNCHED();
-            made[hot] = true;
-        }
-        int first = 0;
-        for (int i = 0; i < ncls - 2; ++i) first += r.count[i];
-        SplitArgs a{};
-        a.row_ptr = r.row_ptr;
-        a.rows = r.order + first;
-        a.chunk_begin = r.chunk_begin;
-        a.chunk_row = r.chunk_row;
-        int third = -1;
-        for (int m = 0, k = 0; m < P->N; ++m) {
-            if (m == n) continue;
-            const uint32_t* c = P->mode[n].cofs + (int64_t)k++ * P->nnz;
-            if (m == lead)
-                a.lead = c;
-            else if (m == hot)
-                a.hot = c;
-            else {
-                a.third = c;
-                third = m;
-            }
-        }
-        a.vals = P->mode[n].vals;
-        a.hot_id = rh.hot_id;
-        a.s_lead = r.s_lead;
-        a.s_hot = r.s_hot;
-        a.s_third = r.s_third;
-        a.s_slot = r.s_slot;
-        a.s_val = r.s_val;
-        a.exact32 = P->exact32 ? 1 : 0;
-        a.hot_before = P->rs.split + CPAPR_MAX_MODES;
-        a.row_hot = a.hot_before + max_chunks(P->nnz, sh);
-        a.chunk = heavy_chunk(P->nnz);
-        a.piece = hot_piece(P->nnz);
-        a.R = P->R;
-        split_count_kernel<<<r.nchunks_all, kBlock, 0, s>>>(a);
-        CPAPR_LAUNCHED();
-        split_scan_kernel<<<r.nlong, 64, 0, s>>>(a);
-        CPAPR_LAUNCHED();
-        split_scatter_kernel<<<r.nchunks_all, kBlock, 0, s>>>(a);
-        CPAPR_LAUNCHED();
-        entries_kernel<<<1, 1024, 0, s>>>(a, r.nlong, (int)max_entries(P->nnz, sh), r.entry, r.entry_begin,
-                                           r.xlist, r.xbegin);
-        CPAPR_LAUNCHED();
-        auto allow = [&](auto M) -> Error {  // more than 64 KB of LDS is asked for
-            constexpr bool MX = decltype(M)::value;
-            return by_heavy_shape<MX>(heavy_shape(P->R, MX), [&](auto G, auto C) -> Error {
-                constexpr int GG = decltype(G)::value, CC = decltype(C)::value;
-                const void* f = third >= 0 ? P->exact32 ? (const void*)hot_kernel<GG, CC, true, MX, float>
-                                                        : (const void*)hot_kernel<GG, CC, true, MX, double>
-                                : P->exact32 ? (const void*)hot_kernel<GG, CC, false, MX, float>
-                                             : (const void*)hot_kernel<GG, CC, false, MX, double>;
-                CPAPR_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kHotLds));
-                return {CPAPR_OK, ""};
-            });
-        };
-        e = word == 4 ? allow(std::true_type{}) : allow(std::false_type{});
-        if (e.code) return e;
         r.lead = lead;
         r.hot = hot;
-        r.third = third;
-        r.nhot = nhot[hot];
+        r.third = -1;
+        for (int m = 0; m < P->N; ++m)
+            if (m != n && m != lead && m != hot) r.third = m;
     }
+    return {CPAPR_OK, ""};
+}
+
+// The split of mode n, before its first inner loop (the caller holds the plan's
+// row buffers): programs that run no inner loop of a mode pay nothing for it.
+static Error rows_hot_make(cpapr_plan* P, int n, hipStream_t s)
+{
+    Shape sh;
+    row_shape(P->R, &sh);
+    const int ncls = class_count(class_shape(sh));
+    RowPlan& r = P->mode[n].rp;
+    RowPlan& rh = P->mode[r.hot].rp;
+    Error e{CPAPR_OK, ""};
+    if (!rh.hot_made) {
+        e = launch_fill((double*)P->rs.split, 1, 0.0, nullptr, s);
+        if (e.code) return e;
+        hot_rows_kernel<<<(unsigned)std::min<int64_t>(cdiv(P->dims[r.hot], kBlock), 1024), kBlock, 0, s>>>(
+            rh.row_ptr, P->dims[r.hot], rh.bucket, rh.nhot, P->rs.split, rh.hot_id, rh.hot_rows);
+        CPAPR_LAUNCHED();
+        rh.hot_made = true;
+    }
+    int first = 0;
+    for (int i = 0; i < ncls - 2; ++i) first += r.count[i];
+    SplitArgs a{};
+    a.row_ptr = r.row_ptr;
+    a.rows = r.order + first;
+    a.chunk_begin = r.chunk_begin;
+    a.chunk_row = r.chunk_row;
+    for (int m = 0, k = 0; m < P->N; ++m) {
+        if (m == n) continue;
+        const uint32_t* c = P->mode[n].cofs + (int64_t)k++ * P->nnz;
+        (m == r.lead ? a.lead : m == r.hot ? a.hot : a.third) = c;
+    }
+    a.vals = P->mode[n].vals;
+    a.hot_id = rh.hot_id;
+    a.s_lead = r.s_lead;
+    a.s_hot = r.s_hot;
+    a.s_third = r.s_third;
+    a.s_slot = r.s_slot;
+    a.s_val = r.s_val;
+    a.exact32 = P->exact32 ? 1 : 0;
+    a.hot_before = P->rs.split + CPAPR_MAX_MODES;
+    a.row_hot = a.hot_before + max_chunks(P->nnz, sh);
+    a.chunk = heavy_chunk(P->nnz);
+    a.piece = hot_piece(P->nnz);
+    a.R = P->R;
+    split_count_kernel<<<r.nchunks_all, kBlock, 0, s>>>(a);
+    CPAPR_LAUNCHED();
+    split_scan_kernel<<<r.nlong, 64, 0, s>>>(a);
+    CPAPR_LAUNCHED();
+    split_scatter_kernel<<<r.nchunks_all, kBlock, 0, s>>>(a);
+    CPAPR_LAUNCHED();
+    entries_kernel<<<1, 1024, 0, s>>>(a, r.nlong, (int)max_entries(P->nnz, sh), r.entry, r.entry_begin,
+                                       r.xlist, r.xbegin);
+    CPAPR_LAUNCHED();
+    auto allow = [&](auto M) -> Error {  // more than 64 KB of LDS is asked for
+        constexpr bool MX = decltype(M)::value;
+        return by_heavy_shape<MX>(heavy_shape(P->R, MX), [&](auto G, auto C) -> Error {
+            constexpr int GG = decltype(G)::value, CC = decltype(C)::value;
+            const void* f = r.third >= 0 ? P->exact32 ? (const void*)hot_kernel<GG, CC, true, MX, float>
+                                                    : (const void*)hot_kernel<GG, CC, true, MX, double>
+                            : P->exact32 ? (const void*)hot_kernel<GG, CC, false, MX, float>
+                                         : (const void*)hot_kernel<GG, CC, false, MX, double>;
+            CPAPR_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kHotLds));
+            return {CPAPR_OK, ""};
+        });
+    };
+    e = P->params.precision == CPAPR_MIXED ? allow(std::true_type{}) : allow(std::false_type{});
+    if (e.code) return e;
+    r.split_made = true;
     return {CPAPR_OK, ""};
 }
 
@@ -2795,6 +2795,8 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
         if (blocks + a.team_blocks > 0) e = light(false);
         if (e.code) return e;
         if (r.nchunks > 0 && r.hot >= 0) {
+            if (!r.split_made) e = rows_hot_make(P, mode, s);
+            if (e.code) return e;
             HotArgs k{};
             k.s_lead = r.s_lead;
             k.s_hot = r.s_hot;
@@ -2806,7 +2808,8 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
             k.xbegin = r.xbegin;
             k.rows = h.rows;
             k.tab = (const uint4*)P->rs.hot_tab;
-            k.tab_vecs = (int)cdiv((int64_t)r.nhot * P->R * (mixed ? 4 : 8), 16);
+            const int nhot = P->mode[r.hot].rp.nhot;
+            k.tab_vecs = (int)cdiv((int64_t)nhot * P->R * (mixed ? 4 : 8), 16);
             k.lead = fac[r.lead];
             k.hot = fac[r.hot];
             k.third = r.third >= 0 ? fac[r.third] : nullptr;
@@ -2819,11 +2822,11 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
             const size_t lds = (size_t)k.tab_vecs * 16;
             if (l0 == 0) {
                 const int32_t* rows = P->mode[r.hot].rp.hot_rows;
-                const unsigned tg = (unsigned)cdiv((int64_t)r.nhot * P->R, kBlock);
+                const unsigned tg = (unsigned)cdiv((int64_t)nhot * P->R, kBlock);
                 if (mixed)
-                    hot_table_kernel<<<tg, kBlock, 0, s>>>((const float*)k.hot, rows, r.nhot, P->R, (float*)P->rs.hot_tab);
+                    hot_table_kernel<<<tg, kBlock, 0, s>>>((const float*)k.hot, rows, nhot, P->R, (float*)P->rs.hot_tab);
                 else
-                    hot_table_kernel<<<tg, kBlock, 0, s>>>((const double*)k.hot, rows, r.nhot, P->R, P->rs.hot_tab);
+                    hot_table_kernel<<<tg, kBlock, 0, s>>>((const double*)k.hot, rows, nhot, P->R, P->rs.hot_tab);
                 CPAPR_LAUNCHED();
             }
             for (int l = 0; l < n; ++l) {
