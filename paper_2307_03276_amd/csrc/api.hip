@@ -207,10 +207,10 @@ Error phi_factors(cpapr_plan* P, int mode, const double* const* A, const void** 
 // start in time, and a plan whose row buffers a batch holds takes the general
 // launches. One iteration alone gathers once either way, and the Phi kernel does
 // that faster (8M uniform nonzeros, R = 32: 224 against 394 us).
-bool runs_by_rows(const cpapr_plan* P)
+bool runs_by_rows(const cpapr_plan* P, int mode)
 {
     return P->by_rows && P->shape_auto && P->params.variant <= CPAPR_VARIANT_SEGMENTED && P->params.lmax > 1 &&
-           !P->params.deterministic;
+           !P->params.deterministic && cpapr::rows_pay(P, mode);
 }
 
 // One inner loop (Algorithm 1): zero Phi, then lmax x {Phi, KKT, MU update},
@@ -597,13 +597,14 @@ int cpapr_mu_inner(cpapr_plan* plan, int32_t mode, double* B, const double* cons
         e = cpapr::launch_reset_state(plan->state, true, true, s);
         if (e.code) return report(e);
         cpapr::RowClaim claim(plan->row_owner.get(), s);
-        e = enqueue_inner(plan, mode, B, fac, Phi_last, claim.ok && runs_by_rows(plan), s);
+        const bool rows = claim.ok && runs_by_rows(plan, mode);
+        e = enqueue_inner(plan, mode, B, fac, Phi_last, rows, s);
         if (e.code) return report(e);
         HostState h{};
         e = read_state(plan, &h, s);
         if (e.code) return report(e);
         claim.queued = false;
-        if (claim.ok && runs_by_rows(plan)) plan->expect[mode] = (int)h.phi_evals;
+        if (rows) plan->expect[mode] = (int)h.phi_evals;
         if (out) {
             out->outer_iters = 0;
             out->converged = h.done;
@@ -733,10 +734,10 @@ int cpapr_solve(cpapr_plan* plan, double* lambda, double* const* A, cpapr_stats*
         if (e.code) return report(e);
         int k = 1, converged = 0;
         cpapr::RowClaim claim(P->row_owner.get(), s);
-        const bool rows = claim.ok && runs_by_rows(P);
         for (; k <= P->params.kmax; ++k) {
             for (int n = 0; n < N; ++n) {
                 const int64_t In = P->dims[n];
+                const bool rows = claim.ok && runs_by_rows(P, n);
                 if (!rows) {
                     e = cpapr::launch_reset_state(P->state, n == 0, false, s);
                     if (e.code) return report(e);
@@ -764,7 +765,7 @@ int cpapr_solve(cpapr_plan* plan, double* lambda, double* const* A, cpapr_stats*
                 HostState h{};
                 e = read_state(P, &h, s);
                 if (e.code) return report(e);
-                for (int n = 0; rows && n < N; ++n) P->expect[n] = std::min(h.mode_updates[n] + 1, P->params.lmax);
+                for (int n = 0; claim.ok && n < N; ++n) P->expect[n] = std::min(h.mode_updates[n] + 1, P->params.lmax);
                 if (h.sweep_updates == 0) {
                     converged = 1;
                     break;

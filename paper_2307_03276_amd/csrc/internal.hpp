@@ -129,6 +129,7 @@ struct RowPlan {
     int32_t count[kRowClasses];
     int32_t nmembers;           // members of the teams
     bool use_teams;             // teams take the long rows but the longest; else all of them are heavy
+    double resident;            // share of the nonzeros in light rows and teams
     int32_t nlong, nchunks_all; // long rows and their chunks
     int32_t nchunks;            // chunks of the heavy rows
     int32_t rows_in[kLenBuckets];   // rows per length bucket
@@ -407,6 +408,8 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
                          hipStream_t s);
 // Whether the loop's first iteration runs by the Phi / KKT / update launches.
 bool rows_first_alone(const cpapr_plan* P, int mode);
+// Whether an inner loop of the mode is faster row by row than by those launches.
+bool rows_pay(const cpapr_plan* P, int mode);
 // Nonzeros per chunk of a long row.
 int heavy_chunk(int64_t nnz);
 // The four-trial line-search sums of launch_delta4, row by row (R >= 4, the

@@ -1268,9 +1268,9 @@ __device__ __forceinline__ int class_of(ClassShape c, int len)
 }
 
 // Bucket of a row length > 0, four per octave (longer rows in later buckets).
-__device__ __forceinline__ int len_bucket(int len)
+__host__ __device__ inline int len_bucket(int len)
 {
-    const int e = 31 - __clz(len);
+    const int e = 31 - __builtin_clz((unsigned)len);
     return 4 * e + (e >= 2 ? (len >> (e - 2)) & 3 : (len << (2 - e)) & 3);
 }
 
@@ -1920,6 +1920,11 @@ Error rows_hot_choose(cpapr_plan* P)
         for (int m = 0; m < P->N; ++m)
             if (m != n && m != lead && (hot < 0 || share[m] > share[hot])) hot = m;
         if (share[hot] < 0.25) continue;
+        // Two gathered factors beside the table's and four columns per lane do not fit
+        // hot_kernel's 128 registers (85 to 96 spilled): 4-way 5M Zipf nonzeros, 401
+        // rows, ten iterations, R = 16 / 32 mixed / 64: 1.66 / 1.86 / 1.48 times the Phi
+        // launches' time.
+        if (P->N == 4 && heavy_shape(P->R, word == 4).C == 4) continue;
         r.lead = lead;
         r.hot = hot;
         r.third = -1;
@@ -2045,6 +2050,12 @@ void rows_finish(cpapr_plan* P, int mode, const int* meta)
         r.rows_in[i] = meta[64 + i];
         r.nnz_in[i] = meta[64 + kLenBuckets + i];
     }
+    // rows longer than a workgroup's registers (teams: than all members'), by length
+    // bucket (one starts at either bound; rows of just that length count as longer)
+    const int cap = class_cap(class_shape(sh)) * (r.use_teams ? kTeamMax : 1);
+    int64_t longer = 0;
+    for (int i = len_bucket(cap); i < kLenBuckets; ++i) longer += r.nnz_in[i];
+    r.resident = P->nnz > 0 ? 1.0 - (double)longer / (double)P->nnz : 1.0;
     r.hot = -1;
     P->mode[mode].segments = P->dims[mode] - r.count[0];
 }
@@ -2711,6 +2722,54 @@ static int first_chunk(const cpapr_plan* P, int mode, int lmax)
 {
     const int e = P->expect[mode];
     return !schedule_by_last(P) || e <= 1 || e >= lmax ? inner_step(lmax) : std::min(e, kInnerChunk);
+}
+
+namespace {
+
+// What an iteration of a mode's heavy rows takes, in units of the Phi launches'
+// time for the same nonzeros: both gather every factor row again. Measured at 300k,
+// 1.1M, 5M and 20M nonzeros, R = 8 .. 64, both precisions, uniform and Zipf(1.1)
+// coordinates, modes of 53 to 40,003 rows:
+//  * two modes: 0.55 to 1.1, rows of a few hundred nonzeros 1.2 to 1.5;
+//  * split by hot rows, three modes: 0.6 to 0.9, above R = 32 to 1.06 at 5M;
+//    four modes: 0.75 to 0.95 up to R = 32 at 20M, 0.9 to 1.1 below, 0.9 to 1.19 above;
+//  * else, three modes: 0.8 to 1.0 up to 1.1M, from there 0.92 to 1.34, rows of up
+//    to 1,000 nonzeros to 2.7;
+//  * four modes: 0.86 to 1.0 at 300k, to 1.3 at 1.1M, 0.85 to 1.25 above, with four
+//    columns per lane and FP32-stored factors to 1.6, short rows to 2.0;
+//  * more modes: 0.7 to 1.0 at 300k, to 1.2 at 1.1M, 0.8 to 1.66 above, but R > 48 in
+//    FP64 with long rows 0.7 to 1.0.
+double heavy_cost(const cpapr_plan* P, const RowPlan& r)
+{
+    const int N = P->N, R = P->R;
+    const bool mixed = P->params.precision == CPAPR_MIXED;
+    const bool middle = P->nnz >= (int64_t(1) << 20), large = P->nnz >= (int64_t(1) << 21);
+    const bool huge = P->nnz >= (int64_t(1) << 23);
+    const bool brief = (1.0 - r.resident) * (double)P->nnz < 2048.0 * r.nlong;
+    if (N == 2) return brief && huge ? 1.3 : 0.9;
+    if (r.hot >= 0 && N == 3) return R <= 32 ? 0.85 : huge ? 0.95 : 1.02;
+    if (r.hot >= 0) return R > 32 ? 1.1 : huge || (R <= 8 && !mixed) ? 0.95 : 1.05;
+    if (!middle) return 0.95;
+    if (N == 3) return !large ? 0.95 : brief ? 2.0 : 1.2;
+    if (N == 4) return !large ? (mixed ? 1.3 : 1.1) : brief || (mixed && heavy_shape(R, true).C == 4) ? 1.6 : 1.25;
+    return R <= 48 || mixed || brief ? 1.4 : large ? 0.95 : 1.05;
+}
+
+}  // namespace
+
+// Row by row or by the Phi launches: resident nonzeros gather once per loop, at about
+// the cost of one Phi, and then take about a tenth of it per iteration (8M uniform
+// nonzeros, R = 32: 394 us for the first, Phi 224, and 70 for each further one);
+// with FP32-stored factors at R > 24 the gather costs over two of that Phi once the
+// factors' rows come from memory (20M nonzeros, lmax = 2: 1.13 to 1.2 times the Phi
+// launches).
+bool rows_pay(const cpapr_plan* P, int mode)
+{
+    const RowPlan& r = P->mode[mode].rp;
+    const bool mixed = P->params.precision == CPAPR_MIXED;
+    const double gather = mixed && P->R > 24 && P->nnz >= (int64_t(1) << 22) ? 2.2 : 1.0;
+    const double resident = 0.1 + gather / P->params.lmax;
+    return r.resident * resident + (1.0 - r.resident) * heavy_cost(P, r) <= 1.0;
 }
 
 Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* fac, double* Phi, int lmax,

@@ -106,6 +106,18 @@ def test_heavy_rows_split_by_hot_coordinates(R, others, precision, frac):
     _check(X, R, 3, tol=float(min(hist[:2])) * (1 + 1e-5), precision=precision)
 
 
+@pytest.mark.parametrize("R,others,precision", [(6, (700, 60, 30), cpapr.CPAPR_FP64), (24, (500, 90, 40), cpapr.CPAPR_MIXED),
+                                                (32, (800, 60, 30), cpapr.CPAPR_FP64), (48, (600, 50, 30), cpapr.CPAPR_MIXED)])
+def test_four_modes_split_by_hot_coordinates(R, others, precision):
+    """The same with four modes and a quarter of the nonzeros in light rows, beside
+    which the heavy rows run by hot and cold parts (alone, the Phi launches)."""
+    rng = np.random.default_rng(3)
+    lengths = np.concatenate([[420_000, 160_000], rng.integers(1_500, 12_000, 40), [300] * 1_000, EDGES])
+    X = _tensor(lengths, others, 220 + R, skew=1.1)
+    hist = _check(X, R, 3, precision=precision)
+    _check(X, R, 3, tol=float(min(hist[:2])) * (1 + 1e-5), precision=precision)
+
+
 def test_hot_rows_at_rank_one():
     """Rank 1 with FP32-stored factors: more rows of the second factor would fit
     the LDS (35,840) than a plan has places for (17,920)."""
@@ -329,7 +341,7 @@ def test_stops_of_large_tensors(R, others, precision, lmax=5):
     and heavy rows halt at the stop: stops before, at and after the end of a
     chunk, for a new plan and for one whose last loop stopped elsewhere."""
     rng = np.random.default_rng(2)
-    lengths = np.concatenate([[420_000, 160_000], rng.integers(1_500, 12_000, 90), EDGES])
+    lengths = np.concatenate([[420_000, 160_000], rng.integers(1_500, 12_000, 90), [500] * 600, EDGES])
     X = _tensor(lengths, others, 120 + R, skew=1.1)
     M = synth.random_model(7, X.dims, R)
     Bh, A = M.factors[0] * M.lam, [dev(a) for a in M.factors]
