@@ -141,11 +141,11 @@ struct RowPlan {
     int32_t bucket, nhot;           // this mode's own hot rows: its rows in length buckets >= bucket, their number
     bool hot_made;                  // and their places
     uint32_t* s_lead;               // [nnz] offsets into the lead mode's factor
-    uint16_t* s_slot;               // [nnz] place among the hot rows (hot part)
-    uint32_t* s_hot;                // [nnz] offsets into the hot mode's factor (cold part)
+    uint32_t* s_hot;                // [nnz] offsets into the hot mode's factor (cold part); in the hot part,
+                                    // which comes first, 16-bit places among the hot rows from the row's start on
     uint32_t* s_third;              // [nnz] offsets (three other modes)
-    void* s_val;                    // [nnz] FP32 where every value is exact in it, else FP64
-    int4* entry;                    // pieces {long row, first, end, hot} of the parts
+    uint32_t* s_val;                // [nnz] FP32 values where all are exact in it, else positions in the sorted copy
+    int4* entry;                    // pieces {long row, first, end, hot: 1 + the row's start} of the parts
     int32_t* entry_begin;           // [long rows + 1] first piece of each long row
     int32_t* xlist;                 // [pieces] pieces by die
     int32_t* xbegin;                // [kXcds + 1] first of each die

@@ -172,7 +172,7 @@ struct ResArgs {
     const void* fac[kMaxOther];
     double* B;
     double* B0;     // saved start of the chunk (tol > 0), else nullptr
-    double* B1;     // b before the chunk's last update (tol > 0)
+    double* B1;     // b before the chunk's last update (or nullptr)
     double* Phi;
     const int32_t* done;       // the inner loop has stopped: no work
     const int32_t* rerun;      // iteration to run again to (-1: none)
@@ -576,7 +576,7 @@ __device__ __forceinline__ void back_to(const ResArgs& a, int l, int n_it, int a
 {
     if (at >= a.light_blocks)
         restore_rows(a, l, at - a.light_blocks, blocks - a.light_blocks);
-    else if (l + 1 == n_it)
+    else if (l + 1 == n_it && (n_it == 1 || a.B1 != nullptr))
         restore_last(a, n_it, at);
     else
         resident_rows<G, C, K, MIXED, false>(a, at, true, l + 1);
@@ -914,9 +914,8 @@ constexpr uint16_t kCold = 0xffff;
 static_assert(kMaxHot < kCold, "places fit 16 bits");
 
 struct HotArgs {
-    const uint32_t *s_lead, *s_hot, *s_third;
-    const uint16_t* s_slot;
-    const void* s_val;
+    const uint32_t *s_lead, *s_hot, *s_third, *s_val;
+    const double* vals;       // the sorted copy's, where s_val holds positions
     const int4* entry;
     const int32_t *xlist, *xbegin;
     const int32_t* rows;      // long rows (in `order`)
@@ -953,7 +952,7 @@ __device__ __forceinline__ void load_lds(const L* tab, uint32_t at, double (&v)[
 // heavy_kernel) are left to the other factors. The pieces of a long row go to
 // the dies by their place in the row, and a die takes them in that order, so
 // that the rows of the leading factor it gathers at a time stay in its L2.
-template <int G, int C, bool THIRD, bool MIXED, typename V>
+template <int G, int C, bool THIRD, bool MIXED, bool EXACT>
 __global__ __launch_bounds__(kHotThreads) void hot_kernel(HotArgs a)
 {
     using L = typename std::conditional<MIXED, float, double>::type;
@@ -987,17 +986,24 @@ __global__ __launch_bounds__(kHotThreads) void hot_kernel(HotArgs a)
         }
         auto run = [&](auto hotpart) {
             constexpr bool HOT = decltype(hotpart)::value;
-            uint32_t ol = 0, oh = 0, o3 = 0, cur = 0;
+            uint32_t ol = 0, oh = 0, o3 = 0, cur = 0, at = 0;
             double x = 0.0;
             bool have = false;
+            const uint16_t* slot = (const uint16_t*)a.s_hot + (en.w - 1);
+            if (!EXACT) at = a.s_val[min(w0 + (uint32_t)(g * 4 + q), w1 - 1)];
             auto load_meta = [&](uint32_t base) {
                 const uint32_t p = base + (uint32_t)(g * 4 + q);
                 const uint32_t pc = min(p, w1 - 1);
-                x = (double)__builtin_nontemporal_load((const V*)a.s_val + pc);
+                if constexpr (EXACT) {
+                    x = (double)__uint_as_float(__builtin_nontemporal_load(a.s_val + pc));
+                } else {  // the position was loaded a step ahead
+                    x = a.vals[at];
+                    at = __builtin_nontemporal_load(a.s_val + min(p + STEP, w1 - 1));
+                }
                 if (p >= w1) x = 0.0;
                 ol = __builtin_nontemporal_load(a.s_lead + pc);
                 if constexpr (HOT)
-                    oh = (uint32_t)__builtin_nontemporal_load(a.s_slot + pc) * (uint32_t)R;
+                    oh = (uint32_t)__builtin_nontemporal_load(slot + pc) * (uint32_t)R;
                 else
                     oh = __builtin_nontemporal_load(a.s_hot + pc);
                 if constexpr (THIRD) o3 = __builtin_nontemporal_load(a.s_third + pc);
@@ -1252,6 +1258,7 @@ __host__ __device__ inline int class_cap(ClassShape c) { return 4 * c.KB * c.NG 
 // team running.
 constexpr int kTeamMax = 128;
 constexpr int kTeamMembers = 256;
+constexpr int kTeamParts = 32768;   // members with room for their partial rows: of a batch slot's teams
 constexpr int kSpreadBlocks = 256;  // one workgroup per compute unit
 
 __device__ __forceinline__ int class_of(ClassShape c, int len)
@@ -1426,9 +1433,7 @@ struct SplitArgs {
     const uint32_t *lead, *hot, *third;  // the sorted copy's offsets
     const double* vals;
     const uint16_t* hot_id;
-    uint32_t *s_lead, *s_hot, *s_third;
-    uint16_t* s_slot;
-    void* s_val;
+    uint32_t *s_lead, *s_hot, *s_third, *s_val;
     int exact32;
     int* hot_before;   // [chunks] hot nonzeros of the chunk, then of the row's chunks before it
     int* row_hot;      // [long rows] hot nonzeros
@@ -1515,14 +1520,11 @@ __global__ __launch_bounds__(kBlock) void split_scatter_kernel(SplitArgs a)
             const uint32_t to = ishot ? hot_at + before : cold_at + (threadIdx.x - before);
             a.s_lead[to] = a.lead[p];
             if (ishot)
-                a.s_slot[to] = id;
+                ((uint16_t*)a.s_hot)[start + to] = id;
             else
                 a.s_hot[to] = off;
             if (a.third != nullptr) a.s_third[to] = a.third[p];
-            if (a.exact32)
-                ((float*)a.s_val)[to] = (float)a.vals[p];
-            else
-                ((double*)a.s_val)[to] = a.vals[p];
+            a.s_val[to] = a.exact32 ? __float_as_uint((float)a.vals[p]) : p;
         }
         const uint32_t n = min((uint32_t)kBlock, p1 - base);
         hot_at += total;
@@ -1628,7 +1630,7 @@ __global__ __launch_bounds__(1024) void entries_kernel(SplitArgs a, int nlong, i
                     if (pass == 0) {
                         const uint32_t lo = (hot ? q0 : qm) + (uint32_t)(ip * a.piece);
                         entry[b0 + i] =
-                            make_int4(hk, (int)lo, (int)min(lo + (uint32_t)a.piece, hot ? qm : q1), hot ? 1 : 0);
+                            make_int4(hk, (int)lo, (int)min(lo + (uint32_t)a.piece, hot ? qm : q1), hot ? (int)q0 + 1 : 0);
                     } else if (at < max_entries) {
                         xlist[at] = b0 + i;
                     }
@@ -1764,34 +1766,40 @@ int64_t max_entries(int64_t nnz, const Shape& s) { return nnz / hot_piece(nnz) +
 int64_t max_partials(int64_t nnz, const Shape& s) { return std::max(max_chunks(nnz, s), max_entries(nnz, s)); }
 
 // Tensors whose long rows may be split by hot rows: three- and four-way ones of
-// at least 2^20 nonzeros (below, the launches weigh more than the gathers).
+// at least 2^20 nonzeros (below, the launches weigh more than the gathers) and at
+// most 2^28 (the split takes 12 and 16 bytes per nonzero and mode, 17 GB there).
 bool hot_supported(int N, int64_t nnz, int R)
 {
     Shape s;
-    return (N == 3 || N == 4) && nnz >= (1 << 20) && row_shape(R, &s);
+    return (N == 3 || N == 4) && nnz >= (1 << 20) && nnz <= (1 << 28) && row_shape(R, &s);
 }
+constexpr int64_t kScheduled = int64_t(1) << 20;  // nonzeros from which chunks follow the last loop
+
 int64_t max_members(int64_t nnz, const Shape& s) { return nnz / class_cap(class_shape(s)) + max_long(nnz, s); }
 
 // Doubles of the long rows' history (tol > 0). A single loop keeps one iteration of
 // its heavy rows, or, where it runs teams, kInnerChunk iterations of theirs (at
 // most kTeamMembers / 2 rows: a team has two members or more) and one of the rows
 // too long for a team. In a batch all long rows are teams: kInnerChunk iterations
-// of theirs while that is no more than a double per nonzero, else the batch takes
-// shorter chunks (R = 64, every row just longer than a workgroup's registers:
-// one iteration takes 3.2 bytes per nonzero).
+// of theirs while that is no more than a double per nonzero and 64 MiB, else the
+// batch takes shorter chunks (R = 64, every row just longer than a workgroup's
+// registers: one iteration takes 3.2 bytes per nonzero).
 int64_t hist_doubles(int64_t nnz, const Shape& s, int R)
 {
     const int64_t nl = max_long(nnz, s), row = 2 * (int64_t)R;
     const int64_t longest = nnz / ((int64_t)kTeamMax * class_cap(class_shape(s)) + 1);
     const int64_t single = std::max(nl * row, (longest + std::min<int64_t>(nl, kTeamMembers / 2) * kInnerChunk) * row);
-    return std::max(single, std::min(nl * row * kInnerChunk, nnz));
+    return std::max(single, std::min({nl * row * kInnerChunk, nnz, int64_t(1) << 23}));
 }
 
 }  // namespace
 
-// Up to 2^30 nonzeros: positions are 32-bit with room for a step past the end,
-// and the structures below (up to 45 bytes per nonzero beyond a plan without
-// them, which takes 168 GB there) stay within the device's memory.
+// Up to 2^30 nonzeros: positions are 32-bit with room for a step past the end. The
+// structures below lie where the plan's sort had its temporaries (44 bytes per
+// nonzero), so that a plan takes, beyond one without them, 8 bytes per row of every
+// mode and at most 0.065 bytes per nonzero and mode, except with three modes and R = 64
+// below 2^23 nonzeros (up to 14) and with four modes and 2^20 to 2^28 nonzeros: 16 to
+// 28 by rank (R = 32: 23 at 20M), up to 42 below 2^23 (R = 64).
 bool rows_supported(int R, int64_t nnz)
 {
     Shape s;
@@ -1832,7 +1840,7 @@ size_t rows_state_bind(RowState* r, char* base, int64_t nnz, int64_t maxI, int R
     };
     RowState o{};
     o.partial = (double*)take(max_partials(nnz, s) * R * 8);
-    o.team_part = (double*)take(3 * max_members(nnz, s) * R * 8);
+    o.team_part = (double*)take(3 * std::min<int64_t>(max_members(nnz, s), kTeamParts) * R * 8);
     o.tickets = (1 + 2 * nl + 1 + kInnerSlots) * kCountStride;
     o.ticket = (unsigned int*)take(o.tickets * 4);
     o.finished = o.ticket + (1 + 2 * nl) * kCountStride;
@@ -1840,7 +1848,7 @@ size_t rows_state_bind(RowState* r, char* base, int64_t nnz, int64_t maxI, int R
     o.hot_tab = (double*)take(kHotLds);
     if (stops) {
         o.B0 = (double*)take(maxI * R * 8);
-        o.B1 = (double*)take(maxI * R * 8);
+        if (nnz >= kScheduled) o.B1 = (double*)take(maxI * R * 8);
         o.hist_n = hist_doubles(nnz, s, R);
         o.hist = (double*)take(o.hist_n * 8);
     }
@@ -1863,8 +1871,7 @@ size_t rows_hot_bind(cpapr_plan* P, char* base, int N, int64_t nnz, const int64_
         uint32_t* lead = (uint32_t*)take(nnz * 4);
         uint32_t* hot = (uint32_t*)take(nnz * 4);
         uint32_t* third = N == 4 ? (uint32_t*)take(nnz * 4) : nullptr;
-        uint16_t* slot = (uint16_t*)take(nnz * 2);
-        void* val = take(nnz * 8);
+        uint32_t* val = (uint32_t*)take(nnz * 4);
         int32_t* xlist = (int32_t*)take((max_entries(nnz, s) + 1) * 4);
         int32_t* xbegin = (int32_t*)take((kXcds + 1) * 4);
         int4* entry = (int4*)take((max_entries(nnz, s) + 1) * 16);
@@ -1876,7 +1883,6 @@ size_t rows_hot_bind(cpapr_plan* P, char* base, int N, int64_t nnz, const int64_
             r.s_lead = lead;
             r.s_hot = hot;
             r.s_third = third;
-            r.s_slot = slot;
             r.s_val = val;
             r.xlist = xlist;
             r.xbegin = xbegin;
@@ -1969,7 +1975,6 @@ static Error rows_hot_make(cpapr_plan* P, int n, hipStream_t s)
     a.s_lead = r.s_lead;
     a.s_hot = r.s_hot;
     a.s_third = r.s_third;
-    a.s_slot = r.s_slot;
     a.s_val = r.s_val;
     a.exact32 = P->exact32 ? 1 : 0;
     a.hot_before = P->rs.split + CPAPR_MAX_MODES;
@@ -1990,10 +1995,10 @@ static Error rows_hot_make(cpapr_plan* P, int n, hipStream_t s)
         constexpr bool MX = decltype(M)::value;
         return by_heavy_shape<MX>(heavy_shape(P->R, MX), [&](auto G, auto C) -> Error {
             constexpr int GG = decltype(G)::value, CC = decltype(C)::value;
-            const void* f = r.third >= 0 ? P->exact32 ? (const void*)hot_kernel<GG, CC, true, MX, float>
-                                                    : (const void*)hot_kernel<GG, CC, true, MX, double>
-                            : P->exact32 ? (const void*)hot_kernel<GG, CC, false, MX, float>
-                                         : (const void*)hot_kernel<GG, CC, false, MX, double>;
+            const void* f = r.third >= 0 ? P->exact32 ? (const void*)hot_kernel<GG, CC, true, MX, true>
+                                                    : (const void*)hot_kernel<GG, CC, true, MX, false>
+                            : P->exact32 ? (const void*)hot_kernel<GG, CC, false, MX, true>
+                                         : (const void*)hot_kernel<GG, CC, false, MX, false>;
             CPAPR_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kHotLds));
             return {CPAPR_OK, ""};
         });
@@ -2629,14 +2634,14 @@ Error launch_loglik_fused(const cpapr_plan* P, const double* lam, const double* 
     return {CPAPR_OK, ""};
 }
 
-// A batch slot can run row by row when its plan's single inner loop would, and
-// no row is longer than the largest team.
+// A batch slot can run row by row when its plan's single inner loop could, no row
+// is longer than the largest team, and the teams' partial rows have room.
 int rows_batch_shape(const cpapr_plan* P, int mode)
 {
     Shape sh;
     if (!P->by_rows || P->params.method != CPAPR_METHOD_MU || !P->shape_auto ||
         P->params.variant > CPAPR_VARIANT_SEGMENTED || !row_shape(P->R, &sh)) return -1;
-    if (P->mode[mode].rp.count[class_count(class_shape(sh)) - 2] > 0) return -1;
+    if (P->mode[mode].rp.count[class_count(class_shape(sh)) - 2] > 0 || P->mode[mode].rp.nmembers > kTeamParts) return -1;
     const int mixed = P->params.precision == CPAPR_MIXED ? 1 : 0;
     return 2 * (P->R <= 16 ? (P->R - 1) / 4 : P->R <= 32 ? 4 + (P->R - 17) / 8 : 6 + (P->R - 33) / 16) + mixed;
 }
@@ -2711,7 +2716,7 @@ Error launch_rows_batch_decide(const void* items, int n, BatchState st, int32_t*
 // all ten iterations).
 static bool schedule_by_last(const cpapr_plan* P)
 {
-    return P->params.tol > 0.0 && P->nnz >= (int64_t(1) << 20);
+    return P->params.tol > 0.0 && P->nnz >= kScheduled;
 }
 
 // A loop that is expected to stop at its first iteration, or of which nothing is
@@ -2861,7 +2866,7 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
             k.s_hot = r.s_hot;
             k.s_third = r.s_third;
             k.s_val = r.s_val;
-            k.s_slot = r.s_slot;
+            k.vals = pm.vals;
             k.entry = r.entry;
             k.xlist = r.xlist;
             k.xbegin = r.xbegin;
@@ -2894,13 +2899,13 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
                     return by_heavy_shape<MX>(heavy_shape(P->R, mixed), [&](auto G, auto C) -> Error {
                         constexpr int GG = decltype(G)::value, CC = decltype(C)::value;
                         if (r.third >= 0 && P->exact32)
-                            hot_kernel<GG, CC, true, MX, float><<<P->rs.cus, kHotThreads, lds, s>>>(k);
+                            hot_kernel<GG, CC, true, MX, true><<<P->rs.cus, kHotThreads, lds, s>>>(k);
                         else if (r.third >= 0)
-                            hot_kernel<GG, CC, true, MX, double><<<P->rs.cus, kHotThreads, lds, s>>>(k);
+                            hot_kernel<GG, CC, true, MX, false><<<P->rs.cus, kHotThreads, lds, s>>>(k);
                         else if (P->exact32)
-                            hot_kernel<GG, CC, false, MX, float><<<P->rs.cus, kHotThreads, lds, s>>>(k);
+                            hot_kernel<GG, CC, false, MX, true><<<P->rs.cus, kHotThreads, lds, s>>>(k);
                         else
-                            hot_kernel<GG, CC, false, MX, double><<<P->rs.cus, kHotThreads, lds, s>>>(k);
+                            hot_kernel<GG, CC, false, MX, false><<<P->rs.cus, kHotThreads, lds, s>>>(k);
                         CPAPR_LAUNCHED();
                         return {CPAPR_OK, ""};
                     });

@@ -208,3 +208,31 @@ def test_phi_coo_workspace_size(lib):
     assert size([40, 30, 20], 1000, 3, 8)[0] == cpapr.CPAPR_EINVAL
     assert size([40, 30, 20], 1000, -1, 8)[0] == cpapr.CPAPR_EINVAL
     assert size([40, 30, 20], 1000, 0, 0)[0] == cpapr.CPAPR_EUNSUPPORTED
+
+
+@pytest.mark.parametrize("tol", [0.0, 1e-4])
+@pytest.mark.parametrize("precision", [cpapr.CPAPR_FP64, cpapr.CPAPR_MIXED])
+@pytest.mark.parametrize("nmodes", [2, 3, 4, 5, 8])
+def test_rows_by_class_take_little_workspace(lib, nmodes, precision, tol):
+    """What the row-by-row inner loop (R <= 64) adds to a plan, against one without
+    it (R = 65, whose matrices of 1,000 rows are a row's 8 bytes larger): 0.065
+    bytes per nonzero and mode (R = 64, lists by rows of at least 321 nonzeros and
+    their pieces of 320: 8 / 321 + 4 (1 / 2048 + 1 / 321) + 4 (1 / 320 + 1 / 321)
+    bytes; the rest lies where the sort had its temporaries), and with four modes and 2^20 to 2^28 nonzeros 28, up
+    to 42 below 2^23. Above 2^30 nonzeros nothing."""
+    dims = [1000] * nmodes
+
+    def size(nnz, R):
+        rc, n = _size(_coo(dims, nnz), R, cpapr.cpapr_params_default(tol=tol, precision=precision))
+        assert rc == 0
+        return n
+
+    fixed = 8_000 * nmodes + 2 * 1000 * 64 * 8 + (2 << 20)  # rows, saved starts, rounding, tables of constant size
+    for nnz in (300_000, 3_000_000, 20_000_000, 1 << 28, (1 << 28) + 1, 1 << 30):
+        split = nmodes == 4 and 1 << 20 <= nnz <= 1 << 28
+        per = 0.065 * nmodes if not split else 42 if nnz < 1 << 23 else 28
+        if nmodes == 3 and nnz == 3_000_000:
+            per = 14
+        for R in (1, 4, 10, 16, 32, 64):
+            assert size(nnz, R) - size(nnz, 65) <= per * nnz + fixed, (nnz, R)
+    assert size((1 << 30) + 1, 64) <= size((1 << 30) + 1, 65)
