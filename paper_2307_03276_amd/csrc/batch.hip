@@ -170,7 +170,8 @@ struct cpapr_batch {
     {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         const bool free = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
-        if (!free || (row_used == nullptr && hipEventCreateWithFlags(&row_used, hipEventDisableTiming) != hipSuccess) ||
+        constexpr unsigned kFlags = hipEventDisableTiming | hipEventDisableSystemFence;  // the host only waits for the end
+        if (!free || (row_used == nullptr && hipEventCreateWithFlags(&row_used, kFlags) != hipSuccess) ||
             hipEventRecord(row_used, s) != hipSuccess)
             row_untracked = true;
     }

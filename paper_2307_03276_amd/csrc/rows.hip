@@ -502,12 +502,8 @@ __device__ __forceinline__ void resident_rows(const ResArgs& a, int at, bool rer
                         hist[0] = b[c];
                         hist[n] = acc[c];
                     }
-            if (!TEAM && a.B1 != nullptr && lead && n_it > 1 && l + 1 == n_it)
-#pragma unroll
-                for (int c = 0; c < C; ++c)
-                    if (own[c]) a.B1[(int64_t)row * R + colbase + c] = b[c];
         }
-        if (!rerun || l + 1 < n_it)
+        if (l + 1 < n_it)
 #pragma unroll
             for (int c = 0; c < C; ++c) b[c] *= acc[c];
     }
@@ -515,8 +511,10 @@ __device__ __forceinline__ void resident_rows(const ResArgs& a, int at, bool rer
 #pragma unroll
         for (int c = 0; c < C; ++c)
             if (own[c]) {
-                a.B[(int64_t)row * R + colbase + c] = b[c];
-                a.Phi[(int64_t)row * R + colbase + c] = acc[c];
+                const int64_t e = (int64_t)row * R + colbase + c;
+                if (!TEAM && !rerun && a.B1 != nullptr) a.B1[e] = b[c];
+                a.B[e] = rerun ? b[c] : b[c] * acc[c];
+                a.Phi[e] = acc[c];
             }
     if (!rerun) {
         __syncthreads();
@@ -1995,10 +1993,12 @@ static Error rows_hot_make(cpapr_plan* P, int n, hipStream_t s)
         constexpr bool MX = decltype(M)::value;
         return by_heavy_shape<MX>(heavy_shape(P->R, MX), [&](auto G, auto C) -> Error {
             constexpr int GG = decltype(G)::value, CC = decltype(C)::value;
-            const void* f = r.third >= 0 ? P->exact32 ? (const void*)hot_kernel<GG, CC, true, MX, true>
-                                                    : (const void*)hot_kernel<GG, CC, true, MX, false>
-                            : P->exact32 ? (const void*)hot_kernel<GG, CC, false, MX, true>
-                                         : (const void*)hot_kernel<GG, CC, false, MX, false>;
+            const void* f = P->exact32 ? (const void*)hot_kernel<GG, CC, false, MX, true>
+                                       : (const void*)hot_kernel<GG, CC, false, MX, false>;
+            if constexpr (CC < 4)
+                if (r.third >= 0)
+                    f = P->exact32 ? (const void*)hot_kernel<GG, CC, true, MX, true>
+                                   : (const void*)hot_kernel<GG, CC, true, MX, false>;
             CPAPR_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kHotLds));
             return {CPAPR_OK, ""};
         });
@@ -2898,11 +2898,16 @@ Error enqueue_inner_rows(cpapr_plan* P, int mode, double* B, const void* const* 
                     constexpr bool MX = decltype(M)::value;
                     return by_heavy_shape<MX>(heavy_shape(P->R, mixed), [&](auto G, auto C) -> Error {
                         constexpr int GG = decltype(G)::value, CC = decltype(C)::value;
-                        if (r.third >= 0 && P->exact32)
-                            hot_kernel<GG, CC, true, MX, true><<<P->rs.cus, kHotThreads, lds, s>>>(k);
-                        else if (r.third >= 0)
-                            hot_kernel<GG, CC, true, MX, false><<<P->rs.cus, kHotThreads, lds, s>>>(k);
-                        else if (P->exact32)
+                        if (r.third >= 0) {
+                            if constexpr (CC < 4) {
+                                if (P->exact32)
+                                    hot_kernel<GG, CC, true, MX, true><<<P->rs.cus, kHotThreads, lds, s>>>(k);
+                                else
+                                    hot_kernel<GG, CC, true, MX, false><<<P->rs.cus, kHotThreads, lds, s>>>(k);
+                            } else {
+                                return {CPAPR_EUNSUPPORTED, "no split of four modes with four columns per lane"};
+                            }
+                        } else if (P->exact32)
                             hot_kernel<GG, CC, false, MX, true><<<P->rs.cus, kHotThreads, lds, s>>>(k);
                         else
                             hot_kernel<GG, CC, false, MX, false><<<P->rs.cus, kHotThreads, lds, s>>>(k);
