@@ -114,7 +114,7 @@ __device__ __forceinline__ double div_pos(double x, double m)
 // What the segmented kernel computes per nonzero and where it goes.
 constexpr int kPhi = 0;     // s_k = x_k / max(m_k, eps); Phi[i_n] += s_k pi_k
 constexpr int kMttkrp = 1;  // s_k = x_k;                  M[i_n]  += s_k pi_k
-constexpr int kLoglik = 2;  // x_k log(max(m_k, eps)) summed per tile (no scatter)
+constexpr int kLoglik = 2;  // x_k log(max(m_k, eps)) summed per tile (no scatter); R > 64
 constexpr int kDelta = 3;   // x_k log(max(m_k + dm_k, eps) / max(m_k, eps)) summed per row (column 0)
 constexpr int kDelta4 = 4;  // the same for the four trial steps max(b + alpha d, 0) - b, alpha = 1, 1/2, 1/4, 1/8 (columns 0-3)
 constexpr int kTrials4 = 4;
@@ -1030,23 +1030,23 @@ Error dispatch_seg_n(int G, int RPL, const PhiArgs& a, dim3 grid, hipStream_t s)
         CPAPR_LAUNCHED();                                                             \
         return {CPAPR_OK, ""};                                                        \
     }
-    CPAPR_SEG_CASE(4, 1)
-    CPAPR_SEG_CASE(8, 1)
-    CPAPR_SEG_CASE(16, 1)
-    CPAPR_SEG_CASE(32, 1)
-    CPAPR_SEG_CASE(64, 1)
     CPAPR_SEG_CASE(64, 2)
     CPAPR_SEG_CASE(64, 3)
     CPAPR_SEG_CASE(64, 4)
-    CPAPR_SEG_CASE(8, 2)
-    CPAPR_SEG_CASE(16, 2)
-    CPAPR_SEG_CASE(8, 3)
-    CPAPR_SEG_CASE(16, 3)
-    if constexpr (NM1 <= 3) {
-        CPAPR_SEG_CASE(8, 4)
-        CPAPR_SEG_CASE(16, 4)
+    if constexpr (KIND != kLoglik) {  // of the likelihood R > 64 alone
+        CPAPR_SEG_CASE(4, 1)
+        CPAPR_SEG_CASE(8, 1)
+        CPAPR_SEG_CASE(16, 1)
+        CPAPR_SEG_CASE(32, 1)
+        CPAPR_SEG_CASE(64, 1)
+        CPAPR_SEG_CASE(8, 2)
+        CPAPR_SEG_CASE(16, 2)
+        CPAPR_SEG_CASE(8, 3)
+        CPAPR_SEG_CASE(16, 3)
     }
     if constexpr (NM1 <= 3 && KIND != kLoglik) {
+        CPAPR_SEG_CASE(8, 4)
+        CPAPR_SEG_CASE(16, 4)
         CPAPR_SEG_CASE(4, 2)
         CPAPR_SEG_CASE(4, 3)
         CPAPR_SEG_CASE(4, 4)
@@ -1060,8 +1060,9 @@ Error dispatch_seg_n(int G, int RPL, const PhiArgs& a, dim3 grid, hipStream_t s)
 
 // Shapes the reduce-scatter tile is built for: 8 or 16 lanes per nonzero, up
 // to 8 gathered words per lane and nonzero (its Q rounds keep them in
-// registers).
-bool xr_shape_supported(int G, int RPL, int NM1) { return (G == 8 || G == 16) && RPL != 3 && NM1 * RPL <= 8; }
+// registers). Three columns per lane run as four.
+int xr_columns(int RPL) { return RPL == 3 ? 4 : RPL; }
+bool xr_shape_supported(int G, int RPL, int NM1) { return (G == 8 || G == 16) && NM1 * xr_columns(RPL) <= 8; }
 
 template <bool MIXED>
 Error dispatch_xr(int G, int RPL, const PhiArgs& a, hipStream_t s)
@@ -1388,7 +1389,7 @@ Error launch_phi(const cpapr_plan* P, int mode, const double* B, const void* con
     if (e.code) return e;
     prof_begin(mode, s);
     if (P->params.variant == CPAPR_VARIANT_XR && xr_shape_supported(G, RPL, a.NM1))
-        e = mixed ? dispatch_xr<true>(G, RPL, a, s) : dispatch_xr<false>(G, RPL, a, s);
+        e = mixed ? dispatch_xr<true>(G, xr_columns(RPL), a, s) : dispatch_xr<false>(G, xr_columns(RPL), a, s);
     else
         e = mixed ? dispatch_seg<true, kPhi>(G, RPL, a, s) : dispatch_seg<false, kPhi>(G, RPL, a, s);
     prof_end(s);
@@ -1546,7 +1547,7 @@ PhiArgs phi_args(const cpapr_plan* P, int mode, const double* B, const void* con
 Error launch_loglik_terms(const cpapr_plan* P, const double* B, const double* const* A, double eps, double* partial,
                           int* nparts, hipStream_t s)
 {
-    // Default shape for this rank (always instantiated), 512 nonzeros per tile.
+    // Default shape for this rank (R > 64: the others run launch_loglik_fused), 512 nonzeros per tile.
     const int G = resolve_group(P->R, 0, P->N - 1);
     const int RPL = rank_block(P->R, G);
     PhiArgs a = make_args(P, 0, B, (const void* const*)A, eps, partial, nullptr);

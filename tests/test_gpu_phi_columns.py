@@ -52,3 +52,21 @@ def test_batch_and_atomic_three_columns(R, group):
         assert_parity(host(Q.phi(0, dev(Bh), A)), ref, TOL64, "variant")
         Q.close()
     P.close()
+
+
+@pytest.mark.parametrize("R,group", [(17, 8), (20, 8), (24, 8), (33, 16), (40, 16), (48, 16)])
+@pytest.mark.parametrize("dims", [(900, 80), (900, 80, 50)])
+def test_reduce_scatter_variant_at_three_columns(R, group, dims):
+    """CPAPR_VARIANT_XR runs its own kernel at these ranks, not the segmented one:
+    its dot products are summed in another order, so the bits differ (rows that
+    cross one tile boundary at most: each kernel repeats its own)."""
+    X = synth.random_tensor(R, dims, 9_001)
+    M = synth.random_model(6, X.dims, R)
+    A, Bh = [dev(a) for a in M.factors], M.factors[0] * M.lam
+    out = []
+    for variant in (cpapr.CPAPR_VARIANT_XR, cpapr.CPAPR_VARIANT_SEGMENTED, cpapr.CPAPR_VARIANT_SEGMENTED):
+        P = cpapr.Plan.from_tensor(X, R, group=group, variant=variant)
+        out.append(host(P.phi(0, dev(Bh), A)))
+        P.close()
+    assert_parity(out[0], oracle.phi(X, 0, Bh, M.factors), TOL64, "XR")
+    assert np.array_equal(out[1], out[2]) and not np.array_equal(out[0], out[1])
