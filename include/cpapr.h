@@ -70,7 +70,8 @@ enum { CPAPR_FP64 = 0, CPAPR_MIXED = 1 };
  * products reduced across the lane group by a reduce-scatter through LDS
  * (one sum and one division per nonzero in one lane), for 8 or 16 lanes per
  * nonzero and up to 8 gathered words per lane; other shapes run SEGMENTED.
- * AUTO picks SEGMENTED. */
+ * AUTO picks SEGMENTED for Phi, and MU inner loops may then keep a row's
+ * nonzeros in registers over the iterations (see cpapr_plan_set_team_wait). */
 enum { CPAPR_VARIANT_AUTO = 0, CPAPR_VARIANT_SEGMENTED = 1, CPAPR_VARIANT_ATOMIC = 2, CPAPR_VARIANT_XR = 3 };
 
 /* Order of the nonzeros inside a row of the mode-n sorted copy (Phi's sum over

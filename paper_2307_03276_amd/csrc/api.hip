@@ -209,7 +209,7 @@ Error phi_factors(cpapr_plan* P, int mode, const double* const* A, const void** 
 // that faster (8M uniform nonzeros, R = 32: 224 against 394 us).
 bool runs_by_rows(const cpapr_plan* P, int mode)
 {
-    return P->by_rows && P->shape_auto && P->params.variant <= CPAPR_VARIANT_SEGMENTED && P->params.lmax > 1 &&
+    return P->by_rows && P->shape_auto && P->params.variant == CPAPR_VARIANT_AUTO && P->params.lmax > 1 &&
            !P->params.deterministic && cpapr::rows_pay(P, mode);
 }
 

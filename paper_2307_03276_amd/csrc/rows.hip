@@ -2640,7 +2640,7 @@ int rows_batch_shape(const cpapr_plan* P, int mode)
 {
     Shape sh;
     if (!P->by_rows || P->params.method != CPAPR_METHOD_MU || !P->shape_auto ||
-        P->params.variant > CPAPR_VARIANT_SEGMENTED || !row_shape(P->R, &sh)) return -1;
+        P->params.variant != CPAPR_VARIANT_AUTO || !row_shape(P->R, &sh)) return -1;
     if (P->mode[mode].rp.count[class_count(class_shape(sh)) - 2] > 0 || P->mode[mode].rp.nmembers > kTeamParts) return -1;
     const int mixed = P->params.precision == CPAPR_MIXED ? 1 : 0;
     return 2 * (P->R <= 16 ? (P->R - 1) / 4 : P->R <= 32 ? 4 + (P->R - 17) / 8 : 6 + (P->R - 33) / 16) + mixed;

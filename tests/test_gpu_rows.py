@@ -390,3 +390,24 @@ def test_batch_of_rows_just_longer_than_a_workgroups_registers():
         assert_parity(host(B), Bo, TOL64, f"B slot {i}")
         assert_parity(host(Phi), Po, TOL64, f"Phi slot {i}")
     b.close()
+
+
+def test_explicit_segmented_variant_runs_the_tile_kernel():
+    """CPAPR_VARIANT_SEGMENTED: the inner loop by Phi launches, bit for bit those of a
+    plan with an explicit shape (rows of at most 24 of a tile's 32 nonzeros, whose
+    two atomic sums commute)."""
+    X = _tensor(EDGES[:10] * 12, (60, 45), 94)
+    M = synth.random_model(94, X.dims, 10)
+    Bh, A = M.factors[0] * M.lam, [dev(a) for a in M.factors]
+    out = []
+    for variant, shaped in ((cpapr.CPAPR_VARIANT_SEGMENTED, False), (cpapr.CPAPR_VARIANT_AUTO, True),
+                            (cpapr.CPAPR_VARIANT_AUTO, False)):
+        P = cpapr.Plan.from_tensor(X, 10, lmax=6, tol=0.0, variant=variant)
+        if shaped:
+            P.set_shape(*P.shape())
+        B = dev(Bh)
+        P.mu_inner(0, B, A)
+        out.append(host(B))
+        P.close()
+    assert np.array_equal(out[0], out[1]) and not np.array_equal(out[0], out[2])
+    assert_parity(out[0], oracle.mu_inner(X, 0, Bh, M.factors, lmax=6, tau=0.0)[0], TOL64, "B")
