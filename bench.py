@@ -9,15 +9,17 @@ HBM before timing.
 
 value = Phi nonzero visits per second over the whole step (Phi evaluations
         the solve actually computed x nnz / step time).
-roofline: the Phi kernel, timed by HIP events on its own stream around every
-        7th Phi launch of the timed steps, against HBM peak. achieved = the compulsory traffic
-        M_min of one launch / its average duration, M_min per mode n being
+roofline: the inner loops, timed by HIP events on their stream (every 2nd or 3rd
+        record of the library: a loop run row by row, or a Phi launch), against HBM
+        peak. achieved = the compulsory traffic M_min of the loops, once per
+        loop, / their time, M_min per mode n being
         nnz (4(N-1) + 8) (the other modes' coordinates and the value; i_n
         follows from the segment table) + S_n (2 R 8 + 8) (per nonempty row
         the B row read, the Phi row written and a segment entry) + sum over
         m != n of I_m R w (every row of the other factors once, w = 8 or 4
-        bytes as stored). traffic: bytes past L2 per launch from committed
-        counter runs / the same duration.
+        bytes as stored). Row solves (--method): per Phi or Hessian launch,
+        every 7th of them timed; traffic: bytes past L2 per launch from
+        committed counter runs / the same duration.
 hbm_probe: a measured 1 GiB device copy, for reference beside the peak.
 cpu_baseline: the FP64 CPU oracle pinned to one host core, Phi over every
         mode of the same tensor (zipf4: a sample of it), median of 5 runs,
@@ -37,6 +39,7 @@ Prints one JSON line. Only one GPU is supported.
 import argparse
 import hashlib
 import json
+import math
 import os
 import sys
 import time
@@ -45,7 +48,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-PROF_EVERY = 7  # Phi launches per timed one in the job benchmarks
+PROF_EVERY = 7  # Phi launches per timed one of the row solves
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "phi_traffic.json")
 
 
@@ -84,6 +87,57 @@ def phi_issued_bytes(N, R, nnz, segs, mode, word=8):
     counted per nonzero): the fused-kernel model of the paper's Section 3.2
     applied to this kernel."""
     return nnz * (4 * N + 8 + (N - 1) * R * word) + segs[mode] * R * (8 + 8)
+
+
+def loop_report(N, R, nnz, dims, segs, word, recs, every, steps, st, ms_per_step):
+    """Roofline and timing of a job's MU inner loops. The records are whole loops
+    or single Phi launches, whichever ran, so that only their total is used: a
+    loop reads the nonzeros once at least, however many passes it takes."""
+    tot_ms = every * sum(ms for _, ms in recs) / steps
+    passes, loops = st["phi_evals"], st["outer_iters"]
+    min_bytes = loops * sum(phi_min_bytes(N, R, nnz, dims, segs, n, word) for n in range(N))
+    achieved = min_bytes / (tot_ms / 1000.0) / 1e9
+    avg_ms = tot_ms / max(1, passes)
+    roofline = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": achieved / HBM_PEAK_GBS, "traffic": None}
+    return roofline, {
+        "kernel": "the inner loops' kernels (resident_kernel, hot_kernel, hot_step_kernel, heavy_kernel, phi_seg_kernel)",
+        "records": len(recs), "sampled_every": every, "loops_per_step": loops * N, "passes_per_step": passes,
+        "loops_ms_per_step": tot_ms, "avg_ms": avg_ms, "nnz_per_s": nnz / (avg_ms / 1000.0),
+        "min_bytes_per_loop": min_bytes / max(1, loops * N), "segments": segs, "share_of_step": tot_ms / ms_per_step}
+
+
+def launch_report(N, R, nnz, dims, segs, word, recs, every, steps, pdnr, ms_per_step, traffic_bytes):
+    """Roofline and timing of the row solves' Phi (PQNR) or Hessian (PDNR) launches."""
+    # launches enqueued after an inner loop stopped exit at once; time only real ones
+    med = sorted(ms for _, ms in recs)[len(recs) // 2] if recs else 0.0
+    recs = [(m, ms) for m, ms in recs if ms > 0.2 * med]
+    minb = hess_min_bytes if pdnr else phi_min_bytes
+    tot_bytes = sum(minb(N, R, nnz, dims, segs, m, word) for m, _ in recs)
+    kern_bytes = sum(phi_kernel_bytes(N, R, nnz, segs, m, word) for m, _ in recs)
+    issued = sum(phi_issued_bytes(N, R, nnz, segs, m, word) for m, _ in recs)
+    tot_ms = sum(ms for _, ms in recs)
+    achieved = tot_bytes / (tot_ms / 1000.0) / 1e9
+    avg_ms = tot_ms / max(1, len(recs))
+    per_mode_ms = [sum(ms for m, ms in recs if m == n) / max(1, sum(1 for m, _ in recs if m == n)) for n in range(N)]
+    if pdnr:
+        traffic_bytes = None
+    roofline = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": achieved / HBM_PEAK_GBS,
+                "traffic": None if traffic_bytes is None else traffic_bytes / (avg_ms / 1000.0) / 1e9}
+    return roofline, {
+        "kernel": "pdnr_hess_kernel or pdnr_row_kernel" if pdnr else "phi_seg_kernel",
+        "launches": len(recs), "avg_ms": avg_ms, "avg_ms_per_mode": per_mode_ms,
+        "nnz_per_s": nnz / (avg_ms / 1000.0),
+        "min_bytes_per_launch": tot_bytes / max(1, len(recs)),
+        "kernel_bytes_per_launch": kern_bytes / max(1, len(recs)),
+        "kernel_bytes_frac": kern_bytes / (tot_ms / 1000.0) / 1e9 / HBM_PEAK_GBS,
+        "issued_bytes_per_launch": issued / max(1, len(recs)),
+        "issued_GBs": issued / (tot_ms / 1000.0) / 1e9,
+        "measured_bytes_per_launch": traffic_bytes,
+        "segments": segs, "sampled_every": every,
+        # the sampled launches stand for `every` launches each
+        "share_of_step": every * tot_ms / (ms_per_step * steps)}
 
 
 def kernel_source_hash():
@@ -576,7 +630,6 @@ def mttkrp_workload(args):
     as Phi: one step = one MTTKRP per mode of the zipf3 (or, with --tensor
     zipf4, the zipf4) tensor, FP64, with the plan built beforehand (an ALS
     solver builds it once and calls MTTKRP every sweep)."""
-    import math
 
     import torch
 
@@ -861,22 +914,22 @@ def main():
         step()
     torch.cuda.synchronize()
     progress(f"{args.steps} timed steps")
-    # MU: an event pair per inner loop (all its Phi passes); row solves: per launch
-    passes = sched["lmax"] if args.method == "mu" else 1
-    every = 2 if args.method == "mu" else PROF_EVERY
-    launches_per_step = sched["kmax"] * N * sched["lmax"] // passes
-    # Every 2nd inner loop (row solves: every 7th launch) of the timed steps is
-    # bracketed by HIP events (2 and 7 are coprime to the 3 modes, 7 to the 10
-    # inner iterations, so every mode and position is sampled); an event pair
-    # holds the stream for about 5 us on either side.
-    cpapr.cpapr_prof_enable_sampled(launches_per_step * args.steps // every + 16, every)
+    # Row solves: every 7th launch is bracketed by HIP events (7 is coprime to the
+    # 3 modes and 10 inner iterations, so that every mode and position is sampled).
+    # MU: every 2nd or 3rd record (coprime to the modes), a whole inner loop (row by
+    # row) or one Phi launch. An event pair holds the stream for about 5 us on
+    # either side.
+    mu = args.method == "mu"
+    every = next(k for k in range(2, 10) if math.gcd(k, N) == 1) if mu else PROF_EVERY
+    cap = sched["kmax"] * N * (sched["lmax"] + 1) * args.steps // every + 16
+    cpapr.cpapr_prof_enable_sampled(cap, every)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for _ in range(args.steps):
         st, segs = step()
     torch.cuda.synchronize()
     t1 = time.perf_counter()
-    recs = cpapr.cpapr_prof_read(launches_per_step * args.steps // every + 16)
+    recs = cpapr.cpapr_prof_read(cap)
     cpapr.cpapr_prof_disable()
 
     ms_per_step = (t1 - t0) * 1000.0 / args.steps
@@ -884,23 +937,14 @@ def main():
     # the line-search passes of PQNR
     visits = (st["phi_evals"] + st["trial_evals"]) * X.nnz
     value = visits / (ms_per_step / 1000.0)
-    # launches enqueued after an inner loop stopped exit at once; time only real ones
-    med = sorted(ms for _, ms in recs)[len(recs) // 2] if recs else 0.0
-    recs = [(m, ms / passes) for m, ms in recs if ms > 0.2 * med]  # per Phi pass
     word = 4 if prec == cpapr.CPAPR_MIXED else 8
     dims = list(X.dims)
-    pdnr = method == cpapr.CPAPR_METHOD_PDNR
-    # the timed launches: Phi (MU, PQNR) or the Hessian pass (PDNR)
-    minb = hess_min_bytes if pdnr else phi_min_bytes
-    tot_bytes = sum(minb(N, R, X.nnz, dims, segs, m, word) for m, _ in recs)
-    kern_bytes = sum(phi_kernel_bytes(N, R, X.nnz, segs, m, word) for m, _ in recs)
-    issued = sum(phi_issued_bytes(N, R, X.nnz, segs, m, word) for m, _ in recs)
-    tot_ms = sum(ms for _, ms in recs)
-    achieved = tot_bytes / (tot_ms / 1000.0) / 1e9
-    avg_ms = tot_ms / max(1, len(recs))
-    per_mode_ms = [sum(ms for m, ms in recs if m == n) / max(1, sum(1 for m, _ in recs if m == n)) for n in range(N)]
-    traffic_bytes = measured_traffic(wl_name, args.precision) if not pdnr else None
-    traffic = None if traffic_bytes is None else traffic_bytes / (avg_ms / 1000.0) / 1e9
+    if mu:
+        roofline, phi_kernel = loop_report(N, R, X.nnz, dims, segs, word, recs, every, args.steps, st, ms_per_step)
+    else:
+        roofline, phi_kernel = launch_report(N, R, X.nnz, dims, segs, word, recs, every, args.steps,
+                                             method == cpapr.CPAPR_METHOD_PDNR, ms_per_step,
+                                             measured_traffic(wl_name, args.precision))
     out = {
         "metric": "Phi^(n) nonzeros/s" if args.method == "mu" else "nonzero passes/s (Phi + line search)",
         "value": value,
@@ -916,21 +960,8 @@ def main():
         "data": "synthetic",
         "config": {"workload": wl_desc, "nnz": X.nnz, "rank": R, "outer": sched["kmax"], "inner": sched["lmax"],
                    "tol": sched["tau"], "precision": args.precision},
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS, "traffic": traffic},
-        "phi_kernel": {"kernel": "pdnr_hess_kernel" if pdnr else "phi_seg_kernel" if args.method != "mu" else
-                       "the inner loop's kernels (resident_kernel, hot_kernel, hot_step_kernel), per Phi pass",
-                       "launches": len(recs), "avg_ms": avg_ms, "avg_ms_per_mode": per_mode_ms,
-                       "nnz_per_s": X.nnz / (avg_ms / 1000.0),
-                       "min_bytes_per_launch": tot_bytes / max(1, len(recs)),
-                       "kernel_bytes_per_launch": kern_bytes / max(1, len(recs)),
-                       "kernel_bytes_frac": kern_bytes / (tot_ms / 1000.0) / 1e9 / HBM_PEAK_GBS,
-                       "issued_bytes_per_launch": issued / max(1, len(recs)),
-                       "issued_GBs": issued / (tot_ms / 1000.0) / 1e9,
-                       "measured_bytes_per_launch": traffic_bytes,
-                       "segments": segs, "sampled_every": every,
-                       # the sampled launches stand for `every` launches each
-                       "share_of_step": every * passes * tot_ms / (ms_per_step * args.steps)},
+        "roofline": roofline,
+        "phi_kernel": phi_kernel,
         "solve": {"method": args.method, "outer": st["outer_iters"], "inner_updates": st["inner_iters"],
                   "phi_evals": st["phi_evals"], "trial_evals": st["trial_evals"], "row_steps": st["row_steps"],
                   "converged": bool(st["converged"]), "kkt": st["kkt_violation"], "loglik": st["loglik"]},

@@ -451,15 +451,17 @@ int cpapr_modes_advance(int32_t count, cpapr_plan* const* plans, const int32_t* 
 int cpapr_plan_sync_f32(cpapr_plan* plan, const double* const* A, void* stream);
 
 /* Kernel timing for measurement: while enabled, every Phi, MTTKRP and PDNR
- * Hessian-pass kernel launch is bracketed by HIP events on its stream (up to
- * `capacity` launches).
- * cpapr_prof_enable_sampled brackets only every `every`-th launch after the
+ * Hessian-pass kernel launch is bracketed by HIP events on its stream, and so
+ * are the iterations of an MU inner loop that runs row by row, as one record (up
+ * to `capacity` records; such a loop whose first iteration is a Phi launch gives
+ * that launch and the others' record).
+ * cpapr_prof_enable_sampled brackets only every `every`-th of these after the
  * call (the 1st, the every+1-th, ...): each event pair holds the stream for a
- * few microseconds on either side of its kernel, so sampling keeps the timed
+ * few microseconds on either side of its kernels, so sampling keeps the timed
  * work close to an unobserved run. cpapr_prof_read waits for the recorded
- * events and writes, per recorded launch, the mode and the kernel's duration
- * in milliseconds; returns the number of launches written (<= cap) or a
- * negative error. Not thread-safe. */
+ * events and writes, per record, the mode and the duration in milliseconds;
+ * returns the number of records written (<= cap) or a negative error. Not
+ * thread-safe. */
 int cpapr_prof_enable(int32_t capacity);
 int cpapr_prof_enable_sampled(int32_t capacity, int32_t every);
 int cpapr_prof_disable(void);
