@@ -108,7 +108,8 @@ int slot_class(const cpapr_plan* P)
 {
     int G, L;
     cpapr::batch_shape(P, &G, &L);
-    return cpapr::batch_class_of(G, cpapr::rank_block(P->R, G), P->N - 1, P->params.precision == CPAPR_MIXED);
+    return cpapr::batch_class_of(G, cpapr::rank_columns(P->R, G, P->N - 1, P->params.precision == CPAPR_MIXED), P->N - 1,
+                                 P->params.precision == CPAPR_MIXED);
 }
 
 }  // namespace

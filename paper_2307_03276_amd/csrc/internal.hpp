@@ -333,6 +333,7 @@ void batch_shape(const cpapr_plan* P, int* group, int* chunk);
 inline int64_t det_tile_capacity(int64_t nnz) { return nnz / 128 + 2; }
 // Rank columns per lane (1, 2 or 4) for rank R on `group` lanes; -1 if R > 4 * group.
 int rank_block(int R, int group);
+int rank_columns(int R, int group, int nm1, bool mixed);
 Error launch_phi(const cpapr_plan* P, int mode, const double* B, const void* const* fac, bool mixed,
                  double eps, double* Phi, const int* done, hipStream_t s);
 Error launch_mttkrp(const cpapr_plan* P, int mode, const double* const* A, double* M, hipStream_t s);

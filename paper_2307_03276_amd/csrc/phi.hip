@@ -1224,6 +1224,18 @@ int rank_block(int R, int group)
     return -1;
 }
 
+// Columns per lane of a launch: as few as the rank takes, but four instead of three
+// on 16 lanes with FP64 factors and three or four modes, whose rows are then read
+// in whole 32-byte words: R = 33 .. 48, 3M and 12M nonzeros, MTTKRP 1.00 to 1.10
+// times as long with three columns, Phi 0.99 to 1.06 (two modes: 0.87 to 1.04;
+// FP32-stored factors 0.85 to 1.05; more modes, where the choice is one column on
+// 64 lanes: 0.55 to 0.8).
+int rank_columns(int R, int group, int nm1, bool mixed)
+{
+    const int rpl = rank_block(R, group);
+    return rpl == 3 && group == 16 && !mixed && (nm1 == 2 || nm1 == 3) ? 4 : rpl;
+}
+
 int resolve_chunk(int group, int requested)
 {
     if (requested > 0) return requested;
@@ -1243,7 +1255,8 @@ int resolve_chunk(int group, int requested)
 //    17 <= R <= 32: in FP64 16 lanes x 2 columns at every mode count, on 512
 //    nonzeros for up to three modes from 3 * 2^20 nonzeros on (24 tiles per
 //    compute unit; 1.85M uniform nonzeros, R = 24: 75.7 on 512 against 73.5 us
-//    on 256) and 256 else; with FP32-stored factors (half
+//    on 256) and for more than four below 2^20 (500k, R = 32: 31 against 35 us on
+//    256; 3M 127 against 123), 256 else; with FP32-stored factors (half
 //    the gathered words per lane) 8 lanes x 3 or 4 columns, on 1024 for up to
 //    four modes and 512 for more (from five modes on four columns no longer
 //    fit: 16 x 2). Measured, 8 lanes on 512 / 1024 against 16 lanes on 256 /
@@ -1293,7 +1306,7 @@ void model_shape(const ModelIn& m, int* tile, int* group)
     const int g0 = !wide ? resolve_group(m.R, 0, m.nm1) : m.mixed && (m.nm1 <= 3 || m.R <= 24) ? 8 : 16;
     int tb = 512;  // a large tensor's tile
     if (wide && !m.mixed) {
-        tb = m.nm1 <= 2 && m.nnz >= (3 << 20) ? 512 : 256;
+        tb = (m.nm1 <= 2 && m.nnz >= (3 << 20)) || (m.nm1 > 3 && m.nnz < (1 << 20)) ? 512 : 256;
     } else if (wide && m.nm1 <= 3) {
         tb = 1024;
     } else if (m.packed && m.R > 4 && m.R <= 16) {
@@ -1376,7 +1389,7 @@ Error launch_phi(const cpapr_plan* P, int mode, const double* B, const void* con
                  double eps, double* Phi, const int* done, hipStream_t s)
 {
     const int G = P->group;
-    const int RPL = rank_block(P->R, G);
+    const int RPL = rank_columns(P->R, G, P->N - 1, P->params.precision == CPAPR_MIXED);
     PhiArgs a = make_args(P, mode, B, fac, eps, Phi, done);
     if (P->params.variant == CPAPR_VARIANT_ATOMIC) {
         if (mixed) return {CPAPR_EUNSUPPORTED, "the atomic variant is FP64 only"};
@@ -1401,7 +1414,7 @@ Error launch_delta(const cpapr_plan* P, int mode, const double* B, const double*
                    const void* const* fac, double eps, double* out, const int* skip, hipStream_t s)
 {
     const int G = P->group;
-    const int RPL = rank_block(P->R, G);
+    const int RPL = rank_columns(P->R, G, P->N - 1, P->params.precision == CPAPR_MIXED);
     PhiArgs a = make_args(P, mode, B, fac, eps, out, skip);
     a.D = D;
     a.live = live;
@@ -1417,7 +1430,7 @@ Error launch_delta4(const cpapr_plan* P, int mode, const double* B, const double
 {
     if (P->R < kTrials4) return {CPAPR_EUNSUPPORTED, "the four-trial line-search pass needs R >= 4"};
     int G = P->group;
-    int RPL = rank_block(P->R, G);
+    int RPL = rank_columns(P->R, G, P->N - 1, P->params.precision == CPAPR_MIXED);
     PhiArgs a = make_args(P, mode, B, fac, eps, out, skip);
     // Three or four rank columns per lane hold 12 or 16 trial-step words per lane: such shapes
     // take twice the lanes per nonzero for this pass, on the same tiles.
@@ -1438,7 +1451,7 @@ Error launch_delta4(const cpapr_plan* P, int mode, const double* B, const double
 Error launch_mttkrp(const cpapr_plan* P, int mode, const double* const* A, double* M, hipStream_t s)
 {
     const int G = P->group;
-    const int RPL = rank_block(P->R, G);
+    const int RPL = rank_columns(P->R, G, P->N - 1, P->params.precision == CPAPR_MIXED);
     PhiArgs a = make_args(P, mode, nullptr, (const void* const*)A, 0.0, M, nullptr);
     Error e = zero_matrix(M, P->dims[mode] * (int64_t)P->R, s);
     if (e.code) return e;
@@ -1549,7 +1562,7 @@ Error launch_loglik_terms(const cpapr_plan* P, const double* B, const double* co
 {
     // Default shape for this rank (R > 64: the others run launch_loglik_fused), 512 nonzeros per tile.
     const int G = resolve_group(P->R, 0, P->N - 1);
-    const int RPL = rank_block(P->R, G);
+    const int RPL = rank_columns(P->R, G, P->N - 1, P->params.precision == CPAPR_MIXED);
     PhiArgs a = make_args(P, 0, B, (const void* const*)A, eps, partial, nullptr);
     a.L = resolve_chunk(G, 0);
     const int64_t tiles = cdiv(P->nnz, (int64_t)(kBlock / G) * a.L);

@@ -2616,13 +2616,15 @@ Error launch_loglik_fused(const cpapr_plan* P, const double* lam, const double* 
     a.per = (int)per;
     const int64_t blocks = cdiv(P->nnz, per * (kBlock / 64));
     const dim3 grid((unsigned)(blocks + (int64_t)a.N * a.parts));
-    Shape sh = heavy_shape(P->R, false);
+    // four columns instead of three at R = 33 .. 48 as rank_columns has it
+    const Shape sh = P->R > 32 && P->R <= 48 && (P->N == 3 || P->N == 4) ? Shape{16, 4, 0} : heavy_shape(P->R, false);
     Error e = by_heavy_shape<false>(sh, [&](auto G, auto C) -> Error {
         constexpr int GG = decltype(G)::value, CC = decltype(C)::value;
         switch (P->N) {
             case 2: loglik_kernel<GG, CC, 1><<<grid, kBlock, 0, s>>>(a); break;
             case 3: loglik_kernel<GG, CC, 2><<<grid, kBlock, 0, s>>>(a); break;
             case 4: loglik_kernel<GG, CC, 3><<<grid, kBlock, 0, s>>>(a); break;
+            case 5: loglik_kernel<GG, CC, 4><<<grid, kBlock, 0, s>>>(a); break;
             default: loglik_kernel<GG, CC, 0><<<grid, kBlock, 0, s>>>(a); break;
         }
         CPAPR_LAUNCHED();
