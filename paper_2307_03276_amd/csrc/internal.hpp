@@ -393,9 +393,9 @@ bool rows_supported(int R, int64_t nnz);
 // unless r is nullptr (stops: tol > 0).
 size_t rows_mode_bind(RowPlan* r, char* base, int64_t nnz, int64_t dim, int R);
 size_t rows_state_bind(RowState* r, char* base, int64_t nnz, int64_t maxI, int R, bool stops);
-// Device part of a mode's row classes (meta: kRowMeta zeroed device ints), then
-// the host part from meta's host copy.
-Error rows_build(const cpapr_plan* P, int mode, int* meta, hipStream_t s);
+// Device part of all modes' row classes (meta: kRowMeta zeroed device ints per
+// mode), then the host part of one from its meta's host copy.
+Error rows_build(const cpapr_plan* P, int* meta, hipStream_t s);
 void rows_finish(cpapr_plan* P, int mode, const int* meta);
 // Long rows' nonzeros split by a second mode's hot rows, where that pays. Bytes
 // bound to `base` unless P is nullptr.

@@ -1279,12 +1279,35 @@ __host__ __device__ inline int len_bucket(int len)
     return 4 * e + (e >= 2 ? (len >> (e - 2)) & 3 : (len << (2 - e)) & 3);
 }
 
-// First sorted position of every row (row_ptr[rows] = nnz), by binary search.
-__global__ __launch_bounds__(kBlock) void row_ptr_kernel(const int32_t* __restrict__ rows, int64_t nnz, int64_t nrows,
-                                                         int32_t* __restrict__ row_ptr)
+// What the kernels below need of every mode: each is one launch for all modes of a
+// plan (blockIdx.y), as a mode's own share is a few microseconds.
+struct ModeRows {
+    const int32_t* rows;  // [nnz] sorted
+    int64_t nrows;
+    int32_t *row_ptr, *order, *chunk_begin, *chunk_row, *team_begin, *team_row;
+    int* meta;            // class counts, the classes' cursors, pieces; rows and nonzeros per length bucket
+};
+struct AllModes {
+    ModeRows m[CPAPR_MAX_MODES];
+    int64_t nnz;
+};
+
+// First sorted position of every row (row_ptr[rows] = nnz), by binary search, and
+// the counts of the classes and length buckets. A workgroup's last thread finds
+// the end of the row before it.
+__global__ __launch_bounds__(kBlock) void class_hist_kernel(AllModes a, ClassShape cs)
 {
-    for (int64_t r = blockIdx.x * (int64_t)kBlock + threadIdx.x; r <= nrows; r += (int64_t)gridDim.x * kBlock) {
-        int64_t lo = 0, hi = nnz;
+    const int32_t* __restrict__ rows = a.m[blockIdx.y].rows;
+    int32_t* __restrict__ row_ptr = a.m[blockIdx.y].row_ptr;
+    int* __restrict__ meta = a.m[blockIdx.y].meta;
+    const int64_t nrows = a.m[blockIdx.y].nrows;
+    __shared__ int h[kRowClasses], hr[kLenBuckets], hn[kLenBuckets], at[kBlock];
+    const int t = threadIdx.x;
+    if (t < kRowClasses) h[t] = 0;
+    if (t < kLenBuckets) hr[t] = hn[t] = 0;
+    for (int64_t r0 = blockIdx.x * (int64_t)(kBlock - 1); r0 < nrows; r0 += (int64_t)gridDim.x * (kBlock - 1)) {
+        const int64_t r = r0 + t;
+        int64_t lo = 0, hi = r <= nrows ? a.nnz : 0;
         while (lo < hi) {
             const int64_t mid = lo + (hi - lo) / 2;
             if (rows[mid] < r)
@@ -1292,40 +1315,36 @@ __global__ __launch_bounds__(kBlock) void row_ptr_kernel(const int32_t* __restri
             else
                 hi = mid;
         }
-        row_ptr[r] = (int32_t)lo;
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void class_hist_kernel(const int32_t* __restrict__ row_ptr, int64_t nrows,
-                                                            ClassShape cs, int* __restrict__ meta)
-{
-    __shared__ int h[kRowClasses], hr[kLenBuckets], hn[kLenBuckets];
-    if (threadIdx.x < kRowClasses) h[threadIdx.x] = 0;
-    if (threadIdx.x < kLenBuckets) hr[threadIdx.x] = hn[threadIdx.x] = 0;
-    __syncthreads();
-    for (int64_t r = blockIdx.x * (int64_t)kBlock + threadIdx.x; r < nrows; r += (int64_t)gridDim.x * kBlock) {
-        const int len = row_ptr[r + 1] - row_ptr[r];
-        atomicAdd(&h[class_of(cs, len)], 1);
-        if (len > 0) {
-            atomicAdd(&hr[len_bucket(len)], 1);
-            atomicAdd(&hn[len_bucket(len)], len);
+        __syncthreads();
+        at[t] = (int)lo;
+        __syncthreads();
+        if (r <= nrows && (t < kBlock - 1 || r == nrows)) row_ptr[r] = (int32_t)lo;
+        if (t < kBlock - 1 && r < nrows) {
+            const int len = at[t + 1] - (int)lo;
+            atomicAdd(&h[class_of(cs, len)], 1);
+            if (len > 0) {
+                atomicAdd(&hr[len_bucket(len)], 1);
+                atomicAdd(&hn[len_bucket(len)], len);
+            }
         }
     }
     __syncthreads();
-    if (threadIdx.x < kRowClasses && h[threadIdx.x]) atomicAdd(&meta[threadIdx.x], h[threadIdx.x]);
-    if (threadIdx.x < kLenBuckets && hr[threadIdx.x]) {
-        atomicAdd(&meta[64 + threadIdx.x], hr[threadIdx.x]);
-        atomicAdd(&meta[64 + kLenBuckets + threadIdx.x], hn[threadIdx.x]);
+    if (t < kRowClasses && h[t]) atomicAdd(&meta[t], h[t]);
+    if (t < kLenBuckets && hr[t]) {
+        atomicAdd(&meta[64 + t], hr[t]);
+        atomicAdd(&meta[64 + kLenBuckets + t], hn[t]);
     }
 }
 
 // Counting sort of the rows by class. meta: class counts, then the classes'
 // cursors (zero before). A workgroup reserves its share of every class at
 // once; the order inside a class does not matter to any row's result.
-__global__ __launch_bounds__(kBlock) void class_scatter_kernel(const int32_t* __restrict__ row_ptr, int64_t nrows,
-                                                               ClassShape cs, int* __restrict__ meta,
-                                                               int32_t* __restrict__ order)
+__global__ __launch_bounds__(kBlock) void class_scatter_kernel(AllModes a, ClassShape cs)
 {
+    const int32_t* __restrict__ row_ptr = a.m[blockIdx.y].row_ptr;
+    int32_t* __restrict__ order = a.m[blockIdx.y].order;
+    int* __restrict__ meta = a.m[blockIdx.y].meta;
+    const int64_t nrows = a.m[blockIdx.y].nrows;
     __shared__ int h[kRowClasses], base[kRowClasses];
     for (int64_t r0 = blockIdx.x * (int64_t)kBlock; r0 < nrows; r0 += (int64_t)gridDim.x * kBlock) {
         if (threadIdx.x < kRowClasses) h[threadIdx.x] = 0;
@@ -1350,18 +1369,21 @@ __global__ __launch_bounds__(kBlock) void class_scatter_kernel(const int32_t* __
 }
 
 // Rows of one class cut into pieces of at most `piece` nonzeros: the prefix of
-// their counts (begin), the piece -> row map and the total. Block 0: the long rows'
-// chunks (and the longest class's share of them), block 1: the team rows' members.
+// their counts (begin), the piece -> row map and the total. Block 0 of a mode: the
+// long rows' chunks (and the longest class's share of them), block 1: the team
+// rows' members.
 struct Pieces {
     int cls, ncls, piece, max_rows, max_pieces;
-    int32_t *begin, *row;
 };
 
-__global__ __launch_bounds__(1024) void pieces_kernel(const int32_t* __restrict__ row_ptr,
-                                                      const int32_t* __restrict__ order, Pieces heavy, Pieces teams,
-                                                      int* __restrict__ meta)
+__global__ __launch_bounds__(1024) void pieces_kernel(AllModes all, Pieces heavy, Pieces teams)
 {
+    const ModeRows& m = all.m[blockIdx.y];
+    const int32_t *__restrict__ row_ptr = m.row_ptr, *__restrict__ order = m.order;
+    int* __restrict__ meta = m.meta;
     const Pieces a = blockIdx.x == 0 ? heavy : teams;
+    int32_t* const out_begin = blockIdx.x == 0 ? m.chunk_begin : m.team_begin;
+    int32_t* const out_row = blockIdx.x == 0 ? m.chunk_row : m.team_row;
     __shared__ int scan[1024];
     const int t = threadIdx.x;
     int row0 = 0;
@@ -1386,21 +1408,21 @@ __global__ __launch_bounds__(1024) void pieces_kernel(const int32_t* __restrict_
             __syncthreads();
         }
         const int begin = run + scan[t] - n;
-        if (h < nheavy) a.begin[h] = begin;
+        if (h < nheavy) out_begin[h] = begin;
         run += scan[1023];
         // the map: a wave per row
         const int lane = t & 63, w0 = t & ~63;
         for (int k = 0; k < 64; ++k) {
             const int b0 = __shfl(begin, k), nk = __shfl(n, k);
             for (int i = lane; i < nk; i += 64)
-                if (b0 + i < a.max_pieces) a.row[b0 + i] = h0 + w0 + k;
+                if (b0 + i < a.max_pieces) out_row[b0 + i] = h0 + w0 + k;
         }
         __syncthreads();
     }
     if (t == 0) {
-        a.begin[nheavy] = run;
+        out_begin[nheavy] = run;
         meta[2 * kRowClasses + blockIdx.x] = run;
-        if (blockIdx.x == 0) meta[2 * kRowClasses + 2] = a.begin[min(meta[a.cls], nheavy)];
+        if (blockIdx.x == 0) meta[2 * kRowClasses + 2] = out_begin[min(meta[a.cls], nheavy)];
     }
 }
 
@@ -2009,27 +2031,32 @@ static Error rows_hot_make(cpapr_plan* P, int n, hipStream_t s)
     return {CPAPR_OK, ""};
 }
 
-// Rows of one mode by class, from its sorted copy. meta: kRowMeta zeroed ints on
-// the device; rows_finish takes their host copy.
-Error rows_build(const cpapr_plan* P, int mode, int* meta, hipStream_t s)
+// Every mode's rows by class, from its sorted copy. meta: kRowMeta zeroed ints per
+// mode on the device; rows_finish takes their host copy.
+Error rows_build(const cpapr_plan* P, int* meta, hipStream_t s)
 {
     Shape sh;
     if (!row_shape(P->R, &sh)) return {CPAPR_OK, ""};
-    const RowPlan& r = P->mode[mode].rp;
-    const int64_t nrows = P->dims[mode];
     const ClassShape cs = class_shape(sh);
-    const unsigned grid = (unsigned)std::min<int64_t>(cdiv(nrows + 1, kBlock), 4096);
-    row_ptr_kernel<<<grid, kBlock, 0, s>>>(P->mode[mode].rows, P->nnz, nrows, r.row_ptr);
+    AllModes a{};
+    a.nnz = P->nnz;
+    int64_t most = 0;
+    for (int n = 0; n < P->N; ++n) {
+        const RowPlan& r = P->mode[n].rp;
+        a.m[n] = {P->mode[n].rows, P->dims[n], r.row_ptr, r.order, r.chunk_begin, r.chunk_row, r.team_begin, r.team_row,
+                  meta + n * kRowMeta};
+        most = std::max(most, P->dims[n]);
+    }
+    const dim3 grid((unsigned)std::min<int64_t>(cdiv(most, kBlock - 1), 2048), P->N);
+    class_hist_kernel<<<grid, kBlock, 0, s>>>(a, cs);
     CPAPR_LAUNCHED();
-    class_hist_kernel<<<std::min(grid, 1024u), kBlock, 0, s>>>(r.row_ptr, nrows, cs, meta);
-    CPAPR_LAUNCHED();
-    class_scatter_kernel<<<std::min(grid, 1024u), kBlock, 0, s>>>(r.row_ptr, nrows, cs, meta, r.order);
+    class_scatter_kernel<<<dim3(std::min(grid.x, 1024u), P->N), kBlock, 0, s>>>(a, cs);
     CPAPR_LAUNCHED();
     if (max_long(P->nnz, sh) > 0) {
         const int n = class_count(cs), nl = (int)max_long(P->nnz, sh);
-        const Pieces heavy{n - 2, 2, heavy_chunk(P->nnz), nl, (int)max_chunks(P->nnz, sh), r.chunk_begin, r.chunk_row};
-        const Pieces teams{n - 1, 1, class_cap(cs), nl, (int)max_members(P->nnz, sh), r.team_begin, r.team_row};
-        pieces_kernel<<<2, 1024, 0, s>>>(r.row_ptr, r.order, heavy, teams, meta);
+        const Pieces heavy{n - 2, 2, heavy_chunk(P->nnz), nl, (int)max_chunks(P->nnz, sh)};
+        const Pieces teams{n - 1, 1, class_cap(cs), nl, (int)max_members(P->nnz, sh)};
+        pieces_kernel<<<dim3(2, P->N), 1024, 0, s>>>(a, heavy, teams);
         CPAPR_LAUNCHED();
     }
     return {CPAPR_OK, ""};

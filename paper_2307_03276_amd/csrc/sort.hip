@@ -460,10 +460,6 @@ Error build_sorted(cpapr_plan* P, const cpapr_coo* X, char* scratch, hipStream_t
         PlanMode& pm = P->mode[n];
         if (nnz == 0) {
             pm.segments = 0;
-            if (P->by_rows) {
-                Error e = rows_build(P, n, meta + n * kRowMeta, s);
-                if (e.code) return e;
-            }
             continue;
         }
         // LSD passes over the low `bits` bits of the keys in (kin, pin); outputs
@@ -515,12 +511,7 @@ Error build_sorted(cpapr_plan* P, const cpapr_coo* X, char* scratch, hipStream_t
             gather_sorted_kernel<16><<<grid_for(nnz), kBlock, 0, s>>>(rec, nnz, N, n, pin, P->R, pm.rows, pm.cofs,
                                                                       pm.vals, pm.pk);
         CPAPR_LAUNCHED();
-        if (P->by_rows) {  // counts the segments too
-            Error e = rows_build(P, n, meta + n * kRowMeta, s);
-            if (e.code) return e;
-            continue;
-        }
-        if (only >= 0) continue;  // a transient Phi has no use for the segment count
+        if (P->by_rows || only >= 0) continue;  // rows_build counts the segments; a transient Phi has no use for them
         const int gseg = std::min(grid_for(nnz), kSegPartials);
         count_segments_kernel<<<gseg, kBlock, 0, s>>>(pm.rows, nnz, segpart);
         CPAPR_LAUNCHED();
@@ -528,6 +519,10 @@ Error build_sorted(cpapr_plan* P, const cpapr_coo* X, char* scratch, hipStream_t
         CPAPR_LAUNCHED();
     }
     if (only >= 0) return {CPAPR_OK, ""};
+    if (P->by_rows) {
+        Error e = rows_build(P, meta, s);
+        if (e.code) return e;
+    }
     int host[64 + CPAPR_MAX_MODES * kRowMeta];
     CPAPR_HIP(hipMemcpyAsync(host, flags, sizeof(int) * (64 + (P->by_rows ? N * kRowMeta : 0)), hipMemcpyDeviceToHost, s));
     CPAPR_HIP(hipStreamSynchronize(s));
