@@ -231,7 +231,8 @@ Error enqueue_inner(cpapr_plan* P, int mode, double* B, const void* const* fac, 
     if (e.code) return e;
     e = cpapr::launch_fill(Phi, n, 0.0, done, s);
     if (e.code) return e;
-    const int lmax = first ? 1 : P->params.lmax;
+    const bool then_rows = first && P->params.lmax > 2;  // a single further iteration gathers once either way
+    const int lmax = then_rows ? 1 : P->params.lmax;
     for (int l = 0; l < lmax; ++l) {
         e = cpapr::launch_phi(P, mode, B, fac, mixed, P->params.eps, Phi, done, s);
         if (e.code) return e;
@@ -245,7 +246,7 @@ Error enqueue_inner(cpapr_plan* P, int mode, double* B, const void* const* fac, 
         }
         if (e.code) return e;
     }
-    if (first) return cpapr::enqueue_inner_rows(P, mode, B, fac, Phi, P->params.lmax - 1, s);
+    if (then_rows) return cpapr::enqueue_inner_rows(P, mode, B, fac, Phi, P->params.lmax - 1, s);
     if (fused && lmax > 0) return cpapr::launch_kkt_fold(P->state, lmax - 1, mode, s);
     return {CPAPR_OK, ""};
 }

@@ -411,3 +411,76 @@ def test_explicit_segmented_variant_runs_the_tile_kernel():
         P.close()
     assert np.array_equal(out[0], out[1]) and not np.array_equal(out[0], out[2])
     assert_parity(out[0], oracle.mu_inner(X, 0, Bh, M.factors, lmax=6, tau=0.0)[0], TOL64, "B")
+
+
+@pytest.mark.parametrize("use_graph", [False, True])
+def test_batch_whose_slots_mostly_stop_at_once(use_graph, lmax=12):
+    """After a round in which most slots stopped at their first iteration the batch
+    takes that one by the Phi / update launches: the same results in the round
+    that shows it and in the next ones, for slots that stop there, later or not at
+    all."""
+    import torch
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        slots = []
+        for i, at in enumerate([0, 0, 3, None, 0, 0]):
+            X = _tensor(EDGES + ([9_000] if i % 2 else []), (60, 45), 160 + i)
+            M = synth.random_model(160 + i, X.dims, 10)
+            Bh = M.factors[0] * M.lam
+            low = np.minimum.accumulate(oracle.mu_inner(X, 0, Bh, M.factors, lmax=lmax, tau=0.0)[2])
+            tol = 0.0 if at is None else float(low[at]) * (1 + 1e-6)
+            prec = cpapr.CPAPR_MIXED if i == 4 else cpapr.CPAPR_FP64
+            if prec == cpapr.CPAPR_MIXED:
+                tol = float(low[0]) * 1.01
+            ref = oracle.mu_inner(X, 0, Bh, M.factors, lmax=lmax, tau=tol)
+            P = cpapr.Plan.from_tensor(X, 10, lmax=lmax, tol=tol, precision=prec)
+            slots.append((P, Bh, ref, prec, [dev(a) for a in M.factors], dev(Bh), dev(np.zeros_like(Bh))))
+        b = cpapr.Batch(len(slots), sum(it[0].tiles() for it in slots) + 1)
+        for i, (P, Bh, ref, prec, A, B, Phi) in enumerate(slots):
+            b.set(i, P, 0, B, A, Phi)
+        b.commit()
+        for turn in range(4):
+            for it in slots:
+                it[5].copy_(dev(it[1]))
+            b.inner(lmax, use_graph=use_graph)
+            viol, upd, done = b.status()
+            for i, (P, Bh, (Bo, Po, hist, nup), prec, A, B, Phi) in enumerate(slots):
+                t, el = (TOL64, True) if prec == cpapr.CPAPR_FP64 else (TOL32, False)
+                assert upd[i] == nup and done[i] == (1 if nup < lmax else 0), (turn, i)
+                assert_parity(host(B), Bo, t, f"B slot {i} turn {turn}", elementwise=el)
+                assert_parity(host(Phi), Po, t, f"Phi slot {i} turn {turn}", elementwise=el)
+        b.close()
+
+
+@pytest.mark.parametrize("use_graph", [False, True])
+def test_batch_with_a_slot_that_cannot_run_row_by_row(use_graph):
+    """A slot with a row longer than the largest team: the whole batch takes the
+    general launches; without that slot, after a commit, the rows again."""
+    import torch
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        slots = []
+        for i, extra in enumerate([[], [170_000], [9_000]]):
+            X = _tensor(EDGES + extra, (60, 45), 170 + i)
+            M = synth.random_model(170 + i, X.dims, 16)
+            Bh = M.factors[0] * M.lam
+            ref = oracle.mu_inner(X, 0, Bh, M.factors, lmax=4, tau=0.0)
+            P = cpapr.Plan.from_tensor(X, 16, lmax=4, tol=0.0)
+            slots.append((P, Bh, ref, [dev(a) for a in M.factors], dev(Bh), dev(np.zeros_like(Bh))))
+        b = cpapr.Batch(len(slots), sum(it[0].tiles() for it in slots) + 1)
+        for i, (P, Bh, ref, A, B, Phi) in enumerate(slots):
+            b.set(i, P, 0, B, A, Phi)
+        b.commit()
+        for turn in range(3):
+            if turn == 2:
+                b.clear(1)
+                b.commit()
+            for it in slots:
+                it[4].copy_(dev(it[1]))
+            b.inner(4, use_graph=use_graph)
+            for i, (P, Bh, (Bo, Po, _, _), A, B, Phi) in enumerate(slots):
+                if turn == 2 and i == 1:
+                    continue
+                assert_parity(host(B), Bo, TOL64, f"B slot {i} turn {turn}")
+                assert_parity(host(Phi), Po, TOL64, f"Phi slot {i} turn {turn}")
+        b.close()
