@@ -183,7 +183,8 @@ int cpapr_plan_set_shape(cpapr_plan* plan, int32_t group, int32_t chunk);
  * paper names as future work in Section 4): 512-nonzero tiles, smaller ones
  * (down to 64 nonzeros, 16 lanes per nonzero) when the tensor has fewer than
  * about 512,000 nonzeros; for 17 <= R <= 32 16 lanes x 2 columns in FP64
- * (256-nonzero tiles from four modes on or below 3 * 2^20 nonzeros) and 8 lanes x 3 or 4 columns on
+ * (256-nonzero tiles at four modes, below 3 * 2^20 nonzeros at two and three and from
+ * 2^20 on at five and more) and 8 lanes x 3 or 4 columns on
  * 1024-nonzero tiles with FP32-stored factors and up to four modes (512 above);
  * otherwise lanes by rank (4 up to R = 4, 8 up to R = 16, then 16 or 64).
  * Host-only. */

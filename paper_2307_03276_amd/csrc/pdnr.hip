@@ -602,7 +602,7 @@ __global__ __launch_bounds__(64) void pdnr_begin16_kernel(RowArgs a)
 // and leaves the four trials' quadratic terms (delta_k . H delta_k) for the
 // accept kernel. Through memory a row's R^2 + R words were written, read twice
 // and cleared in every iteration (5M four-way nonzeros in 40k rows, R = 32: the
-// three kernels took 823 + 343 + 173 us, now 299 + 370 + 15). Rows longer than
+// three kernels took 823 + 343 + 173 us, now 321 (long rows) + 442 + 15). Rows longer than
 // a workgroup's share (RowPlan's long rows) are still accumulated in memory, a
 // workgroup per chunk of one row, and solved from there. One wave per short row
 // bounds this: 16 nonzeros' gathers in flight, then a chain of 32 pivots.

@@ -20,10 +20,15 @@
 //  * up to K nonzeros: one group of G lanes per row (each lane holds C rank
 //    columns, R <= G * C, of up to K pi rows); 64 / G rows per wave;
 //  * longer: 2, 4, .. 64 / G groups of a wave, then 2 or 4 waves of a workgroup;
-//  * longer than 4 waves' registers: heavy rows. Their nonzeros are cut into
-//    chunks of one row each; every iteration gathers again (heavy_kernel), the
-//    last workgroup of a row to finish sums the chunks' partial rows in order
-//    and takes the MU step of that row.
+//  * longer than 4 waves' registers, in a mode with few nonzeros in such rows: team
+//    rows, each shared by several workgroups of 4 waves that meet once per iteration
+//    and sum their partial rows in a fixed order (single loops: while all members
+//    fit the device at once; batches: always);
+//  * longer: heavy rows. Their nonzeros are cut into chunks of one row each; every
+//    iteration gathers again (heavy_kernel), the last workgroup of a row to finish
+//    sums the chunks' partial rows in order and takes the MU step of that row. With
+//    three or four modes their nonzeros may be split by a second mode's longest
+//    rows, which a workgroup keeps in LDS (hot_kernel).
 // Every sum has a fixed order, so results repeat bit for bit while the same path
 // is taken: the row of a team whose members were not all running in time is summed
 // by one workgroup, in other pieces.
