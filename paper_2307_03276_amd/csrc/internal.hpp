@@ -331,8 +331,9 @@ int model_chunk(const cpapr_plan* P, int group);  // launch-policy model: nonzer
 void batch_shape(const cpapr_plan* P, int* group, int* chunk);
 // Deterministic mode: tiles the partial buffers are sized for (tiles of >= 128 nonzeros).
 inline int64_t det_tile_capacity(int64_t nnz) { return nnz / 128 + 2; }
-// Rank columns per lane (1, 2 or 4) for rank R on `group` lanes; -1 if R > 4 * group.
+// Rank columns per lane (1 to 4) for rank R on `group` lanes; -1 if R > 4 * group.
 int rank_block(int R, int group);
+// The columns per lane that the Phi and MTTKRP launches take (nm1 other modes).
 int rank_columns(int R, int group, int nm1, bool mixed);
 Error launch_phi(const cpapr_plan* P, int mode, const double* B, const void* const* fac, bool mixed,
                  double eps, double* Phi, const int* done, hipStream_t s);
@@ -343,10 +344,10 @@ constexpr int kRowShapes = 16;  // launch shapes by rank and precision
 // Whether a batch slot of this plan can run row by row, and as which shape (-1: not).
 int rows_batch_shape(const cpapr_plan* P, int mode);
 size_t rows_batch_item_bytes();
-// Device-side descriptor of one slot (written to `out`), its workgroups without
-// and with the rows restored after a stop, and its team members.
 // Iterations a chunk of such a slot may take (its team rows' history).
 int rows_batch_chunk(const cpapr_plan* P, int mode);
+// Device-side descriptor of one slot (written to `out`), its workgroups without
+// and with the rows restored after a stop, and its team members.
 void rows_batch_item(const cpapr_plan* P, int mode, const double* B, const void* const* fac, double* Phi, int slot,
                      const int32_t* done, int32_t* rerun, unsigned long long* iv, void* out, int* light, int* again,
                      int* members);
